@@ -347,7 +347,7 @@ def tolerance(case):
             return {"rel": 4e-3, "max": 2e-2}
         return {"rel": 1e-5, "max": 1e-3}
     if case["chain"]:
-        return {"rel": 3e-2, "max": 1.0}  # bf16 from layer to layer, int8 codes that flip with it
+        return {"rel": 3e-2, "max": 0.9}  # bf16 from layer to layer, int8 codes that flip with it
     return {"rel": 1e-5, "max": 1e-3}
 
 
