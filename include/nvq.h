@@ -393,11 +393,12 @@ int nvq_dequant_bf16(const uint8_t *qweight, const uint16_t *scales, int64_t N, 
  * hundred and more (below that the batch-1 and small-batch paths read the
  * weights once and are faster).  Note that the weights are rounded to bf16
  * here, as in the paper's prefill path, and are not in nvq_gemv_w4a16.
- * Two kernels: tiles of 256 tokens x 256 rows when K % 256 == 0, the scales
- * are 16-byte aligned and the output has at least 32 of them, tiles of 256 x
- * 128 otherwise (the environment
- * variable NVQ_GEMM_TILE = wide | narrow overrides the choice where both can
- * run; both add the same products in the same order).  On an MI355X the 8B
+ * Two kernels: tiles of 256 tokens x 256 rows (K % 256 == 0, scales 16-byte
+ * aligned), and smaller tiles down to 64 x 32 whose waves may split K; the one
+ * with the smallest estimated time runs (the environment variable
+ * NVQ_GEMM_TILE = wide | 128x256 (or narrow) | 128x128 | 128x64 | 64x64 |
+ * 64x32 overrides the choice where the kernel can run; wide and 128x256 add
+ * the same products in the same order).  On an MI355X the 8B
  * block's projections at 4096 tokens (q+k+v, o, gate+up, down as one launch
  * each) run at 1.1-1.2 PFLOP/s, 47 % of the bf16 matrix peak; the paper's own
  * route, weights dequantised with nvq_dequant_bf16 and a library bf16 GEMM on

@@ -16,23 +16,18 @@
 // contiguous bytes; for the weights the lane loads the group's 16 packed bytes
 // once (adjacent to the other lane's group: 32 contiguous bytes per row) and
 // step s uses the low (s < 2) or high nibbles of bytes 8 (s % 2) .. + 7.
-// Nibble -> fp32 (byte convert), one FMA with the group's scale ((n - 8) * s is
-// exact), round to bf16.
+// Nibble -> fp32 (n - 8) * s, exact, round to bf16.
 //
-// Two kernels.  The one with wide tiles (256 x 256 per workgroup, second half of
-// this file) runs when K is a multiple of 256 and the output has at least 32
-// such tiles; the other one, described here, takes everything else.
-//
-// A workgroup of four waves owns 256 tokens x 128 weight rows, a wave 128 x 64
-// (4 x 2 MFMA tiles, 128 accumulator registers); a wave's dequantised operand
-// serves its four token tiles.  Activations pass through LDS (rows of 128 bytes
-// padded to 144: 16 lanes reading 16 bytes each then cover all 64 banks),
-// double buffered, eight neighbouring threads staging a token's 128 bytes; one
-// barrier per pair of groups.  The next pair's activations and packed weights
-// are requested before the current pair is multiplied.
+// Two kernels, which add the products of a slice of K in the same order:
+//  - tiles of 256 tokens x 256 rows ("wide", K a multiple of 256), whose waves dequantise
+//    a weight once per 256 tokens: the best rate, if the output has enough of them;
+//  - smaller tiles (second half of this file), 64 to 128 tokens x 32 to 256 rows, whose
+//    waves share out rows and slices of K, for everything else.
+// gemm_choose weighs them by what they were measured to take.
 #include "nvq_internal.h"
 
 #include <cstdlib>
+#include <cstring>
 
 namespace nvq {
 
@@ -41,183 +36,17 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef unsigned uint4v __attribute__((ext_vector_type(4)));
 
-constexpr int kGemmTokens = 256;  // per workgroup
-constexpr int kGemmRows = 128;
 constexpr int kGemmThreads = 256;
-constexpr int kXRowBytes = 144;  // 64 bf16 + 16 bytes of padding
 
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
     const floatx2 f = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));  // nearest even
 }
-
-// Eight weights of a lane: the nibbles of two dwords (already masked to
-// 0x0f0f0f0f) times the scale, as bf16.  neg8s = -8 * s.
-__device__ __forceinline__ bf16x8 dequant8(uint32_t n0, uint32_t n1, float s, float neg8s) {
-    float w[8];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        w[i] = fmaf((float)((n0 >> (8 * i)) & 0xffu), s, neg8s);
-        w[4 + i] = fmaf((float)((n1 >> (8 * i)) & 0xffu), s, neg8s);
-    }
-    const uint4 p = make_uint4(pack_bf16(w[0], w[1]), pack_bf16(w[2], w[3]), pack_bf16(w[4], w[5]),
-                               pack_bf16(w[6], w[7]));
-    return __builtin_bit_cast(bf16x8, p);
-}
-
-template <bool F32>
-__global__ __launch_bounds__(kGemmThreads) void gemm_w4a16_kernel(
-    const uint4 *__restrict__ qw, const uint16_t *__restrict__ sc, int N, int G,
-    const uint4 *__restrict__ x, int M, void *__restrict__ y) {
-    __shared__ __attribute__((aligned(16))) unsigned char xs[2][kGemmTokens * kXRowBytes];
-
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm = wave >> 1, wn = wave & 1;
-    const int li = lane & 31, lb = lane >> 5;
-    const int m0 = blockIdx.y * kGemmTokens, n0 = blockIdx.x * kGemmRows;
-    const int P = (G + 1) >> 1;  // pairs of groups
-
-    // Staging: eight neighbouring threads copy the 128 bytes of a token and
-    // pair (one cache line), thread t those of tokens m0 + t / 8 + 32 i (the
-    // last token again past the end: those results are not stored).
-    const uint4 *xrow[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int m = m0 + (t >> 3) + 32 * i;
-        xrow[i] = x + (size_t)(m < M ? m : M - 1) * (size_t)(G * 4);
-    }
-    // The lane's weight rows, one per row tile (the last row again past the end).
-    const uint4 *qrow[2];
-    const uint16_t *srow[2];
-#pragma unroll
-    for (int rt = 0; rt < 2; ++rt) {
-        const int n = n0 + wn * 64 + rt * 32 + li;
-        const int nc = n < N ? n : N - 1;
-        qrow[rt] = qw + (size_t)nc * (size_t)G;
-        srow[rt] = sc + (size_t)nc * (size_t)G;
-    }
-
-    floatx16 acc[4][2];
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[tt][rt][r] = 0.0f;
-
-    // In flight between pairs: the activations and the packed weights of the
-    // next pair.  An odd number of groups: the missing group of the last pair is
-    // the last group again, with scale 0 (all its weights 0).
-    uint4 xn0, xn1, xn2, xn3, xn4, xn5, xn6, xn7, wn0, wn1;
-    uint32_t hn0, hn1;
-#define NVQ_REQUEST(p_)                                                              \
-    do {                                                                             \
-        {                                                                            \
-            const int gx_ = 2 * (p_) + ((t >> 2) & 1);                               \
-            const int cx_ = 4 * (gx_ < G ? gx_ : G - 1) + (t & 3);                   \
-            xn0 = xrow[0][cx_];                                                      \
-            xn1 = xrow[1][cx_];                                                      \
-            xn2 = xrow[2][cx_];                                                      \
-            xn3 = xrow[3][cx_];                                                      \
-            xn4 = xrow[4][cx_];                                                      \
-            xn5 = xrow[5][cx_];                                                      \
-            xn6 = xrow[6][cx_];                                                      \
-            xn7 = xrow[7][cx_];                                                      \
-        }                                                                            \
-        const int gw_ = 2 * (p_) + lb;                                               \
-        const int gc_ = gw_ < G ? gw_ : G - 1;                                       \
-        wn0 = qrow[0][gc_];                                                          \
-        wn1 = qrow[1][gc_];                                                          \
-        hn0 = gw_ < G ? (uint32_t)srow[0][gc_] : 0u;                                 \
-        hn1 = gw_ < G ? (uint32_t)srow[1][gc_] : 0u;                                 \
-    } while (0)
-#define NVQ_STAGE_X(buf_)                                                            \
-    do {                                                                             \
-        unsigned char *dst_ = &xs[(buf_)][(t >> 3) * kXRowBytes + 16 * (t & 7)];     \
-        *reinterpret_cast<uint4 *>(dst_) = xn0;                                      \
-        *reinterpret_cast<uint4 *>(dst_ + 32 * kXRowBytes) = xn1;                    \
-        *reinterpret_cast<uint4 *>(dst_ + 64 * kXRowBytes) = xn2;                    \
-        *reinterpret_cast<uint4 *>(dst_ + 96 * kXRowBytes) = xn3;                    \
-        *reinterpret_cast<uint4 *>(dst_ + 128 * kXRowBytes) = xn4;                   \
-        *reinterpret_cast<uint4 *>(dst_ + 160 * kXRowBytes) = xn5;                   \
-        *reinterpret_cast<uint4 *>(dst_ + 192 * kXRowBytes) = xn6;                   \
-        *reinterpret_cast<uint4 *>(dst_ + 224 * kXRowBytes) = xn7;                   \
-    } while (0)
-
-    NVQ_REQUEST(0);
-    NVQ_STAGE_X(0);
-    uint4 wc0 = wn0, wc1 = wn1;
-    uint32_t hc0 = hn0, hc1 = hn1;
-    NVQ_REQUEST((P > 1 ? 1 : 0));
-    __syncthreads();
-
-    for (int p = 0; p < P; ++p) {
-        const int cur = p & 1;
-        // next pair: stage what was requested during the pair before, ask for the one after
-        const uint4 wnext0 = wn0, wnext1 = wn1;
-        const uint32_t hnext0 = hn0, hnext1 = hn1;
-        NVQ_STAGE_X(cur ^ 1);  // everyone left this buffer before the last barrier
-        {
-            const int p2 = p + 2 < P ? p + 2 : P - 1;
-            NVQ_REQUEST(p2);
-        }
-        const uint4 wc[2] = {wc0, wc1};
-        const float sv[2] = {half_bits_to_float((uint16_t)hc0), half_bits_to_float((uint16_t)hc1)};
-        const float m8[2] = {-8.0f * sv[0], -8.0f * sv[1]};
-#pragma unroll
-        for (int st = 0; st < 4; ++st) {
-            bf16x8 b[2];
-#pragma unroll
-            for (int rt = 0; rt < 2; ++rt) {
-                const uint32_t d0 = (st & 1) ? wc[rt].z : wc[rt].x, d1 = (st & 1) ? wc[rt].w : wc[rt].y;
-                b[rt] = (st < 2) ? dequant8(d0 & 0x0f0f0f0fu, d1 & 0x0f0f0f0fu, sv[rt], m8[rt])
-                                 : dequant8((d0 >> 4) & 0x0f0f0f0fu, (d1 >> 4) & 0x0f0f0f0fu, sv[rt],
-                                            m8[rt]);
-            }
-#pragma unroll
-            for (int tt = 0; tt < 4; ++tt) {
-                const unsigned char *row =
-                    &xs[cur][(wm * 128 + tt * 32 + li) * kXRowBytes + 64 * lb + 16 * st];
-                const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(row));
-#pragma unroll
-                for (int rt = 0; rt < 2; ++rt)
-                    acc[tt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[rt], acc[tt][rt], 0, 0, 0);
-            }
-        }
-        wc0 = wnext0;
-        wc1 = wnext1;
-        hc0 = hnext0;
-        hc1 = hnext1;
-        __syncthreads();
-    }
-
-#undef NVQ_REQUEST
-#undef NVQ_STAGE_X
-
-    // result tile: lane (j, b) holds weight row j; register r holds token
-    // 8 * (r / 4) + 4 * b + r % 4
-#pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-        for (int rt = 0; rt < 2; ++rt) {
-            const int n = n0 + wn * 64 + rt * 32 + li;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int m = m0 + wm * 128 + tt * 32 + 8 * (r >> 2) + 4 * lb + (r & 3);
-                if (m < M && n < N) {
-                    if (F32)
-                        reinterpret_cast<float *>(y)[(size_t)m * N + n] = acc[tt][rt][r];
-                    else
-                        reinterpret_cast<uint16_t *>(y)[(size_t)m * N + n] =
-                            float_to_bf16_bits(acc[tt][rt][r]);
-                }
-            }
-        }
-}
-
 
 // ---- wide tiles --------------------------------------------------------------
 // 256 tokens x 256 weight rows per workgroup, four waves, one per SIMD with the
@@ -613,6 +442,514 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
         }
 }
 
+// ---- smaller tiles -----------------------------------------------------------
+// For outputs too small to give every compute unit a 256 x 256 tile: a workgroup of
+// four waves owns 32 TT tokens x 32 RT WN weight rows; WN waves lie side by side along
+// the rows (each 32 RT of them, all the tokens) and WK = 4 / WN share out K in blocks of
+// two pairs of groups (128 inputs), slice k the blocks k, k + WK, ...; the partial tiles
+// are added through LDS in slice order at the end.  As with the wide tiles everything
+// goes straight from global memory into LDS, 16 bytes per lane,
+//  - the activations of a slice's pair (128 bytes per token, three buffers; the WN waves
+//    of a slice load and read them together, one barrier per pair, none for WN = 1),
+//  - a wave's packed weights of a block (64 bytes per row, two buffers; an instruction
+//    covers 16 rows: loaded by the lane that needs them it touches 32 lines, which took a
+//    third of the time),
+//  - its scales of a block (two buffers; 4 bytes per row and pair),
+// in the wide kernel's permuted order, and everything besides the MFMAs is dealt between
+// them.  TAIL: the number of groups is no multiple of four (a block then ends past the
+// row: the last group again, with scale 0) or the scales are not aligned to 4 bytes.
+//
+// What bounds it: the activations' way from L2 into the compute units (about 50 bytes
+// per ns and unit with all of them busy: a 64 x 64 tile moves 10 KiB per 0.5 MFLOP and is
+// held by that, at 580 TFLOP/s; 128 x 128 moves half as much per FLOP, 128 x 256 with one
+// slice a third) and the vector work of the dequantisation, which serves 64 or 128 tokens;
+// against both stands the number of tiles, which has to fill 256 compute units.  One 64 x
+// 64 tile, in us: 4.2 + 0.6 per pair.  1024 tokens x 4096 rows x K = 4096: 39 us, against
+// 78 of the wide tiles (64 of them); 333 x 3072 x 3072: 17 against 69 of the 256 x 128
+// tiles that took these before; 48 x 2048 x 8192: 16 against 173.
+//
+// Nibble -> weight: a nibble under the bits of the fp16 number 1024 is 1024 + n (in bits
+// 4-7: 1024 + 16 n), two per instruction, and a mixed-precision FMA takes the fp16 halves
+// as they are: (1024 + n) * s - 1032 * s, one rounding of a number that needs none (n - 8
+// has 4, s 11 significant bits).  17 instructions per 8 weights against 23 through bytes.
+constexpr int kTileWaves = 4;
+
+template <bool F32, int TT, int RT, int WN, bool TAIL>
+__global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
+gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char *__restrict__ sc,
+                         int N, int G, const unsigned char *__restrict__ x, int M, int row_tiles,
+                         int token_tiles, void *__restrict__ y) {
+    constexpr int WK = kTileWaves / WN;     // slices of K
+    constexpr int NM = TT * RT;           // MFMAs of a step (16 inputs per lane half)
+    constexpr int kTokens = 32 * TT, kBufA = kTokens * 128;  // bytes of an activation buffer
+    constexpr int NA = 4 * TT / WN;       // activation loads of a wave and pair
+    constexpr int kW = RT * 32 * 64;      // packed weights of a block
+    constexpr int kS = RT * 512;          // scales of a block
+    constexpr int kLds = WK * 3 * kBufA + kTileWaves * (2 * kW + 2 * kS);
+    constexpr int kRegs = TT * RT * 16;   // result registers per lane
+    constexpr int kScOps = TAIL ? 2 * RT : 2, kWOps = 2 * RT;
+    constexpr int kEven = kWOps + kScOps + NA, kOdd = NA;  // loads of an even and an odd pair's list
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds];
+
+    // Tiles are numbered along the tokens first; workgroup b runs on XCD b % 8 and takes
+    // one of that XCD's eighth of the numbers, so that the tiles of a row range are worked
+    // off on one XCD and its weights are fetched into one L2.
+    const int tiles = row_tiles * token_tiles, per_xcd = (tiles + 7) >> 3;
+    const int tile = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
+    if (tile >= tiles) return;
+    const int row_tile = tile / token_tiles, token_tile = tile % token_tiles;
+
+    const int t = threadIdx.x, lane = t & 63;
+    const int w = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int li = lane & 31, lb = lane >> 5;
+    const int m0 = token_tile * kTokens;
+    const int wn = w % WN, wk = w / WN;  // the wave's rows and slice of K
+    const int n0 = row_tile * (32 * RT * WN) + wn * (32 * RT) < N ? row_tile * (32 * RT * WN) + wn * (32 * RT)
+                                                                   : N - 1;  // the wave's first row
+    unsigned char *const xa = lds + wk * 3 * kBufA;
+    unsigned char *const bw = lds + WK * 3 * kBufA + w * (2 * kW + 2 * kS);
+    unsigned char *const bs = bw + 2 * kW;
+
+    const int NB = (G + 3) >> 2;  // blocks
+    // Blocks of this wave's slice, and of the longest (waves that share activations meet at
+    // barriers, of which all of the workgroup must see as many).  Nothing is multiplied past
+    // the end of K except by the zero scale of an odd last group's missing partner.
+    const int nblk = NB > wk ? (NB - wk + WK - 1) / WK : 0, nblk_max = (NB + WK - 1) / WK;
+
+    // Activation loads: instruction j fills rows 8 j .. + 7 of a buffer, lane l position
+    // l % 8 of row l / 8 (past the last token: the last token again; not stored).  Weight
+    // loads: instruction j rows 16 j .. + 15, lane l position l % 4 of row l / 4.
+    const unsigned char *const xbase = x + (size_t)m0 * (size_t)(G * 64);
+    uint32_t xo[NA];
+#pragma unroll
+    for (int j = 0; j < NA; ++j) {
+        const int r = 8 * (NA * wn + j) + (lane >> 3);
+        const int c = (lane & 7) ^ ((r >> 1) & 7);
+        xo[j] = (uint32_t)(m0 + r < M ? r : M - 1 - m0) * (uint32_t)(G * 64) + (TAIL ? 0u : 16u * (uint32_t)c);
+    }
+    const int xc0 = (lane & 7) ^ (lane >> 4), xc1 = xc0 ^ 4;  // the piece, even and odd j
+    const unsigned char *const qbase = qw + (size_t)n0 * (size_t)(G * 16);
+    const unsigned char *const sbase = sc + (size_t)n0 * (size_t)(G * 2);
+    const int qc = (lane & 3) ^ ((lane >> 4) & 3);
+    uint32_t qo[2 * RT], so[RT];
+#pragma unroll
+    for (int j = 0; j < 2 * RT; ++j) {
+        const int r = 16 * j + (lane >> 2);
+        qo[j] = (uint32_t)(n0 + r < N ? r : N - 1 - n0) * (uint32_t)(G * 16) + (TAIL ? 0u : 16u * (uint32_t)qc);
+    }
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        // TAIL: per row tile, the lane's own scale; else lane = row, both scales of a pair
+        const int r = TAIL ? rt * 32 + li : (RT == 2 ? lane : li);
+        so[rt] = (uint32_t)(n0 + r < N ? r : N - 1 - n0) * (uint32_t)(G * 2);
+    }
+    const int last = nblk > 0 ? nblk - 1 : 0;
+    auto group_of = [&](int b) { return 4 * (wk + WK * (b < last ? b : last)); };  // first group of block b
+    auto clamp_g = [&](int g) { return g < G ? g : G - 1; };
+    auto issue_a1 = [&](unsigned char *buf, int q, int j) {  // of the wave's pair q
+        const int g0 = group_of(q >> 1) + 2 * (q & 1);
+        const unsigned char *src;
+        if (TAIL) {
+            const int c = ((NA * wn + j) & 1) ? xc1 : xc0;
+            src = xbase + (xo[j] + 64u * (uint32_t)clamp_g(g0 + (c >> 2)) + 16u * (uint32_t)(c & 3));
+        } else {
+            src = xbase + (size_t)g0 * 64 + xo[j];
+        }
+        __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_ptr)(buf + (NA * wn + j) * 1024), 16, 0, 0);
+    };
+    auto issue_w1 = [&](int b, int sel, int j) {
+        const int g0 = group_of(b);
+        const unsigned char *src = TAIL ? qbase + (qo[j] + 16u * (uint32_t)clamp_g(g0 + qc))
+                                        : qbase + (size_t)g0 * 16 + qo[j];
+        __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_ptr)(bw + sel * kW + j * 1024), 16, 0, 0);
+    };
+    auto issue_s1 = [&](int b, int sel, int k) {
+        const int g0 = group_of(b);
+        if (TAIL) {
+            const int pp = k / RT, rt = k % RT;
+            const unsigned char *src = sbase + (so[rt] + 2u * (uint32_t)clamp_g(g0 + 2 * pp + lb));
+            __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_ptr)(bs + sel * kS + k * 256), 2, 0, 0);
+        } else {
+            const unsigned char *src = sbase + (size_t)(g0 + 2 * k) * 2 + so[0];
+            __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_ptr)(bs + sel * kS + k * 256), 4, 0, 0);
+        }
+    };
+    // op k of the list of pair q: even q the weights and scales of block q / 2 + 2 and the
+    // activations of pair q + 3, odd q those alone; quarter `qu` of the list
+    auto load_op = [&](int q, bool even, int sel, unsigned char *abuf, int k) {
+        if (even) {
+            if (k < kWOps) return issue_w1((q >> 1) + 2, sel, k);
+            k -= kWOps;
+            if (k < kScOps) return issue_s1((q >> 1) + 2, sel, k);
+            k -= kScOps;
+        }
+        issue_a1(abuf, q + 3, k);
+    };
+
+    floatx16 acc[TT][RT];
+#pragma unroll
+    for (int tt = 0; tt < TT; ++tt)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[tt][rt][r] = 0.0f;
+
+    const uint32_t xa0 = (uint32_t)(uintptr_t)xa;
+    uint32_t apos[4];
+#pragma unroll
+    for (int st = 0; st < 4; ++st) apos[st] = xa0 + li * 128 + 16 * ((4 * lb + st) ^ ((li >> 1) & 7));
+    const uint32_t bwpos = (uint32_t)(uintptr_t)bw + li * 64 + 16 * (lb ^ ((li >> 2) & 3));
+    const uint32_t bspos = (uint32_t)(uintptr_t)bs + 4 * (TAIL ? lane : li);
+    uint32_t mask_lo = 0x000f000fu, mask_hi = 0x00f000f0u, magic = 0x64006400u;
+    asm("" : "+s"(mask_lo));
+    asm("" : "+s"(mask_hi));
+    asm("" : "+v"(magic));
+
+    struct BRaw {
+        uint4v w[RT];
+        uint32_t h[RT];
+    };
+    struct Nibbles {
+        uint32_t d[RT][4], e[RT][4];  // packed words, and shifted by 8
+        float s[RT][2], c[RT][2];     // scale and offset for low and high nibbles
+    };
+    uint4v a[2][TT];
+    uint32_t bo[2][RT][4];
+    BRaw braw;
+    Nibbles nba, nbb;
+    auto read_a = [&](uint32_t addr, uint4v (&v)[TT]) {
+        asm volatile("ds_read_b128 %0, %1" : "=v"(v[0]) : "v"(addr));
+        asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(v[1]) : "v"(addr));
+        if (TT == 4) {
+            asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(v[TT - 2]) : "v"(addr));
+            asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(v[TT - 1]) : "v"(addr));
+        }
+    };
+    auto read_b = [&](uint32_t waddr, uint32_t saddr) {
+        asm volatile("ds_read_b128 %0, %1" : "=v"(braw.w[0]) : "v"(waddr));
+        if (RT == 2) asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(braw.w[RT - 1]) : "v"(waddr));
+        asm volatile("ds_read_b32 %0, %1" : "=v"(braw.h[0]) : "v"(saddr));
+        if (RT == 2) {
+            if (TAIL)
+                asm volatile("ds_read_b32 %0, %1 offset:256" : "=v"(braw.h[RT - 1]) : "v"(saddr));
+            else
+                asm volatile("ds_read_b32 %0, %1 offset:128" : "=v"(braw.h[RT - 1]) : "v"(saddr));
+        }
+    };
+    auto arrived_a = [&](uint4v (&v)[TT]) {
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]));
+        if (TT == 4) asm volatile("" : "+v"(v[TT - 2]), "+v"(v[TT - 1]));
+    };
+    auto arrived_b = [&](uint4v (&v)[TT]) {
+        if (RT == 2)
+            asm volatile("s_waitcnt lgkmcnt(0)"
+                         : "+v"(v[0]), "+v"(v[1]), "+v"(braw.w[0]), "+v"(braw.w[RT - 1]),
+                           "+v"(braw.h[0]), "+v"(braw.h[RT - 1]));
+        else
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(braw.w[0]), "+v"(braw.h[0]));
+        if (TT == 4) asm volatile("" : "+v"(v[TT - 2]), "+v"(v[TT - 1]));
+    };
+    // row tile rt of the pair whose first group is g
+    auto unpack = [&](Nibbles &nb, int rt, int g) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            nb.d[rt][i] = braw.w[rt][i];
+            nb.e[rt][i] = braw.w[rt][i] >> 8;
+        }
+        uint32_t hb = braw.h[rt];
+        if (TAIL)
+            hb = g + lb < G ? hb : 0u;
+        else
+            hb >>= 16 * lb;
+        const float s = half_bits_to_float((uint16_t)hb);
+        nb.s[rt][0] = s;
+        nb.s[rt][1] = 0.0625f * s;
+        nb.c[rt][0] = -1032.0f * s;
+        nb.c[rt][1] = -72.0f * s;
+    };
+    // four weights (words 2 h, 2 h + 1 of the operand) of row tile rt, MFMA step st
+    auto dequant4 = [&](const Nibbles &nb, int st, int rt, int h, uint32_t (&o)[4]) {
+        const int hi = st >> 1, i = 2 * (st & 1) + h;
+        const uint32_t mask = hi ? mask_hi : mask_lo;
+        const halfx2 ev = __builtin_bit_cast(halfx2, (nb.d[rt][i] & mask) | magic);
+        const halfx2 od = __builtin_bit_cast(halfx2, (nb.e[rt][i] & mask) | magic);
+        const float s = nb.s[rt][hi], c = nb.c[rt][hi];
+        o[2 * h] = pack_bf16(fmaf((float)ev.x, s, c), fmaf((float)od.x, s, c));
+        o[2 * h + 1] = pack_bf16(fmaf((float)ev.y, s, c), fmaf((float)od.y, s, c));
+    };
+
+    // Step st of the pair in registers while the operands of step nst of the pair at LDS
+    // offset `nbuf` with the nibbles wn are made.  extra = 1: also reads the next pair's
+    // packed weights; 2: also unpacks them.  A quarter of the load list of pair lq.
+    auto step = [&](int st, uint32_t nbuf, const Nibbles &wc, int nst, int extra, uint32_t waddr,
+                    uint32_t saddr, Nibbles &wnext, int gnext, int lq, bool even, int quarter, int sel,
+                    unsigned char *abuf) {
+        const int c = st & 1, n = c ^ 1;
+        const int ops = even ? kEven : kOdd;
+        const int first = ops * quarter / 4, count = ops * (quarter + 1) / 4 - first;
+#pragma unroll
+        for (int i = 0; i < NM; ++i) {
+            const int tt = i / RT, rt = i % RT;
+            acc[tt][rt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                __builtin_bit_cast(bf16x8, a[c][tt]),
+                __builtin_bit_cast(bf16x8, make_uint4(bo[c][rt][0], bo[c][rt][1], bo[c][rt][2], bo[c][rt][3])),
+                acc[tt][rt], 0, 0, 0);
+            if (i == 0) read_a(apos[nst] + nbuf, a[n]);
+            if (extra == 1 && i == 0) read_b(waddr, saddr);
+            if (NM == 2 * RT)
+                dequant4(wc, nst, i >> 1, i & 1, bo[n][i >> 1]);
+            else if (!(i & 1))
+                dequant4(wc, nst, i >> 2, (i >> 1) & 1, bo[n][i >> 2]);
+            if (extra == 2 && i < RT) unpack(wnext, i, gnext);
+#pragma unroll
+            for (int m = 0; m < count; ++m)
+                if (m * NM / count == i) load_op(lq, even, sel, abuf, first + m);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (extra == 1)
+            arrived_b(a[n]);
+        else
+            arrived_a(a[n]);
+    };
+#define NVQ_PIN asm volatile("" ::: "memory")
+    if (nblk > 0) {
+        // weights of blocks 0 and 1, activations of pairs 0 and 1 and a quarter of pair 2's
+#pragma unroll
+        for (int k = 0; k < kWOps; ++k) issue_w1(0, 0, k);
+#pragma unroll
+        for (int k = 0; k < kScOps; ++k) issue_s1(0, 0, k);
+#pragma unroll
+        for (int j = 0; j < NA; ++j) issue_a1(xa, 0, j);
+#pragma unroll
+        for (int j = 0; j < NA; ++j) issue_a1(xa + kBufA, 1, j);
+#pragma unroll
+        for (int k = 0; k < kWOps; ++k) issue_w1(1, 1, k);
+#pragma unroll
+        for (int k = 0; k < kScOps; ++k) issue_s1(1, 1, k);
+#pragma unroll
+        for (int j = 0; j < NA / 4; ++j) issue_a1(xa + 2 * kBufA, 2, j);
+        NVQ_PIN;
+        __builtin_amdgcn_s_waitcnt(wide_vmcnt(NA + kWOps + kScOps + NA / 4));
+        if (WN > 1) __builtin_amdgcn_s_barrier();
+        NVQ_PIN;
+        read_b(bwpos, bspos);
+        read_a(apos[0], a[0]);
+        arrived_b(a[0]);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) unpack(nba, rt, group_of(0));
+#pragma unroll
+        for (int i = 0; i < 2 * RT; ++i) dequant4(nba, 0, i >> 1, i & 1, bo[0][i >> 1]);
+
+        // Pair q: the wait before step 3 lets the list of pair q - 1 stay in flight and ends
+        // all older loads: the activations of pair q + 1, read next, are in the list of pair
+        // q - 2, its weights in that of pair q - 2 or older.
+        int cur = 0, prv = 2 * kBufA, wsel = 0;
+        for (int b = 0; b < nblk; ++b) {
+#define NVQ_PAIR(odd_, nb, nnb)                                                                    \
+    do {                                                                                           \
+        const int q_ = 2 * b + (odd_);                                                             \
+        const int nsel_ = (odd_) ? wsel ^ 1 : wsel; /* weight buffer of the next pair */           \
+        const uint32_t waddr_ = (bwpos + nsel_ * kW) ^ ((odd_) ? 0 : 32);                          \
+        const uint32_t saddr_ = bspos + nsel_ * kS + ((odd_) ? 0 : (TAIL ? RT * 256 : 256));       \
+        const int gnext_ = (odd_) ? group_of(b + 1) : group_of(b) + 2;                             \
+        const int nxt_ = cur + kBufA == 3 * kBufA ? 0 : cur + kBufA;                                  \
+        step(0, cur, nb, 1, 0, 0, 0, nnb, 0, q_ - 1, (odd_), 1, wsel, xa + prv);                   \
+        step(1, cur, nb, 2, 1, waddr_, saddr_, nnb, 0, q_ - 1, (odd_), 2, wsel, xa + prv);         \
+        step(2, cur, nb, 3, 2, 0, 0, nnb, gnext_, q_ - 1, (odd_), 3, wsel, xa + prv);              \
+        __builtin_amdgcn_s_waitcnt(wide_vmcnt((odd_) ? kEven : kOdd));                             \
+        if (WN > 1) __builtin_amdgcn_s_barrier();                                                  \
+        NVQ_PIN;                                                                                   \
+        step(3, nxt_, nnb, 0, 0, 0, 0, nb, 0, q_, !(odd_), 0, wsel, xa + cur);                     \
+        NVQ_PIN;                                                                                   \
+        prv = cur;                                                                                 \
+        cur = nxt_;                                                                                \
+    } while (0)
+            NVQ_PAIR(0, nba, nbb);
+            if (TAIL && group_of(b) + 2 >= G) {  // the last block has one pair only
+                if (WN > 1) __builtin_amdgcn_s_barrier();
+                break;
+            }
+            NVQ_PAIR(1, nbb, nba);
+#undef NVQ_PAIR
+            wsel ^= 1;
+        }
+    } else if (WN > 1) {
+        __builtin_amdgcn_s_barrier();
+    }
+    if (WN > 1)
+        for (int b = 2 * nblk; b < 2 * nblk_max; ++b) __builtin_amdgcn_s_barrier();
+#undef NVQ_PIN
+    // no load into LDS may outlive the loop
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+
+    // Result tile: lane (j, b) holds weight row j; register r token 8 (r / 4) + 4 b + r % 4.
+    // The partial tiles of the slices are added through LDS: of the WK waves with the same
+    // rows, wave u owns registers u kMine .. and the others hand theirs over, four registers
+    // (16 bytes) per lane at a time; the sum is taken in slice order.
+    constexpr int kMine = kRegs / WK;
+    constexpr int kOwnRt = kMine >= 16 * RT ? RT : 1;  // row tiles and tokens a wave owns
+    constexpr int kOwnTok = kMine * 2 / kOwnRt;
+    constexpr int kRed = kTileWaves * kRegs * 256 / WK * (WK - 1), kOut = kMine * 128;
+    static_assert(kRed + kTileWaves * kOut <= kLds, "partial tiles and results fit");
+    float v[kMine];
+    __syncthreads();  // every wave has left the loop
+    if (WK > 1) {
+        auto part = [&](int owner, int from) {  // where `from` leaves its part for `owner`
+            const int slot = from < owner ? from : from - 1;
+            return reinterpret_cast<floatx4 *>(lds) + (((wn * WK + owner) * (WK - 1) + slot) * (kMine / 4)) * 64 + lane;
+        };
+#pragma unroll
+        for (int u = 0; u < WK; ++u) {
+            if (u == wk) continue;
+            floatx4 *const dst = part(u, wk);
+#pragma unroll
+            for (int i = 0; i < kMine / 4; ++i) {
+                const int k = u * kMine + 4 * i, tt = k / (16 * RT), rt = (k >> 4) % RT, r = k & 15;
+                const floatx4 f = {acc[tt][rt][r], acc[tt][rt][r + 1], acc[tt][rt][r + 2], acc[tt][rt][r + 3]};
+                dst[i * 64] = f;
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) v[i] = 0.0f;
+#pragma unroll
+        for (int u = 0; u < WK; ++u) {
+            if (u == wk) {
+#pragma unroll
+                for (int i = 0; i < kMine; ++i) {
+                    const int k = u * kMine + i;
+                    v[i] += acc[k / (16 * RT)][(k >> 4) % RT][k & 15];
+                }
+            } else {
+                const floatx4 *const src = part(wk, u);
+#pragma unroll
+                for (int i = 0; i < kMine / 4; ++i) {
+                    const floatx4 f = src[i * 64];
+                    v[4 * i] += f.x;
+                    v[4 * i + 1] += f.y;
+                    v[4 * i + 2] += f.z;
+                    v[4 * i + 3] += f.w;
+                }
+            }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) v[i] = acc[i / (16 * RT)][(i >> 4) % RT][i & 15];
+    }
+    // first token and row of what this wave owns
+    const int k0 = wk * kMine;
+    const int mo = m0 + (k0 / (16 * RT)) * 32 + 2 * (k0 & 15);
+    const int no = row_tile * (32 * RT * WN) + wn * (32 * RT) + (kOwnRt == RT ? 0 : ((k0 >> 4) % RT) * 32);
+    auto token_of = [&](int i) { return (i / (16 * kOwnRt)) * 32 + 8 * ((i & 15) >> 2) + 4 * lb + (i & 3); };
+    if (!F32 && (N & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0) {
+        // bf16 results leave as 16 bytes per lane, whole lines where a wave owns 64 rows: through
+        // LDS, pieces permuted as in the wide kernel; the wave reads back what it wrote itself
+        constexpr int kPieces = kOwnRt * 4;
+        unsigned char *const out = lds + kRed + w * kOut;
+#pragma unroll
+        for (int i = 0; i < kMine; ++i) {
+            const int tok = token_of(i), nl = ((i >> 4) % kOwnRt) * 32 + li;
+            const int pos = (nl >> 3) ^ ((tok >> 2) & (kPieces - 1));
+            *reinterpret_cast<uint16_t *>(out + (tok * kPieces + pos) * 16 + (nl & 7) * 2) = float_to_bf16_bits(v[i]);
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < kOwnTok * kPieces / 64; ++i) {
+            const int idx = i * 64 + lane;
+            const int tok = idx / kPieces, pos = idx % kPieces;
+            const int c = pos ^ ((tok >> 2) & (kPieces - 1));
+            const uint4v q = *reinterpret_cast<const uint4v *>(out + idx * 16);
+            const int m = mo + tok, n = no + c * 8;
+            if (m < M && n < N)
+                *reinterpret_cast<uint4v *>(reinterpret_cast<uint16_t *>(y) + (size_t)m * N + n) = q;
+        }
+        return;
+    }
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+        const int m = mo + token_of(i), n = no + ((i >> 4) % kOwnRt) * 32 + li;
+        if (m < M && n < N) store_out(y, F32 ? NVQ_F32 : NVQ_BF16, (int64_t)m * N + n, v[i]);
+    }
+}
+
+// The tiles a product can be cut into, and what they take (us, measured on one box): a
+// tile `fixed` and per pair of groups and slice `pair`, plus `busy` times the share of the
+// compute units that are at work (they share the L2 caches and the power).
+struct GemmTile {
+    int tokens, rows, slices;
+    float fixed, pair, busy;
+    const char *name;  // for NVQ_GEMM_TILE
+};
+constexpr GemmTile kGemmTiles[] = {
+    {256, 256, 1, 4.0f, 1.34f, 0.25f, "wide"},   {128, 256, 1, 5.5f, 0.72f, 0.30f, "128x256"},
+    {128, 128, 2, 4.7f, 0.70f, 0.37f, "128x128"}, {128, 64, 2, 5.0f, 0.44f, 0.12f, "128x64"},
+    {64, 64, 4, 4.2f, 0.52f, 0.10f, "64x64"},     {64, 32, 4, 3.9f, 0.37f, 0.11f, "64x32"},
+};
+constexpr int kGemmTileKinds = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
+
+int64_t gemm_tiles(const GemmTile &k, int64_t N, int64_t M) {
+    return ((N + k.rows - 1) / k.rows) * ((M + k.tokens - 1) / k.tokens);
+}
+
+// The kind of tile with the smallest estimated time: whole rounds of all compute units,
+// then the rest.  Between neighbouring kinds the estimates are within 15 % of what was
+// measured over 33 to 4096 tokens; where two are that close either will do.
+int gemm_choose(int64_t N, int64_t G, int64_t M, bool can_wide) {
+    const int64_t cus = device_cu_count();
+    int best = -1;
+    double best_us = 0.0;
+    for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i) {
+        const GemmTile &k = kGemmTiles[i];
+        const int64_t n = gemm_tiles(k, N, M), full = n / cus;
+        const double part = (double)(n % cus) / (double)cus;
+        const double steps = (double)(((G + 1) / 2 + k.slices - 1) / k.slices);
+        double us = (double)full * (k.fixed + steps * (k.pair + k.busy));
+        if (part > 0.0) us += k.fixed + steps * (k.pair + k.busy * (full ? 1.0 : part));
+        if (best < 0 || us < best_us) {
+            best = i;
+            best_us = us;
+        }
+    }
+    return best;
+}
+
+template <bool F32, int TT, int RT, int WN>
+void launch_tile(bool tail, dim3 grid, hipStream_t st, const unsigned char *q, const unsigned char *s,
+                 int N, int G, const unsigned char *x, int M, int row_tiles, int token_tiles, void *y) {
+    const dim3 block(kTileWaves * 64);
+    if (tail)
+        hipLaunchKernelGGL((gemm_w4a16_tile_kernel<F32, TT, RT, WN, true>), grid, block, 0, st, q, s, N, G, x,
+                           M, row_tiles, token_tiles, y);
+    else
+        hipLaunchKernelGGL((gemm_w4a16_tile_kernel<F32, TT, RT, WN, false>), grid, block, 0, st, q, s, N, G,
+                           x, M, row_tiles, token_tiles, y);
+}
+
+template <bool F32>
+int launch_gemm(int kind, const unsigned char *q, const unsigned char *s, int N, int G,
+                const unsigned char *x, int M, void *y, hipStream_t st) {
+    const GemmTile &k = kGemmTiles[kind];
+    const int64_t tiles = gemm_tiles(k, N, M);
+    if (tiles > (int64_t)0x7ffffff8) return NVQ_ERR_SHAPE;
+    if (kind == 0) {
+        hipLaunchKernelGGL(gemm_w4a16_wide_kernel<F32>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, q, s,
+                           N, G, x, M, y);
+    } else {
+        const int rt = (int)((N + (int64_t)k.rows - 1) / k.rows), tt = (M + k.tokens - 1) / k.tokens;
+        const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
+        const bool tail = (G & 3) != 0 || !aligned(s, 4);
+        switch (kind) {
+            case 1: launch_tile<F32, 4, 2, 4>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
+            case 2: launch_tile<F32, 4, 2, 2>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
+            case 3: launch_tile<F32, 4, 1, 2>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
+            case 4: launch_tile<F32, 2, 2, 1>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
+            default: launch_tile<F32, 2, 1, 1>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
+        }
+    }
+    NVQ_HIP_TRY(hipGetLastError());
+    return NVQ_OK;
+}
+
 }  // namespace
 
 }  // namespace nvq
@@ -629,43 +966,19 @@ extern "C" int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, in
     if (!aligned(qweight, 16) || !aligned(scales, 2) || !aligned(x_bf16, 16) ||
         !aligned(y, y_dtype == NVQ_F32 ? 4 : 2))
         return NVQ_ERR_ALIGN;
-    // The wide tiles need K % 256 == 0 and enough tiles to occupy the machine; the
-    // environment variable NVQ_GEMM_TILE (wide | narrow) overrides the choice where
-    // both kernels can run (used by the tests to reach both on small shapes).
-    const int64_t tiles = ((N + kWideRows - 1) / kWideRows) * ((M + kWideTokens - 1) / kWideTokens);
-    // (its loads move 16 bytes of scales at a time: the scales 16-byte aligned, too)
+    // The wide tiles take whole blocks of K and move 16 bytes of scales at a time.  The
+    // environment variable NVQ_GEMM_TILE (the name of a tile; "narrow" for 128x256) overrides
+    // the choice where the kernel can run (the tests reach all of them on small shapes).
     const bool can_wide = (K % 256) == 0 && aligned(scales, 16);
-    bool wide = can_wide && tiles >= 32;
+    int kind = gemm_choose(N, K / 32, M, can_wide);
     if (const char *force = getenv("NVQ_GEMM_TILE")) {
-        if (force[0] == 'w' && can_wide) wide = true;
-        if (force[0] == 'n') wide = false;
+        if (strcmp(force, "narrow") == 0) force = "128x256";
+        for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i)
+            if (strcmp(force, kGemmTiles[i].name) == 0) kind = i;
     }
-    if (wide) {
-        if (tiles > (int64_t)0x7fffffff) return NVQ_ERR_SHAPE;
-        const dim3 wgrid((unsigned)tiles);
-        const unsigned char *xb = reinterpret_cast<const unsigned char *>(x_bf16);
-        const unsigned char *sb = reinterpret_cast<const unsigned char *>(scales);
-        if (y_dtype == NVQ_F32)
-            hipLaunchKernelGGL(gemm_w4a16_wide_kernel<true>, wgrid, dim3(kGemmThreads), 0,
-                               (hipStream_t)stream, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y);
-        else
-            hipLaunchKernelGGL(gemm_w4a16_wide_kernel<false>, wgrid, dim3(kGemmThreads), 0,
-                               (hipStream_t)stream, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y);
-        NVQ_HIP_TRY(hipGetLastError());
-        return NVQ_OK;
-    }
-    const dim3 grid((unsigned)((N + kGemmRows - 1) / kGemmRows),
-                    (unsigned)((M + kGemmTokens - 1) / kGemmTokens)),
-        block(kGemmThreads);
-    if (grid.y > 65535u) return NVQ_ERR_SHAPE;
-    const uint4 *qw = reinterpret_cast<const uint4 *>(qweight);
-    const uint4 *x = reinterpret_cast<const uint4 *>(x_bf16);
+    const unsigned char *const sb = reinterpret_cast<const unsigned char *>(scales);
+    const unsigned char *const xb = reinterpret_cast<const unsigned char *>(x_bf16);
     if (y_dtype == NVQ_F32)
-        hipLaunchKernelGGL(gemm_w4a16_kernel<true>, grid, block, 0, (hipStream_t)stream, qw, scales,
-                           (int)N, (int)(K / 32), x, (int)M, y);
-    else
-        hipLaunchKernelGGL(gemm_w4a16_kernel<false>, grid, block, 0, (hipStream_t)stream, qw, scales,
-                           (int)N, (int)(K / 32), x, (int)M, y);
-    NVQ_HIP_TRY(hipGetLastError());
-    return NVQ_OK;
+        return launch_gemm<true>(kind, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
+    return launch_gemm<false>(kind, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
 }

@@ -1048,6 +1048,56 @@ def test_gemm_w4a16_wide_tiles_match_oracle(M, N, K, monkeypatch):
     assert torch.equal(y, yn)
 
 
+# The smaller tiles, each kind forced (the library chooses by size): one row and token, edges of
+# the 32 x 32 MFMA tiles and of the workgroup tiles, K from one group on (fewer blocks of four
+# groups than slices, and numbers that the slices cannot share evenly), K that ends inside a block,
+# rows no multiple of 8 (results stored one by one), scales and results off their usual alignment.
+# Tolerance: fp32 sums of exact products, up to 2048 terms in any order.
+@pytest.mark.parametrize("tile", ["128x256", "128x128", "128x64", "64x64", "64x32"])
+@pytest.mark.parametrize("M,N,K,off", [(1, 1, 32, 0), (65, 33, 96, 0), (64, 64, 128, 0),
+                                       (63, 257, 640, 0), (129, 130, 416, 1), (200, 520, 2048, 0),
+                                       (33, 72, 1152, 1)])
+def test_gemm_w4a16_small_tiles_match_oracle(tile, M, N, K, off, monkeypatch):
+    say("gemm tile", tile, M, N, K, off)
+    monkeypatch.setenv("NVQ_GEMM_TILE", tile)
+    _, q, s = packed(9170 + M + N, N, K)
+    xh = act(9270 + K, M, K)
+    want = oracle.gemm_w4a16_dense(q, s, u16(xh))
+    qd, sd = to_dev_packed(q, s)
+    if off:  # scales aligned to their two bytes only
+        buf = torch.zeros(sd.numel() + off, dtype=sd.dtype, device=DEV)
+        buf[off:] = sd.flatten()
+        sd = buf[off:].view(sd.shape)
+    y = nvq.gemm_w4a16(qd, sd, xh.to(DEV))
+    yb = torch.empty(M * N + off, dtype=torch.bfloat16, device=DEV)[off:].view(M, N)
+    nvq.gemm_w4a16(qd, sd, xh.to(DEV), out=yb)
+    torch.cuda.synchronize()
+    err = np_ref.rel_l2(y.cpu().numpy(), want)
+    say("  rel l2", err)
+    assert err < 1e-5
+    # the bf16 results are the fp32 ones rounded
+    assert torch.equal(yb, y.to(torch.bfloat16))
+
+
+# An infinite activation in the last group of K: infinite results, NaN only where the weight is
+# zero (K that ends inside a block, an odd number of blocks, a single one).
+@pytest.mark.parametrize("tile", ["128x256", "128x128", "128x64", "64x64", "64x32"])
+@pytest.mark.parametrize("K", [64, 192, 384])
+def test_gemm_w4a16_small_tiles_infinite_input(tile, K, monkeypatch):
+    monkeypatch.setenv("NVQ_GEMM_TILE", tile)
+    M, N = 3, 40
+    _, q, s = packed(9180, N, K)
+    xh = act(9280, M, K)
+    xh[1, K - 1] = float("inf")
+    with np.errstate(invalid="ignore"):
+        want = oracle.gemm_w4a16_dense(q, s, u16(xh))
+    qd, sd = to_dev_packed(q, s)
+    y = nvq.gemm_w4a16(qd, sd, xh.to(DEV)).cpu().numpy()
+    assert np.array_equal(np.isnan(y), np.isnan(want))
+    assert np.array_equal(np.isinf(y), np.isinf(want)) and np.isinf(y[1]).any()
+    assert np.array_equal(np.sign(y[1]), np.sign(want[1]), equal_nan=True)
+
+
 def test_gemm_w4a16_full_size_sampled():
     """A projection of the 8B block at 4096 tokens, as the benchmark launches it (the kernel with
     wide tiles, chosen by the library): sampled tokens and rows against the oracle."""
