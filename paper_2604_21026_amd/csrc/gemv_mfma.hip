@@ -1,5 +1,6 @@
 // Small-batch (2 <= M <= 32 tokens) W4A8 and W4A16 products on the matrix
-// cores.  Paper: the W4A8 / W4A16 kernel descriptions and the remark in the
+// cores, many independent phases in one launch (plans whose K are not all
+// multiples of 512; single phases go to gemv_slice.h).  Paper: the W4A8 / W4A16 kernel descriptions and the remark in the
 // limitations that batch > 1 moves the product towards compute; the weights
 // are still read once per step, so the kernel stays bound by HBM.
 //
@@ -31,7 +32,7 @@
 // loads that fetch each lane's operand bytes directly touch four times as many
 // cache lines per instruction and were bound by the L1 lookup rate.
 //
-// A workgroup owns 16 * R consecutive rows; its W (8 or 16) waves split K by
+// A workgroup owns 16 * R consecutive rows; its W waves split K by
 // 64-byte columns, each requests all loads of a pass of B columns before the
 // first MFMA, and the partial tiles are summed through LDS in wave order.
 #include "gemv_tile.h"
@@ -58,7 +59,7 @@ struct Column {
 // mfma_units works through the units unit_first, unit_first + unit_step, ...
 // of one phase (a unit = 16 * R rows); `red` is W x (R * MT * 4) x 64 floats
 // of LDS.
-template <int PREC, int R, int MT, int W, int B, bool DEBUG>
+template <int PREC, int R, int MT, int W, int B>
 __device__ __forceinline__ void mfma_units(const GemvSegs &S, int G, int M,
                                            const char *__restrict__ xin,
                                            const float *__restrict__ xscale, int unit_first,
@@ -125,7 +126,6 @@ __device__ __forceinline__ void mfma_units(const GemvSegs &S, int G, int M,
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int b = 0; b < B; ++b) {
-                const int c = c0 + b * W;
                 uint32_t q[R][4];
                 float sw[R][4];
 #pragma unroll
@@ -157,18 +157,6 @@ __device__ __forceinline__ void mfma_units(const GemvSegs &S, int G, int M,
                             f[r][mt][1] = fmaf(sw[r][i], p.y, f[r][mt][1]);
                             f[r][mt][2] = fmaf(sw[r][i], p.z, f[r][mt][2]);
                             f[r][mt][3] = fmaf(sw[r][i], p.w, f[r][mt][3]);
-                            if (DEBUG && PREC == NVQ_W4A8) {
-                                if (rr[r].valid && rr[r].dbg && c < C4) {
-                                    const int acc[4] = {raw.x, raw.y, raw.z, raw.w};
-#pragma unroll
-                                    for (int jj = 0; jj < 4; ++jj) {
-                                        const int m = mt * 16 + kb * 4 + jj;
-                                        if (m < M)
-                                            rr[r].dbg[((int64_t)m * rr[r].N + rr[r].n) * G + 4 * c +
-                                                      i] = acc[jj];
-                                    }
-                                }
-                            }
                         }
                     }
                 }
@@ -202,13 +190,6 @@ __device__ __forceinline__ void mfma_units(const GemvSegs &S, int G, int M,
     }
 }
 
-template <int PREC, int R, int MT, int W, int B, bool DEBUG>
-__global__ __launch_bounds__(W * 64) void gemv_mfma_kernel(
-    GemvSegs S, int G, int M, const char *__restrict__ xin, const float *__restrict__ xscale) {
-    __shared__ float red[W][R * MT * 4][64];
-    mfma_units<PREC, R, MT, W, B, DEBUG>(S, G, M, xin, xscale, blockIdx.x, gridDim.x, red);
-}
-
 // Grouped launch: the row tiles of many phases in one grid, one tile per
 // workgroup.  unit_phase[u] names the phase of grid unit u.
 constexpr int kGroupWaves = 4;
@@ -221,42 +202,11 @@ __global__ __launch_bounds__(kGroupWaves * 64) void gemv_mfma_group_kernel(
     const int unit = u - P.unit_begin;
     // one pass of the unit loop: the step is larger than any unit count
     if (P.precision == NVQ_W4A8)
-        mfma_units<NVQ_W4A8, R, MT, kGroupWaves, 2, false>(
+        mfma_units<NVQ_W4A8, R, MT, kGroupWaves, 2>(
             P.segs, P.G, M, reinterpret_cast<const char *>(P.xq), P.xscale, unit, 1 << 30, red);
     else
-        mfma_units<NVQ_W4A16, R, MT, kGroupWaves, 2, false>(
+        mfma_units<NVQ_W4A16, R, MT, kGroupWaves, 2>(
             P.segs, P.G, M, reinterpret_cast<const char *>(P.x_bf16), nullptr, unit, 1 << 30, red);
-}
-
-template <int PREC, int R, int MT, int W, int B, bool DEBUG>
-int launch_one(const GemvSegs &S, int G, int M, const void *x, const float *xscale,
-               hipStream_t st) {
-    const int units = (S.total_rows + 16 * R - 1) / (16 * R);
-    const int cap = device_cu_count() * 8;
-    const dim3 grid(units < cap ? units : cap), block(W * 64);
-    hipLaunchKernelGGL((gemv_mfma_kernel<PREC, R, MT, W, B, DEBUG>), grid, block, 0, st, S, G, M,
-                       reinterpret_cast<const char *>(x), xscale);
-    NVQ_HIP_TRY(hipGetLastError());
-    return NVQ_OK;
-}
-
-template <int PREC>
-int launch_prec(const GemvSegs &S, int G, int M, const void *x, const float *xscale, bool debug,
-                hipStream_t st) {
-    const bool wide = M > 16;
-    // Eight waves share a row tile, so that a compute unit holds two or three
-    // workgroups whose load and compute passes overlap; sixteen when there are
-    // too few tiles for that and each wave still gets two columns (K >= 4096).
-    const int tiles = (S.total_rows + 15) / 16;
-    const bool many = (G >> 2) >= 32 && tiles <= 2 * device_cu_count();
-#define NVQ_GO(MT, W, DBG) return launch_one<PREC, 1, MT, W, 2, DBG>(S, G, M, x, xscale, st)
-    if (debug) {  // accumulator dump, same summation order as the plain kernel
-        if (wide) { if (many) NVQ_GO(2, 16, true); else NVQ_GO(2, 8, true); }
-        if (many) NVQ_GO(1, 16, true); else NVQ_GO(1, 8, true);
-    }
-    if (wide) { if (many) NVQ_GO(2, 16, false); else NVQ_GO(2, 8, false); }
-    if (many) NVQ_GO(1, 16, false); else NVQ_GO(1, 8, false);
-#undef NVQ_GO
 }
 
 }  // namespace
@@ -278,15 +228,6 @@ int launch_gemv_mfma_group(const GroupPhase *tab, const uint16_t *unit_phase, in
         hipLaunchKernelGGL((gemv_mfma_group_kernel<1, 2>), grid, block, 0, st, tab, unit_phase, M);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
-}
-
-int launch_gemv_mfma(const GemvSegs &S, int K, int precision, const void *x, const float *xscale,
-                     int M, hipStream_t st) {
-    bool debug = false;
-    for (int i = 0; i < S.nseg; ++i) debug |= S.dbg[i] != nullptr;
-    if (precision == NVQ_W4A8)
-        return launch_prec<NVQ_W4A8>(S, K / 32, M, x, xscale, debug, st);
-    return launch_prec<NVQ_W4A16>(S, K / 32, M, x, nullptr, false, st);
 }
 
 }  // namespace nvq

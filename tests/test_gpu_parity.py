@@ -161,6 +161,40 @@ def test_gemv_w4a8_acc_bit_exact_and_output(N, K, M, group):
     assert np_ref.rel_l2(y.cpu().numpy(), y_r) < 1e-5        # what fp32 accumulation gives
 
 
+# The small-batch kernel behind the single calls: tokens at the edges of its three sizes, rows at
+# the edges of its tiles (16 rows; 32 from 12,288 rows on), K from one group on (fewer blocks of
+# eight groups than waves, blocks that end early by one to seven groups, odd numbers of groups),
+# scales aligned to 16, 4 and 2 bytes, K beyond 16384 with one token.  Tolerance: fp32 sums of
+# products that are exact or, with a scale per group, rounded twice.
+@pytest.mark.parametrize("M,N,K,off", [(2, 1, 32, 0), (8, 17, 256, 0), (9, 33, 288, 0), (16, 15, 448, 2),
+                                       (17, 48, 2112, 0), (32, 100, 4096, 1), (5, 12301, 512, 0),
+                                       (20, 12289, 352, 0), (32, 12320, 256, 2), (3, 70, 2720, 0),
+                                       (1, 40, 16416, 0)])
+def test_small_batch_kernel_edges(M, N, K, off):
+    say("slice", M, N, K, off)
+    _, q, s = packed(3300 + N, N, K)
+    xh = act(3400 + K, M, K)
+    qd, sd = to_dev_packed(q, s)
+    if off:
+        buf = torch.zeros(sd.numel() + off, dtype=sd.dtype, device=DEV)
+        buf[off:] = sd.flatten()
+        sd = buf[off:].view(sd.shape)
+    y = nvq.gemv_w4a16(qd, sd, xh.to(DEV))
+    yb = nvq.gemv_w4a16(qd, sd, xh.to(DEV), out_dtype=torch.bfloat16)
+    torch.cuda.synchronize()
+    assert np_ref.rel_l2(y.cpu().numpy(), oracle.gemv_w4a16(q, s, u16(xh))) < 1e-5
+    assert torch.equal(yb, y.to(torch.bfloat16))
+    for group in (0, 32):
+        xq, xs, gs = oracle.quant_act_i8(u16(xh), group)
+        want = oracle.gemv_w4a8(q, s, xq, xs, group)
+        xqd, xsd, gsd = nvq.quant_act_i8(xh.to(DEV), group)
+        y = nvq.gemv_w4a8(qd, sd, xqd, xsd, gsd, group)
+        torch.cuda.synchronize()
+        err = np_ref.rel_l2(y.cpu().numpy(), want)
+        say("  rel l2", group, err)
+        assert err < 1e-5
+
+
 @pytest.mark.parametrize("M", [1, 20])
 def test_gemv_w4a8_accepts_every_nibble_and_extreme_codes(M):
     say("w4a8 extremes", M)
