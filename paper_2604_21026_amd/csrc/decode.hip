@@ -227,22 +227,13 @@ int walk_per_phase(const nvq_linear *L, const std::vector<Phase> &phases, int M,
         const nvq_linear &e0 = L[ph.first];
         const bool w4a8 = e0.precision == NVQ_W4A8;
         const bool fresh = !(p > 0 && same_input(L, phases[p - 1], ph));
-        const uint16_t *x = e0.x_bf16;
-        if (e0.in_op != NVQ_IN_PLAIN) {
-            // the transformed input of the previous phase is still in ws.xt if it was the same
-            if (fresh) {
-                const int t = e0.in_op == NVQ_IN_RMSNORM
-                                  ? launch_rms_norm(e0.x_bf16, e0.x2_bf16, e0.gamma_bf16, e0.eps, M,
-                                                    e0.K, ws.xt, e0.h_out_bf16, st)
-                                  : launch_silu_mul(e0.x_bf16, e0.x2_bf16, M, e0.K, ws.xt, st);
-                if (t != NVQ_OK) return t;
-            }
-            x = ws.xt;
+        // what the previous phase prepared (transformed input or codes) still stands if it
+        // read the same input the same way
+        if (fresh) {
+            const int t = launch_prep(e0, M, act_group, w4a8, ws.xt, ws.xq, ws.xscale, ws.xgsum, st);
+            if (t != NVQ_OK) return t;
         }
-        if (w4a8 && fresh) {
-            const int q = launch_quant_act(x, M, e0.K, act_group, ws.xq, ws.xscale, ws.xgsum, st);
-            if (q != NVQ_OK) return q;
-        }
+        const uint16_t *x = e0.in_op != NVQ_IN_PLAIN ? ws.xt : e0.x_bf16;
         const GemvSegs S = make_segs(L, ph);
         const int g = w4a8 ? launch_gemv_w4a8(S, e0.K, ws.xq, ws.xscale, ws.xgsum, act_group, M, st)
                            : launch_gemv_w4a16(S, e0.K, x, M, st);

@@ -45,6 +45,11 @@ struct GemvSegs {
 // Internal launchers (validated arguments; enqueue only).
 int launch_quant_act(const uint16_t *x, int M, int K, int act_group, int8_t *xq, float *xscale,
                      int32_t *xgsum, hipStream_t st);
+// The input of layer e for M tokens: its transform (if any) and, with `quant`, its codes,
+// scales and code sums; without it the transformed values go to xt (plain input: nothing).
+// xt is scratch either way.
+int launch_prep(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
+                float *xscale, int32_t *xgsum, hipStream_t st);
 int launch_gemv_w4a8(const GemvSegs &segs, int K, const int8_t *xq, const float *xscale,
                      const int32_t *xgsum, int act_group, int M, hipStream_t st);
 int launch_gemv_w4a16(const GemvSegs &segs, int K, const uint16_t *x, int M, hipStream_t st);

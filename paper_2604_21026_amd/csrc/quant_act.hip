@@ -9,7 +9,7 @@
 // and reduce its code sum (and, for per-group scales, its absmax) with two
 // cross-lane exchanges.  Pass 1 finds the token's absmax, pass 2 re-reads the
 // (cache-resident) row and quantises.
-#include "nvq_internal.h"
+#include "transform.h"
 
 namespace nvq {
 
@@ -30,6 +30,30 @@ __device__ __forceinline__ int quant_one(float x, float s) {
     float r = rintf(x / s);
     r = fminf(fmaxf(r, -127.0f), 127.0f);
     return (int)r;
+}
+
+// Codes and code sum of chunk c (eight values, a quarter of a group) of a token.
+__device__ __forceinline__ void quant_chunk(const uint4 &v, float s, int c, uint2 *__restrict__ qr,
+                                            int32_t *__restrict__ gs) {
+    const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+    int q[8];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        q[2 * i] = (s != 0.0f) ? quant_one(bf16_bits_to_float(w[i] & 0xffffu), s) : 0;
+        q[2 * i + 1] = (s != 0.0f) ? quant_one(bf16_bits_to_float(w[i] >> 16), s) : 0;
+    }
+    int sum = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sum += q[i];
+    uint2 out;
+    out.x = (uint32_t)(q[0] & 0xff) | ((uint32_t)(q[1] & 0xff) << 8) |
+            ((uint32_t)(q[2] & 0xff) << 16) | ((uint32_t)(q[3] & 0xff) << 24);
+    out.y = (uint32_t)(q[4] & 0xff) | ((uint32_t)(q[5] & 0xff) << 8) |
+            ((uint32_t)(q[6] & 0xff) << 16) | ((uint32_t)(q[7] & 0xff) << 24);
+    qr[c] = out;
+    sum += __shfl_xor(sum, 1, 64);
+    sum += __shfl_xor(sum, 2, 64);
+    if ((c & 3) == 0) gs[c >> 2] = sum;
 }
 
 // Token m of one [M][K] input, by one workgroup.
@@ -71,25 +95,96 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
             s = a / 127.0f;
             if ((c & 3) == 0) xscale[(int64_t)m * G + (c >> 2)] = s;
         }
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        int q[8];
+        quant_chunk(v, s, c, qr, gs);
+    }
+}
+
+// Input transform (transform.h) and quantisation of a token in one pass, K <= 16384: a
+// thread keeps its one or two chunks of eight values in registers from the load to the
+// codes.  The grid is a handful of workgroups, so what it costs is its launch and a chain
+// of memory and barrier latencies: one launch and one trip to memory instead of two and
+// four (norm and quantisation of 8 x 4096, and SiLU and quantisation of 8 x 14336, as
+// kernels of their own with 256 threads each: 8.7 us by the trace, 4.6 as one).
+// OP: nvq_linear.in_op; Q: 0 = the transformed bf16 values (xt), 1 = codes with a scale
+// per token, 2 = codes with a scale per group.
+constexpr int kPrepMaxK = 16384, kPrepThreads = 1024;
+
+__device__ __forceinline__ float block_max_or_sum(float a, bool sum, float *red) {
+    const int waves = (int)blockDim.x >> 6;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            q[2 * i] = (s != 0.0f) ? quant_one(bf16_bits_to_float(w[i] & 0xffffu), s) : 0;
-            q[2 * i + 1] = (s != 0.0f) ? quant_one(bf16_bits_to_float(w[i] >> 16), s) : 0;
+    for (int off = 32; off > 0; off >>= 1) {
+        const float b = __shfl_xor(a, off, 64);
+        a = sum ? a + b : fmaxf(a, b);
+    }
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    __syncthreads();
+    a = red[0];
+    for (int i = 1; i < waves; ++i) a = sum ? a + red[i] : fmaxf(a, red[i]);
+    return a;
+}
+
+template <int OP, int Q, int NCH>
+__global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
+    const uint4 *__restrict__ x, const uint4 *__restrict__ x2, const uint4 *__restrict__ gamma,
+    float eps, int K, uint4 *__restrict__ xt, uint4 *__restrict__ h_out, int8_t *__restrict__ xq,
+    float *__restrict__ xscale, int32_t *__restrict__ xgsum) {
+    __shared__ float red[2][kPrepThreads / 64];
+    const int m = blockIdx.x, chunks = K / 8, G = K / 32;
+    const int64_t row = (int64_t)m * chunks;
+    uint4 v[NCH];
+    float acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = (int)threadIdx.x + i * (int)blockDim.x;
+        v[i] = make_uint4(0u, 0u, 0u, 0u);
+        if (c < chunks) {
+            v[i] = x[row + c];
+            if (OP == NVQ_IN_RMSNORM) {
+                if (x2) v[i] = add_bf16x8(v[i], x2[row + c]);
+                if (h_out) h_out[row + c] = v[i];
+                acc += sumsq_bf16x8(v[i]);
+            } else if (OP == NVQ_IN_SILU_MUL) {
+                v[i] = silu_mul_bf16x8(v[i], x2[row + c]);
+            }
         }
-        int sum = 0;
+    }
+    if (OP == NVQ_IN_RMSNORM) {
+        const float r = rms_scale(block_max_or_sum(acc, true, red[0]), K, eps);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) sum += q[i];
-        uint2 out;
-        out.x = (uint32_t)(q[0] & 0xff) | ((uint32_t)(q[1] & 0xff) << 8) |
-                ((uint32_t)(q[2] & 0xff) << 16) | ((uint32_t)(q[3] & 0xff) << 24);
-        out.y = (uint32_t)(q[4] & 0xff) | ((uint32_t)(q[5] & 0xff) << 8) |
-                ((uint32_t)(q[6] & 0xff) << 16) | ((uint32_t)(q[7] & 0xff) << 24);
-        qr[c] = out;
-        sum += __shfl_xor(sum, 1, 64);
-        sum += __shfl_xor(sum, 2, 64);
-        if ((c & 3) == 0) gs[c >> 2] = sum;
+        for (int i = 0; i < NCH; ++i) {
+            const int c = (int)threadIdx.x + i * (int)blockDim.x;
+            if (c < chunks) v[i] = scale_bf16x8(v[i], r, gamma[c]);
+        }
+    }
+    if (Q == 0) {
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) {
+            const int c = (int)threadIdx.x + i * (int)blockDim.x;
+            if (c < chunks) xt[row + c] = v[i];
+        }
+        return;
+    }
+    float s = 0.0f;
+    if (Q == 1) {
+        float a = 0.0f;
+#pragma unroll
+        for (int i = 0; i < NCH; ++i) a = fmaxf(a, chunk_absmax(v[i]));
+        s = block_max_or_sum(a, false, red[1]) / 127.0f;
+        if (threadIdx.x == 0) xscale[m] = s;
+    }
+    // four neighbouring lanes hold a group: chunks and blockDim.x are multiples of four
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+        const int c = (int)threadIdx.x + i * (int)blockDim.x;
+        if (c >= chunks) continue;
+        if (Q == 2) {
+            float a = chunk_absmax(v[i]);
+            a = fmaxf(a, __shfl_xor(a, 1, 64));
+            a = fmaxf(a, __shfl_xor(a, 2, 64));
+            s = a / 127.0f;
+            if ((c & 3) == 0) xscale[(int64_t)m * G + (c >> 2)] = s;
+        }
+        quant_chunk(v[i], s, c, reinterpret_cast<uint2 *>(xq + (int64_t)m * K), xgsum + (int64_t)m * G);
     }
 }
 
@@ -216,6 +311,12 @@ int launch_quant_act_group(const GroupPhase *tab, const uint16_t *jobs, int njob
 
 int launch_quant_act(const uint16_t *x, int M, int K, int act_group, int8_t *xq, float *xscale,
                      int32_t *xgsum, hipStream_t st) {
+    if (K <= kPrepMaxK) {
+        nvq_linear e = {};
+        e.x_bf16 = x;
+        e.K = K;
+        return launch_prep(e, M, act_group, true, nullptr, xq, xscale, xgsum, st);
+    }
     if (act_group == 0)
         hipLaunchKernelGGL(quant_act_kernel<false>, dim3(M), dim3(kQuantThreads), 0, st,
                            reinterpret_cast<const uint4 *>(x), K, xq, xscale, xgsum);
@@ -224,6 +325,62 @@ int launch_quant_act(const uint16_t *x, int M, int K, int act_group, int8_t *xq,
                            reinterpret_cast<const uint4 *>(x), K, xq, xscale, xgsum);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
+}
+
+namespace {
+
+template <int OP, int Q>
+int prep_go(const nvq_linear &e, int M, uint16_t *xt, int8_t *xq, float *xscale, int32_t *xgsum,
+            hipStream_t st) {
+    const int chunks = e.K / 8;
+    const int nch = chunks <= kPrepThreads ? 1 : 2, per = (chunks + nch - 1) / nch;
+    const dim3 grid(M), block((per + 63) / 64 * 64);
+    const uint4 *x = reinterpret_cast<const uint4 *>(e.x_bf16), *x2 = reinterpret_cast<const uint4 *>(e.x2_bf16);
+    const uint4 *gamma = reinterpret_cast<const uint4 *>(e.gamma_bf16);
+    uint4 *out = reinterpret_cast<uint4 *>(xt), *h = reinterpret_cast<uint4 *>(e.h_out_bf16);
+    if (nch == 1)
+        hipLaunchKernelGGL((prep_token_kernel<OP, Q, 1>), grid, block, 0, st, x, x2, gamma, e.eps, e.K, out, h,
+                           xq, xscale, xgsum);
+    else
+        hipLaunchKernelGGL((prep_token_kernel<OP, Q, 2>), grid, block, 0, st, x, x2, gamma, e.eps, e.K, out, h,
+                           xq, xscale, xgsum);
+    NVQ_HIP_TRY(hipGetLastError());
+    return NVQ_OK;
+}
+
+template <int OP>
+int prep_quant(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
+               float *xscale, int32_t *xgsum, hipStream_t st) {
+    if (!quant) return prep_go<OP, 0>(e, M, xt, xq, xscale, xgsum, st);
+    if (act_group == 0) return prep_go<OP, 1>(e, M, xt, xq, xscale, xgsum, st);
+    return prep_go<OP, 2>(e, M, xt, xq, xscale, xgsum, st);
+}
+
+}  // namespace
+
+int launch_prep(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
+                float *xscale, int32_t *xgsum, hipStream_t st) {
+    if (e.K > kPrepMaxK) {  // step by step
+        const uint16_t *x = e.x_bf16;
+        if (e.in_op != NVQ_IN_PLAIN) {
+            const int t = e.in_op == NVQ_IN_RMSNORM
+                              ? launch_rms_norm(e.x_bf16, e.x2_bf16, e.gamma_bf16, e.eps, M, e.K, xt,
+                                                e.h_out_bf16, st)
+                              : launch_silu_mul(e.x_bf16, e.x2_bf16, M, e.K, xt, st);
+            if (t != NVQ_OK) return t;
+            x = xt;
+        }
+        return quant ? launch_quant_act(x, M, e.K, act_group, xq, xscale, xgsum, st) : NVQ_OK;
+    }
+    if (e.in_op == NVQ_IN_RMSNORM)
+        return prep_quant<NVQ_IN_RMSNORM>(e, M, act_group, quant, xt, xq, xscale, xgsum, st);
+    if (e.in_op == NVQ_IN_SILU_MUL) {
+        // without the codes nothing spans a token: one workgroup per 256 chunks instead
+        if (!quant) return launch_silu_mul(e.x_bf16, e.x2_bf16, M, e.K, xt, st);
+        return prep_quant<NVQ_IN_SILU_MUL>(e, M, act_group, quant, xt, xq, xscale, xgsum, st);
+    }
+    if (!quant) return NVQ_OK;
+    return prep_quant<NVQ_IN_PLAIN>(e, M, act_group, quant, xt, xq, xscale, xgsum, st);
 }
 
 }  // namespace nvq
