@@ -429,6 +429,8 @@ struct GroupBatch {
     int img_first, nimg;     // range in the image unit list
     int part_first, nparts;  // the batch's table in the part list (2 * (nparts + 1) words)
     int grid;                // workgroups of the persistent kernel
+    int phase_first, nphases;  // phases of the batch
+    bool single;             // 17 tokens and more: phase by phase instead of as one grid
 };
 struct GroupPlan {
     bool ring;  // the persistent kernel serves the list: every phase has a job and an operand image
@@ -437,6 +439,24 @@ struct GroupPlan {
     std::vector<uint32_t> parts;  // per batch: nparts + 1 unit cuts, then the phases at the cuts
     std::vector<GroupBatch> batches;
 };
+
+// Whether a batch of 17 or more tokens goes phase by phase (gemv_slice.h) instead of as one
+// persistent grid (gemv_rows.hip).  The grid moves 3.9 TB/s once it has work for every compute
+// unit, but a workgroup takes 128 rows and all of their K, 1.7 us per 256 inputs however few
+// there are; a phase by itself costs 3 us and 2.4 TB/s (4096 x 14336 alone: 17 us against 107;
+// 32 blocks of 8B: 1,130 us against 2,200).
+bool rows_or_single(const GroupPlan &gp, const GroupBatch &b) {
+    double bytes = 0.0, single_us = 0.0;
+    int steps = 0;
+    for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
+        const GroupPhase &g = gp.tab[(size_t)p];
+        const double w = 18.0 * g.G * g.segs.total_rows;
+        bytes += w;
+        single_us += 3.0 + w * 1e-6 / 2.4;
+        steps = std::max(steps, g.G / 8);
+    }
+    return single_us < 12.0 + std::max(bytes * 1e-6 / 3.9, 1.7 * steps);
+}
 
 // Cut the units of a batch into contiguous parts of (nearly) equal weight
 // bytes, one per XCD of the persistent kernel's grid; a unit of phase p weighs
@@ -483,14 +503,23 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         gp.ring = gp.ring && gemv_mfma_ring_supported(make_segs(L, ph), L[ph.first].K);
     const std::vector<int> deps = phase_deps(L, phases, M, ordered);
     size_t qoff = 0;
-    GroupBatch cur = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    GroupBatch cur = {};
     int batch_first = 0;
+    auto close = [&]() {
+        cut_batch(gp, cur, M);
+        cur.phase_first = batch_first;
+        cur.nphases = (int)gp.tab.size() - batch_first;
+        cur.single = rows_or_single(gp, cur);
+        gp.batches.push_back(cur);
+    };
     for (size_t p = 0; p < phases.size(); ++p) {
         const nvq_linear &e0 = L[phases[p].first];
         if (deps[p] >= batch_first) {  // depends on a phase of the open batch: close it
-            cut_batch(gp, cur, M);
-            gp.batches.push_back(cur);
-            cur = {(int)gp.jobs.size(), 0, (int)gp.units.size(), 0, (int)gp.imgs.size(), 0, 0, 0, 0};
+            close();
+            cur = {};
+            cur.job_first = (int)gp.jobs.size();
+            cur.unit_first = (int)gp.units.size();
+            cur.img_first = (int)gp.imgs.size();
             batch_first = (int)p;
         }
         GroupPhase g = {};
@@ -502,6 +531,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         if (gp.ring) {
             char *b = ws.gquant + qoff;
             g.xa = b;
+            g.xq = reinterpret_cast<int8_t *>(b);  // 17 tokens and more: the codes instead of an image
             g.xscale = reinterpret_cast<float *>(b + operand_image_bytes(M, e0.K, e0.precision));
             qoff += operand_image_bytes(M, e0.K, e0.precision) + round_up((size_t)M * 4, 256);
             gp.jobs.push_back((uint16_t)p);
@@ -527,8 +557,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         cur.nunits += units;
         gp.tab.push_back(g);
     }
-    cut_batch(gp, cur, M);
-    gp.batches.push_back(cur);
+    close();
     return gp;
 }
 
@@ -808,6 +837,7 @@ struct nvq_plan {
     bool mail;         // some phase of the streaming table posts or reads mail
     int nmail;         // phases that take an operand from a mailbox
     size_t mail_stride;  // words between the replicas of a mailbox
+    std::vector<nvq::GroupPhase> group_phases;  // 17 tokens and more: the phases of `batches`
     unsigned long long *trace;  // device buffer for per-phase timestamps, or nullptr
     int trace_wgs;     // workgroups that record there
 };
@@ -931,6 +961,7 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
                 return NVQ_ERR_HIP;
             }
             pl->batches = gp.batches;
+            if (gp.ring && M >= kRowsMinTokens) pl->group_phases = gp.tab;
             pl->nwaits = (int)gp.batches.size() - 1;
             pl->ring = gp.ring;
         }
@@ -955,15 +986,30 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
     }
     if (!pl->batches.empty()) {
         for (const GroupBatch &b : pl->batches) {
-            int rc = pl->ring ? launch_operand_images(pl->ws.gtab, pl->ws.gjobs + b.job_first, b.njobs,
-                                                      pl->ws.gimgs + b.img_first, b.nimg, pl->M, st)
-                              : launch_quant_act_group(pl->ws.gtab, pl->ws.gjobs + b.job_first,
-                                                       b.njobs, pl->M, st);
-            if (rc != NVQ_OK) return rc;
-            rc = pl->ring ? launch_gemv_mfma_ring(pl->ws.gtab, pl->ws.gteams + b.part_first, b.nparts,
-                                                  b.grid, pl->M, pl->ws.status, st)
-                          : launch_gemv_mfma_group(pl->ws.gtab, pl->ws.gunits + b.unit_first,
-                                                   b.nunits, pl->M, st);
+            const uint16_t *jobs = pl->ws.gjobs + b.job_first;
+            const uint32_t *parts = pl->ws.gteams + b.part_first;
+            int rc;
+            if (!pl->ring) {
+                rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, nullptr, st);
+                if (rc == NVQ_OK)
+                    rc = launch_gemv_mfma_group(pl->ws.gtab, pl->ws.gunits + b.unit_first, b.nunits, pl->M, st);
+            } else if (pl->M >= kRowsMinTokens) {
+                uint32_t *const tickets = pl->ws.status + 16;
+                rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, tickets, st);
+                for (int p = b.phase_first; b.single && rc == NVQ_OK && p < b.phase_first + b.nphases; ++p) {
+                    const GroupPhase &g = pl->group_phases[(size_t)p];
+                    rc = g.precision == NVQ_W4A8
+                             ? launch_gemv_slice_w4a8(g.segs, g.G * 32, g.xq, g.xscale, 0, pl->M, st)
+                             : launch_gemv_slice_w4a16(g.segs, g.G * 32, g.x_bf16, pl->M, st);
+                }
+                if (rc == NVQ_OK && !b.single)
+                    rc = launch_gemv_rows(pl->ws.gtab, parts, b.nparts, b.nunits, pl->M, tickets, st);
+            } else {
+                rc = launch_operand_images(pl->ws.gtab, jobs, b.njobs, pl->ws.gimgs + b.img_first, b.nimg,
+                                           pl->M, st);
+                if (rc == NVQ_OK)
+                    rc = launch_gemv_mfma_ring(pl->ws.gtab, parts, b.nparts, b.grid, pl->M, pl->ws.status, st);
+            }
             if (rc != NVQ_OK) return rc;
         }
         return NVQ_OK;

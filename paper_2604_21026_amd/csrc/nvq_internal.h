@@ -77,8 +77,10 @@ struct GroupPhase {
     int img_begin;           // first image unit of the phase in its batch (launch_operand_images)
 };
 // jobs[j] names the phase whose M tokens grid blocks j*M .. j*M+M-1 quantise.
+// Phases that are not W4A8 are passed over; xgsum may be null.  The first eight words at
+// `clear` (unless null) are set to zero.
 int launch_quant_act_group(const GroupPhase *tab, const uint16_t *jobs, int njobs, int M,
-                           hipStream_t st);
+                           uint32_t *clear, hipStream_t st);
 // The operand images `xa` of the phases named in `jobs` (per-token scales of
 // the W4A8 ones first, then the images: img_units[u] names the phase of image
 // unit u, a token tile times eight 128-input columns; image_units(M, K) of
@@ -111,6 +113,12 @@ int ring_grid(int M, int nunits);
 int ring_parts(int grid);
 int launch_gemv_mfma_ring(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int grid,
                           int M, uint32_t *status, hipStream_t st);
+
+// The same work for 17 to 32 tokens, from the inputs themselves (codes and scales of
+// launch_quant_act_group for the W4A8 phases); tickets: eight words that are zero.
+constexpr int kRowsMinTokens = 17;
+int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int nunits, int M,
+                     uint32_t *tickets, hipStream_t st);
 
 // ---- device helpers -------------------------------------------------------
 #if defined(__HIPCC__)

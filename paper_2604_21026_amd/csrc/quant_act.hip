@@ -53,7 +53,7 @@ __device__ __forceinline__ void quant_chunk(const uint4 &v, float s, int c, uint
     qr[c] = out;
     sum += __shfl_xor(sum, 1, 64);
     sum += __shfl_xor(sum, 2, 64);
-    if ((c & 3) == 0) gs[c >> 2] = sum;
+    if ((c & 3) == 0 && gs) gs[c >> 2] = sum;
 }
 
 // Token m of one [M][K] input, by one workgroup.
@@ -65,7 +65,7 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
     const int G = K / 32;
     const uint4 *xr = x + (int64_t)m * chunks;
     uint2 *qr = reinterpret_cast<uint2 *>(xq + (int64_t)m * K);
-    int32_t *gs = xgsum + (int64_t)m * G;
+    int32_t *gs = xgsum ? xgsum + (int64_t)m * G : nullptr;
 
     float s_tok = 0.0f;
     if (!PER_GROUP) {
@@ -197,9 +197,12 @@ __global__ __launch_bounds__(kQuantThreads) void quant_act_kernel(
 
 // Per-token scales, the inputs of many phases in one grid.
 __global__ __launch_bounds__(kQuantThreads) void quant_act_group_kernel(
-    const GroupPhase *__restrict__ tab, const uint16_t *__restrict__ jobs, int M) {
+    const GroupPhase *__restrict__ tab, const uint16_t *__restrict__ jobs, int M,
+    uint32_t *__restrict__ clear) {
+    if (clear && blockIdx.x == 0 && threadIdx.x < 8) clear[threadIdx.x] = 0u;
     const int job = blockIdx.x / M, m = blockIdx.x - job * M;
     const GroupPhase &P = tab[jobs[job]];
+    if (P.precision != NVQ_W4A8) return;
     quant_token<false>(reinterpret_cast<const uint4 *>(P.x_bf16), P.G * 32, m, P.xq, P.xscale,
                        P.xgsum);
 }
@@ -301,10 +304,10 @@ int launch_operand_images(const GroupPhase *tab, const uint16_t *jobs, int njobs
 }
 
 int launch_quant_act_group(const GroupPhase *tab, const uint16_t *jobs, int njobs, int M,
-                           hipStream_t st) {
+                           uint32_t *clear, hipStream_t st) {
     if (njobs <= 0) return NVQ_OK;
     hipLaunchKernelGGL(quant_act_group_kernel, dim3(njobs * M), dim3(kQuantThreads), 0, st, tab, jobs,
-                       M);
+                       M, clear);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }

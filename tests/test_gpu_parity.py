@@ -610,6 +610,58 @@ def test_ring_plan_matches_oracle(M, bits):
     dl.close()
 
 
+def test_rows_plan_draws_tickets_and_replays():
+    """More groups of units than workgroups fit the device, so that groups are drawn from the
+    counters; captured in a graph and replayed with eager work in between, every replay equal to
+    the eager run (bit for bit: a row's sums do not depend on who takes it)."""
+    say("rows plan, tickets")
+    M = 20
+    entries, host = model_entries([(120001, 512, 0), (900, 512, 0), (33, 1536, 1), (70000, 512, 2)], (0, 1),
+                                  M=M, seed=8650)
+    rows = np.unique(np.concatenate([[0, 31, 32, 127, 128], np.random.default_rng(1).integers(0, 33, 8)]))
+    dl = nvq.DecodeList(entries, M, 0)
+    assert dl.plan_info()["persistent_grouped"]
+    dl.run_plan()
+    torch.cuda.synchronize()
+    eager = [e["y"].clone() for e in entries]
+    for e, h in zip(entries, host):
+        N = e["y"].shape[1]
+        pick = np.unique(np.concatenate([rows[rows < N], [N - 1, N // 2, N // 3]]))
+        sub = dict(h, qweight=h["qweight"][pick], scales=h["scales"][pick])
+        want = oracle.decode_linears([sub], M, 0)[0]
+        assert np_ref.rel_l2(e["y"].cpu().numpy()[:, pick], want) < 1e-5
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        dl.run_plan()
+    for rep in range(3):
+        for e in entries:
+            e["y"].zero_()
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(e["y"], w) for e, w in zip(entries, eager)), rep
+    del g
+    dl.close()
+
+
+@pytest.mark.parametrize("M", [17, 32])
+def test_rows_plan_short_batches_run_phase_by_phase(M):
+    """Forced order: every phase is a batch of its own, too small for the persistent grid."""
+    say("rows plan, single phases", M)
+    entries, host = model_entries([(300, 1536, 0), (45, 1536, 0), (512, 1024, 1), (64, 14336, 2)], (0, 1), M=M,
+                                  seed=8660)
+    ys_ref = oracle.decode_linears(host, M, 0)
+    dl = nvq.DecodeList(entries, M, 0, ordered=True)
+    for rep in range(2):
+        for e in entries:
+            e["y"].zero_()
+        dl.run_plan()
+        torch.cuda.synchronize()
+        for e, y_r in zip(entries, ys_ref):
+            assert np_ref.rel_l2(e["y"].cpu().numpy(), y_r) < 1e-5, rep
+    dl.close()
+
+
 def test_ring_plan_needs_k_multiple_of_512():
     say("ring plan fallback")
     M = 4
