@@ -53,6 +53,28 @@ def test_pack_int4_bit_exact(N, K):
     assert np.array_equal(u16(s), s_ref)
 
 
+@pytest.mark.parametrize("exp", [-26, -18, -6, 12])
+def test_pack_int4_near_ties(exp):
+    """Weights at most four units of last place from a tie between two codes (the kernel divides
+    only there), at scales from subnormal fp16 numbers to large ones; a group count that is no
+    multiple of what a workgroup takes."""
+    say("pack ties", exp)
+    rng = np.random.default_rng(700 + exp)
+    N, K = 67, 1056
+    top = np.ldexp(1 + rng.random((N, K // 32, 1)), exp).astype(np.float32)
+    s = (top / np.float32(7)).astype(np.float16).astype(np.float32)
+    W = ((rng.integers(-7, 7, (N, K // 32, 32)) + 0.5).astype(np.float32) * s).astype(np.float32)
+    W = (W.view(np.int32) + rng.integers(-4, 5, W.shape).astype(np.int32)).view(np.float32)
+    W = np.where(np.abs(W) <= top, W, 0.5 * top).astype(np.float32)
+    W[:, :, :1] = top
+    W = W.reshape(N, K)
+    q_ref, s_ref = oracle.pack_int4(W)
+    q, sc = nvq.pack_int4(torch.from_numpy(W).to(DEV))
+    torch.cuda.synchronize()
+    assert np.array_equal(q.cpu().numpy(), q_ref)
+    assert np.array_equal(sc.cpu().numpy().view(np.uint16), s_ref)
+
+
 def test_pack_int4_edge_values():
     say("pack edge")
     W = torch.zeros(4, 64)
