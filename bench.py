@@ -47,6 +47,7 @@ STREAM_KERNEL = "nvq::decode_stream_kernel"  # <per-group scales, paired rows, m
 GROUP_KERNEL = "nvq::gemv_mfma_group_kernel (+ nvq::quant_act_group_kernel)"
 RING_KERNEL = ("nvq::gemv_mfma_ring_kernel (+ nvq::token_scale_group_kernel, "
                "nvq::operand_image_group_kernel)")
+ROWS_KERNEL = "nvq::gemv_rows_kernel (+ nvq::quant_act_group_kernel)"  # 17 tokens and more
 # model copies a step rotates over so that no weight byte is read out of the 256 MB
 # Infinity Cache or the L2s (at least 1 GB of distinct bytes between two uses)
 DEFAULT_COPIES = {"llama-1b": 3, "llama-3b": 2, "llama-8b": 1}
@@ -223,7 +224,8 @@ def traffic_from_profile(model, which, batch, kind="group"):
     """HBM bytes per step measured with rocprofv3 --pmc (FETCH_SIZE + WRITE_SIZE, scaled by a
     copy kernel of known size); read from the committed summary, None if it is not there."""
     name = ("decode_stream_%s_%s_pmc.md" % (model, which) if batch == 1 else
-            "gemv_mfma_%s_%s_%s_batch%d_pmc.md" % (kind, model, which, batch))
+            "gemv_rows_%s_%s_batch%d_pmc.md" % (model, which, batch) if kind == "ring" and batch > 16
+            else "gemv_mfma_%s_%s_%s_batch%d_pmc.md" % (kind, model, which, batch))
     path = os.path.join(ROOT, "profiles", name)
     try:
         m = re.search(r"traffic_bytes_per_launch:\s*([0-9.eE+]+)", open(path).read())
@@ -649,7 +651,7 @@ def main():
         "config": {"workload": "%s-shaped decode step, batch %d, %d linears in %s, precision map "
                                "%s (%d of %d blocks W4A16%s), own input buffer per layer%s" %
                                (a.model, M, len(specs),
-                                "one launch" if M == 1 else "three launches", a.map,
+                                "one launch" if M == 1 else "three launches" if M <= 16 else "two launches", a.map,
                                 sum(bits), len(bits),
                                 ", lm_head W4A16" if specs[-1].block < 0 else "",
                                 ", steps rotate over %d model copies (%.2f GB)" %
@@ -684,7 +686,8 @@ def main():
             "frac": round(gbs / HBM_PEAK_GBS, 4),
             "traffic": traffic, "traffic_source": traffic_src,
             "kernel": (STREAM_KERNEL if info["streaming"] else
-                       RING_KERNEL if info["persistent_grouped"] else
+                       (ROWS_KERNEL if M > 16 else RING_KERNEL)
+                       if info["persistent_grouped"] else
                        GROUP_KERNEL if info["grouped"] else "per-phase launches"),
             "launches": a.steps, "avg_launch_us": round(per_launch * 1e6, 2),  # per step
             "min_launch_us": round(min(per) * 1e6, 2),
