@@ -41,6 +41,15 @@ def act(seed, M, K, outliers=True):
     return synth.make_activation(seed, M, K, outliers)
 
 
+def test_calls_go_to_the_current_stream():
+    """The stream the binding passes is torch's current one, inside a stream context and outside."""
+    assert nvq._stream() == torch.cuda.current_stream().cuda_stream
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert nvq._stream() == side.cuda_stream == torch.cuda.current_stream().cuda_stream
+    assert nvq._stream() == torch.cuda.current_stream().cuda_stream
+
+
 # ---- a1 pack -----------------------------------------------------------------
 @pytest.mark.parametrize("N,K", [(5, 32), (64, 2048), (33, 3072), (257, 4096), (7, 14336),
                                  (1, 64), (1031, 1024)])
