@@ -52,6 +52,25 @@ struct SliceBlock {
     static constexpr int kW = 0, kSc = kW + RT * kWTile, kA = kSc + kScBytes;
     static constexpr int kXs = kA + TOK * kTokenBytes, kBytes = kXs + kXsOps * 256;
     static constexpr int kOps = kWOps + kScOps + kAOps + kXsOps;
+
+    // Where lane row kb finds the scales of its first token, and its token's place among the
+    // activations: what stands for tokens that are not there is read from another's.
+    static constexpr int xs_place(int kb) { return 128 * (TOK < 16 ? kb & (TOK / 4 - 1) : kb); }
+    static constexpr int token_place(int n) { return (TOK < 16 ? n & (TOK - 1) : n) * kTokenBytes; }
+    // The last byte that the reads of a block touch lies inside the piece it belongs to.
+    static constexpr int kTiles = (TOK + 15) / 16, kRowBytes = 16 * NG;
+    static constexpr int kScWords = SCB == 2 ? NG : NG / 2;  // words with the scales of a row
+    static constexpr int largest(int (*place)(int), int n) {
+        int m = 0;
+        for (int i = 0; i < n; ++i) m = place(i) > m ? place(i) : m;
+        return m;
+    }
+    static_assert(15 * kRowBytes + 16 * (NG - 1) + 16 <= kWTile, "weights");
+    static_assert((SCB == 16 ? RT * 256 : kScWords * 16 * RT * 4) <= kScBytes, "scales");
+    static_assert(largest(token_place, 16) + (kTiles - 1) * 16 * kTokenBytes + kTokenBytes <= TOK * kTokenBytes,
+                  "activations");
+    static_assert(!PG || largest(xs_place, 4) + ((kTiles - 1) * 16 + 3) * 32 + 32 <= kXsOps * 256,
+                  "activation scales");
 };
 
 // Waves per workgroup.
@@ -171,7 +190,7 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
     // activations: for W4A16 half a piece twice (inputs 4 kb .. + 3 and 16 + 4 kb .. + 3 of
     // the group), for W4A8 a dword twice.
     const uint32_t at = (uint32_t)(uintptr_t)slot;
-    const int mn = TOK < 16 ? n & (TOK - 1) : n;  // tokens that are not there read another's
+    const int mn = TOK < 16 ? n & (TOK - 1) : n;
     uint32_t wpos[NG], apos[NG][2];
 #pragma unroll
     for (int i = 0; i < NG; ++i) {
@@ -179,13 +198,13 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             if (PREC == NVQ_W4A8)
-                apos[i][h] = at + mn * B::kTokenBytes + 16 * ((2 * i + h) ^ mn) + 4 * kb;
+                apos[i][h] = at + B::token_place(n) + 16 * ((2 * i + h) ^ mn) + 4 * kb;
             else
-                apos[i][h] = at + mn * B::kTokenBytes + 16 * ((4 * i + 2 * h + (kb >> 1)) ^ mn) + 8 * (kb & 1);
+                apos[i][h] = at + B::token_place(n) + 16 * ((4 * i + 2 * h + (kb >> 1)) ^ mn) + 8 * (kb & 1);
         }
     }
     const uint32_t spos = at + (SCB == 16 ? 16 : 4) * n;
-    const uint32_t xspos = at + 128 * kb;  // token 4 kb, 32 bytes per token
+    const uint32_t xspos = at + B::xs_place(kb);  // token 4 kb, 32 bytes per token
 
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD64(dst_, addr_, off_) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
@@ -195,7 +214,7 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
         __builtin_amdgcn_s_waitcnt(slice_vmcnt(0));
         asm volatile("" ::: "memory");
 
-        constexpr int kSc = SCB == 2 ? NG : NG / 2;  // words with the scales of a row
+        constexpr int kSc = B::kScWords;
         uint32_t q[RT][NG], sc[RT][kSc];
         uint2v a2[PREC == NVQ_W4A8 ? 1 : MT][NG][2];
         uint32_t a1[PREC == NVQ_W4A8 ? MT : 1][NG][2];
