@@ -109,18 +109,38 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
 // per token, 2 = codes with a scale per group.
 constexpr int kPrepMaxK = 16384, kPrepThreads = 1024;
 
-__device__ __forceinline__ float block_max_or_sum(float a, bool sum, float *red) {
+__device__ __forceinline__ float block_max(float a, float *red) {
     const int waves = (int)blockDim.x >> 6;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float b = __shfl_xor(a, off, 64);
-        a = sum ? a + b : fmaxf(a, b);
-    }
+    for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
     a = red[0];
-    for (int i = 1; i < waves; ++i) a = sum ? a + red[i] : fmaxf(a, red[i]);
+    for (int i = 1; i < waves; ++i) a = fmaxf(a, red[i]);
     return a;
+}
+
+// The sum of the chunks' sums in the order of the norm kernel (transform.hip), so that a layer
+// prepared here reads the same bf16 values, and gets the same codes, as one prepared by that
+// call: thread t of 256 adds chunks t, t + 256, ... one after the other, then the lanes of a
+// wave and the waves.  (With the chunks added as the threads here hold them, one value in some
+// ten thousand rounded the other way, and every layer behind it saw that.)
+constexpr int kNormThreads = 256;
+__device__ __forceinline__ float chunk_sums_in_norm_order(const float *part, int chunks, float *red) {
+    const int t = (int)threadIdx.x;
+    if (t < kNormThreads) {
+        float ss = 0.0f;
+        for (int c = t; c < chunks; c += kNormThreads) ss += part[c];
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        if ((t & 63) == 0) red[t >> 6] = ss;
+    }
+    __syncthreads();
+    const int waves = (int)blockDim.x >> 6;
+    float ss = red[0];
+    for (int i = 1; i < kNormThreads / 64; ++i)
+        if (i < waves) ss += red[i];  // waves that are not there would add zero
+    return ss;
 }
 
 template <int OP, int Q, int NCH>
@@ -129,10 +149,10 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
     float eps, int K, uint4 *__restrict__ xt, uint4 *__restrict__ h_out, int8_t *__restrict__ xq,
     float *__restrict__ xscale, int32_t *__restrict__ xgsum) {
     __shared__ float red[2][kPrepThreads / 64];
+    __shared__ float part[OP == NVQ_IN_RMSNORM ? kPrepThreads * NCH : 1];
     const int m = blockIdx.x, chunks = K / 8, G = K / 32;
     const int64_t row = (int64_t)m * chunks;
     uint4 v[NCH];
-    float acc = 0.0f;
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         const int c = (int)threadIdx.x + i * (int)blockDim.x;
@@ -142,14 +162,15 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
             if (OP == NVQ_IN_RMSNORM) {
                 if (x2) v[i] = add_bf16x8(v[i], x2[row + c]);
                 if (h_out) h_out[row + c] = v[i];
-                acc += sumsq_bf16x8(v[i]);
+                part[c] = sumsq_bf16x8(v[i]);
             } else if (OP == NVQ_IN_SILU_MUL) {
                 v[i] = silu_mul_bf16x8(v[i], x2[row + c]);
             }
         }
     }
     if (OP == NVQ_IN_RMSNORM) {
-        const float r = rms_scale(block_max_or_sum(acc, true, red[0]), K, eps);
+        __syncthreads();
+        const float r = rms_scale(chunk_sums_in_norm_order(part, chunks, red[0]), K, eps);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const int c = (int)threadIdx.x + i * (int)blockDim.x;
@@ -169,7 +190,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
         float a = 0.0f;
 #pragma unroll
         for (int i = 0; i < NCH; ++i) a = fmaxf(a, chunk_absmax(v[i]));
-        s = block_max_or_sum(a, false, red[1]) / 127.0f;
+        s = block_max(a, red[1]) / 127.0f;
         if (threadIdx.x == 0) xscale[m] = s;
     }
     // four neighbouring lanes hold a group: chunks and blockDim.x are multiples of four

@@ -9,7 +9,7 @@
 
 namespace nvq {
 
-constexpr int kTransformThreads = 256;
+constexpr int kTransformThreads = 256;  // (quant_act.hip repeats the order of the norm's sum)
 
 __global__ __launch_bounds__(kTransformThreads) void rms_norm_kernel(
     const uint4 *__restrict__ x, const uint4 *__restrict__ res, const uint4 *__restrict__ gamma,

@@ -855,6 +855,58 @@ def test_decode_linears_with_input_transforms(M, bits):
     dl.close()
 
 
+# Several tokens: the walk prepares a layer's input in one launch (transform and quantisation
+# together).  K with one and with two chunks of eight values per thread, the second round filled in
+# part (8224: 1028 chunks) and nearly in full; K beyond 16384, which is prepared step by step; fewer
+# values than one wave takes.
+@pytest.mark.parametrize("M,group", [(2, 0), (8, 32), (32, 0), (32, 32)])
+@pytest.mark.parametrize("K", [96, 4096, 8224, 14336, 16416])
+def test_prepared_inputs_equal_the_standalone_calls(M, group, K):
+    """A norm (with and without a residual), a SiLU-multiply and a plain input in front of W4A8 and
+    W4A16 layers: bit for bit what the entry points give one after the other, so the norm's sum,
+    the bf16 values, the codes and their scales are the same; and the oracle's product of them."""
+    say("prepared inputs", M, group, K)
+    N = 40
+    a, b = act(9720 + K, M, K), act(9730 + K, M, K)
+    gamma = (1.0 + 0.1 * torch.randn(K, generator=torch.Generator().manual_seed(K))).to(torch.bfloat16)
+    ad, bd, gd = a.to(DEV), b.to(DEV), gamma.to(DEV)
+    _, q, s = packed(9740 + K, N, K)
+    qd, sd = to_dev_packed(q, s)
+    ops = [dict(x=ad), dict(x=ad, x2=bd, in_op=nvq.IN_SILU_MUL),
+           dict(x=ad, in_op=nvq.IN_RMSNORM, gamma=gd, eps=1e-5),
+           dict(x=ad, x2=bd, in_op=nvq.IN_RMSNORM, gamma=gd, eps=1e-5, h_out=torch.zeros_like(ad))]
+    entries = [dict(op, qweight=qd, scales=sd, precision=p,
+                    y=torch.zeros((M, N), dtype=torch.float32, device=DEV))
+               for op in ops for p in (nvq.W4A8, nvq.W4A16)]
+    for e in entries:
+        if "h_out" in e:
+            e["h_out"] = torch.zeros_like(ad)
+    dl = nvq.DecodeList(entries, M, group)
+    dl.run_plan()
+    torch.cuda.synchronize()
+    for e in entries:
+        x = e["x"]
+        if e.get("in_op") == nvq.IN_RMSNORM:
+            x, h = nvq.rms_norm(ad, gd, 1e-5, e.get("x2"))
+            if "h_out" in e:
+                assert torch.equal(e["h_out"], h)
+        elif e.get("in_op") == nvq.IN_SILU_MUL:
+            x = nvq.silu_mul(ad, bd)
+        if e["precision"] == nvq.W4A16:
+            want = nvq.gemv_w4a16(qd, sd, x)
+        else:
+            xq, xs, gs = nvq.quant_act_i8(x, group)
+            want = nvq.gemv_w4a8(qd, sd, xq, xs, gs, group)
+        torch.cuda.synchronize()
+        what = (e.get("in_op", 0), "x2" in e, e["precision"])
+        assert torch.equal(e["y"], want), (what, int((e["y"] != want).sum()))
+        # the oracle on the transformed values themselves (an input that the two transforms round
+        # differently can move a token's scale, and with it every one of its codes)
+        h = dict(qweight=q, scales=s, x=u16(x), precision=e["precision"])
+        assert np_ref.rel_l2(e["y"].cpu().numpy(), oracle.decode_linears([h], M, group)[0]) < 1e-5, what
+    dl.close()
+
+
 def test_chain_of_blocks_with_transforms_in_one_launch():
     say("block chain with transforms")
     # two blocks at the 1B shapes, the second fed by the first (the residual add of the first
