@@ -5,25 +5,51 @@
 // the constant nibble offset removed by a second MFMA).
 //
 // A workgroup of W waves owns 16 RT consecutive rows; the waves share out K in blocks of
-// eight groups (256 inputs: a whole 128-byte line of every row), wave w the blocks w, w +
-// W, ..., and the partial tiles are added through LDS, in pairs, at the end.  Until
-// then the waves do not meet.  Each copies what it needs of a block (the rows' weights and
-// scales, the tokens' 256 inputs) straight from global memory into its own piece of LDS,
-// takes it into registers, asks for its next block and only then multiplies; what covers
-// the memory's latency are the three or four workgroups that share a compute unit.
+// NG groups (eight: 256 inputs, a whole 128-byte line of every row), wave w the blocks w, w
+// + W, ..., and the partial sums are added through LDS at the end.  Until then the waves do
+// not meet.  Each copies what it needs of a block (the rows' weights and scales, the tokens'
+// inputs) straight from global memory into its own piece of LDS, takes it into registers,
+// asks for its next block and only then multiplies; what covers the memory's latency are
+// the workgroups that share a compute unit (see SliceBlock for how many).
 //
-// What bounds it: neither memory nor arithmetic alone.  28672 x 4096 at 8 tokens takes 18.2
-// us (3.6 TB/s; 33 with a workgroup per 16 rows that loaded straight into registers);
-// without the loads it takes 12, the vector ALUs busy three quarters of that (18
-// instructions per 16 x 16 x 32 product), without either 6.  Two to four blocks in flight
-// per wave instead of one, with fewer workgroups per compute unit, were no faster; blocks
-// of four groups, whose loads move half lines, 5-15 % slower.
+// The order of a result's additions is a property of the call, not of W, NG and RT: V
+// chains of groups, each added from the first group to the last, whose sums then meet.
+//   V = 8, 16  chain v holds the columns (four groups) v, v + V, ...; the chains are added
+//              in order.  K a multiple of 128, scales aligned to 8 bytes, and a scale per
+//              token (or none).
+//   V = 64     chain v holds the groups v, v + 64, ...; the chains are added in pairs, those
+//              32 apart first.  Everything else.
+// (One chain per wave, as its blocks follow each other, is a shorter way to the sum; but the
+// sums get longer, four to eight times in parts, and a chain of layers amplifies the bits that
+// differ from the other kernels' to a hundredth of the result.)
+//
+// What bounds it: neither memory nor arithmetic alone.  28672 x 4096 at 8 tokens takes 16.5
+// (W4A8) to 18.8 us (W4A16), 3.5 to 4 TB/s; the per-tile grid that loaded straight into
+// registers took 25 and 31.  Without the loads it takes 12, the vector ALUs busy most of that,
+// without either 6.  The sixty-four chains cost registers and a longer way through LDS: with a
+// scale per group 16384 x 3072 takes 10.1 us at 4 tokens (8.6 in one chain per wave; a wave per
+// row, which served these calls before, 18.7), 28672 x 4096 20, 27 and 57 us at 8, 16 and 32
+// tokens (that: 63, 111 and 202).  Two to four blocks in flight per wave instead of one, with
+// fewer workgroups per compute unit, were no faster.
+//
+// W, NG: eight waves with blocks of eight groups, or where that is better
+//  - four waves, in eight column chains (see slice_eight_waves), and with a scale per group and up to
+//    eight tokens from two row tiles per compute unit on (28672 x 4096: 20.4 against 21.6;
+//    4096 x 14336 14.5 against 10.2, so not below);
+//  - blocks of four groups.  They load half lines, which costs 5-15 % where nothing else
+//    changes, and are taken where eight leave room in LDS for one workgroup only: W4A16 at 17
+//    tokens and more (16384 x 3072, 32 tokens: 12.9 us against 17.5), W4A16 at 9 to 16 and W4A8
+//    at 17 and more tokens with more row tiles than compute units (8192 x 4096: 8.3 against 9.0
+//    and 9.5 against 11.7; with fewer tiles 14.6 against 13.5 at K = 14336); and where eight
+//    waves in eight chains need them (slice_eight_waves).
 //
 // SCB: bytes per scale load.  16: K is a multiple of 256 and the scales are aligned to
 // that (one load per row and block); 4 or 2: any other K, scales aligned to 4 bytes and an
 // even number of groups, or not; the last block may then end early (its missing groups
 // are loaded as the last one again and not multiplied).
 #pragma once
+
+#include <type_traits>
 
 #include "gemv_tile.h"
 #include "mfma_act.h"
@@ -34,32 +60,49 @@ namespace {
 
 typedef __attribute__((address_space(3))) void *slice_lds_ptr;
 
+// The value of lane i ^ 1 or i ^ 2.
+constexpr int kDppXor1 = 0xb1, kDppXor2 = 0x4e;
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float v) {
+    const int i = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, CTRL, 0xf, 0xf, false));
+}
+
 constexpr int slice_vmcnt(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 
-// What a block takes in a wave's ring: TOK tokens (8, 16 or 32), RT 16-row tiles.
-template <int PREC, bool PG, int TOK, int RT, int SCB>
+// What a block of NG groups takes in a wave's ring: TOK tokens (8, 16 or 32), RT 16-row tiles.
+template <int PREC, bool PG, int TOK, int RT, int NG, int SCB>
 struct SliceBlock {
-    // groups per block: half as many where the activations would fill the ring
-    static constexpr int NG = PREC == NVQ_W4A16 && TOK == 32 ? 4 : 8;
     static_assert(SCB != 16 || NG == 8, "16 bytes are the scales of eight groups");
     static constexpr int kTokenBytes = NG * (PREC == NVQ_W4A8 ? 32 : 64);
     // scales: [16 bytes of a row], or words of 4 bytes, [pair of groups or group][row]
-    static constexpr int kScOps = SCB == 16 ? (RT + 3) / 4 : NG == 4 && SCB == 4 && RT == 1 ? 1 : RT * (SCB == 4 ? 1 : 2) * NG / 8;
+    static constexpr int kScOps = SCB == 16 ? 1 : NG == 4 && SCB == 4 && RT == 1 ? 1 : RT * (SCB == 4 ? 1 : 2) * NG / 8;
     static constexpr int kScBytes = SCB == 16 ? RT * 256 : kScOps * 256;
+    static constexpr int kPieces = kTokenBytes / 16, kMixed = (kPieces < 16 ? kPieces : 16) - 1;
     static constexpr int kAOps = TOK * kTokenBytes / 1024;
-    static constexpr int kXsOps = PG ? TOK / 8 : 0;  // 64 lanes x 4 bytes, eight scales per token
+    static constexpr int kXsOps = PG ? TOK * NG / 64 : 0;  // 64 lanes x 4 bytes, NG scales per token
     static constexpr int kWOps = RT * NG / 4, kWTile = 256 * NG;
     static constexpr int kW = 0, kSc = kW + RT * kWTile, kA = kSc + kScBytes;
     static constexpr int kXs = kA + TOK * kTokenBytes, kBytes = kXs + kXsOps * 256;
-    static constexpr int kOps = kWOps + kScOps + kAOps + kXsOps;
 
-    // Where lane row kb finds the scales of its first token, and its token's place among the
+    // With up to eight tokens lane rows 2 and 3 of a product hold no token.  The products of
+    // groups i and i + 4 of a block are therefore put into one register each, group i + 4 in the
+    // upper half of the lanes, and rescaled and added together: a pair of groups costs 4 fmaf, 4
+    // (W4A8) conversions and 4 exchanges instead of 8 and 8, with half the registers.
+    static constexpr bool kPair = TOK == 8 && NG == 8;
+    static constexpr int group_half(int kb) { return kPair ? kb >> 1 : 0; }  // whose groups lane row kb adds
+
+    // Where lane row kb finds the scales of its first token, and a token's place among the
     // activations: what stands for tokens that are not there is read from another's.
-    static constexpr int xs_place(int kb) { return 128 * (TOK < 16 ? kb & (TOK / 4 - 1) : kb); }
+    static constexpr int xs_place(int kb) {
+        return 16 * NG * (TOK < 16 ? kb & (TOK / 4 - 1) : kb) + 16 * group_half(kb);
+    }
     static constexpr int token_place(int n) { return (TOK < 16 ? n & (TOK - 1) : n) * kTokenBytes; }
     // The last byte that the reads of a block touch lies inside the piece it belongs to.
     static constexpr int kTiles = (TOK + 15) / 16, kRowBytes = 16 * NG;
     static constexpr int kScWords = SCB == 2 ? NG : NG / 2;  // words with the scales of a row
+    static constexpr int kScRead = kPair ? kScWords / 2 : kScWords, kXsRead = kPair ? 1 : NG / 4;  // per lane
+    static constexpr int kScStep = SCB == 16 ? 4 : 64 * RT;  // from word to word
     static constexpr int largest(int (*place)(int), int n) {
         int m = 0;
         for (int i = 0; i < n; ++i) m = place(i) > m ? place(i) : m;
@@ -69,22 +112,28 @@ struct SliceBlock {
     static_assert((SCB == 16 ? RT * 256 : kScWords * 16 * RT * 4) <= kScBytes, "scales");
     static_assert(largest(token_place, 16) + (kTiles - 1) * 16 * kTokenBytes + kTokenBytes <= TOK * kTokenBytes,
                   "activations");
-    static_assert(!PG || largest(xs_place, 4) + ((kTiles - 1) * 16 + 3) * 32 + 32 <= kXsOps * 256,
+    static_assert(!PG || largest(xs_place, 4) + ((kTiles - 1) * 16 + 3) * 4 * NG + 16 * kXsRead <= kXsOps * 256,
                   "activation scales");
 };
 
-// Waves per workgroup.
-constexpr int slice_waves(int RT) { return RT == 1 ? 8 : 4; }
-
-template <int PREC, bool PG, int TOK, int RT, int SCB, bool DEBUG>
-__global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
-    GemvSegs S, int G, int M, const char *__restrict__ xin, const float *__restrict__ xscale) {
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, bool DEBUG>
+__global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, int M, const char *__restrict__ xin,
+                                                            const float *__restrict__ xscale) {
     typedef Act<PREC> A;
-    typedef SliceBlock<PREC, PG, TOK, RT, SCB> B;
+    typedef SliceBlock<PREC, PG, TOK, RT, NG, SCB> B;
     constexpr bool TAIL = SCB != 16;
-    constexpr int NG = B::NG, W = slice_waves(RT), MT = (TOK + 15) / 16;
+    constexpr int MT = B::kTiles;
     constexpr int kTile = RT * MT * 4;  // result registers per lane
-    constexpr int kRing = W * B::kBytes, kRed = W * kTile * 256;
+    // The chains that meet in a wave: C of every block, and the blocks take turns over U sets
+    // of them (block b belongs to set b % U).  Chain of set u, place c: (C (w + W u) + c) % V.
+    constexpr bool kByGroup = V == 64;
+    constexpr int C = kByGroup ? NG : NG / 4, U = V / (C * W);
+    constexpr int CR = B::kPair ? C / 2 : C;  // their registers: place c + C / 2 in the upper half
+    static_assert(U * C * W == V && (U == 1 || U == 2), "every chain has one place");
+    constexpr int SH = W / 2;  // by group: lanes that share a result
+    static_assert(!kByGroup || SH == 2 || SH == 4, "128 results at a time");
+    constexpr int kRing = W * B::kBytes, kRedStride = 128 + 64 / SH;
+    constexpr int kRed = kByGroup ? W * C * kRedStride * 4 : V * kTile * 256;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing > kRed ? kRing : kRed];
 
     const int lane = threadIdx.x & 63;
@@ -115,21 +164,21 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
         ssrc[k] = reinterpret_cast<const char *>(locate_row(S, row0 + word % kRows, G).sc);
     }
     // activations: 2 or 4 tokens per instruction, pieces permuted against each other
-    constexpr int kPieces = B::kTokenBytes / 16;  // 16 or 32
+    constexpr int kPieces = B::kPieces;
     uint32_t aoff[B::kAOps];
     int apiece[B::kAOps];
 #pragma unroll
     for (int j = 0; j < B::kAOps; ++j) {
         const int m = j * (64 / kPieces) + lane / kPieces;
-        const int p = (lane % kPieces) ^ (m & 15);
+        const int p = (lane % kPieces) ^ (m & B::kMixed);
         aoff[j] = (uint32_t)(m < M ? m : M - 1) * (uint32_t)(G * 32 * A::kBytes) + (TAIL ? 0u : 16u * (uint32_t)p);
         apiece[j] = p;
     }
-    uint32_t xsoff[PG ? B::kXsOps : 1];  // word l: scale l % 8 of token l / 8
+    uint32_t xsoff[PG ? B::kXsOps : 1];  // word l: scale l % NG of token l / NG
     if (PG) {
 #pragma unroll
         for (int j = 0; j < B::kXsOps; ++j) {
-            const int m = j * 8 + (lane >> 3);
+            const int m = j * (64 / NG) + lane / NG;
             xsoff[j] = (uint32_t)(m < M ? m : M - 1) * (uint32_t)G;
         }
     }
@@ -145,7 +194,7 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
         for (int k = 0; k < B::kScOps; ++k) {
             if (SCB == 16) {
                 const char *p = ssrc[k] + (size_t)g0 * 2;
-                if (RT == 4 || lane < kRows)
+                if (lane < kRows)
                     __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kSc), 16, 0, 0);
             } else if (SCB == 4) {  // (a pair of groups is inside the row or outside it)
                 const int g = g0 + sg[k];
@@ -171,19 +220,23 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
         if (PG) {
 #pragma unroll
             for (int j = 0; j < B::kXsOps; ++j) {
-                const float *p = xscale + (xsoff[j] + (uint32_t)clamp_g(g0 + (lane & 7)));
+                const float *p = xscale + (xsoff[j] + (uint32_t)clamp_g(g0 + lane % NG));
                 __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kXs + j * 256), 4, 0, 0);
             }
         }
     };
 
-    float f[RT][MT][4];
+    float f[U][CR][RT][MT][4];
 #pragma unroll
-    for (int r = 0; r < RT; ++r)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int c = 0; c < CR; ++c)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) f[r][mt][jj] = 0.0f;
+            for (int r = 0; r < RT; ++r)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj) f[u][c][r][mt][jj] = 0.0f;
 
     // The lane's places in its piece of LDS, for group i of the block.  Weights: dword kb of
     // piece i of row n (what the MFMA's weight operand of group i wants), 64 different banks;
@@ -191,43 +244,47 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
     // the group), for W4A8 a dword twice.
     const uint32_t at = (uint32_t)(uintptr_t)slot;
     const int mn = TOK < 16 ? n & (TOK - 1) : n;
-    uint32_t wpos[NG], apos[NG][2];
-#pragma unroll
-    for (int i = 0; i < NG; ++i) {
-        wpos[i] = at + n * (16 * NG) + 16 * (i ^ ((n / (16 / NG)) % NG)) + 4 * kb;
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (PREC == NVQ_W4A8)
-                apos[i][h] = at + B::token_place(n) + 16 * ((2 * i + h) ^ mn) + 4 * kb;
-            else
-                apos[i][h] = at + B::token_place(n) + 16 * ((4 * i + 2 * h + (kb >> 1)) ^ mn) + 8 * (kb & 1);
-        }
-    }
-    const uint32_t spos = at + (SCB == 16 ? 16 : 4) * n;
-    const uint32_t xspos = at + B::xs_place(kb);  // token 4 kb, 32 bytes per token
+    // The permutations leave the rest of an address alone: another piece is one xor away.  With
+    // 9 to 16 tokens and a scale per group the addresses are made anew for every block, so that
+    // the registers suffice for two workgroups per compute unit (28672 x 4096, 16 tokens: 27 us
+    // against 36); elsewhere they stay in registers.
+    constexpr bool kFresh = PG && TOK == 16;
+    const uint32_t wpos0 = at + n * (16 * NG) + 16 * ((n / (16 / NG)) % NG) + 4 * kb;
+    const uint32_t apos0 = B::token_place(n) + (PREC == NVQ_W4A8 ? 16 * (mn & B::kMixed) + 4 * kb
+                                                                : 16 * ((kb >> 1) ^ mn) + 8 * (kb & 1));
+    auto wpiece = [&](uint32_t p0, int i) { return p0 ^ (uint32_t)(16 * i); };
+    auto apiece_at = [&](uint32_t p0, int i, int h) {
+        return at + (p0 ^ (uint32_t)(16 * (PREC == NVQ_W4A8 ? 2 * i + h : 4 * i + 2 * h)));
+    };
+    const int half = B::group_half(kb);
+    const uint32_t spos = at + (SCB == 16 ? 16 : 4) * n + half * B::kScRead * B::kScStep;
+    const uint32_t xspos = at + B::xs_place(kb);  // token 4 kb, 4 NG bytes per token
 
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD64(dst_, addr_, off_) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD128(dst_, addr_, off_) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
-    if (nblk > 0) issue(0);
-    for (int b = 0; b < nblk; ++b) {
+    // block b of set u
+    auto block = [&](int b, auto set) {
+        constexpr int u = decltype(set)::value;
         __builtin_amdgcn_s_waitcnt(slice_vmcnt(0));
         asm volatile("" ::: "memory");
 
-        constexpr int kSc = B::kScWords;
+        constexpr int kSc = B::kScRead;
         uint32_t q[RT][NG], sc[RT][kSc];
+        uint32_t wpos = wpos0, apos = apos0;
+        if (kFresh) asm volatile("" : "+v"(wpos), "+v"(apos));
         uint2v a2[PREC == NVQ_W4A8 ? 1 : MT][NG][2];
         uint32_t a1[PREC == NVQ_W4A8 ? MT : 1][NG][2];
-        float4v xs4[PG ? MT : 1][4][2];
+        float4v xs4[PG ? MT : 1][4][B::kXsRead];
 #pragma unroll
         for (int i = 0; i < NG; ++i)
 #pragma unroll
-            for (int r = 0; r < RT; ++r) NVQ_RD32(q[r][i], wpos[i], B::kW + r * B::kWTile);
+            for (int r = 0; r < RT; ++r) NVQ_RD32(q[r][i], wpiece(wpos, i), B::kW + r * B::kWTile);
 #pragma unroll
         for (int r = 0; r < RT; ++r)
 #pragma unroll
             for (int k = 0; k < kSc; ++k)
-                NVQ_RD32(sc[r][k], spos, B::kSc + (SCB == 16 ? r * 256 + k * 4 : (k * kRows + 16 * r) * 4));
+                NVQ_RD32(sc[r][k], spos, B::kSc + r * (SCB == 16 ? 256 : 64) + k * B::kScStep);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -235,9 +292,9 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     if (PREC == NVQ_W4A8)
-                        NVQ_RD32(a1[mt][i][h], apos[i][h], B::kA + mt * 16 * B::kTokenBytes);
+                        NVQ_RD32(a1[mt][i][h], apiece_at(apos, i, h), B::kA + mt * 16 * B::kTokenBytes);
                     else
-                        NVQ_RD64(a2[mt][i][h], apos[i][h], B::kA + mt * 16 * B::kTokenBytes);
+                        NVQ_RD64(a2[mt][i][h], apiece_at(apos, i, h), B::kA + mt * 16 * B::kTokenBytes);
                 }
         if (PG) {
 #pragma unroll
@@ -245,8 +302,8 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        NVQ_RD128(xs4[mt][jj][h], xspos, B::kXs + (mt * 16 + jj) * 32 + h * 16);
+                    for (int h = 0; h < B::kXsRead; ++h)
+                        NVQ_RD128(xs4[mt][jj][h], xspos, B::kXs + (mt * 16 + jj) * 4 * NG + h * 16);
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
@@ -264,144 +321,206 @@ __global__ __launch_bounds__(slice_waves(RT) * 64) void gemv_slice_kernel(
                     asm volatile("" : "+v"(a1[mt][i][0]), "+v"(a1[mt][i][1]));
                 else
                     asm volatile("" : "+v"(a2[mt][i][0]), "+v"(a2[mt][i][1]));
-                if (PG) asm volatile("" : "+v"(xs4[mt][i & 3][i >> 2]));
+                if (PG && i < 4 * B::kXsRead) asm volatile("" : "+v"(xs4[mt][i & 3][i >> 2]));
             }
         if (b + 1 < nblk) issue(b + 1);
 
-        // With a scale per group the products are rounded and the sums have no low zero bits to
-        // lose: half a block is summed by itself first, so that fewer terms meet the large sum
-        // (relative error 0.9e-7 instead of 1.5e-7 at K = 14336).
-        float fb[PG ? RT : 1][PG ? MT : 1][4];
-        if (PG) {
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) fb[PG ? r : 0][PG ? mt : 0][jj] = 0.0f;
-        }
         const int g0 = NG * (w + W * b);
-#pragma unroll
-        for (int i = 0; i < NG; ++i) {
-            if (TAIL && g0 + i >= G) break;  // the last block may end early
-            if (PG && (i & 3) == 0 && i > 0) {
-#pragma unroll
-                for (int r = 0; r < RT; ++r)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int jj = 0; jj < 4; ++jj) {
-                            f[r][mt][jj] += fb[PG ? r : 0][PG ? mt : 0][jj];
-                            fb[PG ? r : 0][PG ? mt : 0][jj] = 0.0f;
-                        }
+        auto activation = [&](int mt, int i) {
+            if constexpr (PREC == NVQ_W4A8) {
+                return (long)((uint64_t)a1[mt][i][0] | ((uint64_t)a1[mt][i][1] << 32));
+            } else {
+                const uint4v v = {a2[mt][i][0].x, a2[mt][i][0].y, a2[mt][i][1].x, a2[mt][i][1].y};
+                return __builtin_bit_cast(bf16x8, v);
             }
+        };
+        auto dump = [&](const int4v &raw, int i, int r, int mt) {
+            const RowRef o = locate_row(S, row0 + 16 * r + n, G);
+            if (!o.valid || !o.dbg || g0 + i >= G) return;
+            const int acc[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                typename A::operand act;
-                if constexpr (PREC == NVQ_W4A8) {
-                    act = (long)((uint64_t)a1[mt][i][0] | ((uint64_t)a1[mt][i][1] << 32));
-                } else {
-                    const uint4v v = {a2[mt][i][0].x, a2[mt][i][0].y, a2[mt][i][1].x, a2[mt][i][1].y};
-                    act = __builtin_bit_cast(bf16x8, v);
-                }
-                const typename A::offset_t off = A::offset(act);
+            for (int jj = 0; jj < 4; ++jj) {
+                const int m = mt * 16 + kb * 4 + jj;
+                if (m < M) o.dbg[((int64_t)m * o.N + o.n) * G + g0 + i] = acc[jj];
+            }
+        };
+        // what the lane adds in round i: group i, or i + 4 in the upper half of a pair
+        auto add = [&](const float4v &p, int i, int r, int mt) {
+            const uint32_t sb = SCB == 2 ? sc[r][i] : sc[r][i >> 1] >> (16 * (i & 1));
+            const float sw = half_bits_to_float((uint16_t)sb);
+            float (&sum)[4] = f[u][kByGroup ? i : i >> 2][r][mt];
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) {
+                const float sj = PG ? sw * xs4[PG ? mt : 0][jj][i >> 2][i & 3] : sw;
+                sum[jj] = fmaf(sj, p[jj], sum[jj]);
+            }
+        };
+        if constexpr (B::kPair) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (TAIL && g0 + i >= G) break;  // the last block may end early
+                const auto lo = activation(0, i), hi = activation(0, i + 4);
+                const auto off_lo = A::offset(lo), off_hi = A::offset(hi);
 #pragma unroll
                 for (int r = 0; r < RT; ++r) {
-                    const uint32_t sb = SCB == 2 ? sc[r][i] : sc[r][i >> 1] >> (16 * (i & 1));
-                    const float sw = half_bits_to_float((uint16_t)sb);
-                    int4v raw;
-                    float4v p = A::product(act, A::weights(q[r][i]), off, raw);
-                    if (PG) {
-                        p.x *= xs4[mt][0][i >> 2][i & 3];
-                        p.y *= xs4[mt][1][i >> 2][i & 3];
-                        p.z *= xs4[mt][2][i >> 2][i & 3];
-                        p.w *= xs4[mt][3][i >> 2][i & 3];
-                    }
-                    float (&sum)[4] = PG ? fb[PG ? r : 0][PG ? mt : 0] : f[r][mt];
-                    sum[0] = fmaf(sw, p.x, sum[0]);
-                    sum[1] = fmaf(sw, p.y, sum[1]);
-                    sum[2] = fmaf(sw, p.z, sum[2]);
-                    sum[3] = fmaf(sw, p.w, sum[3]);
+                    int4v raw_lo, raw_hi;
+                    const float4v plo = A::product(lo, A::weights(q[r][i]), off_lo, raw_lo);
+                    const float4v phi = A::product(hi, A::weights(q[r][i + 4]), off_hi, raw_hi);
                     if (DEBUG && PREC == NVQ_W4A8) {
-                        const RowRef o = locate_row(S, row0 + 16 * r + n, G);
-                        if (o.valid && o.dbg) {
-                            const int acc[4] = {raw.x, raw.y, raw.z, raw.w};
+                        dump(raw_lo, i, r, 0);
+                        dump(raw_hi, i + 4, r, 0);
+                    }
+                    float4v p;
 #pragma unroll
-                            for (int jj = 0; jj < 4; ++jj) {
-                                const int m = mt * 16 + kb * 4 + jj;
-                                if (m < M) o.dbg[((int64_t)m * o.N + o.n) * G + g0 + i] = acc[jj];
-                            }
-                        }
+                    for (int jj = 0; jj < 4; ++jj) {
+                        if constexpr (PREC == NVQ_W4A8)
+                            p[jj] = (float)(int)__builtin_amdgcn_permlane32_swap((uint32_t)raw_lo[jj], (uint32_t)raw_hi[jj],
+                                                                                 false, false)[0];
+                        else
+                            p[jj] = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(plo[jj]),
+                                                                                     __float_as_uint(phi[jj]), false, false)[0]);
+                    }
+                    if (!TAIL || g0 + i + 4 * half < G) add(p, i, r, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NG; ++i) {
+                if (TAIL && g0 + i >= G) break;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const auto act = activation(mt, i);
+                    const auto off = A::offset(act);
+#pragma unroll
+                    for (int r = 0; r < RT; ++r) {
+                        int4v raw;
+                        const float4v p = A::product(act, A::weights(q[r][i]), off, raw);
+                        if (DEBUG && PREC == NVQ_W4A8) dump(raw, i, r, mt);
+                        add(p, i, r, mt);
                     }
                 }
             }
         }
-        if (PG) {
-#pragma unroll
-            for (int r = 0; r < RT; ++r)
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) f[r][mt][jj] += fb[PG ? r : 0][PG ? mt : 0][jj];
-        }
+    };
+    if (nblk > 0) issue(0);
+    for (int b = 0; b < nblk; b += U) {
+        block(b, std::integral_constant<int, 0>());
+        if (U == 2 && b + 1 < nblk) block(b + 1, std::integral_constant<int, U - 1>());
     }
 #undef NVQ_RD32
 #undef NVQ_RD64
 #undef NVQ_RD128
 
-    // Sum the slices.
-    float xs[MT][4];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int m = mt * 16 + kb * 4 + jj;
-            xs[mt][jj] = (PREC == NVQ_W4A8 && !PG && m < M) ? as_global<float>(xscale)[m] : 1.0f;
-        }
-    float (*const red)[kTile][64] = reinterpret_cast<float (*)[kTile][64]>(lds);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < RT; ++r)
+    // a W4A8 layer with a scale per token: that scale, else 1
+    auto token_scale = [&](int m) { return PREC == NVQ_W4A8 && !PG && m < M ? as_global<float>(xscale)[m] : 1.0f; };
+    auto store = [&](int row, int m, float sum) {
+        const RowRef o = locate_row(S, row, G);
+        if (o.valid && m < M) store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, sum);
+    };
+    __syncthreads();  // the blocks' LDS is free
+    if constexpr (!kByGroup) {
+        // the chains one after the other
+        float (*const red)[kTile][64] = reinterpret_cast<float (*)[kTile][64]>(lds);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int jj = 0; jj < 4; ++jj) red[w][(r * MT + mt) * 4 + jj][lane] = f[r][mt][jj] * xs[mt][jj];
-    __syncthreads();
+            for (int jj = 0; jj < 4; ++jj) {
+                const float xs = token_scale(mt * 16 + (B::kPair ? kb & 1 : kb) * 4 + jj);
 #pragma unroll
-    for (int pass = 0; pass < (kTile + W - 1) / W; ++pass) {
-        const int reg = pass * W + w;
-        if (reg < kTile) {
-            float part[W];  // added in pairs
+                for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int k = 0; k < W; ++k) part[k] = red[k][reg][lane];
+                    for (int c = 0; c < CR; ++c)
 #pragma unroll
-            for (int step = 1; step < W; step *= 2)
+                        for (int r = 0; r < RT; ++r)
+                            red[C * (w + W * u) + c + half * (C / 2)][(r * MT + mt) * 4 + jj][B::kPair ? lane & 31 : lane] =
+                                f[u][c][r][mt][jj] * xs;
+            }
+        __syncthreads();
 #pragma unroll
-                for (int k = 0; k < W; k += 2 * step) part[k] += part[k + step];
-            const float sum = part[0];
-            const int r = reg / (MT * 4), mt = (reg >> 2) % MT, jj = reg & 3;
-            const int m = mt * 16 + kb * 4 + jj;
-            const RowRef o = locate_row(S, row0 + 16 * r + n, G);
-            if (o.valid && m < M) store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, sum);
+        for (int pass = 0; pass < (kTile + W - 1) / W; ++pass) {
+            const int reg = pass * W + w;
+            if (reg < kTile) {
+                float sum = 0.0f;
+#pragma unroll
+                for (int k = 0; k < V; ++k) sum += red[k][reg][B::kPair ? lane & 31 : lane];
+                const int r = reg / (MT * 4), mt = (reg >> 2) % MT, jj = reg & 3;
+                store(row0 + 16 * r + n, mt * 16 + kb * 4 + jj, sum);
+            }
+        }
+    } else {
+        // Chain 64 u / U + C w + c.  Those 64 / U apart meet in their wave's registers; then 128
+        // results of every chain at a time (two registers of all lanes, or, in pairs, four of half
+        // of them) go to LDS, and SH neighbouring lanes share a result: lane t of them adds the
+        // chains SH q + t, in pairs, and their sums meet in the lanes.
+        constexpr int kRegs = B::kPair ? 4 : 2, kRounds = kTile / kRegs, NQ = W * C / SH;
+        float (*const red)[kRedStride] = reinterpret_cast<float (*)[kRedStride]>(lds);
+        const int share = (int)threadIdx.x % SH, result = (int)threadIdx.x / SH;
+#pragma unroll
+        for (int round = 0; round < kRounds; ++round) {
+            if (round > 0) __syncthreads();
+#pragma unroll
+            for (int c = 0; c < CR; ++c)
+#pragma unroll
+                for (int p = 0; p < kRegs; ++p) {
+                    const int reg = kRegs * round + p, r = reg / (MT * 4), mt = (reg >> 2) % MT, jj = reg & 3;
+                    const float v = U == 2 ? f[0][c][r][mt][jj] + f[U - 1][c][r][mt][jj] : f[0][c][r][mt][jj];
+                    red[C * w + c + half * (C / 2)][B::kPair ? 32 * p + (lane & 31) : 64 * p + lane] = v;
+                }
+            __syncthreads();
+            {
+                float v[NQ];
+#pragma unroll
+                for (int q = 0; q < NQ; ++q) v[q] = red[SH * q + share][result];
+#pragma unroll
+                for (int apart = NQ / 2; apart > 0; apart >>= 1)
+#pragma unroll
+                    for (int q = 0; q < apart; ++q) v[q] += v[q + apart];
+                if (SH == 4) v[0] += dpp_f32<kDppXor2>(v[0]);
+                v[0] += dpp_f32<kDppXor1>(v[0]);
+                const int reg = kRegs * round + (B::kPair ? result >> 5 : result >> 6);
+                const int r = reg / (MT * 4);
+                const int m = 16 * ((reg >> 2) % MT) + 4 * ((result >> 4) & (B::kPair ? 1 : 3)) + (reg & 3);
+                if (share == 0) store(row0 + 16 * r + (result & 15), m, v[0] * token_scale(m));
+            }
         }
     }
 }
 
-template <int PREC, bool PG, int TOK, int RT, int SCB, bool DEBUG = false>
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, bool DEBUG = false>
 int slice_go(const GemvSegs &S, int G, int M, const void *x, const float *xscale, hipStream_t st) {
     const int units = (S.total_rows + 16 * RT - 1) / (16 * RT);
-    hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, SCB, DEBUG>), dim3(units),
-                       dim3(slice_waves(RT) * 64), 0, st, S, G, M, reinterpret_cast<const char *>(x), xscale);
+    hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, W, NG, V, SCB, DEBUG>), dim3(units), dim3(W * 64), 0, st,
+                       S, G, M, reinterpret_cast<const char *>(x), xscale);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }
 
-// Row tiles per workgroup.  Sixteen rows and eight waves where there are few rows (8 tokens,
-// 4096 x 14336: 10.7 us against 16.9 with 32 rows; 6144 x 4096: 6.6 against 7.6), 32 where
-// those make about two workgroups per compute unit and the tokens' inputs, which every
-// workgroup reads, count (28672 x 4096: 18.2 against 21.7 us, at 16 tokens 21.8 against
-// 32.0; 16384 x 3072, 4 tokens: 8.8 against 9.3).
-inline int slice_row_tiles(int rows) { return rows >= 48 * device_cu_count() ? 2 : 1; }
+// Whether a phase has more than two row tiles per compute unit.
+inline bool slice_many(int rows) { return (rows + 15) / 16 > 2 * device_cu_count(); }
+
+// How many chains a result is added in (see above): sixteen where there are at most two row
+// tiles per compute unit, so that eight waves share a tile, and every chain still gets two
+// columns (8 tokens, 4096 x 14336: 9.5 us against 16.9 with four waves and two tiles each).
+inline int slice_chains(const GemvSegs &S, int G, int M, bool per_group) {
+    if (per_group || !gemv_mfma_supported(S, G * 32, M)) return 64;
+    return G >= 128 && !slice_many(S.total_rows) ? 16 : 8;
+}
+
+// Row tiles per workgroup of four waves (eight chains): two where those still make two
+// workgroups per compute unit and the tokens' inputs, which every workgroup reads, count.  28672
+// x 4096, W4A16: 18.9, 21.7 and 32.0 us at 8, 16 and 32 tokens against 20.4, 26.2 and 39.8 with
+// one, W4A8 17.1, 19.2, 26.6 against 17.9, 21.9, 33.3; 16384 x 3072 8.8 to 12.8 against 8.3 to
+// 15.4; 12288 x 2048 6.6 to 9.7 against 5.7 to 9.7, and below that one is better at any number of
+// tokens (5120 x 3072: 5.2 against 6.1).
+inline int slice_row_tiles(int rows) { return rows >= 64 * device_cu_count() ? 2 : 1; }
+
+// Whether a phase has more row tiles than compute units, so that two workgroups share one.
+inline bool slice_shared(int rows) { return (rows + 15) / 16 > device_cu_count(); }
+
+// Eight column chains and one row tile: eight waves with half blocks instead of four with whole
+// ones, where a compute unit has no second row tile (2048 x 2048, 16 tokens: 3.5 us against 4.0;
+// 12288 x 3072 7.6 against 7.1), and at 17 tokens and more (3072 x 3072: 5.7 against 6.7).
+inline bool slice_eight_waves(int rows, int tokens) { return tokens > 16 || !slice_shared(rows); }
 
 // The scale loads a phase allows (see SCB).
 inline int slice_scale_bytes(const GemvSegs &S, int G) {

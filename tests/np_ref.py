@@ -37,3 +37,32 @@ def rel_l2(a: np.ndarray, b: np.ndarray) -> float:
     d = np.linalg.norm(a - b)
     n = np.linalg.norm(b)
     return float(d / n) if n > 0 else float(d)
+
+
+def sums_in_order(acc, sw, chains, xs=None, by_group=False):
+    """float32 [M, N]: sum_g sw[n, g] * (xs[m, g]) * acc[m, n, g] in the order of the multi-token
+    kernels, every step one fused multiply-add rounded to float32.  chains = 64: chain v takes groups
+    v, v + 64, ..., and the chains are added in pairs, those 32 apart first; else chain v takes the
+    columns (four groups) v, v + chains, ..., and the chains are added in order.  A scale per group
+    (by_group) multiplies the weights' scale; one per token multiplies a chain's sum (columns) or the
+    result.  (The steps are taken in 64-bit significands: rounding twice instead of once shows at
+    one step in some 2^39.)"""
+    M, N, G = acc.shape
+    sw = np.asarray(sw, np.float32)
+    xs = np.ones((M, G) if by_group else M, np.float32) if xs is None else np.asarray(xs, np.float32)
+    f = np.zeros((chains, M, N), np.float32)
+    for g in range(G):
+        v = g % chains if chains == 64 else (g // 4) % chains
+        s = np.broadcast_to(sw[None, :, g], (M, N))
+        if by_group:
+            s = s * xs[:, None, g]
+        f[v] = (s.astype(np.longdouble) * acc[:, :, g] + f[v]).astype(np.float32)
+    if chains == 64:
+        while f.shape[0] > 1:
+            h = f.shape[0] // 2
+            f = f[:h] + f[h:]
+        return f[0] if by_group else f[0] * xs[:, None]
+    y = np.zeros((M, N), np.float32)
+    for v in range(chains):
+        y = y + (f[v] if by_group else f[v] * xs[:, None])
+    return y

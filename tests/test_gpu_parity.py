@@ -226,6 +226,57 @@ def test_small_batch_kernel_edges(M, N, K, off):
         assert err < 1e-5
 
 
+# The order of the additions, which decides the last bits, is that of the call and not of the
+# kernel's tiling: eight or sixteen chains of columns (K % 128 == 0, scales aligned to 8 bytes, a
+# scale per token), or sixty-four of groups.  Rows and tokens that reach each tiling (16 and 32
+# rows per workgroup, up to 8, 16 and 32 tokens, more and fewer row tiles than compute units), K
+# whose last block of eight groups ends early, K beyond 16384.
+@pytest.mark.parametrize("M,N,K,off", [(3, 48, 4096, 0), (12, 33, 14336, 0), (20, 48, 8320, 0), (9, 4200, 4096, 0),
+                                       (32, 4200, 4224, 0), (8, 40, 3072, 0), (16, 40, 2176, 0), (17, 40, 3072, 0),
+                                       (2, 8300, 4096, 0), (5, 16400, 1024, 0), (16, 16400, 640, 0),
+                                       (24, 16400, 512, 0), (6, 40, 4096, 1), (16, 40, 2720, 0), (25, 40, 2720, 0),
+                                       (4, 16400, 352, 0), (1, 40, 16416, 0), (30, 17, 65536, 0)])
+def test_multi_token_sums_are_added_in_the_stated_order(M, N, K, off):
+    """Bit for bit against the same additions on the CPU.  W4A8: the block sums are integers.  W4A16
+    on small whole inputs: a group's products and their sums are exact whatever their order."""
+    say("order of sums", M, N, K, off)
+    rng = np.random.default_rng(N + K)
+    q = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+    s = rng.integers(0x1400, 0x2c00, (N, K // 32)).astype(np.uint16)
+    qd, sd = to_dev_packed(q, s)
+    if off:
+        buf = torch.zeros(sd.numel() + off, dtype=sd.dtype, device=DEV)
+        buf[off:] = sd.flatten()
+        sd = buf[off:].view(sd.shape)
+    x = act(3600 + K, M, K)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    chains = 64
+    if M > 1 and K % 128 == 0 and not off:
+        chains = 16 if K >= 4096 and (N + 15) // 16 <= 2 * cus else 8
+    rows = np.unique(np.concatenate([np.arange(min(N, 17)), [N - 1], rng.integers(0, N, 16)]))
+    sw = np_ref.half_bits_to_f64(s[rows])
+
+    def check(y, want, what):
+        got = y.cpu().numpy()[:, rows]
+        assert np.array_equal(got, want), (what, int((got != want).sum()), np_ref.rel_l2(got, want))
+
+    for group in (0, 32):
+        xq, xs, gs = nvq.quant_act_i8(x.to(DEV), group)
+        y, dump = nvq.gemv_w4a8(qd, sd, xq, xs, gs, group, want_acc=True)
+        y2 = nvq.gemv_w4a8(qd, sd, xq, xs, gs, group)
+        torch.cuda.synchronize()
+        _, acc = oracle.gemv_w4a8(q[rows], s[rows], xq.cpu().numpy(), xs.cpu().numpy(), group, want_acc=True)
+        assert np.array_equal(dump.cpu().numpy()[:, rows], acc)
+        want = np_ref.sums_in_order(acc, sw, 64 if group else chains, xs.cpu().numpy(), group == 32)
+        check(y2, want, ("w4a8", group))
+        check(y, want, ("w4a8 with the accumulators", group))
+    xi = rng.integers(-99, 100, (M, K)).astype(np.int8)
+    _, acc = oracle.gemv_w4a8(q[rows], s[rows], xi, np.ones(M, np.float32), 0, want_acc=True)
+    y = nvq.gemv_w4a16(qd, sd, torch.from_numpy(xi).to(torch.bfloat16).to(DEV))
+    torch.cuda.synchronize()
+    check(y, np_ref.sums_in_order(acc, sw, chains), "w4a16")
+
+
 @pytest.mark.parametrize("M", [1, 20])
 def test_gemv_w4a8_accepts_every_nibble_and_extreme_codes(M):
     say("w4a8 extremes", M)
