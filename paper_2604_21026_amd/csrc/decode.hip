@@ -509,7 +509,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         cut_batch(gp, cur, M);
         cur.phase_first = batch_first;
         cur.nphases = (int)gp.tab.size() - batch_first;
-        cur.single = rows_or_single(gp, cur);
+        cur.single = gp.ring && M >= kRowsMinTokens && rows_or_single(gp, cur);
         gp.batches.push_back(cur);
     };
     for (size_t p = 0; p < phases.size(); ++p) {
@@ -1019,7 +1019,11 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
 
 extern "C" int nvq_plan_info(const nvq_plan *pl, int *streaming, int *phases, int *waits) {
     if (!pl) return NVQ_ERR_INVALID_ARG;
-    if (streaming) *streaming = pl->nwg > 0 ? 1 : pl->batches.empty() ? 0 : pl->ring ? 3 : 2;
+    if (streaming) {
+        bool grid = false;  // some batch runs as a persistent grid
+        for (const nvq::GroupBatch &b : pl->batches) grid = grid || (pl->ring && !b.single);
+        *streaming = pl->nwg > 0 ? 1 : grid ? 3 : pl->batches.empty() || pl->ring ? 0 : 2;
+    }
     if (phases) *phases = (int)pl->phases.size();
     if (waits) *waits = pl->nwaits;
     return NVQ_OK;
@@ -1123,7 +1127,7 @@ extern "C" int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M,
         o[1] = gb.nunits > 0 ? gp.units[(size_t)gb.unit_first + gb.nunits - 1] : -1;
         o[2] = gb.nunits;
         o[3] = gb.njobs;
-        o[4] = gb.grid;
+        o[4] = gb.single ? 0 : gb.grid;
         o[5] = gb.nparts;
         for (int k = 0; k <= gb.nparts && gb.nparts > 0; ++k) {
             o[6 + k] = (int32_t)gp.parts[(size_t)gb.part_first + k];

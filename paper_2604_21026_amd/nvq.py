@@ -356,7 +356,7 @@ class DecodeList:
 
 def plan_describe_batches(linears: Sequence[Linear], M: int, ordered: bool = False):
     """Host-side planning of the grouped small-batch launches (no device needed):
-    (persistent kernel used, [dict per batch])."""
+    (every phase qualifies for a persistent kernel, [dict per batch; grid 0: phase by phase])."""
     n = len(linears)
     arr = (Linear * max(n, 1))(*linears)
     per = 6 + 2 * 9

@@ -61,6 +61,7 @@ def test_full_step_sampled_rows_match_oracle(model, M):
     dl.plan()
     info = dl.plan_info()
     assert info["streaming"] == (M == 1)       # batch 1 is the one-launch persistent kernel
+    assert info["persistent_grouped"] == (M > 1)
     for _ in range(2):                          # the second walk reuses flags and images
         dl.run_plan()
     torch.cuda.synchronize()

@@ -495,6 +495,8 @@ STREAM_MODELS = {
     # 8b block shapes, one W4A8 block
     "8b": ([(4096, 4096, 0), (1024, 4096, 0), (1024, 4096, 0), (4096, 4096, 1),
             (14336, 4096, 2), (14336, 4096, 2), (4096, 14336, 3)], (0,)),
+    "8b twice": ([(4096, 4096, 0), (1024, 4096, 0), (1024, 4096, 0), (4096, 4096, 1),
+                  (14336, 4096, 2), (14336, 4096, 2), (4096, 14336, 3)], (0, 1)),
     # llama-3b block shapes (rows of 96 groups go to the waves in pairs), one block of
     # each precision; in the third, layers with an odd number of rows (no pairs there)
     "3b": ([(3072, 3072, 0), (1024, 3072, 0), (1024, 3072, 0), (3072, 3072, 1),
@@ -627,9 +629,12 @@ def test_streaming_plan_orders_dependent_phases():
 
 
 # ---- grouped small-batch walker (2..32 tokens on the matrix cores) -------------------
-@pytest.mark.parametrize("name,M,ordered", [("1b", 5, False), ("1b", 20, True), ("8b", 16, False),
-                                            ("8b", 32, False)])
-def test_grouped_plan_matches_oracle_on_repeated_runs(name, M, ordered):
+# grid: whether the product runs as a persistent grid (every K of these models is a multiple of
+# 512; from 17 tokens on the work has to be enough, otherwise it goes phase by phase)
+@pytest.mark.parametrize("name,M,ordered,grid", [("1b", 5, False, True), ("1b", 20, True, False),
+                                                 ("8b", 16, False, True), ("8b", 32, False, False),
+                                                 ("8b twice", 32, False, True)])
+def test_grouped_plan_matches_oracle_on_repeated_runs(name, M, ordered, grid):
     say("grouped plan", name, M, ordered)
     shapes, bits = STREAM_MODELS[name]
     entries, host = model_entries(shapes, bits, M=M, seed=8300)
@@ -638,7 +643,7 @@ def test_grouped_plan_matches_oracle_on_repeated_runs(name, M, ordered):
     info = dl.plan_info()
     say("  plan", info)
     assert not info["streaming"]
-    assert info["persistent_grouped"]              # every K of these models is a multiple of 512
+    assert info["persistent_grouped"] == grid
     # "waits" counts the batch boundaries: independent buffers make one batch of all phases
     assert info["waits"] == (info["phases"] - 1 if ordered else 0)
     for rep in range(3):
@@ -661,18 +666,20 @@ def test_grouped_plan_matches_oracle_on_repeated_runs(name, M, ordered):
     dl.close()
 
 
-# The persistent small-batch kernel (loader wave + LDS rings) serves lists with every K a
-# multiple of 512; these shapes exercise what its bookkeeping has to get right:
-# row counts that end inside a unit of 32 rows and inside a 16-row tile, phases of several
-# matrices whose boundaries fall inside a unit, a phase with fewer units than teams next to
-# long ones (team ranges that cross phases), K from one step (512) to 28 steps, both
-# precisions, and token counts from 2 to 32 (one or two token tiles).
+# The persistent small-batch kernels (loader wave and LDS rings up to 16 tokens, shared activations
+# and tickets from 17 on) serve lists with every K a multiple of 512; these shapes exercise what
+# their bookkeeping has to get right: row counts that end inside a unit of 32 rows and inside a
+# 16-row tile, phases of several matrices whose boundaries fall inside a unit, a phase with fewer
+# units than teams next to long ones (groups of units that cross phases of other K and precision),
+# K from one step (512) to 28 steps, both precisions, and token counts from 2 to 32 (one or two
+# token tiles).  From 17 tokens on a grid needs a long list: the shapes six times over; two
+# times over they go phase by phase.
 RING_SHAPES = [(1000, 1536, 0), (37, 1536, 0), (3, 1536, 1), (2500, 3072, 2), (777, 3072, 2),
                (64, 14336, 3), (48, 512, 4), (4100, 512, 4), (16, 1024, 5)]
 
 
 @pytest.mark.parametrize("M,bits", [(2, (0, 1)), (7, (1, 0)), (16, (0, 1, 1)), (17, (0, 1)),
-                                    (32, (1, 0))])
+                                    (32, (1, 0)), (17, (0, 1, 0, 1, 1, 0)), (32, (1, 0, 0, 1, 0, 1))])
 def test_ring_plan_matches_oracle(M, bits):
     say("ring plan", M, bits)
     entries, host = model_entries(RING_SHAPES, bits, M=M, seed=8600)
@@ -680,7 +687,7 @@ def test_ring_plan_matches_oracle(M, bits):
     dl = nvq.DecodeList(entries, M, 0)
     info = dl.plan_info()
     say("  plan", info)
-    assert info["grouped"] and info["persistent_grouped"]
+    assert info["grouped"] == info["persistent_grouped"] == (M <= 16 or len(bits) == 6)
     for rep in range(3):
         for e in entries:
             e["y"].zero_()
@@ -734,6 +741,8 @@ def test_rows_plan_short_batches_run_phase_by_phase(M):
                                   seed=8660)
     ys_ref = oracle.decode_linears(host, M, 0)
     dl = nvq.DecodeList(entries, M, 0, ordered=True)
+    info = dl.plan_info()
+    assert not info["grouped"] and info["waits"] == info["phases"] - 1
     for rep in range(2):
         for e in entries:
             e["y"].zero_()
@@ -1046,23 +1055,25 @@ EXACT_SHAPES = [(4096, 4096, 0), (1024, 4096, 0), (1031, 4096, 1), (640, 14336, 
                 (2500, 2048, 3), (77, 8192, 4), (3000, 1024, 5)]
 
 
-@pytest.mark.parametrize("M,group,ordered", [(1, 0, False), (1, 0, True), (1, 32, False),
-                                             (1, 32, True), (2, 0, False), (5, 0, False),
-                                             (16, 0, False), (17, 0, False), (32, 0, False),
-                                             (3, 32, False)])
-def test_exact_sums_are_bit_equal_on_the_timed_kernels(M, group, ordered):
+@pytest.mark.parametrize("M,group,ordered,times", [
+    (1, 0, False, 1), (1, 0, True, 1), (1, 32, False, 1), (1, 32, True, 1), (2, 0, False, 1),
+    (5, 0, False, 1), (16, 0, False, 1), (17, 0, False, 1), (32, 0, False, 1), (17, 0, False, 5),
+    (32, 0, False, 5), (3, 32, False, 1)])
+def test_exact_sums_are_bit_equal_on_the_timed_kernels(M, group, ordered, times):
     """Batch 1: the persistent streaming kernel with its fused quantiser, images prepared in
-    the prologue (independent phases) and built after a wait (forced ordering).  2 to 32
-    tokens: the persistent matrix-core kernel (every K a multiple of 512).  A scale per 32
-    activations at several tokens: launches per phase."""
-    say("exact sums", M, group, ordered)
-    entries, host = exact_list(9000 + M + group, EXACT_SHAPES, M, group == 32)
+    the prologue (independent phases) and built after a wait (forced ordering).  2 to 16
+    tokens: the persistent matrix-core kernel (every K a multiple of 512); 17 to 32: the one of
+    those token counts for a list long enough (the shapes five times), launches per phase for a
+    short one.  A scale per 32 activations at several tokens: launches per phase."""
+    say("exact sums", M, group, ordered, times)
+    shapes = [(N, K, ph + 6 * i) for i in range(times) for N, K, ph in EXACT_SHAPES]
+    entries, host = exact_list(9000 + M + group, shapes, M, group == 32)
     ys_ref = oracle.decode_linears(host, M, group)
     dl = nvq.DecodeList(entries, M, group, ordered=ordered)
     info = dl.plan_info()
     say("  plan", info)
     assert info["streaming"] == (M == 1)
-    assert info["persistent_grouped"] == (M > 1 and group == 0)
+    assert info["persistent_grouped"] == (M > 1 and group == 0 and (M <= 16 or times == 5))
     for rep in range(2):
         for e in entries:
             e["y"].zero_()

@@ -401,11 +401,31 @@ def test_a_chain_makes_one_batch_per_phase_and_small_batches_few_workgroups():
         assert all(p == i for p in b["cut_phases"])
 
 
+@pytest.mark.parametrize("M", [17, 32])
+def test_batches_of_17_tokens_and_more_run_as_a_grid_if_there_is_enough_work(M):
+    """A phase by itself costs 3 us and 2.4 TB/s, the grid 12 us and 3.9 TB/s or 1.7 us per 256
+    inputs of the widest phase, whichever is more."""
+    for blocks, grid in ((1, False), (2, True), (32, True)):
+        layers = model_list_m("llama-8b", [b % 2 for b in range(32)], M)[:7 * blocks]
+        ring, batches = nvq.plan_describe_batches(layers, M)
+        assert ring and len(batches) == 1 and (batches[0]["grid"] > 0) == grid, blocks
+    a = Arena()
+    few = [linear(a, 64, 512, a.take(M * 1024), M=M) for _ in range(5)]      # 15 us against 15.4
+    many = [linear(a, 64, 512, a.take(M * 1024), M=M) for _ in range(6)]
+    assert nvq.plan_describe_batches(few, M)[1][0]["grid"] == 0
+    assert nvq.plan_describe_batches(many, M)[1][0]["grid"] > 0
+    # forced order: every phase is a batch of its own
+    ring, batches = nvq.plan_describe_batches(many, M, ordered=True)
+    assert ring and [b["grid"] for b in batches] == [0] * 6
+    # up to 16 tokens every such batch is a grid
+    assert all(b["grid"] > 0 for b in nvq.plan_describe_batches(many, 16, ordered=True)[1])
+
+
 def test_lists_the_persistent_small_batch_kernel_does_not_take():
     a = Arena()
     x = a.take(32 * 4096 * 2)
     ring, batches = nvq.plan_describe_batches([linear(a, 128, 4096, x, M=32)], 32)
-    assert ring and batches[0]["grid"] == 2        # 4 units, two teams per workgroup beyond 16 tokens
+    assert ring and batches[0]["grid"] == 0        # too little work for a grid: phase by phase
     ring, batches = nvq.plan_describe_batches([linear(a, 128, 640, x, M=4)], 4)
     assert not ring and len(batches) == 1          # K is no multiple of 512
     ring, batches = nvq.plan_describe_batches([linear(a, 128, 4128, x, M=4)], 4)
