@@ -19,8 +19,8 @@
 // workgroups of a part take its groups of four units first come first served from a
 // counter, which the quantisation launch in front has cleared.
 //
-// What bounds it: 8B layers at 32 tokens take 1,134 us (3.9 TB/s; 1,470 with the ring
-// kernel); without the loads 820-870, without the products 1,030, so either alone comes
+// What bounds it: 8B layers at 32 tokens take 1,133 us (3.9 TB/s; 1,124 with the sums of a
+// result in one chain, 1,480 with the ring kernel); without the loads 820-870, without the products 1,030, so either alone comes
 // close and the two overlap by half.  Eight waves and 256 rows per workgroup are as fast
 // on long lists and 15 % slower on short ones; 64 rows per wave 4 % slower, two steps of
 // weights in flight with two thirds of the waves 15 %.
@@ -176,14 +176,26 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
     const uint32_t apos16 = abase + mn * 512 + 16 * ((kb >> 1) ^ mn) + 8 * (kb & 1);
     const uint32_t apos8 = abase + mn * 256 + 16 * mn + 4 * kb;
 
-    float f[R][MT][4];
-    auto clear = [&]() {
+    // A result's sum in three levels: the eight groups of a step, eight steps, all of K.  (One
+    // chain over all of K had up to twice the error of the four that the kernel for up to 16 tokens
+    // adds, registers for four would be 64; this is closer than those, at any K, for 2 % more
+    // vector instructions.)
+    float f[R][MT][4], total[R][MT][4];
+    auto clear = [&](float (&v)[R][MT][4]) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj) f[r][mt][jj] = 0.0f;
+                for (int jj = 0; jj < 4; ++jj) v[r][mt][jj] = 0.0f;
+    };
+    auto add = [&](float (&to)[R][MT][4], const float (&v)[R][MT][4]) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) to[r][mt][jj] += v[r][mt][jj];
     };
 
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
@@ -193,6 +205,7 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
     auto products = [&](auto prec, uint32_t abuf, const uint32_t (&q)[R][8], const uint32_t (&sc)[R][4]) {
         constexpr int PREC = decltype(prec)::value;
         typedef Act<PREC> A;
+        float part[R][MT][4];
         uint2v a2[2][PREC == NVQ_W4A8 ? 1 : MT][2];
         uint32_t a1[2][PREC == NVQ_W4A8 ? MT : 1][2];
         auto read = [&](int g) {
@@ -251,13 +264,17 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                 for (int mt = 0; mt < MT; ++mt) {
                     int4v raw;
                     const float4v p = A::product(act[mt], wt, off[mt], raw);
-                    f[r][mt][0] = fmaf(sw, p.x, f[r][mt][0]);
-                    f[r][mt][1] = fmaf(sw, p.y, f[r][mt][1]);
-                    f[r][mt][2] = fmaf(sw, p.z, f[r][mt][2]);
-                    f[r][mt][3] = fmaf(sw, p.w, f[r][mt][3]);
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+                        part[r][mt][jj] = g > 0 ? fmaf(sw, p[jj], part[r][mt][jj]) : sw * p[jj];
+                    // (here and now: the compiler would gather the additions of a step at its end and keep
+                    // the products until then)
+                    asm volatile("" : "+v"(part[r][mt][0]), "+v"(part[r][mt][1]), "+v"(part[r][mt][2]),
+                                 "+v"(part[r][mt][3]));
                 }
             }
         }
+        add(f, part);
     };
 
     const int first = part_begin + t * kRowsWaves;
@@ -273,7 +290,8 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
         bool more = false;
         RowsBundle nxt = cur;
         int drawn = 0;
-        clear();
+        clear(f);
+        clear(total);
         for (int c = 0; c < steps; ++c) {
             // this step's operands have arrived; everyone has left the other buffer
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
@@ -322,8 +340,13 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                 else
                     products(std::integral_constant<int, NVQ_W4A16>(), apos16 + buf * kA, q, sc);
             }
+            if ((c & 7) == 7) {
+                add(total, f);
+                clear(f);
+            }
             buf ^= 1;
         }
+        add(total, f);
         if (active) {
             CGroup &P = tab[cur.p];
             // (opaque: what follows from them would be kept in registers across the whole loop, and
@@ -347,7 +370,7 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                     for (int jj = 0; jj < 4; ++jj) {
                         const int m = mt * 16 + kb * 4 + jj;
                         if (o.valid && m < M)
-                            store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, f[r][mt][jj] * xs[mt][jj]);
+                            store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, total[r][mt][jj] * xs[mt][jj]);
                     }
             }
         }

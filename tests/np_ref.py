@@ -66,3 +66,21 @@ def sums_in_order(acc, sw, chains, xs=None, by_group=False):
     for v in range(chains):
         y = y + (f[v] if by_group else f[v] * xs[:, None])
     return y
+
+
+def sums_in_steps(acc, sw, xs=None):
+    """float32 [M, N]: the same sum in the order of the persistent grid for 17 tokens and more: the
+    eight groups of a step one after the other, the steps' sums eight at a time, then those."""
+    M, N, G = acc.shape
+    sw = np.asarray(sw, np.float32)
+    zero = lambda: np.zeros((M, N), np.float32)
+    total, f = zero(), zero()
+    for c in range(G // 8):
+        part = zero()
+        for g in range(8 * c, 8 * c + 8):
+            part = (sw[None, :, g].astype(np.longdouble) * acc[:, :, g] + part).astype(np.float32)
+        f = f + part
+        if c % 8 == 7:
+            total, f = total + f, zero()
+    total = total + f
+    return total if xs is None else total * np.asarray(xs, np.float32)[:, None]

@@ -734,6 +734,38 @@ def test_rows_plan_draws_tickets_and_replays():
 
 
 @pytest.mark.parametrize("M", [17, 32])
+def test_rows_plan_sums_are_added_in_the_stated_order(M):
+    """Bit for bit against the same additions on the CPU (see the test of the single calls): K of one
+    step pair, of whole eights of steps, and beyond; inputs of W4A16 layers small and whole."""
+    say("rows plan, order of sums", M)
+    rng = np.random.default_rng(8670 + M)
+    entries, refs = [], []
+    for i, K in enumerate([512, 1536, 2048, 2560, 4096, 4608, 6144, 1024] * 4):
+        N, prec = int(rng.integers(20, 300)), i % 2
+        q = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+        s = rng.integers(0x1400, 0x2c00, (N, K // 32)).astype(np.uint16)
+        qd, sd = to_dev_packed(q, s)
+        if prec == nvq.W4A16:
+            xq, xs = rng.integers(-99, 100, (M, K)).astype(np.int8), None
+            x = torch.from_numpy(xq).to(torch.bfloat16)
+        else:
+            x = act(8680 + i, M, K)
+            xq, xs, _ = oracle.quant_act_i8(u16(x), 0)
+        _, acc = oracle.gemv_w4a8(q, s, xq, np.ones(M, np.float32), 0, want_acc=True)
+        refs.append(np_ref.sums_in_steps(acc, np_ref.half_bits_to_f64(s), xs))
+        entries.append(dict(qweight=qd, scales=sd, x=x.to(DEV), precision=prec,
+                            y=torch.zeros((M, N), dtype=torch.float32, device=DEV)))
+    dl = nvq.DecodeList(entries, M, 0)
+    assert dl.plan_info()["persistent_grouped"]
+    dl.run_plan()
+    torch.cuda.synchronize()
+    for i, (e, want) in enumerate(zip(entries, refs)):
+        got = e["y"].cpu().numpy()
+        assert np.array_equal(got, want), (i, int((got != want).sum()), np_ref.rel_l2(got, want))
+    dl.close()
+
+
+@pytest.mark.parametrize("M", [17, 32])
 def test_rows_plan_short_batches_run_phase_by_phase(M):
     """Forced order: every phase is a batch of its own, too small for the persistent grid."""
     say("rows plan, single phases", M)
