@@ -14,7 +14,8 @@
 //
 // Batch 1 (fast path): decomposition as in gemv_tile.h with the lane's bf16
 // activations register-resident (16 dwords per owned group).  More
-// tokens, and K beyond 16384, go to the matrix-core kernel (gemv_slice.h).
+// tokens, and K beyond 16384, go to the matrix-core kernel (gemv_slice.h) or, up to three tokens
+// and few rows, to a wave per row.
 #include "gemv_tile.h"
 
 namespace nvq {
@@ -128,6 +129,52 @@ __global__ __launch_bounds__(256) void gemv_w4a16_m1_kernel(GemvSegs S, int G,
     }
 }
 
+// One wave per row, lanes stride over the groups, tokens in chunks of MT, activations read
+// from memory.
+template <int MT>
+__global__ __launch_bounds__(256) void gemv_w4a16_row_kernel(GemvSegs S, int G, int M,
+                                                                 const uint4 *__restrict__ x) {
+    const int lane = threadIdx.x & 63;
+    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int waves = gridDim.x * 4;
+    for (int row = wave; row < S.total_rows; row += waves) {
+        const RowRef r = locate_row(S, row, G);
+        for (int m0 = 0; m0 < M; m0 += MT) {
+            float sum[MT];
+#pragma unroll
+            for (int mm = 0; mm < MT; ++mm) sum[mm] = 0.0f;
+            for (int g = lane; g < G; g += 64) {
+                const uint4 w = r.qw[g];
+                const float sw = half_bits_to_float(r.sc[g]);
+#pragma unroll
+                for (int mm = 0; mm < MT; ++mm) {
+                    const int m = m0 + mm;
+                    if (m < M) {
+                        const int64_t xg = ((int64_t)m * G + g) * 4;
+                        uint32_t xv[16];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const uint4 a = x[xg + q];
+                            xv[4 * q + 0] = a.x;
+                            xv[4 * q + 1] = a.y;
+                            xv[4 * q + 2] = a.z;
+                            xv[4 * q + 3] = a.w;
+                        }
+                        const float acc = block_dot_bf16(w, xv, group_offset(xv));
+                        sum[mm] = fmaf(sw, acc, sum[mm]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int mm = 0; mm < MT; ++mm) {
+                const int m = m0 + mm;
+                const float tot = group_sum<64>(sum[mm]);
+                if (lane == 0 && m < M) store_out(r.y, r.y_dtype, (int64_t)m * r.N + r.n, tot);
+            }
+        }
+    }
+}
+
 template <int GPL, int LPR>
 static int launch_m1(const GemvSegs &S, int G, const uint16_t *x, hipStream_t st) {
     constexpr int U = tile_rows(GPL);
@@ -157,7 +204,11 @@ int launch_gemv_w4a16(const GemvSegs &S, int K, const uint16_t *x, int M, hipStr
             default: return launch_m1<8, 64>(S, G, x, st);
         }
     }
-    return launch_gemv_slice_w4a16(S, K, x, M, st);
+    if (!gemv_wave_per_row(S, K, M, false)) return launch_gemv_slice_w4a16(S, K, x, M, st);
+    const dim3 grid(gemv_grid(S.total_rows, 4, 8)), block(256);
+    hipLaunchKernelGGL(gemv_w4a16_row_kernel<4>, grid, block, 0, st, S, G, M, reinterpret_cast<const uint4 *>(x));
+    NVQ_HIP_TRY(hipGetLastError());
+    return NVQ_OK;
 }
 
 }  // namespace nvq

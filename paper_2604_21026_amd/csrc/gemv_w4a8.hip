@@ -13,7 +13,7 @@
 // int8 codes of the lane's groups are register-resident, the loop body per
 // 32 weights is one 128-bit load, 12 bit operations, 8 dot4, one convert and
 // one FMA.  More tokens, and K beyond 16384, go to the matrix-core kernel
-// (gemv_slice.h).
+// (gemv_slice.h) or, up to three tokens and few rows, to a wave per row.
 #include "gemv_tile.h"
 
 namespace nvq {
@@ -110,6 +110,52 @@ __global__ __launch_bounds__(256) void gemv_w4a8_m1_kernel(GemvSegs S, int G,
     }
 }
 
+// One wave per row, lanes stride over the groups (sixty-four chains, added in pairs: the order
+// gemv_slice.h states), tokens in chunks of MT.  Activations are read from memory (cache-resident).
+template <int MT, bool PER_GROUP, bool DEBUG>
+__global__ __launch_bounds__(256) void gemv_w4a8_row_kernel(
+    GemvSegs S, int G, int M, const uint4 *__restrict__ xq, const float *__restrict__ xscale,
+    const int32_t *__restrict__ xgsum) {
+    const int lane = threadIdx.x & 63;
+    const int wave = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int waves = gridDim.x * 4;
+    for (int row = wave; row < S.total_rows; row += waves) {
+        const RowRef r = locate_row(S, row, G);
+        for (int m0 = 0; m0 < M; m0 += MT) {
+            float sum[MT];
+#pragma unroll
+            for (int mm = 0; mm < MT; ++mm) sum[mm] = 0.0f;
+            for (int g = lane; g < G; g += 64) {
+                const uint4 w = r.qw[g];
+                const float sw = half_bits_to_float(r.sc[g]);
+#pragma unroll
+                for (int mm = 0; mm < MT; ++mm) {
+                    const int m = m0 + mm;
+                    if (m < M) {
+                        const int64_t xg = (int64_t)m * G + g;
+                        const uint4 a = xq[xg * 2], b = xq[xg * 2 + 1];
+                        const uint32_t x[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+                        const int acc = block_dot_i8(w, x, -8 * xgsum[xg]);
+                        if (DEBUG) {
+                            if (r.dbg) r.dbg[((int64_t)m * r.N + r.n) * G + g] = acc;
+                        }
+                        const float s = PER_GROUP ? sw * xscale[xg] : sw;
+                        sum[mm] = fmaf(s, (float)acc, sum[mm]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int mm = 0; mm < MT; ++mm) {
+                const int m = m0 + mm;
+                const float tot = group_sum<64>(sum[mm]);
+                if (lane == 0 && m < M)
+                    store_out(r.y, r.y_dtype, (int64_t)m * r.N + r.n,
+                              PER_GROUP ? tot : tot * xscale[m]);
+            }
+        }
+    }
+}
+
 template <int GPL, int LPR>
 static int launch_m1(const GemvSegs &S, int G, const int8_t *xq, const float *xscale,
                      const int32_t *xgsum, bool per_group, bool debug, hipStream_t st) {
@@ -152,7 +198,20 @@ int launch_gemv_w4a8(const GemvSegs &S, int K, const int8_t *xq, const float *xs
             default: return launch_m1<8, 64>(S, G, xq, xscale, xgsum, pg, debug, st);
         }
     }
-    return launch_gemv_slice_w4a8(S, K, xq, xscale, act_group, M, st);
+    if (!gemv_wave_per_row(S, K, M, pg)) return launch_gemv_slice_w4a8(S, K, xq, xscale, act_group, M, st);
+    const dim3 grid(gemv_grid(S.total_rows, 4, 8)), block(256);
+    const uint4 *x4 = reinterpret_cast<const uint4 *>(xq);
+#define NVQ_GO(PG, DBG)                                                                      \
+    hipLaunchKernelGGL((gemv_w4a8_row_kernel<4, PG, DBG>), grid, block, 0, st, S, G, M, x4, \
+                       xscale, xgsum)
+    if (pg) {
+        if (debug) NVQ_GO(true, true); else NVQ_GO(true, false);
+    } else {
+        if (debug) NVQ_GO(false, true); else NVQ_GO(false, false);
+    }
+#undef NVQ_GO
+    NVQ_HIP_TRY(hipGetLastError());
+    return NVQ_OK;
 }
 
 }  // namespace nvq

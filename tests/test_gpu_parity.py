@@ -230,12 +230,14 @@ def test_small_batch_kernel_edges(M, N, K, off):
 # kernel's tiling: eight or sixteen chains of columns (K % 128 == 0, scales aligned to 8 bytes, a
 # scale per token), or sixty-four of groups.  Rows and tokens that reach each tiling (16 and 32
 # rows per workgroup, up to 8, 16 and 32 tokens, more and fewer row tiles than compute units), K
-# whose last block of eight groups ends early, K beyond 16384.
+# whose last block of eight groups ends early, K beyond 16384, and the calls of up to three tokens
+# that take a wave per row, with their neighbours.
 @pytest.mark.parametrize("M,N,K,off", [(3, 48, 4096, 0), (12, 33, 14336, 0), (20, 48, 8320, 0), (9, 4200, 4096, 0),
                                        (32, 4200, 4224, 0), (8, 40, 3072, 0), (16, 40, 2176, 0), (17, 40, 3072, 0),
                                        (2, 8300, 4096, 0), (5, 16400, 1024, 0), (16, 16400, 640, 0),
                                        (24, 16400, 512, 0), (6, 40, 4096, 1), (16, 40, 2720, 0), (25, 40, 2720, 0),
-                                       (4, 16400, 352, 0), (1, 40, 16416, 0), (30, 17, 65536, 0)])
+                                       (4, 16400, 352, 0), (1, 40, 16416, 0), (30, 17, 65536, 0),
+                                       (1, 4097, 16416, 0), (2, 1024, 2720, 0), (2, 1025, 2720, 0), (3, 682, 1056, 1)])
 def test_multi_token_sums_are_added_in_the_stated_order(M, N, K, off):
     """Bit for bit against the same additions on the CPU.  W4A8: the block sums are integers.  W4A16
     on small whole inputs: a group's products and their sums are exact whatever their order."""
