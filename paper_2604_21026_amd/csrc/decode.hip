@@ -423,6 +423,10 @@ std::vector<int> phase_deps(const nvq_linear *L, const std::vector<Phase> &phase
 // each other form a batch, and a batch is two launches: one grid quantises the
 // inputs of all its W4A8 phases, one grid holds the row tiles of all its
 // phases.  Empty if some phase does not qualify for the matrix-core kernel.
+enum GroupKind {
+    kGroupTiles,  // the per-tile grid (gemv_mfma.hip)
+    kGroupRing, kGroupRows, kGroupSingle,  // see group_kind
+};
 struct GroupBatch {
     int job_first, njobs;    // range in the job list
     int unit_first, nunits;  // range in the unit list
@@ -430,7 +434,7 @@ struct GroupBatch {
     int part_first, nparts;  // the batch's table in the part list (2 * (nparts + 1) words)
     int grid;                // workgroups of the persistent kernel
     int phase_first, nphases;  // phases of the batch
-    bool single;             // 17 tokens and more: phase by phase instead of as one grid
+    GroupKind kind;
 };
 struct GroupPlan {
     bool ring;  // the persistent kernel serves the list: every phase has a job and an operand image
@@ -440,22 +444,29 @@ struct GroupPlan {
     std::vector<GroupBatch> batches;
 };
 
-// Whether a batch of 17 or more tokens goes phase by phase (gemv_slice.h) instead of as one
-// persistent grid (gemv_rows.hip).  The grid moves 3.9 TB/s once it has work for every compute
-// unit, but a workgroup takes 128 rows and all of their K, 1.7 us per 256 inputs however few
-// there are; a phase by itself costs 3 us and 2.4 TB/s (4096 x 14336 alone: 17 us against 107;
-// 32 blocks of 8B: 1,130 us against 2,200).
-bool rows_or_single(const GroupPlan &gp, const GroupBatch &b) {
-    double bytes = 0.0, single_us = 0.0;
-    int steps = 0;
+// How a batch is worked off.  Up to 16 tokens: the persistent grid fed through LDS rings.  From
+// 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
+// activations (gemv_rows.hip), which moves the most bytes but takes 128 rows and all of their K
+// per workgroup, and launches phase by phase (gemv_slice.h), by what they were measured to take
+// (us; MB of weights, phases, the largest K): 186 lists of 1 to 128 phases and 0.1 to 3900 MB
+// fit within 13, 17 and 10 % (rms), and the choice costs 0.8 % on average, 20 % at worst (6
+// phases, 44 MB: 56 us, with the rings 47).  Where the lines lie, rings / rows / phases: 4096 x
+// 14336 alone 30 / 107 / 20; one block of 8B 79 / 156 / 64, two 135 / 169 / 138, four 193 / 177 /
+// 289, 32 of them 1337 / 1054 / 2225; six blocks of 1B 118 / 119 / 193, sixteen 247 / 201 / 576.
+GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
+    if (!gp.ring) return kGroupTiles;
+    if (M < kRowsMinTokens) return kGroupRing;
+    double mb = 0.0, widest = 0.0, single = 3.3;
     for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
         const GroupPhase &g = gp.tab[(size_t)p];
-        const double w = 18.0 * g.G * g.segs.total_rows;
-        bytes += w;
-        single_us += 3.0 + w * 1e-6 / 2.4;
-        steps = std::max(steps, g.G / 8);
+        const double w = 18e-6 * g.G * g.segs.total_rows, steps = g.G / 8;
+        mb += w;
+        widest = std::max(widest, steps);
+        single += 3.0 + 0.165 * steps + w / 3.1;
     }
-    return single_us < 12.0 + std::max(bytes * 1e-6 / 3.9, 1.7 * steps);
+    const double ring = 12.6 + 0.57 * widest + 0.27 * b.nphases + mb / 2.9;
+    const double rows = 7.2 + 2.44 * widest + 0.36 * b.nphases + mb / 5.8;
+    return single < std::min(ring, rows) ? kGroupSingle : ring <= rows ? kGroupRing : kGroupRows;
 }
 
 // Cut the units of a batch into contiguous parts of (nearly) equal weight
@@ -509,7 +520,18 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         cut_batch(gp, cur, M);
         cur.phase_first = batch_first;
         cur.nphases = (int)gp.tab.size() - batch_first;
-        cur.single = gp.ring && M >= kRowsMinTokens && rows_or_single(gp, cur);
+        cur.kind = group_kind(gp, cur, M);
+        if (cur.kind == kGroupRows || cur.kind == kGroupSingle) {
+            // codes for the W4A8 phases instead of operand images for all of them
+            const auto first = gp.jobs.begin() + cur.job_first;
+            gp.jobs.erase(std::remove_if(first, gp.jobs.end(),
+                                         [&](uint16_t p) { return gp.tab[p].precision != NVQ_W4A8; }),
+                          gp.jobs.end());
+            cur.njobs = (int)gp.jobs.size() - cur.job_first;
+            gp.imgs.resize((size_t)cur.img_first);
+            cur.nimg = 0;
+        }
+        if (cur.kind == kGroupRows) cur.grid = rows_grid(cur.nunits, cur.nparts);
         gp.batches.push_back(cur);
     };
     for (size_t p = 0; p < phases.size(); ++p) {
@@ -531,7 +553,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         if (gp.ring) {
             char *b = ws.gquant + qoff;
             g.xa = b;
-            g.xq = reinterpret_cast<int8_t *>(b);  // 17 tokens and more: the codes instead of an image
+            g.xq = reinterpret_cast<int8_t *>(b);  // codes, where they take the place of an image
             g.xscale = reinterpret_cast<float *>(b + operand_image_bytes(M, e0.K, e0.precision));
             qoff += operand_image_bytes(M, e0.K, e0.precision) + round_up((size_t)M * 4, 256);
             gp.jobs.push_back((uint16_t)p);
@@ -988,27 +1010,35 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
         for (const GroupBatch &b : pl->batches) {
             const uint16_t *jobs = pl->ws.gjobs + b.job_first;
             const uint32_t *parts = pl->ws.gteams + b.part_first;
-            int rc;
-            if (!pl->ring) {
-                rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, nullptr, st);
-                if (rc == NVQ_OK)
-                    rc = launch_gemv_mfma_group(pl->ws.gtab, pl->ws.gunits + b.unit_first, b.nunits, pl->M, st);
-            } else if (pl->M >= kRowsMinTokens) {
-                uint32_t *const tickets = pl->ws.status + 16;
-                rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, tickets, st);
-                for (int p = b.phase_first; b.single && rc == NVQ_OK && p < b.phase_first + b.nphases; ++p) {
-                    const GroupPhase &g = pl->group_phases[(size_t)p];
-                    rc = g.precision == NVQ_W4A8
-                             ? launch_gemv_slice_w4a8(g.segs, g.G * 32, g.xq, g.xscale, 0, pl->M, st)
-                             : launch_gemv_slice_w4a16(g.segs, g.G * 32, g.x_bf16, pl->M, st);
+            int rc = NVQ_OK;
+            switch (b.kind) {
+                case kGroupTiles:
+                    rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, nullptr, st);
+                    if (rc == NVQ_OK)
+                        rc = launch_gemv_mfma_group(pl->ws.gtab, pl->ws.gunits + b.unit_first, b.nunits, pl->M, st);
+                    break;
+                case kGroupRing:
+                    rc = launch_operand_images(pl->ws.gtab, jobs, b.njobs, pl->ws.gimgs + b.img_first, b.nimg, pl->M,
+                                               st);
+                    if (rc == NVQ_OK)
+                        rc = launch_gemv_mfma_ring(pl->ws.gtab, parts, b.nparts, b.grid, pl->M, pl->ws.status, st);
+                    break;
+                case kGroupRows: {
+                    uint32_t *const tickets = pl->ws.status + 16;
+                    rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, tickets, st);
+                    if (rc == NVQ_OK)
+                        rc = launch_gemv_rows(pl->ws.gtab, parts, b.nparts, b.grid, pl->M, tickets, st);
+                    break;
                 }
-                if (rc == NVQ_OK && !b.single)
-                    rc = launch_gemv_rows(pl->ws.gtab, parts, b.nparts, b.nunits, pl->M, tickets, st);
-            } else {
-                rc = launch_operand_images(pl->ws.gtab, jobs, b.njobs, pl->ws.gimgs + b.img_first, b.nimg,
-                                           pl->M, st);
-                if (rc == NVQ_OK)
-                    rc = launch_gemv_mfma_ring(pl->ws.gtab, parts, b.nparts, b.grid, pl->M, pl->ws.status, st);
+                case kGroupSingle:
+                    rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, nullptr, st);
+                    for (int p = b.phase_first; rc == NVQ_OK && p < b.phase_first + b.nphases; ++p) {
+                        const GroupPhase &g = pl->group_phases[(size_t)p];
+                        rc = g.precision == NVQ_W4A8
+                                 ? launch_gemv_slice_w4a8(g.segs, g.G * 32, g.xq, g.xscale, 0, pl->M, st)
+                                 : launch_gemv_slice_w4a16(g.segs, g.G * 32, g.x_bf16, pl->M, st);
+                    }
+                    break;
             }
             if (rc != NVQ_OK) return rc;
         }
@@ -1021,7 +1051,8 @@ extern "C" int nvq_plan_info(const nvq_plan *pl, int *streaming, int *phases, in
     if (!pl) return NVQ_ERR_INVALID_ARG;
     if (streaming) {
         bool grid = false;  // some batch runs as a persistent grid
-        for (const nvq::GroupBatch &b : pl->batches) grid = grid || (pl->ring && !b.single);
+        for (const nvq::GroupBatch &b : pl->batches)
+            grid = grid || b.kind == nvq::kGroupRing || b.kind == nvq::kGroupRows;
         *streaming = pl->nwg > 0 ? 1 : grid ? 3 : pl->batches.empty() || pl->ring ? 0 : 2;
     }
     if (phases) *phases = (int)pl->phases.size();
@@ -1127,7 +1158,7 @@ extern "C" int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M,
         o[1] = gb.nunits > 0 ? gp.units[(size_t)gb.unit_first + gb.nunits - 1] : -1;
         o[2] = gb.nunits;
         o[3] = gb.njobs;
-        o[4] = gb.single ? 0 : gb.grid;
+        o[4] = gb.kind == kGroupSingle ? 0 : gb.grid;
         o[5] = gb.nparts;
         for (int k = 0; k <= gb.nparts && gb.nparts > 0; ++k) {
             o[6 + k] = (int32_t)gp.parts[(size_t)gb.part_first + k];

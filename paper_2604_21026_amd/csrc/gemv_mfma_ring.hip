@@ -1,4 +1,4 @@
-// Small-batch (2 <= M <= 16 tokens) products on the matrix cores, as one
+// Small-batch (2 <= M <= 32 tokens) products on the matrix cores, as one
 // persistent grid per batch of independent phases.  Paper: the W4A8 / W4A16
 // kernel descriptions; the arithmetic is that of the per-tile kernel
 // (gemv_mfma.hip), what differs is how the weights reach the waves.
@@ -571,8 +571,6 @@ bool gemv_mfma_ring_supported(const GemvSegs &S, int K) {
     return true;
 }
 
-// (Beyond 16 tokens the same batches and parts are worked off by gemv_rows.hip, or the parts
-// by nobody: what ring_grid says there is the team count the cuts were sized for.)
 int ring_teams_per_workgroup(int M) { return M > 16 ? 2 : 3; }
 int ring_bundle_units(int M) { return M > 16 ? 1 : kRingBundle; }
 
@@ -593,8 +591,12 @@ int ring_parts(int grid) { return grid < 8 ? grid : 8; }
 int launch_gemv_mfma_ring(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int grid,
                           int M, uint32_t *status, hipStream_t st) {
     if (nparts <= 0 || grid <= 0) return NVQ_OK;
-    hipLaunchKernelGGL((gemv_mfma_ring_kernel<1, 3, kRingBundle>), dim3(grid), dim3(3 * kTeamThreads), 0, st,
-                       tab, part_tab, nparts, M, status);
+    const dim3 g(grid), block(ring_teams_per_workgroup(M) * kTeamThreads);
+    if (M > 16)
+        hipLaunchKernelGGL((gemv_mfma_ring_kernel<2, 2, 1>), g, block, 0, st, tab, part_tab, nparts, M, status);
+    else
+        hipLaunchKernelGGL((gemv_mfma_ring_kernel<1, 3, kRingBundle>), g, block, 0, st, tab, part_tab, nparts, M,
+                           status);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }

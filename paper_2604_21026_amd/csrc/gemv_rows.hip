@@ -4,8 +4,8 @@
 //
 // With two token tiles 32 weight rows need 3.6 times their own bytes of bf16 activations,
 // and the L2 caches deliver about 10 TB/s to all compute units together: a kernel whose
-// waves each fetch their own (the ring kernel, which serves up to 16 tokens) stands at 3
-// TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with 32 rows
+// waves each fetch their own (the ring kernel, which serves up to 16 tokens and shorter lists)
+// stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with 32 rows
 // of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
 // through LDS, and no sums cross the waves.  K advances by 256 inputs (a whole 128-byte
 // line of a row); per step a wave asks for its quarter of the next step's activations (two
@@ -383,12 +383,17 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
 
 }  // namespace
 
-int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int nunits, int M,
-                     uint32_t *tickets, hipStream_t st) {
-    if (nparts <= 0 || nunits <= 0) return NVQ_OK;
+// A workgroup per group of units (every part may end with a smaller one), at most what is resident.
+int rows_grid(int nunits, int nparts) {
     const int groups = (nunits + kRowsWaves - 1) / kRowsWaves + nparts, cap = kRowsWgPerCu * device_cu_count();
-    hipLaunchKernelGGL(gemv_rows_kernel<32>, dim3(groups < cap ? groups : cap), dim3(kRowsWaves * 64), 0, st, tab,
-                       part_tab, nparts, M, tickets);
+    return groups < cap ? groups : cap;
+}
+
+int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int grid, int M,
+                     uint32_t *tickets, hipStream_t st) {
+    if (nparts <= 0 || grid <= 0) return NVQ_OK;
+    hipLaunchKernelGGL(gemv_rows_kernel<32>, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, M,
+                       tickets);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }

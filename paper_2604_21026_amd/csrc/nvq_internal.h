@@ -76,9 +76,8 @@ struct GroupPhase {
     int unit_count;          // its units
     int img_begin;           // first image unit of the phase in its batch (launch_operand_images)
 };
-// jobs[j] names the phase whose M tokens grid blocks j*M .. j*M+M-1 quantise.
-// Phases that are not W4A8 are passed over; xgsum may be null.  The first eight words at
-// `clear` (unless null) are set to zero.
+// jobs[j] names the (W4A8) phase whose M tokens grid blocks j*M .. j*M+M-1 quantise; xgsum may
+// be null.  The first eight words at `clear` (unless null) are set to zero, also without jobs.
 int launch_quant_act_group(const GroupPhase *tab, const uint16_t *jobs, int njobs, int M,
                            uint32_t *clear, hipStream_t st);
 // The operand images `xa` of the phases named in `jobs` (per-token scales of
@@ -115,9 +114,11 @@ int launch_gemv_mfma_ring(const GroupPhase *tab, const uint32_t *part_tab, int n
                           int M, uint32_t *status, hipStream_t st);
 
 // The same work for 17 to 32 tokens, from the inputs themselves (codes and scales of
-// launch_quant_act_group for the W4A8 phases); tickets: eight words that are zero.
+// launch_quant_act_group for the W4A8 phases); grid = rows_grid(); tickets: eight words that
+// are zero.
 constexpr int kRowsMinTokens = 17;
-int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int nunits, int M,
+int rows_grid(int nunits, int nparts);
+int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int grid, int M,
                      uint32_t *tickets, hipStream_t st);
 
 // ---- device helpers -------------------------------------------------------

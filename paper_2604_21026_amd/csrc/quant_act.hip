@@ -218,12 +218,12 @@ __global__ __launch_bounds__(kQuantThreads) void quant_act_kernel(
 
 // Per-token scales, the inputs of many phases in one grid.
 __global__ __launch_bounds__(kQuantThreads) void quant_act_group_kernel(
-    const GroupPhase *__restrict__ tab, const uint16_t *__restrict__ jobs, int M,
+    const GroupPhase *__restrict__ tab, const uint16_t *__restrict__ jobs, int njobs, int M,
     uint32_t *__restrict__ clear) {
     if (clear && blockIdx.x == 0 && threadIdx.x < 8) clear[threadIdx.x] = 0u;
     const int job = blockIdx.x / M, m = blockIdx.x - job * M;
+    if (job >= njobs) return;
     const GroupPhase &P = tab[jobs[job]];
-    if (P.precision != NVQ_W4A8) return;
     quant_token<false>(reinterpret_cast<const uint4 *>(P.x_bf16), P.G * 32, m, P.xq, P.xscale,
                        P.xgsum);
 }
@@ -326,9 +326,9 @@ int launch_operand_images(const GroupPhase *tab, const uint16_t *jobs, int njobs
 
 int launch_quant_act_group(const GroupPhase *tab, const uint16_t *jobs, int njobs, int M,
                            uint32_t *clear, hipStream_t st) {
-    if (njobs <= 0) return NVQ_OK;
-    hipLaunchKernelGGL(quant_act_group_kernel, dim3(njobs * M), dim3(kQuantThreads), 0, st, tab, jobs,
-                       M, clear);
+    if (njobs <= 0 && !clear) return NVQ_OK;
+    hipLaunchKernelGGL(quant_act_group_kernel, dim3(njobs > 0 ? njobs * M : 1), dim3(kQuantThreads), 0, st, tab,
+                       jobs, njobs, M, clear);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }

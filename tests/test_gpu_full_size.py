@@ -50,7 +50,7 @@ def build_sampled_model(model, M, bits):
                                      ("llama-1b", 1), ("llama-3b", 1)])
 def test_full_step_sampled_rows_match_oracle(model, M):
     """The benchmark's workloads as bench.py builds and launches them: the 8B step at 1, 16 and
-    32 tokens (one and two token tiles of the matrix-core kernel), and the whole 1B and 3B
+    32 tokens (the two persistent matrix-core kernels), and the whole 1B and 3B
     steps at batch 1 (64 and 112 phases: thin phases dealt in larger units, rows of one and a
     half chunks streamed in pairs, the skip table)."""
     import bench

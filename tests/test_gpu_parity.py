@@ -631,6 +631,37 @@ def test_streaming_plan_orders_dependent_phases():
 
 
 # ---- grouped small-batch walker (2..32 tokens on the matrix cores) -------------------
+def kernels_of(dl, ordered=False):
+    """Per batch of a plan that is issued in batches: what it runs on (see nvq_plan_describe_batches;
+    lists that take the grid with shared activations are long, more than a group of rows per compute
+    unit)."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    _, batches = nvq.plan_describe_batches([dl.arr[i] for i in range(dl.n)], dl.M, ordered)
+    return ["phases" if b["grid"] == 0 else "rings" if b["grid"] <= cus else "rows" for b in batches]
+
+
+def bulk_layer(M, mbytes, K=2048, seed=8990):
+    """A layer of that many MB with random codes, made on the device: what a list needs besides the
+    layers under test to be worth the grid for 17 tokens and more.  (entry, rows to look at, host
+    layer of those rows)"""
+    N = int(mbytes * 1e6 / (0.5625 * K))
+    g = torch.Generator(device=DEV).manual_seed(seed)
+    q = torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV, generator=g)
+    s = torch.randint(0x1400, 0x2c00, (N, K // 32), dtype=torch.int16, device=DEV, generator=g)
+    x = act(seed, M, K)
+    rows = torch.tensor([0, 31, 32, 127, 128, N // 3, N // 2, N - 33, N - 1])
+    entry = dict(qweight=q, scales=s, x=x.to(DEV), precision=nvq.W4A8,
+                 y=torch.zeros((M, N), dtype=torch.float32, device=DEV))
+    host = dict(qweight=q[rows.to(DEV)].cpu().numpy(), scales=u16(s[rows.to(DEV)]), x=u16(x), precision=nvq.W4A8)
+    return entry, rows, host
+
+
+def check_bulk(bulk, M):
+    entry, rows, host = bulk
+    want = oracle.decode_linears([host], M, 0)[0]
+    assert np_ref.rel_l2(entry["y"][:, rows.to(DEV)].cpu().numpy(), want) < 1e-5
+
+
 # grid: whether the product runs as a persistent grid (every K of these models is a multiple of
 # 512; from 17 tokens on the work has to be enough, otherwise it goes phase by phase)
 @pytest.mark.parametrize("name,M,ordered,grid", [("1b", 5, False, True), ("1b", 20, True, False),
@@ -674,22 +705,24 @@ def test_grouped_plan_matches_oracle_on_repeated_runs(name, M, ordered, grid):
 # 16-row tile, phases of several matrices whose boundaries fall inside a unit, a phase with fewer
 # units than teams next to long ones (groups of units that cross phases of other K and precision),
 # K from one step (512) to 28 steps, both precisions, and token counts from 2 to 32 (one or two
-# token tiles).  From 17 tokens on a grid needs a long list: the shapes six times over; two
-# times over they go phase by phase.
+# token tiles).  The kernel with shared activations takes long lists only: with a large layer in
+# the middle.
 RING_SHAPES = [(1000, 1536, 0), (37, 1536, 0), (3, 1536, 1), (2500, 3072, 2), (777, 3072, 2),
                (64, 14336, 3), (48, 512, 4), (4100, 512, 4), (16, 1024, 5)]
 
 
-@pytest.mark.parametrize("M,bits", [(2, (0, 1)), (7, (1, 0)), (16, (0, 1, 1)), (17, (0, 1)),
-                                    (32, (1, 0)), (17, (0, 1, 0, 1, 1, 0)), (32, (1, 0, 0, 1, 0, 1))])
-def test_ring_plan_matches_oracle(M, bits):
-    say("ring plan", M, bits)
+@pytest.mark.parametrize("M,bits,kernel", [(2, (0, 1), "rings"), (7, (1, 0), "rings"), (16, (0, 1, 1), "rings"),
+                                           (17, (0, 1), "rings"), (32, (1, 0), "rings"), (17, (0, 1), "rows"),
+                                           (32, (1, 0), "rows")])
+def test_ring_plan_matches_oracle(M, bits, kernel):
+    say("ring plan", M, bits, kernel)
     entries, host = model_entries(RING_SHAPES, bits, M=M, seed=8600)
     ys_ref = oracle.decode_linears(host, M, 0)
-    dl = nvq.DecodeList(entries, M, 0)
+    bulk = bulk_layer(M, 640) if kernel == "rows" else None
+    dl = nvq.DecodeList(entries[:7] + [bulk[0]] + entries[7:] if bulk else entries, M, 0)
     info = dl.plan_info()
     say("  plan", info)
-    assert info["grouped"] == info["persistent_grouped"] == (M <= 16 or len(bits) == 6)
+    assert info["grouped"] and info["persistent_grouped"] and kernels_of(dl) == [kernel]
     for rep in range(3):
         for e in entries:
             e["y"].zero_()
@@ -698,6 +731,8 @@ def test_ring_plan_matches_oracle(M, bits):
         assert not dl.plan_timed_out()
         for e, y_r in zip(entries, ys_ref):
             assert np_ref.rel_l2(e["y"].cpu().numpy(), y_r) < 1e-5, rep
+        if bulk:
+            check_bulk(bulk, M)
     dl.close()
 
 
@@ -711,7 +746,7 @@ def test_rows_plan_draws_tickets_and_replays():
                                   M=M, seed=8650)
     rows = np.unique(np.concatenate([[0, 31, 32, 127, 128], np.random.default_rng(1).integers(0, 33, 8)]))
     dl = nvq.DecodeList(entries, M, 0)
-    assert dl.plan_info()["persistent_grouped"]
+    assert kernels_of(dl) == ["rows"]
     dl.run_plan()
     torch.cuda.synchronize()
     eager = [e["y"].clone() for e in entries]
@@ -735,11 +770,12 @@ def test_rows_plan_draws_tickets_and_replays():
     dl.close()
 
 
-@pytest.mark.parametrize("M", [17, 32])
-def test_rows_plan_sums_are_added_in_the_stated_order(M):
+@pytest.mark.parametrize("M,kernel", [(2, "rings"), (16, "rings"), (17, "rings"), (32, "rings"), (17, "rows"),
+                                      (32, "rows")])
+def test_grid_sums_are_added_in_the_stated_order(M, kernel):
     """Bit for bit against the same additions on the CPU (see the test of the single calls): K of one
     step pair, of whole eights of steps, and beyond; inputs of W4A16 layers small and whole."""
-    say("rows plan, order of sums", M)
+    say("grid plan, order of sums", M, kernel)
     rng = np.random.default_rng(8670 + M)
     entries, refs = [], []
     for i, K in enumerate([512, 1536, 2048, 2560, 4096, 4608, 6144, 1024] * 4):
@@ -754,11 +790,13 @@ def test_rows_plan_sums_are_added_in_the_stated_order(M):
             x = act(8680 + i, M, K)
             xq, xs, _ = oracle.quant_act_i8(u16(x), 0)
         _, acc = oracle.gemv_w4a8(q, s, xq, np.ones(M, np.float32), 0, want_acc=True)
-        refs.append(np_ref.sums_in_steps(acc, np_ref.half_bits_to_f64(s), xs))
+        sw = np_ref.half_bits_to_f64(s)
+        refs.append(np_ref.sums_in_steps(acc, sw, xs) if kernel == "rows" else np_ref.sums_in_order(acc, sw, 4, xs))
         entries.append(dict(qweight=qd, scales=sd, x=x.to(DEV), precision=prec,
                             y=torch.zeros((M, N), dtype=torch.float32, device=DEV)))
-    dl = nvq.DecodeList(entries, M, 0)
-    assert dl.plan_info()["persistent_grouped"]
+    bulk = [bulk_layer(M, 300)[0]] if kernel == "rows" else []
+    dl = nvq.DecodeList(entries[:9] + bulk + entries[9:], M, 0)
+    assert kernels_of(dl) == [kernel]
     dl.run_plan()
     torch.cuda.synchronize()
     for i, (e, want) in enumerate(zip(entries, refs)):
@@ -777,6 +815,7 @@ def test_rows_plan_short_batches_run_phase_by_phase(M):
     dl = nvq.DecodeList(entries, M, 0, ordered=True)
     info = dl.plan_info()
     assert not info["grouped"] and info["waits"] == info["phases"] - 1
+    assert kernels_of(dl, ordered=True) == ["phases"] * info["phases"]
     for rep in range(2):
         for e in entries:
             e["y"].zero_()
@@ -1089,25 +1128,30 @@ EXACT_SHAPES = [(4096, 4096, 0), (1024, 4096, 0), (1031, 4096, 1), (640, 14336, 
                 (2500, 2048, 3), (77, 8192, 4), (3000, 1024, 5)]
 
 
-@pytest.mark.parametrize("M,group,ordered,times", [
-    (1, 0, False, 1), (1, 0, True, 1), (1, 32, False, 1), (1, 32, True, 1), (2, 0, False, 1),
-    (5, 0, False, 1), (16, 0, False, 1), (17, 0, False, 1), (32, 0, False, 1), (17, 0, False, 5),
-    (32, 0, False, 5), (3, 32, False, 1)])
-def test_exact_sums_are_bit_equal_on_the_timed_kernels(M, group, ordered, times):
+@pytest.mark.parametrize("M,group,ordered,kernel", [
+    (1, 0, False, None), (1, 0, True, None), (1, 32, False, None), (1, 32, True, None),
+    (2, 0, False, "rings"), (5, 0, False, "rings"), (16, 0, False, "rings"), (17, 0, False, "phases"),
+    (32, 0, False, "phases"), (17, 0, False, "rings"), (32, 0, False, "rings"), (17, 0, False, "rows"),
+    (32, 0, False, "rows"), (3, 32, False, None)])
+def test_exact_sums_are_bit_equal_on_the_timed_kernels(M, group, ordered, kernel):
     """Batch 1: the persistent streaming kernel with its fused quantiser, images prepared in
-    the prologue (independent phases) and built after a wait (forced ordering).  2 to 16
-    tokens: the persistent matrix-core kernel (every K a multiple of 512); 17 to 32: the one of
-    those token counts for a list long enough (the shapes five times), launches per phase for a
-    short one.  A scale per 32 activations at several tokens: launches per phase."""
-    say("exact sums", M, group, ordered, times)
+    the prologue (independent phases) and built after a wait (forced ordering).  2 to 32
+    tokens: the persistent matrix-core kernels (every K a multiple of 512); from 17 tokens on
+    the shapes alone go phase by phase, three times over through the LDS rings, and with a large
+    layer among them through the grid with shared activations.  A scale per 32 activations at
+    several tokens: launches per phase."""
+    say("exact sums", M, group, ordered, kernel)
+    times = 3 if M > 16 and kernel == "rings" else 1
     shapes = [(N, K, ph + 6 * i) for i in range(times) for N, K, ph in EXACT_SHAPES]
     entries, host = exact_list(9000 + M + group, shapes, M, group == 32)
     ys_ref = oracle.decode_linears(host, M, group)
-    dl = nvq.DecodeList(entries, M, group, ordered=ordered)
+    bulk = [bulk_layer(M, 640)[0]] if kernel == "rows" else []
+    dl = nvq.DecodeList(entries[:3] + bulk + entries[3:], M, group, ordered=ordered)
     info = dl.plan_info()
     say("  plan", info)
     assert info["streaming"] == (M == 1)
-    assert info["persistent_grouped"] == (M > 1 and group == 0 and (M <= 16 or times == 5))
+    assert info["persistent_grouped"] == (kernel in ("rings", "rows"))
+    assert kernel is None or kernels_of(dl) == [kernel]
     for rep in range(2):
         for e in entries:
             e["y"].zero_()
