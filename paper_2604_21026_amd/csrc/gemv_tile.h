@@ -80,11 +80,14 @@ constexpr int tile_rows(int gpl) { return gpl <= 1 ? 8 : gpl <= 2 ? 4 : gpl <= 4
 // 65536 11.8 us against 29.6 (W4A16) and 9.2 against 24.7 (W4A8), 3000 x 16416 10.1 against 11.1
 // and 7.6 against 9.7, 6000 x 16416 21.3 against 21.1 and 15.2 against 19.1, 12000 x 16416 38
 // against 32 and 33 against 27.  Two tokens: 1024 x 16416 9.2 against 10.8 and 8.2 against 9.4,
-// 3000 x 16416 15.9 against 11.3.  Three: 700 x 8000 6.5 against 6.7 and 5.7 against 6.0, 2048 x
-// 2720 5.6 against 4.7.  Four: 512 x 2720 4.8 against 4.1.
-static inline bool gemv_wave_per_row(const GemvSegs &S, int K, int M, bool per_group) {
+// 2048 x 2720 4.8 against 4.3 and 4.1 against 4.2, 3000 x 16416 15.9 against 11.3 and 10.1
+// against 9.8.  Three: 700 x 8000 6.5 against 6.7 and 5.7 against 6.0, 2048 x 2720 5.6 against
+// 4.7.  Four: 512 x 2720 4.8 against 4.1.
+static inline bool gemv_wave_per_row(const GemvSegs &S, int K, int M, int precision, bool per_group) {
     if (!per_group && gemv_mfma_supported(S, K, M)) return false;  // column chains
-    return M == 1 ? S.total_rows <= 16 * device_cu_count() : M <= 3 && M * S.total_rows <= 8 * device_cu_count();
+    const int cus = device_cu_count();
+    if (M == 1) return S.total_rows <= 16 * cus;
+    return M <= 3 && M * S.total_rows <= (M == 2 && precision == NVQ_W4A8 ? 16 : 8) * cus;
 }
 
 // Grid size for a batch-1 GEMV: enough workgroups of `teams_per_wg` teams to
