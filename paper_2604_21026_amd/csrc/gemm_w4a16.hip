@@ -23,7 +23,8 @@
 //    a weight once per 256 tokens: the best rate, if the output has enough of them;
 //  - smaller tiles (second half of this file), 64 to 128 tokens x 32 to 256 rows, whose
 //    waves share out rows and slices of K, for everything else.
-// gemm_choose weighs them by what they were measured to take.
+// gemm_choose weighs them by what they were measured to take; with it goes the order of the
+// additions (one, two or four slices of K), which therefore depends on the number of tokens.
 #include "nvq_internal.h"
 
 #include <cstdlib>

@@ -237,7 +237,8 @@ def test_small_batch_kernel_edges(M, N, K, off):
                                        (2, 8300, 4096, 0), (5, 16400, 1024, 0), (16, 16400, 640, 0),
                                        (24, 16400, 512, 0), (6, 40, 4096, 1), (16, 40, 2720, 0), (25, 40, 2720, 0),
                                        (4, 16400, 352, 0), (1, 40, 16416, 0), (30, 17, 65536, 0),
-                                       (1, 4097, 16416, 0), (2, 1024, 2720, 0), (2, 1025, 2720, 0), (3, 682, 1056, 1)])
+                                       (1, 4097, 16416, 0), (2, 1024, 2720, 0), (2, 1025, 2720, 0), (2, 2049, 2720, 0),
+                                       (3, 682, 1056, 1)])
 def test_multi_token_sums_are_added_in_the_stated_order(M, N, K, off):
     """Bit for bit against the same additions on the CPU.  W4A8: the block sums are integers.  W4A16
     on small whole inputs: a group's products and their sums are exact whatever their order."""
@@ -1386,6 +1387,27 @@ def test_gemm_w4a16_small_tiles_match_oracle(tile, M, N, K, off, monkeypatch):
     assert err < 1e-5
     # the bf16 results are the fp32 ones rounded
     assert torch.equal(yb, y.to(torch.bfloat16))
+
+
+# The order of the additions is the tile's alone: with a tile chosen, a prompt in two pieces gives
+# every token the bits it gets in one.  The wide tile and 128x256 agree, and so do the tiles with
+# as many pieces of K.
+def test_gemm_w4a16_bits_with_a_tile_chosen_do_not_depend_on_the_batch(monkeypatch):
+    say("gemm, prompt in pieces")
+    M, N, K = 200, 300, 2304
+    _, q, s = packed(9185, N, K)
+    xd = act(9285, M, K).to(DEV)
+    qd, sd = to_dev_packed(q, s)
+    whole = {}
+    for tile in ("wide", "128x256", "128x128", "128x64", "64x64", "64x32"):
+        monkeypatch.setenv("NVQ_GEMM_TILE", tile)
+        whole[tile] = nvq.gemm_w4a16(qd, sd, xd)
+        parts = torch.cat([nvq.gemm_w4a16(qd, sd, xd[a:b].contiguous()) for a, b in ((0, 1), (1, 70), (70, M))])
+        torch.cuda.synchronize()
+        assert torch.equal(whole[tile], parts), tile
+    assert torch.equal(whole["wide"], whole["128x256"])
+    assert torch.equal(whole["128x128"], whole["128x64"])
+    assert torch.equal(whole["64x64"], whole["64x32"])
 
 
 # An infinite activation in the last group of K: infinite results, NaN only where the weight is
