@@ -73,14 +73,12 @@ struct RowsSource {
     bool whole;         // its 32 rows follow each other in memory (one matrix, none missing)
 };
 
-template <int TOK>
 __global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu(3))) void
 gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict__ part_tab_, int nparts,
                  int M, uint32_t *__restrict__ tickets) {
-    constexpr int MT = (TOK + 15) / 16, R = 2;
-    constexpr int kA = TOK * 512;  // an activation buffer (bf16; codes fill half of it)
-    constexpr int kASlice = TOK / 2 / kRowsWaves;  // loads of a wave and step, bf16 (codes: half)
-    static_assert(kASlice >= 2, "every wave loads codes, too");
+    constexpr int MT = 2, R = 2;   // token tiles, row tiles of a wave
+    constexpr int kA = 32 * 512;  // an activation buffer (bf16; codes fill half of it)
+    constexpr int kASlice = 16 / kRowsWaves;  // loads of a wave and step, bf16 (codes: half)
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kA + kRowsWaves * kRowsSlot];
     __shared__ int ticket_word;
     CGroup *tab = (CGroup *)tab_;
@@ -172,9 +170,8 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
     const uint32_t at = (uint32_t)(uintptr_t)slot, abase = (uint32_t)(uintptr_t)lds;
     const uint32_t wpos = at + n * 128 + 16 * ((n >> 1) & 7) + 4 * kb;
     const uint32_t spos = at + kRowsW + 16 * n;
-    const int mn = TOK < 16 ? n & (TOK - 1) : n;  // tokens that are not there read another's
-    const uint32_t apos16 = abase + mn * 512 + 16 * ((kb >> 1) ^ mn) + 8 * (kb & 1);
-    const uint32_t apos8 = abase + mn * 256 + 16 * mn + 4 * kb;
+    const uint32_t apos16 = abase + n * 512 + 16 * ((kb >> 1) ^ n) + 8 * (kb & 1);
+    const uint32_t apos8 = abase + n * 256 + 16 * n + 4 * kb;
 
     // A result's sum in three levels: the eight groups of a step, eight steps, all of K.  (One
     // chain over all of K had up to twice the error of the four that the kernel for up to 16 tokens
@@ -392,7 +389,7 @@ int rows_grid(int nunits, int nparts) {
 int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int grid, int M,
                      uint32_t *tickets, hipStream_t st) {
     if (nparts <= 0 || grid <= 0) return NVQ_OK;
-    hipLaunchKernelGGL(gemv_rows_kernel<32>, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, M,
+    hipLaunchKernelGGL(gemv_rows_kernel, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, M,
                        tickets);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;

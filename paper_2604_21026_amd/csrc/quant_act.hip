@@ -103,8 +103,9 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
 // thread keeps its one or two chunks of eight values in registers from the load to the
 // codes.  The grid is a handful of workgroups, so what it costs is its launch and a chain
 // of memory and barrier latencies: one launch and one trip to memory instead of two and
-// four (norm and quantisation of 8 x 4096, and SiLU and quantisation of 8 x 14336, as
-// kernels of their own with 256 threads each: 8.7 us by the trace, 4.6 as one).
+// four (by the trace 4.3 us for norm and quantisation of 8 x 4096, 6.2 for SiLU and
+// quantisation of 8 x 14336; as kernels of their own they cost a chain of four 8B blocks 25
+// of 249 us more).
 // OP: nvq_linear.in_op; Q: 0 = the transformed bf16 values (xt), 1 = codes with a scale
 // per token, 2 = codes with a scale per group.
 constexpr int kPrepMaxK = 16384, kPrepThreads = 1024;
@@ -375,7 +376,8 @@ int prep_go(const nvq_linear &e, int M, uint16_t *xt, int8_t *xq, float *xscale,
 template <int OP>
 int prep_quant(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
                float *xscale, int32_t *xgsum, hipStream_t st) {
-    if (!quant) return prep_go<OP, 0>(e, M, xt, xq, xscale, xgsum, st);
+    if constexpr (OP == NVQ_IN_RMSNORM)  // (the others have launches of their own for that)
+        if (!quant) return prep_go<OP, 0>(e, M, xt, xq, xscale, xgsum, st);
     if (act_group == 0) return prep_go<OP, 1>(e, M, xt, xq, xscale, xgsum, st);
     return prep_go<OP, 2>(e, M, xt, xq, xscale, xgsum, st);
 }
