@@ -1,6 +1,6 @@
 // Products of 2 to 32 tokens with one phase's weight rows, any K that is a whole number
 // of groups, activation scales per token or per group: the kernel behind the single calls
-// and the per-phase walk.  Paper: the W4A8 / W4A16 kernel descriptions; the arithmetic is
+// and the per-phase walk (up to three tokens and few rows: see gemv_wave_per_row).  Paper: the W4A8 / W4A16 kernel descriptions; the arithmetic is
 // that of mfma_act.h (one 16x16x32 MFMA per quantisation group, 16 tokens times 16 rows,
 // the constant nibble offset removed by a second MFMA).
 //
@@ -25,8 +25,8 @@
 //
 // What bounds it: neither memory nor arithmetic alone.  28672 x 4096 at 8 tokens takes 16.5
 // (W4A8) to 18.8 us (W4A16), 3.5 to 4 TB/s; the per-tile grid that loaded straight into
-// registers took 25 and 31.  Without the loads it takes 12, the vector ALUs busy most of that,
-// without either 6.  The sixty-four chains cost registers and a longer way through LDS: with a
+// registers took 25 and 31.  The vector ALUs are busy half of the time (16 to 18 instructions
+// per 16 x 16 x 32 product), the matrix cores a sixth.  The sixty-four chains cost registers and a longer way through LDS: with a
 // scale per group 16384 x 3072 takes 10.1 us at 4 tokens (8.6 in one chain per wave; a wave per
 // row, which served these calls before, 18.7), 28672 x 4096 20, 27 and 57 us at 8, 16 and 32
 // tokens (that: 63, 111 and 202).  Two to four blocks in flight per wave instead of one, with
@@ -244,11 +244,11 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     // the group), for W4A8 a dword twice.
     const uint32_t at = (uint32_t)(uintptr_t)slot;
     const int mn = TOK < 16 ? n & (TOK - 1) : n;
-    // The permutations leave the rest of an address alone: another piece is one xor away.  With
-    // 9 to 16 tokens and a scale per group the addresses are made anew for every block, so that
-    // the registers suffice for two workgroups per compute unit (28672 x 4096, 16 tokens: 27 us
+    // The permutations leave the rest of an address alone: another piece is one xor away.  With more
+    // than 8 tokens and a scale per group the addresses are made anew for every block, so that
+    // the registers suffice, up to 16 tokens for two workgroups per compute unit (28672 x 4096: 27 us
     // against 36); elsewhere they stay in registers.
-    constexpr bool kFresh = PG && TOK == 16;
+    constexpr bool kFresh = PG && TOK > 8;
     const uint32_t wpos0 = at + n * (16 * NG) + 16 * ((n / (16 / NG)) % NG) + 4 * kb;
     const uint32_t apos0 = B::token_place(n) + (PREC == NVQ_W4A8 ? 16 * (mn & B::kMixed) + 4 * kb
                                                                 : 16 * ((kb >> 1) ^ mn) + 8 * (kb & 1));
