@@ -92,7 +92,8 @@ int nvq_pack_int4(const float *W, int64_t N, int64_t K, int group,
  *   xscale    fp32, written
  *   xgsum     [M][K/32] int32, written: sum of the codes of each block of 32,
  *             the "sum_x" term of the paper's deferred bias correction.
- *             Required (the W4A8 GEMV consumes it).
+ *             Required (the W4A8 GEMV consumes it in some of its kernels, for
+ *             one to three tokens).
  */
 int nvq_quant_act_i8(const uint16_t *x_bf16, int M, int K, int act_group,
                      int8_t *xq, float *xscale, int32_t *xgsum, void *stream);
@@ -212,7 +213,8 @@ typedef struct nvq_linear {
  * output projection).  Phases that share no buffer give the same results in
  * any order; NVQ_PLAN_ORDERED keeps the list's order.  At 2 <= M <= 32 with per-token activation scales and every
  * K a multiple of 128, phases that do not depend on each other share two or
- * three launches on the matrix cores.  Otherwise one or two launches per phase
+ * three launches on the matrix cores (from 17 tokens on where that is faster
+ * than launches per phase).  Otherwise one or two launches per phase
  * are enqueued.  All give the same results (up to the fp32 summation order).
  * nvq_decode_linears copies its tables to the device on every call (blocking
  * copies: the phase table, a few KiB, and at M = 1 one byte per streaming wave
@@ -238,7 +240,7 @@ int nvq_decode_status(const void *workspace, void *stream, int *timed_out);
  * nvq_decode_linears_static -- the same walk for callers that cannot allocate
  * device memory or pass a workspace: code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc.  It only enqueues kernels
- * (one or two launches per phase plus one per input transform; no copies, no
+ * (one or two launches per phase, three where K > 16384; no copies, no
  * hipMalloc / hipFree, no allocating library call), so it is slower than the
  * persistent kernel of nvq_decode_linears but can be captured.  The
  * activation codes, scales and code sums of the phase being run (and its

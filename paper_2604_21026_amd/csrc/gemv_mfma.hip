@@ -1,8 +1,9 @@
 // Small-batch (2 <= M <= 32 tokens) W4A8 and W4A16 products on the matrix
 // cores, many independent phases in one launch (plans whose K are not all
-// multiples of 512; single phases go to gemv_slice.h).  Paper: the W4A8 / W4A16 kernel descriptions and the remark in the
-// limitations that batch > 1 moves the product towards compute; the weights
-// are still read once per step, so the kernel stays bound by HBM.
+// multiples of 512; single phases go to gemv_slice.h).  Paper: the W4A8 / W4A16
+// kernel descriptions and the remark in the limitations that batch > 1 moves the
+// product towards compute; the weights are still read once per step, so the
+// kernel stays bound by HBM.
 //
 // One 16x16x32 MFMA covers exactly one quantisation group: 16 tokens x 32
 // inputs (operand A) times 32 inputs x 16 weight rows (operand B).  Lane

@@ -10,11 +10,11 @@
 // lanes 0-3 store one dword each.
 //
 // The codes are those of an IEEE division, without dividing: v * (1 / s) differs
-// from v / s by less than 2^-20 (|v / s| < 16: the fp16 scale is at least half
-// of absmax / 7), so the two round to the same integer unless the product lies
-// within 2^-16 of a tie, where the division decides.  With four divisions per
-// lane the vector ALU was the bound (14336 x 4096: 47.8 us by the trace, now 41; packing and
-// unpacking to bf16 in a row 77.7 -> 67.9 us).
+// from v / s by less than 2^-19 (two roundings; |v / s| < 16: the fp16 scale is at
+// least half of absmax / 7), so the two round to the same integer unless the product lies
+// within 2^-16 of a tie, where the division decides.  The vector ALU is the bound,
+// with four divisions per lane far more so (14336 x 4096, packing and unpacking to bf16 in a
+// row: 77.7 us, now 67.9; by the trace 43 to 47 and 22).
 #include "nvq_internal.h"
 
 namespace nvq {

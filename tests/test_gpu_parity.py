@@ -159,7 +159,8 @@ def test_quant_act_edge_values():
 # ---- a3 W4A8 -------------------------------------------------------------------
 W4A8_CASES = [
     # N, K, M, act_group: every lane/row decomposition of the batch-1 kernel, ragged row
-    # tails, more rows than one grid pass, the generic kernel (M > 1, K > 16384)
+    # tails, more rows than one grid pass, and a wave per row (one token and K > 16384; two or
+    # three tokens and few rows)
     (3, 32, 1, 0), (37, 1024, 1, 0), (70, 2048, 1, 0), (45, 2080, 1, 0), (29, 3072, 1, 0),
     (61, 4096, 1, 0), (19, 6144, 1, 0), (23, 8192, 1, 0), (11, 10240, 1, 0), (9, 12288, 1, 0),
     (13, 14336, 1, 0), (7, 16384, 1, 0), (5, 16416, 1, 0),
@@ -1330,8 +1331,8 @@ def test_gemm_w4a16_matches_oracle(M, N, K):
     assert np_ref.rel_l2(yb.float().cpu().numpy(), want) < 4e-3
 
 
-# The kernel with 256 x 256 tiles (K % 256 == 0; chosen by itself from 96 tiles on, forced here
-# so that small shapes reach it): one tile, ragged tokens and rows inside a tile and inside the
+# The kernel with 256 x 256 tiles (K % 256 == 0; chosen by size, forced here so that small shapes
+# reach it): one tile, ragged tokens and rows inside a tile and inside the
 # MFMA tiles, a single row and token, several tiles in both directions, K from one block of four
 # pairs of groups (no steady state in the loop) to many, K with an odd number of such blocks.
 @pytest.mark.parametrize("M,N,K", [(256, 256, 256), (300, 200, 512), (1, 1, 256), (33, 70, 1280),
