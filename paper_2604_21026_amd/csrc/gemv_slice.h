@@ -334,14 +334,13 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
                 return __builtin_bit_cast(bf16x8, v);
             }
         };
-        auto dump = [&](const int4v &raw, int i, int r, int mt) {
+        auto dump = [&](const typename A::offset_t &raw, int i, int r, int mt) {
             const RowRef o = locate_row(S, row0 + 16 * r + n, G);
             if (!o.valid || !o.dbg || g0 + i >= G) return;
-            const int acc[4] = {raw.x, raw.y, raw.z, raw.w};
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const int m = mt * 16 + kb * 4 + jj;
-                if (m < M) o.dbg[((int64_t)m * o.N + o.n) * G + g0 + i] = acc[jj];
+                if (m < M) o.dbg[((int64_t)m * o.N + o.n) * G + g0 + i] = (int)raw[jj];
             }
         };
         // what the lane adds in round i: group i, or i + 4 in the upper half of a pair
@@ -355,6 +354,10 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
                 sum[jj] = fmaf(sj, p[jj], sum[jj]);
             }
         };
+        // A branch ends the last block of a tail early, and others write the sums of a test.  The
+        // wait costs up to 5% (W4A8, 32 tokens, 16400 x 2720: 31.0 -> 32.5 us) and nothing at
+        // 4096 x 4096.
+        constexpr bool kBranches = TAIL || DEBUG;
         if constexpr (B::kPair) {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
@@ -363,24 +366,24 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
                 const auto off_lo = A::offset(lo), off_hi = A::offset(hi);
 #pragma unroll
                 for (int r = 0; r < RT; ++r) {
-                    int4v raw_lo, raw_hi;
-                    const float4v plo = A::product(lo, A::weights(q[r][i]), off_lo, raw_lo);
-                    const float4v phi = A::product(hi, A::weights(q[r][i + 4]), off_hi, raw_hi);
+                    typename A::offset_t plo = A::multiply(lo, A::weights(q[r][i]), off_lo);
+                    typename A::offset_t phi = A::multiply(hi, A::weights(q[r][i + 4]), off_hi);
+                    if constexpr (kBranches) wait_written(plo, phi);
                     if (DEBUG && PREC == NVQ_W4A8) {
-                        dump(raw_lo, i, r, 0);
-                        dump(raw_hi, i + 4, r, 0);
+                        dump(plo, i, r, 0);
+                        dump(phi, i + 4, r, 0);
                     }
-                    float4v p;
+                    typename A::offset_t mine;
 #pragma unroll
                     for (int jj = 0; jj < 4; ++jj) {
+                        const auto both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint4v, plo)[jj],
+                                                                           __builtin_bit_cast(uint4v, phi)[jj], false, false);
                         if constexpr (PREC == NVQ_W4A8)
-                            p[jj] = (float)(int)__builtin_amdgcn_permlane32_swap((uint32_t)raw_lo[jj], (uint32_t)raw_hi[jj],
-                                                                                 false, false)[0];
+                            mine[jj] = (int)both[0];
                         else
-                            p[jj] = __uint_as_float(__builtin_amdgcn_permlane32_swap(__float_as_uint(plo[jj]),
-                                                                                     __float_as_uint(phi[jj]), false, false)[0]);
+                            mine[jj] = __uint_as_float(both[0]);
                     }
-                    if (!TAIL || g0 + i + 4 * half < G) add(p, i, r, 0);
+                    if (!TAIL || g0 + i + 4 * half < G) add(A::value(mine), i, r, 0);
                 }
             }
         } else {
@@ -393,10 +396,10 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
                     const auto off = A::offset(act);
 #pragma unroll
                     for (int r = 0; r < RT; ++r) {
-                        int4v raw;
-                        const float4v p = A::product(act, A::weights(q[r][i]), off, raw);
-                        if (DEBUG && PREC == NVQ_W4A8) dump(raw, i, r, mt);
-                        add(p, i, r, mt);
+                        typename A::offset_t p = A::multiply(act, A::weights(q[r][i]), off);
+                        if constexpr (kBranches) wait_written(p);
+                        if (DEBUG && PREC == NVQ_W4A8) dump(p, i, r, mt);
+                        add(A::value(p), i, r, mt);
                     }
                 }
             }

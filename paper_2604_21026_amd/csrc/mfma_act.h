@@ -51,6 +51,19 @@ __device__ __forceinline__ void transpose_rows(uint32_t (&r)[4]) {
     r[3] = d.y;
 }
 
+// Nothing in the hardware holds a vector instruction back until the MFMA that writes its operand
+// is done: the compiler counts the eight wait states.  Across a branch it has left them out, and
+// the use then took the registers as they were before, in some runs.  Where a branch stands
+// between products and their use this goes right behind the products: every use comes after it.
+template <typename T>
+__device__ __forceinline__ void wait_written(T &p) {
+    asm volatile("s_nop 7" : "+v"(p));
+}
+template <typename T>
+__device__ __forceinline__ void wait_written(T &p, T &q) {
+    asm volatile("s_nop 7" : "+v"(p), "+v"(q));
+}
+
 template <int PREC>
 struct Act;
 
@@ -86,10 +99,16 @@ struct Act<NVQ_W4A8> {
         const int4v z = {0, 0, 0, 0};
         return __builtin_amdgcn_mfma_i32_16x16x32_i8(a, (long)0xf8f8f8f8f8f8f8f8ull, z, 0, 0, 0);
     }
-    __device__ static float4v product(operand a, operand b, int4v c, int4v &raw) {
-        raw = __builtin_amdgcn_mfma_i32_16x16x32_i8(a, b, c, 0, 0, 0);
+    __device__ static int4v multiply(operand a, operand b, int4v c) {
+        return __builtin_amdgcn_mfma_i32_16x16x32_i8(a, b, c, 0, 0, 0);
+    }
+    __device__ static float4v value(const int4v &raw) {
         const float4v f = {(float)raw.x, (float)raw.y, (float)raw.z, (float)raw.w};
         return f;
+    }
+    __device__ static float4v product(operand a, operand b, int4v c, int4v &raw) {
+        raw = multiply(a, b, c);
+        return value(raw);
     }
     typedef int4v offset_t;
 };
@@ -141,9 +160,13 @@ struct Act<NVQ_W4A16> {
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, c), z, 0, 0,
                                                        0);
     }
+    __device__ static float4v multiply(operand a, operand b, float4v c) {
+        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+    }
+    __device__ static float4v value(const float4v &raw) { return raw; }
     __device__ static float4v product(operand a, operand b, float4v c, int4v &raw) {
         (void)raw;
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+        return multiply(a, b, c);
     }
     typedef float4v offset_t;
 };

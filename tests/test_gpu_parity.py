@@ -239,7 +239,7 @@ def test_small_batch_kernel_edges(M, N, K, off):
                                        (24, 16400, 512, 0), (6, 40, 4096, 1), (16, 40, 2720, 0), (25, 40, 2720, 0),
                                        (4, 16400, 352, 0), (1, 40, 16416, 0), (30, 17, 65536, 0),
                                        (1, 4097, 16416, 0), (2, 1024, 2720, 0), (2, 1025, 2720, 0), (2, 2049, 2720, 0),
-                                       (3, 682, 1056, 1)])
+                                       (3, 682, 1056, 1), (9, 2000, 2016, 0), (16, 2000, 65504, 0)])
 def test_multi_token_sums_are_added_in_the_stated_order(M, N, K, off):
     """Bit for bit against the same additions on the CPU.  W4A8: the block sums are integers.  W4A16
     on small whole inputs: a group's products and their sums are exact whatever their order."""
@@ -279,6 +279,28 @@ def test_multi_token_sums_are_added_in_the_stated_order(M, N, K, off):
     y = nvq.gemv_w4a16(qd, sd, torch.from_numpy(xi).to(torch.bfloat16).to(DEV))
     torch.cuda.synchronize()
     check(y, np_ref.sums_in_order(acc, sw, chains), "w4a16")
+
+
+# A walk whose last block ends after one to seven groups, in the first and in the second of the two
+# blocks that are in flight, with up to 8, 16 and 32 tokens: a product used behind the branch that
+# ends the block must have been written (with three groups of four it was not, in most runs).
+@pytest.mark.parametrize("M", [8, 16, 32])
+@pytest.mark.parametrize("groups", [63, 127, 57, 122, 59, 124, 61])
+def test_a_last_block_that_ends_early_gives_the_same_bits_every_time(M, groups):
+    say("early end", M, groups)
+    N, K = 2000, 32 * groups
+    _, q, s = packed(3700 + groups, N, K)
+    qd, sd = to_dev_packed(q, s)
+    x = act(3800 + K, M, K).to(DEV)
+    a8, a8g = nvq.quant_act_i8(x, 0), nvq.quant_act_i8(x, 32)
+    for what, call in (("w4a16", lambda out: nvq.gemv_w4a16(qd, sd, x, out=out)),
+                       ("w4a8", lambda out: nvq.gemv_w4a8(qd, sd, *a8, 0, out=out)),
+                       ("w4a8 per group", lambda out: nvq.gemv_w4a8(qd, sd, *a8g, 32, out=out))):
+        ys = torch.zeros((40, M, N), device=DEV)
+        for y in ys:
+            call(y)
+        torch.cuda.synchronize()
+        assert int((ys != ys[0]).sum()) == 0, what
 
 
 @pytest.mark.parametrize("M", [1, 20])
