@@ -1,8 +1,9 @@
 // Products of 2 to 32 tokens with one phase's weight rows, any K that is a whole number
 // of groups, activation scales per token or per group: the kernel behind the single calls
-// and the per-phase walk (up to three tokens and few rows: see gemv_wave_per_row).  Paper: the W4A8 / W4A16 kernel descriptions; the arithmetic is
-// that of mfma_act.h (one 16x16x32 MFMA per quantisation group, 16 tokens times 16 rows,
-// the constant nibble offset removed by a second MFMA).
+// and the per-phase walk (up to three tokens and few rows: see gemv_wave_per_row).  Paper:
+// the W4A8 / W4A16 kernel descriptions; the arithmetic is that of mfma_act.h (one 16x16x32
+// MFMA per quantisation group, 16 tokens times 16 rows, the constant nibble offset removed
+// by a second MFMA).
 //
 // A workgroup of W waves owns 16 RT consecutive rows; the waves share out K in blocks of
 // NG groups (eight: 256 inputs, a whole 128-byte line of every row), wave w the blocks w, w
@@ -26,11 +27,11 @@
 // What bounds it: neither memory nor arithmetic alone.  28672 x 4096 at 8 tokens takes 16.5
 // (W4A8) to 18.8 us (W4A16), 3.5 to 4 TB/s; the per-tile grid that loaded straight into
 // registers took 25 and 31.  The vector ALUs are busy half of the time (16 to 18 instructions
-// per 16 x 16 x 32 product), the matrix cores a sixth.  The sixty-four chains cost registers and a longer way through LDS: with a
-// scale per group 16384 x 3072 takes 10.1 us at 4 tokens (8.6 in one chain per wave; a wave per
-// row, which served these calls before, 18.7), 28672 x 4096 20, 27 and 57 us at 8, 16 and 32
-// tokens (that: 63, 111 and 202).  Two to four blocks in flight per wave instead of one, with
-// fewer workgroups per compute unit, were no faster.
+// per 16 x 16 x 32 product), the matrix cores a sixth.  The sixty-four chains cost registers
+// and a longer way through LDS: with a scale per group 16384 x 3072 takes 10.1 us at 4 tokens
+// (8.6 in one chain per wave; a wave per row, which served these calls before, 18.7), 28672 x
+// 4096 20, 27 and 57 us at 8, 16 and 32 tokens (that: 63, 111 and 202).  Two to four blocks in
+// flight per wave instead of one, with fewer workgroups per compute unit, were no faster.
 //
 // W, NG: eight waves with blocks of eight groups, or where that is better
 //  - four waves, in eight column chains (see slice_eight_waves), and with a scale per group and up to
