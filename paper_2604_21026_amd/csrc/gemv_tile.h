@@ -76,17 +76,20 @@ constexpr int tile_rows(int gpl) { return gpl <= 1 ? 8 : gpl <= 2 ? 4 : gpl <= 4
 // Whether a call whose sums are added in sixty-four chains (gemv_slice.h) goes to a kernel with
 // a wave per row instead of a workgroup per 16 rows.  Up to three tokens and few rows: the row
 // tiles leave compute units idle and every one of them takes K by eight waves only, while the
-// inputs of a few tokens cost little to read again for every row.  One token (K > 16384): 16 x
-// 65536 11.8 us against 29.6 (W4A16) and 9.2 against 24.7 (W4A8), 3000 x 16416 10.1 against 11.1
-// and 7.6 against 9.7, 6000 x 16416 21.3 against 21.1 and 15.2 against 19.1, 12000 x 16416 38
-// against 32 and 33 against 27.  Two tokens: 1024 x 16416 9.2 against 10.8 and 8.2 against 9.4,
-// 2048 x 2720 4.8 against 4.3 and 4.1 against 4.2, 3000 x 16416 15.9 against 11.3 and 10.1
-// against 9.8.  Three: 700 x 8000 6.5 against 6.7 and 5.7 against 6.0, 2048 x 2720 5.6 against
-// 4.7.  Four: 512 x 2720 4.8 against 4.1.
+// inputs of a few tokens cost little to read again for every row.  One token (K > 16384), W4A16:
+// 16 x 65536 11.8 us against 29.6, 3000 x 16416 10.1 against 11.1, 6000 x 16416 21.3 against
+// 21.1, 7000 x 65536 98 against 68, 12000 x 16416 38 against 32.  W4A8, whatever the rows: 16 x
+// 65536 9.2 against 24.7, 4200 x 16416 11.6 against 17.2, 8192 x 16416 21.2 against 20.5, 10000
+// x 65536 72 against 78, 20000 x 16416 45 against 47 and 20000 x 65536 148 against 176 (both go
+// up in steps of 8192 rows; just above a step the row tiles are ahead, 12000 x 16416 33 against
+// 28, and a little further on behind again).  Two tokens: 1024 x 16416 9.2 against 10.8 and 8.2
+// against 9.4, 2048 x 2720 4.8 against 4.3 and 4.1 against 4.2, 3000 x 16416 15.9 against 11.3
+// and 10.1 against 9.8.  Three: 700 x 8000 6.5 against 6.7 and 5.7 against 6.0, 2048 x 2720 5.6
+// against 4.7.  Four: 512 x 2720 4.8 against 4.1.
 static inline bool gemv_wave_per_row(const GemvSegs &S, int K, int M, int precision, bool per_group) {
     if (!per_group && gemv_mfma_supported(S, K, M)) return false;  // column chains
     const int cus = device_cu_count();
-    if (M == 1) return S.total_rows <= 16 * cus;
+    if (M == 1) return precision == NVQ_W4A8 || S.total_rows <= 16 * cus;
     return M <= 3 && M * S.total_rows <= (M == 2 && precision == NVQ_W4A8 ? 16 : 8) * cus;
 }
 

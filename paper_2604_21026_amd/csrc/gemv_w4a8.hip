@@ -13,7 +13,7 @@
 // int8 codes of the lane's groups are register-resident, the loop body per
 // 32 weights is one 128-bit load, 12 bit operations, 8 dot4, one convert and
 // one FMA.  More tokens, and K beyond 16384, go to the matrix-core kernel
-// (gemv_slice.h) or, up to three tokens and few rows, to a wave per row.
+// (gemv_slice.h) or, with one token or up to three and few rows, to a wave per row.
 #include "gemv_tile.h"
 
 namespace nvq {
