@@ -84,13 +84,18 @@ constexpr int tile_rows(int gpl) { return gpl <= 1 ? 8 : gpl <= 2 ? 4 : gpl <= 4
 // up in steps of 8192 rows; just above a step the row tiles are ahead, 12000 x 16416 33 against
 // 28, and a little further on behind again).  Two tokens: 1024 x 16416 9.2 against 10.8 and 8.2
 // against 9.4, 2048 x 2720 4.8 against 4.3 and 4.1 against 4.2, 3000 x 16416 15.9 against 11.3
-// and 10.1 against 9.8.  Three: 700 x 8000 6.5 against 6.7 and 5.7 against 6.0, 2048 x 2720 5.6
-// against 4.7.  Four: 512 x 2720 4.8 against 4.1.
+// and 10.1 against 9.8; W4A8 where the scales of a block are not one load (K % 256 != 0), 3000 x
+// 3616 5.0 against 5.3, 4200 x 5568 6.6 against 7.5 (a scale per group: 8.1), 5000 x 8256 9.4
+// against 10.1, 6100 x 12352 16.2 against 15.3, 6600 x 5600 9.4 against 8.6; where they are, 3072 x
+// 8192 6.9 against 6.9; with K beyond 16384 3000 x 20544 14.4 against 12.4, 5000 x 20544 20.5
+// against 22.5.  Three: 700 x 8000 6.5 against 6.7 and 5.7 against 6.0, 2048 x 2720 5.6 against
+// 4.7, 3000 x 8256 8.7 against 7.3 (W4A8).  Four: 512 x 2720 4.8 against 4.1.
 static inline bool gemv_wave_per_row(const GemvSegs &S, int K, int M, int precision, bool per_group) {
     if (!per_group && gemv_mfma_supported(S, K, M)) return false;  // column chains
     const int cus = device_cu_count();
     if (M == 1) return precision == NVQ_W4A8 || S.total_rows <= 16 * cus;
-    return M <= 3 && M * S.total_rows <= (M == 2 && precision == NVQ_W4A8 ? 16 : 8) * cus;
+    if (M == 2 && precision == NVQ_W4A8) return S.total_rows <= (K % 256 != 0 && K <= 16384 ? 24 : 8) * cus;
+    return M <= 3 && M * S.total_rows <= 8 * cus;
 }
 
 // Grid size for a batch-1 GEMV: enough workgroups of `teams_per_wg` teams to

@@ -239,6 +239,7 @@ def test_small_batch_kernel_edges(M, N, K, off):
                                        (24, 16400, 512, 0), (6, 40, 4096, 1), (16, 40, 2720, 0), (25, 40, 2720, 0),
                                        (4, 16400, 352, 0), (1, 40, 16416, 0), (30, 17, 65536, 0),
                                        (1, 4097, 16416, 0), (1, 8300, 16416, 0), (2, 1024, 2720, 0), (2, 1025, 2720, 0), (2, 2049, 2720, 0),
+                                       (2, 6144, 1056, 0), (2, 6145, 1056, 0), (2, 2049, 8224, 1), (2, 2049, 16416, 0),
                                        (3, 682, 1056, 1), (9, 2000, 2016, 0), (16, 2000, 65504, 0)])
 def test_multi_token_sums_are_added_in_the_stated_order(M, N, K, off):
     """Bit for bit against the same additions on the CPU.  W4A8: the block sums are integers.  W4A16
