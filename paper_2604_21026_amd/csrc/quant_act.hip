@@ -15,6 +15,47 @@ namespace nvq {
 
 constexpr int kQuantThreads = 256;
 
+// op(value, value of lane i ^ D) without a trip through LDS, op symmetric.  D = 4 and 8 rotate
+// within sixteen lanes: for 8 that is the exchange, for 4 it is where lanes 8 apart agree.
+template <int D, typename T, typename OP>
+__device__ __forceinline__ T with_lane_xor(T v, OP op) {
+    static_assert(sizeof(T) == 4, "one register");
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    if constexpr (D >= 16) {
+        const auto r = D == 32 ? __builtin_amdgcn_permlane32_swap(b, b, false, false)
+                               : __builtin_amdgcn_permlane16_swap(b, b, false, false);
+        const uint32_t even = r[0], odd = r[1];  // (a bit cast of an element in place takes element 0)
+        return op(__builtin_bit_cast(T, even), __builtin_bit_cast(T, odd));
+    } else {
+        constexpr int kCtrl = D == 8 ? 0x128 : D == 4 ? 0x124 : D == 2 ? 0x4e : 0xb1;
+        return op(v, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(b, b, kCtrl, 0xf, 0xf, false)));
+    }
+}
+
+struct MaxOp {
+    __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
+};
+struct AddOp {
+    template <typename T>
+    __device__ T operator()(T a, T b) const { return a + b; }
+};
+
+// Over the lanes of a wave, in every lane; in the order 32, 16, .. 1 apart.
+template <typename OP>
+__device__ __forceinline__ float over_wave(float a, OP op) {
+    a = with_lane_xor<32>(a, op);
+    a = with_lane_xor<16>(a, op);
+    a = with_lane_xor<8>(a, op);
+    a = with_lane_xor<4>(a, op);
+    a = with_lane_xor<2>(a, op);
+    return with_lane_xor<1>(a, op);
+}
+// Over the four lanes of a group.
+template <typename T, typename OP>
+__device__ __forceinline__ T over_group(T a, OP op) {
+    return with_lane_xor<2>(with_lane_xor<1>(a, op), op);
+}
+
 __device__ __forceinline__ float chunk_absmax(const uint4 &v) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
     float a = 0.0f;
@@ -26,34 +67,53 @@ __device__ __forceinline__ float chunk_absmax(const uint4 &v) {
     return a;
 }
 
-__device__ __forceinline__ int quant_one(float x, float s) {
-    float r = rintf(x / s);
-    r = fminf(fmaxf(r, -127.0f), 127.0f);
-    return (int)r;
-}
-
-// Codes and code sum of chunk c (eight values, a quarter of a group) of a token.
-__device__ __forceinline__ void quant_chunk(const uint4 &v, float s, int c, uint2 *__restrict__ qr,
-                                            int32_t *__restrict__ gs) {
+// The codes of eight values with scale s, packed, and their sum.  One division per scale instead
+// of one per value (some ten instructions each): t = x * fl(1 / s) is within 2^-15 of the
+// quotient fl(x / s) (|x / s| <= 127: two roundings of 2^-24 relative, and the quotient's own),
+// so unless t lies within 2^-14 of a half-integer rounding t gives the integer that rounding
+// the quotient gives.  Where one of the eight does, and where the scale is too small for its
+// reciprocal, the lane divides.
+__device__ __forceinline__ uint2 quant8(const uint4 &v, float s, int *sum) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    int q[8];
+    const bool by_reciprocal = s >= 0x1p-100f;
+    const float inv_s = by_reciprocal ? 1.0f / s : 0.0f;
+    float x[8], r[8];
+    bool redo = !by_reciprocal;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        q[2 * i] = (s != 0.0f) ? quant_one(bf16_bits_to_float(w[i] & 0xffffu), s) : 0;
-        q[2 * i + 1] = (s != 0.0f) ? quant_one(bf16_bits_to_float(w[i] >> 16), s) : 0;
+        x[2 * i] = bf16_bits_to_float(w[i] & 0xffffu);
+        x[2 * i + 1] = bf16_bits_to_float(w[i] >> 16);
     }
-    int sum = 0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sum += q[i];
+    for (int i = 0; i < 8; ++i) {
+        const float t = x[i] * inv_s;
+        r[i] = rintf(t);
+        redo = redo || fabsf(t - r[i]) > 0.5f - 0x1p-14f;
+    }
+    if (redo) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) r[i] = s != 0.0f ? rintf(x[i] / s) : 0.0f;
+    }
+    int q[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) q[i] = (int)fminf(fmaxf(r[i], -127.0f), 127.0f);
+    *sum = ((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7]));
     uint2 out;
     out.x = (uint32_t)(q[0] & 0xff) | ((uint32_t)(q[1] & 0xff) << 8) |
             ((uint32_t)(q[2] & 0xff) << 16) | ((uint32_t)(q[3] & 0xff) << 24);
     out.y = (uint32_t)(q[4] & 0xff) | ((uint32_t)(q[5] & 0xff) << 8) |
             ((uint32_t)(q[6] & 0xff) << 16) | ((uint32_t)(q[7] & 0xff) << 24);
-    qr[c] = out;
-    sum += __shfl_xor(sum, 1, 64);
-    sum += __shfl_xor(sum, 2, 64);
-    if ((c & 3) == 0 && gs) gs[c >> 2] = sum;
+    return out;
+}
+
+// Codes and code sum of chunk c (eight values, a quarter of a group) of a token.
+__device__ __forceinline__ void quant_chunk(const uint4 &v, float s, int c, uint2 *__restrict__ qr,
+                                            int32_t *__restrict__ gs) {
+    int sum;
+    qr[c] = quant8(v, s, &sum);
+    if (!gs) return;  // (uniform)
+    sum = over_group(sum, AddOp());
+    if ((c & 3) == 0) gs[c >> 2] = sum;
 }
 
 // Token m of one [M][K] input, by one workgroup.
@@ -72,8 +132,7 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
         __shared__ float red[kQuantThreads / 64];
         float a = 0.0f;
         for (int c = threadIdx.x; c < chunks; c += kQuantThreads) a = fmaxf(a, chunk_absmax(xr[c]));
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 64));
+        a = over_wave(a, MaxOp());
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
         __syncthreads();
         a = red[0];
@@ -89,10 +148,7 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
         const uint4 v = xr[c];
         float s = s_tok;
         if (PER_GROUP) {
-            float a = chunk_absmax(v);
-            a = fmaxf(a, __shfl_xor(a, 1, 64));
-            a = fmaxf(a, __shfl_xor(a, 2, 64));
-            s = a / 127.0f;
+            s = over_group(chunk_absmax(v), MaxOp()) / 127.0f;
             if ((c & 3) == 0) xscale[(int64_t)m * G + (c >> 2)] = s;
         }
         quant_chunk(v, s, c, qr, gs);
@@ -101,46 +157,53 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
 
 // Input transform (transform.h) and quantisation of a token in one pass, K <= 16384: a
 // thread keeps its one or two chunks of eight values in registers from the load to the
-// codes.  The grid is a handful of workgroups, so what it costs is its launch and a chain
-// of memory and barrier latencies: one launch and one trip to memory instead of two and
-// four (by the trace 4.3 us for norm and quantisation of 8 x 4096, 6.2 for SiLU and
-// quantisation of 8 x 14336; as kernels of their own they cost a chain of four 8B blocks 25
-// of 249 us more).
+// codes.  The grid is a handful of workgroups, so what it costs is its launch (1.7 us) and a
+// chain of memory, exchange and barrier latencies: one trip to memory (the norm's weights are
+// asked for with the input), lane exchanges that do not pass through LDS, and one division per
+// scale.  By the trace 3.9 us for norm and quantisation of 8 x 4096 and 4.5 for SiLU and
+// quantisation of 8 x 14336 (4.3 and 6.2 with two trips, exchanges through LDS and a division
+// per value).
 // OP: nvq_linear.in_op; Q: 0 = the transformed bf16 values (xt), 1 = codes with a scale
 // per token, 2 = codes with a scale per group.
 constexpr int kPrepMaxK = 16384, kPrepThreads = 1024;
 
+// Maximum over the workgroup; red: sixteen words (waves that are not there count as zero).
 __device__ __forceinline__ float block_max(float a, float *red) {
-    const int waves = (int)blockDim.x >> 6;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 64));
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
+    const int waves = (int)blockDim.x >> 6, lane = (int)threadIdx.x & 63;
+    a = over_wave(a, MaxOp());
+    if (lane == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
-    a = red[0];
-    for (int i = 1; i < waves; ++i) a = fmaxf(a, red[i]);
-    return a;
+    a = (lane & 15) < waves ? red[lane & 15] : 0.0f;
+    a = with_lane_xor<8>(a, MaxOp());
+    a = with_lane_xor<4>(a, MaxOp());
+    return over_group(a, MaxOp());
 }
 
 // The sum of the chunks' sums in the order of the norm kernel (transform.hip), so that a layer
 // prepared here reads the same bf16 values, and gets the same codes, as one prepared by that
 // call: thread t of 256 adds chunks t, t + 256, ... one after the other, then the lanes of a
 // wave and the waves.  (With the chunks added as the threads here hold them, one value in some
-// ten thousand rounded the other way, and every layer behind it saw that.)
+// ten thousand rounded the other way, and every layer behind it saw that.)  Chunks and waves that
+// are not there add zero.
 constexpr int kNormThreads = 256;
-__device__ __forceinline__ float chunk_sums_in_norm_order(const float *part, int chunks, float *red) {
+template <int N>  // chunks that part has room for
+__device__ __forceinline__ float chunk_sums_in_norm_order(const float (&part)[N], int chunks, float *red) {
     const int t = (int)threadIdx.x;
     if (t < kNormThreads) {
-        float ss = 0.0f;
-        for (int c = t; c < chunks; c += kNormThreads) ss += part[c];
+        float v[N / kNormThreads], ss = 0.0f;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
+        for (int i = 0; i < N / kNormThreads; ++i)
+            v[i] = t + i * kNormThreads < chunks ? part[t + i * kNormThreads] : 0.0f;
+#pragma unroll
+        for (int i = 0; i < N / kNormThreads; ++i) ss += v[i];
+        ss = over_wave(ss, AddOp());
         if ((t & 63) == 0) red[t >> 6] = ss;
     }
     __syncthreads();
     const int waves = (int)blockDim.x >> 6;
     float ss = red[0];
-    for (int i = 1; i < kNormThreads / 64; ++i)
-        if (i < waves) ss += red[i];  // waves that are not there would add zero
+#pragma unroll
+    for (int i = 1; i < kNormThreads / 64; ++i) ss += i < waves ? red[i] : 0.0f;
     return ss;
 }
 
@@ -149,17 +212,18 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
     const uint4 *__restrict__ x, const uint4 *__restrict__ x2, const uint4 *__restrict__ gamma,
     float eps, int K, uint4 *__restrict__ xt, uint4 *__restrict__ h_out, int8_t *__restrict__ xq,
     float *__restrict__ xscale, int32_t *__restrict__ xgsum) {
-    __shared__ float red[2][kPrepThreads / 64];
+    __shared__ float red[2][16];
     __shared__ float part[OP == NVQ_IN_RMSNORM ? kPrepThreads * NCH : 1];
     const int m = blockIdx.x, chunks = K / 8, G = K / 32;
     const int64_t row = (int64_t)m * chunks;
-    uint4 v[NCH];
+    uint4 v[NCH], gm[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         const int c = (int)threadIdx.x + i * (int)blockDim.x;
         v[i] = make_uint4(0u, 0u, 0u, 0u);
         if (c < chunks) {
             v[i] = x[row + c];
+            if (OP == NVQ_IN_RMSNORM) gm[i] = gamma[c];  // (asked for here: one trip to memory less)
             if (OP == NVQ_IN_RMSNORM) {
                 if (x2) v[i] = add_bf16x8(v[i], x2[row + c]);
                 if (h_out) h_out[row + c] = v[i];
@@ -169,13 +233,13 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
             }
         }
     }
-    if (OP == NVQ_IN_RMSNORM) {
+    if constexpr (OP == NVQ_IN_RMSNORM) {
         __syncthreads();
         const float r = rms_scale(chunk_sums_in_norm_order(part, chunks, red[0]), K, eps);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const int c = (int)threadIdx.x + i * (int)blockDim.x;
-            if (c < chunks) v[i] = scale_bf16x8(v[i], r, gamma[c]);
+            if (c < chunks) v[i] = scale_bf16x8(v[i], r, gm[i]);
         }
     }
     if (Q == 0) {
@@ -200,13 +264,11 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
         const int c = (int)threadIdx.x + i * (int)blockDim.x;
         if (c >= chunks) continue;
         if (Q == 2) {
-            float a = chunk_absmax(v[i]);
-            a = fmaxf(a, __shfl_xor(a, 1, 64));
-            a = fmaxf(a, __shfl_xor(a, 2, 64));
-            s = a / 127.0f;
+            s = over_group(chunk_absmax(v[i]), MaxOp()) / 127.0f;
             if ((c & 3) == 0) xscale[(int64_t)m * G + (c >> 2)] = s;
         }
-        quant_chunk(v[i], s, c, reinterpret_cast<uint2 *>(xq + (int64_t)m * K), xgsum + (int64_t)m * G);
+        quant_chunk(v[i], s, c, reinterpret_cast<uint2 *>(xq + (int64_t)m * K),
+                    xgsum ? xgsum + (int64_t)m * G : nullptr);
     }
 }
 
@@ -251,8 +313,7 @@ __global__ __launch_bounds__(kQuantThreads) void token_scale_group_kernel(
     const uint4 *xr = reinterpret_cast<const uint4 *>(P.x_bf16) + (int64_t)m * chunks;
     float a = 0.0f;
     for (int c = threadIdx.x; c < chunks; c += kQuantThreads) a = fmaxf(a, chunk_absmax(xr[c]));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) a = fmaxf(a, __shfl_xor(a, off, 64));
+    a = over_wave(a, MaxOp());
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = a;
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -264,15 +325,6 @@ __global__ __launch_bounds__(kQuantThreads) void token_scale_group_kernel(
 }
 
 constexpr int kImageColumns = 8;  // columns of 128 inputs per workgroup (two per wave)
-
-__device__ __forceinline__ uint32_t quant_pack4(uint32_t w0, uint32_t w1, float s) {
-    const int q0 = (s != 0.0f) ? quant_one(bf16_bits_to_float(w0 & 0xffffu), s) : 0;
-    const int q1 = (s != 0.0f) ? quant_one(bf16_bits_to_float(w0 >> 16), s) : 0;
-    const int q2 = (s != 0.0f) ? quant_one(bf16_bits_to_float(w1 & 0xffffu), s) : 0;
-    const int q3 = (s != 0.0f) ? quant_one(bf16_bits_to_float(w1 >> 16), s) : 0;
-    return (uint32_t)(q0 & 0xff) | ((uint32_t)(q1 & 0xff) << 8) | ((uint32_t)(q2 & 0xff) << 16) |
-           ((uint32_t)(q3 & 0xff) << 24);
-}
 
 // img_units[u] names the phase of grid unit u; a unit is a token tile times
 // kImageColumns columns of that phase.  Token slots past M are left as they are.
@@ -294,10 +346,10 @@ __global__ __launch_bounds__(kQuantThreads) void operand_image_group_kernel(
             for (int i = 0; i < 2; ++i) {
                 const uint4 *src = reinterpret_cast<const uint4 *>(xr + c * 128 + 32 * kb + 16 * i);
                 const uint4 v0 = src[0], v1 = src[1];
-                const uint4 out = make_uint4(quant_pack4(v0.x, v0.y, s), quant_pack4(v0.z, v0.w, s),
-                                             quant_pack4(v1.x, v1.y, s), quant_pack4(v1.z, v1.w, s));
+                int sum;
+                const uint2 q0 = quant8(v0, s, &sum), q1 = quant8(v1, s, &sum);
                 *reinterpret_cast<uint4 *>(P.xa + ((size_t)(mt * C4 + c) * 2 + i) * 1024 +
-                                           lane * 16) = out;
+                                           lane * 16) = make_uint4(q0.x, q0.y, q1.x, q1.y);
             }
         }
     } else {

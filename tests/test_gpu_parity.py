@@ -140,6 +140,36 @@ def test_quant_act_bit_exact(M, K, group):
     assert np.array_equal(gs.cpu().numpy(), gs_r)
 
 
+# The kernels multiply by the scale's reciprocal and divide where that lies near a tie: rows full of
+# ties and their neighbours, scales from the smallest to the largest, infinities and NaN (which the
+# clamp turns into -127); one and two chunks per thread, and K beyond what one pass takes.
+@pytest.mark.parametrize("group", [0, 32])
+@pytest.mark.parametrize("K", [64, 8192, 8224, 16416])
+def test_quant_act_codes_are_those_of_the_division(K, group):
+    say("quant by reciprocal", K, group)
+    rng = np.random.default_rng(K)
+    amax = np.array([127.0, 254.0, 1.0, 3.0, 2.0 ** -90, 2.0 ** -99, 2.0 ** -110, 2.0 ** -130, 3e38, 5.1, 77.0, 0.3,
+                     127.0, 127.0, 9.0, 0.0], dtype=np.float32)
+    half = (rng.integers(-254, 255, (16, K)) / 2).astype(np.float32)  # in units of the scale
+    x = half * (amax / np.float32(127.0))[:, None]
+    x[:, ::32] = amax[:, None]
+    xb = torch.from_numpy(x).to(torch.bfloat16)
+    xb[12, 5::64] = float("inf")
+    xb[13, 7::64] = float("-inf")
+    xb[14, 9::64] = float("nan")
+    f = xb.float().numpy().reshape(16, -1, 32 if group else K)
+    with np.errstate(all="ignore"):
+        s = np.fmax.reduce(np.abs(f), axis=2) / np.float32(127.0)
+        q = np.fmin(np.fmax(np.rint(f / s[:, :, None]), np.float32(-127)), np.float32(127))
+    q[s == 0] = 0
+    q = q.reshape(16, K).astype(np.int8)
+    xq, xs, gs = nvq.quant_act_i8(xb.to(DEV), group)
+    torch.cuda.synchronize()
+    assert np.array_equal(xs.cpu().numpy().reshape(s.shape).view(np.uint32), s.view(np.uint32))
+    assert np.array_equal(xq.cpu().numpy(), q)
+    assert np.array_equal(gs.cpu().numpy(), q.reshape(16, K // 32, 32).sum(2, dtype=np.int32))
+
+
 def test_quant_act_edge_values():
     say("quant edge")
     x = torch.zeros(3, 64)
