@@ -137,6 +137,16 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     constexpr int kRed = kByGroup ? W * C * kRedStride * 4 : V * kTile * 256;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing > kRed ? kRing : kRed];
 
+    // The arguments are cold memory in every launch, four lines of it: all of them at once, or what
+    // is needed last (where the results go) is waited for when everything else is done (W4A16: 4096
+    // x 4096 at 8 tokens 5.1 -> 4.5 us; the W4A8 instances ask for the last line early anyway).
+    if (PREC == NVQ_W4A16) {
+        typedef const __attribute__((address_space(4))) uint32_t *Words;
+        const Words a = (Words)__builtin_amdgcn_kernarg_segment_ptr();
+        static_assert(sizeof(GemvSegs) > 160 && sizeof(GemvSegs) + 24 <= 256, "four lines of 64 bytes");
+        const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[48];
+        asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3));
+    }
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 15, kb = lane >> 4;
@@ -261,6 +271,27 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     const uint32_t spos = at + (SCB == 16 ? 16 : 4) * n + half * B::kScRead * B::kScStep;
     const uint32_t xspos = at + B::xs_place(kb);  // token 4 kb, 4 NG bytes per token
 
+    if (nblk > 0) issue(0);
+    // The scales of the tokens whose results the lane holds, or (by group) stores at the end (W4A8,
+    // a scale per token): asked for here, they arrive with the first block (at the end, one wait
+    // after the other, they took 0.4 to 0.5 us of every launch).
+    constexpr bool kTokenScale = PREC == NVQ_W4A8 && !PG;
+    constexpr int kRegs = B::kPair ? 4 : 2, kRounds = kByGroup ? kTile / kRegs : 1;  // (see the end)
+    const int share = (int)threadIdx.x % SH, result = (int)threadIdx.x / SH;
+    auto stored_reg = [&](int round) { return kRegs * round + (B::kPair ? result >> 5 : result >> 6); };
+    auto stored_token = [&](int reg) {
+        return 16 * ((reg >> 2) % MT) + 4 * ((result >> 4) & (B::kPair ? 1 : 3)) + (reg & 3);
+    };
+    constexpr int kXsc = kByGroup ? kRounds : MT * 4;
+    float xsc[kXsc];
+    if (kTokenScale) {
+#pragma unroll
+        for (int i = 0; i < kXsc; ++i) {
+            const int m = kByGroup ? stored_token(stored_reg(i)) : (i >> 2) * 16 + (B::kPair ? kb & 1 : kb) * 4 + (i & 3);
+            xsc[i] = as_global<float>(xscale)[m < M ? m : M - 1];
+        }
+    }
+
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD64(dst_, addr_, off_) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD128(dst_, addr_, off_) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
@@ -269,6 +300,10 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
         constexpr int u = decltype(set)::value;
         __builtin_amdgcn_s_waitcnt(slice_vmcnt(0));
         asm volatile("" ::: "memory");
+        if (kTokenScale) {
+#pragma unroll
+            for (float &v : xsc) asm volatile("" : "+v"(v));  // (not to be asked for later)
+        }
 
         constexpr int kSc = B::kScRead;
         uint32_t q[RT][NG], sc[RT][kSc];
@@ -406,7 +441,6 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
             }
         }
     };
-    if (nblk > 0) issue(0);
     for (int b = 0; b < nblk; b += U) {
         block(b, std::integral_constant<int, 0>());
         if (U == 2 && b + 1 < nblk) block(b + 1, std::integral_constant<int, U - 1>());
@@ -415,8 +449,6 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
 #undef NVQ_RD64
 #undef NVQ_RD128
 
-    // a W4A8 layer with a scale per token: that scale, else 1
-    auto token_scale = [&](int m) { return PREC == NVQ_W4A8 && !PG && m < M ? as_global<float>(xscale)[m] : 1.0f; };
     auto store = [&](int row, int m, float sum) {
         const RowRef o = locate_row(S, row, G);
         if (o.valid && m < M) store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, sum);
@@ -429,7 +461,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const float xs = token_scale(mt * 16 + (B::kPair ? kb & 1 : kb) * 4 + jj);
+                const float xs = kTokenScale ? xsc[kByGroup ? 0 : mt * 4 + jj] : 1.0f;
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -456,9 +488,8 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
         // results of every chain at a time (two registers of all lanes, or, in pairs, four of half
         // of them) go to LDS, and SH neighbouring lanes share a result: lane t of them adds the
         // chains SH q + t, in pairs, and their sums meet in the lanes.
-        constexpr int kRegs = B::kPair ? 4 : 2, kRounds = kTile / kRegs, NQ = W * C / SH;
+        constexpr int NQ = W * C / SH;
         float (*const red)[kRedStride] = reinterpret_cast<float (*)[kRedStride]>(lds);
-        const int share = (int)threadIdx.x % SH, result = (int)threadIdx.x / SH;
 #pragma unroll
         for (int round = 0; round < kRounds; ++round) {
             if (round > 0) __syncthreads();
@@ -481,10 +512,9 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
                     for (int q = 0; q < apart; ++q) v[q] += v[q + apart];
                 if (SH == 4) v[0] += dpp_f32<kDppXor2>(v[0]);
                 v[0] += dpp_f32<kDppXor1>(v[0]);
-                const int reg = kRegs * round + (B::kPair ? result >> 5 : result >> 6);
-                const int r = reg / (MT * 4);
-                const int m = 16 * ((reg >> 2) % MT) + 4 * ((result >> 4) & (B::kPair ? 1 : 3)) + (reg & 3);
-                if (share == 0) store(row0 + 16 * r + (result & 15), m, v[0] * token_scale(m));
+                const int reg = stored_reg(round), r = reg / (MT * 4);
+                if (share == 0)
+                    store(row0 + 16 * r + (result & 15), stored_token(reg), v[0] * (kTokenScale ? xsc[round] : 1.0f));
             }
         }
     }
