@@ -30,10 +30,9 @@ size_t round_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Workspace layout (offsets from a 256-byte aligned base).
 struct Workspace {
-    uint16_t *xt;       // [M][maxK]           transformed input (per-phase launches)
-    int8_t *xq;         // [M][maxK]           activation codes (per-phase launches)
-    float *xscale;      // [M][maxK/32]
-    int32_t *xgsum;     // [M][maxK/32]
+    // per-phase launches: the transformed input [M][maxK], or the codes [M][maxK], scales and code
+    // sums [M][maxK/32], of the one or two phases of a launch (the second: K of those that share one)
+    PrepTarget prep[kMaxMerge];
     StreamPhase *tab;   // [n]                 phase table of the streaming kernel
     uint32_t *flags;    // [kStreamMaxWg]      one word per workgroup
     uint32_t *status;   // [64]                word 0: a wait timed out
@@ -54,6 +53,7 @@ struct Workspace {
 // Sizes that depend on the layer list (upper bounds: every entry its own phase).
 struct ListSizes {
     int maxK;
+    int merged_K;        // largest K of phases that share a launch with another, or 0
     size_t image_bytes;  // activation images of the streaming kernel (M = 1)
     size_t group_units;  // 16-row tiles of all entries (M > 1)
     size_t group_quant;  // codes + scales + code sums of all W4A8 entries (M > 1)
@@ -80,7 +80,6 @@ Workspace carve(void *base, int M, int n, const ListSizes &ls) {
     const size_t image_bytes = ls.image_bytes;
     Workspace w;
     char *b = reinterpret_cast<char *>(base);
-    const size_t G = (size_t)maxK / 32;
     size_t off = 0;
     auto take = [&](size_t bytes) {
         char *p = b + off;
@@ -92,10 +91,13 @@ Workspace carve(void *base, int M, int n, const ListSizes &ls) {
     w.status = reinterpret_cast<uint32_t *>(take(256));
     take((size_t)(kFlagReplicas - 1) * kStreamMaxWg * 4);  // the other copies of the flags
     w.imgflags = reinterpret_cast<uint32_t *>(take((size_t)(n > 0 ? n : 1) * 4));
-    w.xt = reinterpret_cast<uint16_t *>(take(ls.transforms ? (size_t)M * maxK * 2 : 0));
-    w.xq = reinterpret_cast<int8_t *>(take((size_t)M * maxK));
-    w.xscale = reinterpret_cast<float *>(take((size_t)M * G * 4));
-    w.xgsum = reinterpret_cast<int32_t *>(take((size_t)M * G * 4));
+    for (int i = 0; i < kMaxMerge; ++i) {
+        const size_t K = (size_t)(i == 0 ? maxK : ls.merged_K);
+        w.prep[i].xt = reinterpret_cast<uint16_t *>(take(ls.transforms ? M * K * 2 : 0));
+        w.prep[i].xq = reinterpret_cast<int8_t *>(take(M * K));
+        w.prep[i].xscale = reinterpret_cast<float *>(take(M * (K / 32) * 4));
+        w.prep[i].xgsum = reinterpret_cast<int32_t *>(take(M * (K / 32) * 4));
+    }
     w.tab = reinterpret_cast<StreamPhase *>(take((size_t)(n > 0 ? n : 1) * sizeof(StreamPhase)));
     w.dummy = take(1024);
     w.images = take(image_bytes);
@@ -156,6 +158,7 @@ int check_layers(const nvq_linear *L, int n, int M, int act_group, ListSizes *si
         if (e.in_op == NVQ_IN_RMSNORM && e.x2_bf16 && e.h_out_bf16) mw += stream_mail_words(e.K);
     }
     sizes->maxK = mk;
+    sizes->merged_K = 0;
     sizes->image_bytes = ib;
     sizes->group_units = gu;
     sizes->group_quant = gq;
@@ -217,29 +220,6 @@ GemvSegs make_segs(const nvq_linear *L, const Phase &ph) {
     S.nseg = ph.count;
     S.total_rows = rows;
     return S;
-}
-
-// One launch (or two) per phase on the caller's stream.
-int walk_per_phase(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
-                   const Workspace &ws, hipStream_t st) {
-    for (size_t p = 0; p < phases.size(); ++p) {
-        const Phase &ph = phases[p];
-        const nvq_linear &e0 = L[ph.first];
-        const bool w4a8 = e0.precision == NVQ_W4A8;
-        const bool fresh = !(p > 0 && same_input(L, phases[p - 1], ph));
-        // what the previous phase prepared (transformed input or codes) still stands if it
-        // read the same input the same way
-        if (fresh) {
-            const int t = launch_prep(e0, M, act_group, w4a8, ws.xt, ws.xq, ws.xscale, ws.xgsum, st);
-            if (t != NVQ_OK) return t;
-        }
-        const uint16_t *x = e0.in_op != NVQ_IN_PLAIN ? ws.xt : e0.x_bf16;
-        const GemvSegs S = make_segs(L, ph);
-        const int g = w4a8 ? launch_gemv_w4a8(S, e0.K, ws.xq, ws.xscale, ws.xgsum, act_group, M, st)
-                           : launch_gemv_w4a16(S, e0.K, x, M, st);
-        if (g != NVQ_OK) return g;
-    }
-    return NVQ_OK;
 }
 
 struct Range {
@@ -307,6 +287,103 @@ bool phases_conflict(const nvq_linear *L, const Phase &a, const Phase &b, int M)
         for (const Range &x : ain)
             if (overlap(y, x)) return true;
     return false;
+}
+
+// Phases that are launched together.
+struct WalkStep {
+    int first, count;
+};
+
+// The steps of a walk in launches per phase.  Two phases that follow each other and do not depend
+// on each other share their launches (input and product) where the multi-token kernel takes both,
+// with the same K and precision: a launch costs 1.7 us before it does anything, and one phase's
+// workgroups alone leave compute units idle.  In a decode step whose attention runs elsewhere that
+// is q/k/v with o: 8192 x 3072 as one product and one input launch 10.7 us, as two each 18.9.
+// Dependent phases, and with `ordered` all, stay apart.
+std::vector<WalkStep> walk_steps(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
+                                 bool ordered) {
+    std::vector<WalkStep> out;
+    for (size_t p = 0; p < phases.size(); ++p) {
+        WalkStep s = {(int)p, 1};
+        if (!ordered && M > 1 && p + 1 < phases.size()) {
+            const nvq_linear &a = L[phases[p].first], &b = L[phases[p + 1].first];
+            if (a.K == b.K && a.precision == b.precision &&
+                gemv_slice_merges(make_segs(L, phases[p]), make_segs(L, phases[p + 1]), a.K, M, a.precision, act_group) &&
+                !phases_conflict(L, phases[p], phases[p + 1], M))
+                s.count = 2;
+        }
+        out.push_back(s);
+        p += (size_t)s.count - 1;
+    }
+    return out;
+}
+
+// Largest K of the steps of two phases, or 0.
+int merged_K(const nvq_linear *L, const std::vector<Phase> &phases, const std::vector<WalkStep> &steps) {
+    int k = 0;
+    for (const WalkStep &s : steps)
+        if (s.count > 1) k = std::max(k, L[phases[(size_t)s.first].first].K);
+    return k;
+}
+
+// Whether some product of phase p's codes (its own, or that of a phase behind it that reads the
+// same input) takes the code sums; the multi-token kernel does not.
+bool needs_code_sums(const nvq_linear *L, const std::vector<Phase> &phases, size_t p, int M, int act_group) {
+    for (size_t q = p; q < phases.size() && (q == p || same_input(L, phases[q - 1], phases[q])); ++q) {
+        const nvq_linear &e = L[phases[q].first];
+        if (!gemv_slice_takes(make_segs(L, phases[q]), e.K, M, e.precision, act_group)) return true;
+    }
+    return false;
+}
+
+// One launch (or two) per step on the caller's stream.
+int walk_per_phase(const nvq_linear *L, const std::vector<Phase> &phases, const std::vector<WalkStep> &steps, int M,
+                   int act_group, const Workspace &ws, hipStream_t st) {
+    int last_slot = 0;  // where the last phase's input was prepared
+    for (const WalkStep &s : steps) {
+        const nvq_linear &e0 = L[phases[(size_t)s.first].first];
+        const bool w4a8 = e0.precision == NVQ_W4A8;
+        GemvSegs S[kMaxMerge];
+        const nvq_linear *fresh[kMaxMerge];
+        PrepTarget target[kMaxMerge];
+        int slot[kMaxMerge], nfresh = 0;
+        for (int i = 0; i < s.count; ++i) {
+            const size_t p = (size_t)(s.first + i);
+            S[i] = make_segs(L, phases[p]);
+            // what the previous phase prepared (transformed input or codes) still stands if it read
+            // the same input the same way
+            slot[i] = last_slot;
+            if (p == 0 || !same_input(L, phases[p - 1], phases[p])) {
+                slot[i] = i == 0 ? 0 : 1 - slot[0];
+                target[nfresh] = ws.prep[slot[i]];
+                if (!needs_code_sums(L, phases, p, M, act_group)) target[nfresh].xgsum = nullptr;
+                fresh[nfresh++] = &L[phases[p].first];
+            }
+            last_slot = slot[i];
+        }
+        if (nfresh > 0) {
+            const int t = launch_prep(fresh, target, nfresh, M, act_group, w4a8, st);
+            if (t != NVQ_OK) return t;
+        }
+        SliceWork w = {};
+        w.n = s.count;
+        for (int i = 0; i < s.count; ++i) {
+            const nvq_linear &e = L[phases[(size_t)(s.first + i)].first];
+            const PrepTarget &in = ws.prep[slot[i]];
+            w.segs[i] = &S[i];
+            w.x[i] = w4a8 ? (const void *)in.xq : e.in_op != NVQ_IN_PLAIN ? in.xt : e.x_bf16;
+            w.xscale[i] = in.xscale;
+        }
+        const PrepTarget &in = ws.prep[slot[0]];
+        int g;
+        if (s.count > 1)
+            g = w4a8 ? launch_gemv_slice_w4a8(w, e0.K, act_group, M, st) : launch_gemv_slice_w4a16(w, e0.K, M, st);
+        else
+            g = w4a8 ? launch_gemv_w4a8(S[0], e0.K, in.xq, in.xscale, in.xgsum, act_group, M, st)
+                     : launch_gemv_w4a16(S[0], e0.K, static_cast<const uint16_t *>(w.x[0]), M, st);
+        if (g != NVQ_OK) return g;
+    }
+    return NVQ_OK;
 }
 
 void schedule_phases(const nvq_linear *L, std::vector<Phase> *phases, int M, bool ordered) {
@@ -846,6 +923,7 @@ constexpr int kDescribeWords = 16;  // words per phase written by nvq_plan_descr
 struct nvq_plan {
     std::vector<nvq_linear> layers;
     std::vector<nvq::Phase> phases;
+    std::vector<nvq::WalkStep> steps;  // of launches per phase
     nvq::Workspace ws;
     int M, act_group;
     int nwg;           // workgroups of the streaming kernel, 0 = per-phase launches
@@ -868,6 +946,8 @@ extern "C" size_t nvq_decode_workspace_bytes(const nvq_linear *layers, int n, in
                                              int act_group) {
     nvq::ListSizes ls;
     if (nvq::check_layers(layers, n, M, act_group, &ls) != NVQ_OK) return 0;
+    const std::vector<nvq::Phase> phases = nvq::group_phases(layers, n);
+    ls.merged_K = nvq::merged_K(layers, phases, nvq::walk_steps(layers, phases, M, act_group, false));
     return nvq::carve(nullptr, M, n, ls).bytes;
 }
 
@@ -881,6 +961,10 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
     const int rc = check_layers(layers, n, M, act_group, &ls);
     if (rc != NVQ_OK) return rc;
     if (!workspace || !aligned(workspace, 256)) return NVQ_ERR_WORKSPACE;
+    {
+        const std::vector<Phase> listed = group_phases(layers, n);
+        ls.merged_K = merged_K(layers, listed, walk_steps(layers, listed, M, act_group, false));
+    }
     const Workspace ws = carve(workspace, M, n, ls);
     if (workspace_bytes < ws.bytes) return NVQ_ERR_WORKSPACE;
     nvq_plan *pl = new (std::nothrow) nvq_plan();
@@ -892,6 +976,7 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
         delete pl;
         return NVQ_ERR_INVALID_ARG;
     }
+    pl->steps = walk_steps(pl->layers.data(), pl->phases, M, act_group, (flags & NVQ_PLAN_ORDERED) != 0);
     pl->ws = ws;
     pl->M = M;
     pl->act_group = act_group;
@@ -1034,9 +1119,10 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
                     rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, nullptr, st);
                     for (int p = b.phase_first; rc == NVQ_OK && p < b.phase_first + b.nphases; ++p) {
                         const GroupPhase &g = pl->group_phases[(size_t)p];
-                        rc = g.precision == NVQ_W4A8
-                                 ? launch_gemv_slice_w4a8(g.segs, g.G * 32, g.xq, g.xscale, 0, pl->M, st)
-                                 : launch_gemv_slice_w4a16(g.segs, g.G * 32, g.x_bf16, pl->M, st);
+                        const bool w4a8 = g.precision == NVQ_W4A8;
+                        const SliceWork w = {1, {&g.segs}, {w4a8 ? (const void *)g.xq : g.x_bf16}, {g.xscale}};
+                        rc = w4a8 ? launch_gemv_slice_w4a8(w, g.G * 32, 0, pl->M, st)
+                                  : launch_gemv_slice_w4a16(w, g.G * 32, pl->M, st);
                     }
                     break;
             }
@@ -1044,7 +1130,7 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
         }
         return NVQ_OK;
     }
-    return walk_per_phase(pl->layers.data(), pl->phases, pl->M, pl->act_group, pl->ws, st);
+    return walk_per_phase(pl->layers.data(), pl->phases, pl->steps, pl->M, pl->act_group, pl->ws, st);
 }
 
 extern "C" int nvq_plan_info(const nvq_plan *pl, int *streaming, int *phases, int *waits) {
@@ -1257,23 +1343,31 @@ extern "C" int nvq_decode_linears_static(const nvq_linear *layers, int n, int M,
     if (n == 0) return NVQ_OK;
     const std::vector<Phase> phases = group_phases(layers, n);
     if (check_phase_hazards(layers, phases, M) != NVQ_OK) return NVQ_ERR_INVALID_ARG;
-    // the part of the workspace that launches per phase use
-    const size_t G = (size_t)ls.maxK / 32;
-    const size_t xt_bytes = round_up(ls.transforms ? (size_t)M * ls.maxK * 2 : 0, 256);
-    const size_t xq_bytes = round_up((size_t)M * ls.maxK, 256);
-    const size_t gs_bytes = round_up((size_t)M * G * 4, 256);
-    if (xt_bytes + xq_bytes + 2 * gs_bytes > (size_t)NVQ_STATIC_SCRATCH_BYTES)
-        return NVQ_ERR_WORKSPACE;
+    // the part of the workspace that launches per phase use; phases share launches if there is room
+    // for both inputs
+    std::vector<WalkStep> steps = walk_steps(layers, phases, M, act_group, false);
+    const int slot_K[kMaxMerge] = {ls.maxK, merged_K(layers, phases, steps)};
+    Workspace ws = {};
+    size_t off[kMaxMerge][4], bytes = 0;
+    for (int i = 0; i < kMaxMerge; ++i) {
+        const size_t K = (size_t)slot_K[i], part[4] = {ls.transforms ? M * K * 2 : 0, M * K, M * (K / 32) * 4,
+                                                       M * (K / 32) * 4};
+        for (int k = 0; k < 4; ++k) {
+            off[i][k] = bytes;
+            bytes += round_up(part[k], 256);
+        }
+        if (bytes <= (size_t)NVQ_STATIC_SCRATCH_BYTES) continue;
+        if (i == 0) return NVQ_ERR_WORKSPACE;
+        steps = walk_steps(layers, phases, M, act_group, true);
+    }
     void *base = nullptr;
     const int sc = scratch_for_current_device(&base);
     if (sc != NVQ_OK) return sc;
-    Workspace ws = {};
     char *b = static_cast<char *>(base);
-    ws.xt = reinterpret_cast<uint16_t *>(b);
-    ws.xq = reinterpret_cast<int8_t *>(b + xt_bytes);
-    ws.xscale = reinterpret_cast<float *>(b + xt_bytes + xq_bytes);
-    ws.xgsum = reinterpret_cast<int32_t *>(b + xt_bytes + xq_bytes + gs_bytes);
+    for (int i = 0; i < kMaxMerge; ++i)
+        ws.prep[i] = PrepTarget{reinterpret_cast<uint16_t *>(b + off[i][0]), reinterpret_cast<int8_t *>(b + off[i][1]),
+                                reinterpret_cast<float *>(b + off[i][2]), reinterpret_cast<int32_t *>(b + off[i][3])};
     // every phase writes what it reads from the scratch before reading it
     // (transform, quantisation), so nothing has to be cleared between calls
-    return walk_per_phase(layers, phases, M, act_group, ws, (hipStream_t)stream);
+    return walk_per_phase(layers, phases, steps, M, act_group, ws, (hipStream_t)stream);
 }

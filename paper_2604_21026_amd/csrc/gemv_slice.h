@@ -117,9 +117,72 @@ struct SliceBlock {
                   "activation scales");
 };
 
-template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, bool DEBUG>
-__global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, int M, const char *__restrict__ xin,
-                                                            const float *__restrict__ xscale) {
+// A phase of a launch.  Arguments cost time twice: the host writes them into device memory (a call
+// with 512 bytes of them takes 0.5 us longer than with 224), and they are cold memory in every
+// launch.  So they are few, there are two phases only where a launch has two, and the kernel asks
+// for all lines of a phase together (one after the other, where they are needed, the last of
+// them, where the results go, was waited for when everything else was done; W4A16, 4096 x 4096 at 8
+// tokens: 5.1 us against 4.5).
+template <bool DEBUG>
+struct SlicePhase {
+    const uint4 *qw[kMaxSeg];
+    const uint16_t *sc[kMaxSeg];
+    void *y[kMaxSeg];
+    int row_end[kMaxSeg];  // of matrices that are not there: as the last one's
+    const char *x;
+    const float *xscale;
+    int G, M;
+    int units;       // workgroups
+    uint32_t bf16;   // bit i: matrix i has bf16 results
+    int32_t *dbg[DEBUG ? kMaxSeg : 1];
+};
+template <int NP, bool DEBUG>
+struct SliceArgs {
+    SlicePhase<DEBUG> phase[NP];  // the first phase's workgroups come first
+};
+static_assert(sizeof(SlicePhase<false>) == 152 && kMaxMerge == 2, "three lines; one comparison finds a workgroup's phase");
+
+// A row of a phase (past the last one: the last one again, not valid).  Selected, not indexed, as in
+// locate_row.
+struct SliceRow {
+    const uint4 *qw;
+    const uint16_t *sc;
+    void *y;
+    int32_t *dbg;
+    int N, n;
+    bool bf16, valid;
+};
+template <bool DEBUG, class PHASE>
+__device__ __forceinline__ SliceRow slice_row(PHASE &P, int row, int G) {
+    SliceRow r;
+    r.valid = row < P.row_end[kMaxSeg - 1];
+    if (!r.valid) row = P.row_end[kMaxSeg - 1] - 1;
+    int first = 0, end = P.row_end[0];
+    r.qw = P.qw[0];
+    r.sc = P.sc[0];
+    r.y = P.y[0];
+    r.dbg = P.dbg[0];
+    r.bf16 = (P.bf16 & 1u) != 0;
+#pragma unroll
+    for (int i = 1; i < kMaxSeg; ++i)
+        if (row >= P.row_end[i - 1]) {
+            first = P.row_end[i - 1];
+            end = P.row_end[i];
+            r.qw = P.qw[i];
+            r.sc = P.sc[i];
+            r.y = P.y[i];
+            if (DEBUG) r.dbg = P.dbg[DEBUG ? i : 0];
+            r.bf16 = (P.bf16 >> i & 1u) != 0;
+        }
+    r.N = end - first;
+    r.n = row - first;
+    r.qw += (int64_t)r.n * G;
+    r.sc += (int64_t)r.n * G;
+    return r;
+}
+
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, bool DEBUG>
+__global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>) {
     typedef Act<PREC> A;
     typedef SliceBlock<PREC, PG, TOK, RT, NG, SCB> B;
     constexpr bool TAIL = SCB != 16;
@@ -137,20 +200,30 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     constexpr int kRed = kByGroup ? W * C * kRedStride * 4 : V * kTile * 256;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing > kRed ? kRing : kRed];
 
-    // The arguments are cold memory in every launch, four lines of it: all of them at once, or what
-    // is needed last (where the results go) is waited for when everything else is done (W4A16: 4096
-    // x 4096 at 8 tokens 5.1 -> 4.5 us; the W4A8 instances ask for the last line early anyway).
-    if (PREC == NVQ_W4A16) {
-        typedef const __attribute__((address_space(4))) uint32_t *Words;
-        const Words a = (Words)__builtin_amdgcn_kernarg_segment_ptr();
-        static_assert(sizeof(GemvSegs) > 160 && sizeof(GemvSegs) + 24 <= 256, "four lines of 64 bytes");
-        const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[48];
+    typedef const __attribute__((address_space(4))) SlicePhase<DEBUG> CPhase;
+    typedef const __attribute__((address_space(4))) uint32_t CWord;
+    // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch)
+    CPhase *phase = (CPhase *)__builtin_amdgcn_kernarg_segment_ptr();
+    auto all_lines = [&] {
+        CWord *a = (CWord *)phase;
+        const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[sizeof(SlicePhase<DEBUG>) / 4 - 1];
         asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3));
+    };
+    all_lines();
+    int unit = (int)blockIdx.x;
+    if (NP > 1 && unit >= phase->units) {
+        unit -= phase->units;
+        ++phase;
+        all_lines();
     }
+    CPhase &S = *phase;
+    const int G = phase->G, M = phase->M;
+    const char *const xin = phase->x;
+    const float *const xscale = phase->xscale;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 15, kb = lane >> 4;
-    const int row0 = (int)blockIdx.x * (16 * RT);
+    const int row0 = unit * (16 * RT);
     const int NB = (G + NG - 1) / NG;
     const int nblk = NB > w ? (NB - w + W - 1) / W : 0;
     unsigned char *const slot = lds + w * B::kBytes;
@@ -164,7 +237,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     for (int j = 0; j < 2; ++j) wc[j] = (lane % NG) ^ (((kWRows * j + lane / NG) / (16 / NG)) % NG);
 #pragma unroll
     for (int j = 0; j < B::kWOps; ++j)
-        wsrc[j] = reinterpret_cast<const char *>(locate_row(S, row0 + kWRows * j + lane / NG, G).qw) +
+        wsrc[j] = reinterpret_cast<const char *>(slice_row<DEBUG>(S, row0 + kWRows * j + lane / NG, G).qw) +
                   (TAIL ? 0 : 16 * wc[j & 1]);
     constexpr int kRows = 16 * RT;
     int sg[B::kScOps];  // first group of the lane's word
@@ -172,7 +245,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     for (int k = 0; k < B::kScOps; ++k) {
         const int word = k * 64 + lane;
         sg[k] = SCB == 16 ? 0 : (word / kRows * (SCB / 2)) % NG;
-        ssrc[k] = reinterpret_cast<const char *>(locate_row(S, row0 + word % kRows, G).sc);
+        ssrc[k] = reinterpret_cast<const char *>(slice_row<DEBUG>(S, row0 + word % kRows, G).sc);
     }
     // activations: 2 or 4 tokens per instruction, pieces permuted against each other
     constexpr int kPieces = B::kPieces;
@@ -371,7 +444,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
             }
         };
         auto dump = [&](const typename A::offset_t &raw, int i, int r, int mt) {
-            const RowRef o = locate_row(S, row0 + 16 * r + n, G);
+            const SliceRow o = slice_row<DEBUG>(S, row0 + 16 * r + n, G);
             if (!o.valid || !o.dbg || g0 + i >= G) return;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
@@ -450,8 +523,8 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
 #undef NVQ_RD128
 
     auto store = [&](int row, int m, float sum) {
-        const RowRef o = locate_row(S, row, G);
-        if (o.valid && m < M) store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, sum);
+        const SliceRow o = slice_row<DEBUG>(S, row, G);
+        if (o.valid && m < M) store_global(o.y, o.bf16 ? NVQ_BF16 : NVQ_F32, (int64_t)m * o.N + o.n, sum);
     };
     __syncthreads();  // the blocks' LDS is free
     if constexpr (!kByGroup) {
@@ -520,13 +593,41 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(GemvSegs S, int G, i
     }
 }
 
-template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, bool DEBUG = false>
-int slice_go(const GemvSegs &S, int G, int M, const void *x, const float *xscale, hipStream_t st) {
-    const int units = (S.total_rows + 16 * RT - 1) / (16 * RT);
-    hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, W, NG, V, SCB, DEBUG>), dim3(units), dim3(W * 64), 0, st,
-                       S, G, M, reinterpret_cast<const char *>(x), xscale);
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, bool DEBUG>
+int slice_launch(const SliceWork &w, int G, int M, hipStream_t st) {
+    SliceArgs<NP, DEBUG> a = {};
+    int units = 0;
+    for (int i = 0; i < NP; ++i) {
+        SlicePhase<DEBUG> &p = a.phase[i];
+        const GemvSegs &S = *w.segs[i];
+        for (int k = 0; k < kMaxSeg; ++k) {
+            const bool there = k < S.nseg;
+            p.row_end[k] = there ? S.row_end[k] : S.total_rows;
+            if (!there) continue;
+            p.qw[k] = S.qw[k];
+            p.sc[k] = S.sc[k];
+            p.y[k] = S.y[k];
+            if (S.y_dtype[k] == NVQ_BF16) p.bf16 |= 1u << k;
+            if (DEBUG) p.dbg[DEBUG ? k : 0] = S.dbg[k];
+        }
+        p.x = reinterpret_cast<const char *>(w.x[i]);
+        p.xscale = w.xscale[i];
+        p.G = G;
+        p.M = M;
+        p.units = (S.total_rows + 16 * RT - 1) / (16 * RT);
+        units += p.units;
+    }
+    hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, W, NG, V, SCB, NP, DEBUG>), dim3(units), dim3(W * 64), 0,
+                       st, a);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
+}
+
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, bool DEBUG = false>
+int slice_go(const SliceWork &w, int G, int M, hipStream_t st) {
+    if constexpr (!DEBUG)  // (the walk asks for no accumulators)
+        if (w.n == 2) return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 2, false>(w, G, M, st);
+    return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 1, DEBUG>(w, G, M, st);
 }
 
 // Whether a phase has more than two row tiles per compute unit.
@@ -556,14 +657,21 @@ inline bool slice_shared(int rows) { return (rows + 15) / 16 > device_cu_count()
 // 12288 x 3072 7.6 against 7.1), and at 17 tokens and more (3072 x 3072: 5.7 against 6.7).
 inline bool slice_eight_waves(int rows, int tokens) { return tokens > 16 || !slice_shared(rows); }
 
-// The scale loads a phase allows (see SCB).
-inline int slice_scale_bytes(const GemvSegs &S, int G) {
+// The scale loads the phases of a launch allow (see SCB).
+inline int slice_scale_bytes(const SliceWork &w, int G) {
     int b = (G & 7) == 0 ? 16 : (G & 1) == 0 ? 4 : 2;
-    for (int i = 0; i < S.nseg; ++i) {
-        if (b == 16 && !aligned(S.sc[i], 16)) b = 4;
-        if (b == 4 && !aligned(S.sc[i], 4)) b = 2;
-    }
+    for (int k = 0; k < w.n; ++k)
+        for (int i = 0; i < w.segs[k]->nseg; ++i) {
+            if (b == 16 && !aligned(w.segs[k]->sc[i], 16)) b = 4;
+            if (b == 4 && !aligned(w.segs[k]->sc[i], 4)) b = 2;
+        }
     return b;
+}
+
+inline int slice_rows(const SliceWork &w) {
+    int rows = 0;
+    for (int i = 0; i < w.n; ++i) rows += w.segs[i]->total_rows;
+    return rows;
 }
 
 }  // namespace

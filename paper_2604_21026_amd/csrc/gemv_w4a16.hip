@@ -204,7 +204,7 @@ int launch_gemv_w4a16(const GemvSegs &S, int K, const uint16_t *x, int M, hipStr
             default: return launch_m1<8, 64>(S, G, x, st);
         }
     }
-    if (!gemv_wave_per_row(S, K, M, NVQ_W4A16, false)) return launch_gemv_slice_w4a16(S, K, x, M, st);
+    if (gemv_slice_takes(S, K, M, NVQ_W4A16, 0)) return launch_gemv_slice_w4a16(SliceWork{1, {&S}, {x}, {}}, K, M, st);
     const dim3 grid(gemv_grid(S.total_rows, 4, 8)), block(256);
     hipLaunchKernelGGL(gemv_w4a16_row_kernel<4>, grid, block, 0, st, S, G, M, reinterpret_cast<const uint4 *>(x));
     NVQ_HIP_TRY(hipGetLastError());

@@ -198,7 +198,8 @@ int launch_gemv_w4a8(const GemvSegs &S, int K, const int8_t *xq, const float *xs
             default: return launch_m1<8, 64>(S, G, xq, xscale, xgsum, pg, debug, st);
         }
     }
-    if (!gemv_wave_per_row(S, K, M, NVQ_W4A8, pg)) return launch_gemv_slice_w4a8(S, K, xq, xscale, act_group, M, st);
+    if (gemv_slice_takes(S, K, M, NVQ_W4A8, act_group))
+        return launch_gemv_slice_w4a8(SliceWork{1, {&S}, {xq}, {xscale}}, K, act_group, M, st);
     const dim3 grid(gemv_grid(S.total_rows, 4, 8)), block(256);
     const uint4 *x4 = reinterpret_cast<const uint4 *>(xq);
 #define NVQ_GO(PG, DBG)                                                                      \

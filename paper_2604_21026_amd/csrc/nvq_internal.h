@@ -45,18 +45,37 @@ struct GemvSegs {
 // Internal launchers (validated arguments; enqueue only).
 int launch_quant_act(const uint16_t *x, int M, int K, int act_group, int8_t *xq, float *xscale,
                      int32_t *xgsum, hipStream_t st);
-// The input of layer e for M tokens: its transform (if any) and, with `quant`, its codes,
-// scales and code sums; without it the transformed values go to xt (plain input: nothing).
-// xt is scratch either way.
-int launch_prep(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
-                float *xscale, int32_t *xgsum, hipStream_t st);
+// The inputs of n <= kMaxMerge layers with the same K, for M tokens, in one launch where K allows:
+// a layer's transform (if any) and, with `quant`, its codes, scales and (unless xgsum is null) code
+// sums; without it the transformed values go to xt (plain input: nothing).  xt is scratch either
+// way.
+constexpr int kMaxMerge = 2;
+struct PrepTarget {
+    uint16_t *xt;
+    int8_t *xq;
+    float *xscale;
+    int32_t *xgsum;
+};
+int launch_prep(const nvq_linear *const *e, const PrepTarget *to, int n, int M, int act_group, bool quant,
+                hipStream_t st);
 int launch_gemv_w4a8(const GemvSegs &segs, int K, const int8_t *xq, const float *xscale,
                      const int32_t *xgsum, int act_group, int M, hipStream_t st);
 int launch_gemv_w4a16(const GemvSegs &segs, int K, const uint16_t *x, int M, hipStream_t st);
-// Up to 32 tokens, any K that is a whole number of groups (gemv_slice.h).
-int launch_gemv_slice_w4a16(const GemvSegs &segs, int K, const uint16_t *x, int M, hipStream_t st);
-int launch_gemv_slice_w4a8(const GemvSegs &segs, int K, const int8_t *xq, const float *xscale,
-                           int act_group, int M, hipStream_t st);
+// Up to 32 tokens, any K that is a whole number of groups (gemv_slice.h).  One launch takes up to
+// kMaxMerge phases of the same K that do not depend on each other, each with its own input, if
+// gemv_slice_merges says so.
+struct SliceWork {
+    int n;
+    const GemvSegs *segs[kMaxMerge];
+    const void *x[kMaxMerge];          // codes or bf16
+    const float *xscale[kMaxMerge];    // W4A8
+};
+// Whether the multi-token kernel takes a phase (of the walk or a single call), and whether it takes
+// two of them in one launch with every result added as in a launch of its own.
+bool gemv_slice_takes(const GemvSegs &segs, int K, int M, int precision, int act_group);
+bool gemv_slice_merges(const GemvSegs &a, const GemvSegs &b, int K, int M, int precision, int act_group);
+int launch_gemv_slice_w4a16(const SliceWork &w, int K, int M, hipStream_t st);
+int launch_gemv_slice_w4a8(const SliceWork &w, int K, int act_group, int M, hipStream_t st);
 // Whether the grouped matrix-core launches take a phase: 2 <= M <= 32 tokens, per-token
 // activation scale, K a multiple of 128, scale rows 8-byte aligned.
 bool gemv_mfma_supported(const GemvSegs &segs, int K, int M);

@@ -9,6 +9,7 @@
 // and reduce its code sum (and, for per-group scales, its absmax) with two
 // cross-lane exchanges.  Pass 1 finds the token's absmax, pass 2 re-reads the
 // (cache-resident) row and quantises.
+#include "mfma_act.h"
 #include "transform.h"
 
 namespace nvq {
@@ -163,8 +164,8 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
 // scale.  By the trace 3.9 us for norm and quantisation of 8 x 4096 and 4.5 for SiLU and
 // quantisation of 8 x 14336 (4.3 and 6.2 with two trips, exchanges through LDS and a division
 // per value).
-// OP: nvq_linear.in_op; Q: 0 = the transformed bf16 values (xt), 1 = codes with a scale
-// per token, 2 = codes with a scale per group.
+// Q: 0 = the transformed bf16 values (xt), 1 = codes with a scale per token, 2 = codes with a
+// scale per group.
 constexpr int kPrepMaxK = 16384, kPrepThreads = 1024;
 
 // Maximum over the workgroup; red: sixteen words (waves that are not there count as zero).
@@ -207,35 +208,62 @@ __device__ __forceinline__ float chunk_sums_in_norm_order(const float (&part)[N]
     return ss;
 }
 
-template <int OP, int Q, int NCH>
-__global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
-    const uint4 *__restrict__ x, const uint4 *__restrict__ x2, const uint4 *__restrict__ gamma,
-    float eps, int K, uint4 *__restrict__ xt, uint4 *__restrict__ h_out, int8_t *__restrict__ xq,
-    float *__restrict__ xscale, int32_t *__restrict__ xgsum) {
-    __shared__ float red[2][16];
-    __shared__ float part[OP == NVQ_IN_RMSNORM ? kPrepThreads * NCH : 1];
-    const int m = blockIdx.x, chunks = K / 8, G = K / 32;
+struct PrepJob {
+    const void *x, *x2, *gamma;
+    void *xt, *h_out;
+    int8_t *xq;
+    float *xscale;
+    int32_t *xgsum;  // null: no code sums
+    float eps;
+    int op;  // nvq_linear.in_op
+};
+template <int NP>
+struct PrepArgs {
+    int K, M;
+    PrepJob job[NP];  // workgroups 0 .. M - 1 the first
+};
+
+// (the pointers come out of memory: see as_global)
+__device__ __forceinline__ uint4 load16(const void *p, int64_t i) {
+    const uint4v v = as_global<uint4v>(p)[i];
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ void store16(void *p, int64_t i, const uint4 &v) {
+    const uint4v o = {v.x, v.y, v.z, v.w};
+    ((__attribute__((address_space(1))) uint4v *)p)[i] = o;
+}
+template <typename T>
+__device__ __forceinline__ void store_word(void *p, int64_t i, T v) {
+    ((__attribute__((address_space(1))) T *)p)[i] = v;
+}
+
+// Token m of a job.
+template <int OP, int Q, int NCH, class JOB>
+__device__ __forceinline__ void prep_token(const JOB &J, int K, int m, float (&red)[2][16],
+                                           float (&part)[kPrepThreads * NCH]) {
+    const int chunks = K / 8, G = K / 32;
     const int64_t row = (int64_t)m * chunks;
+    const void *const x2 = J.x2, *const h_out = J.h_out;
     uint4 v[NCH], gm[NCH];
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
         const int c = (int)threadIdx.x + i * (int)blockDim.x;
         v[i] = make_uint4(0u, 0u, 0u, 0u);
         if (c < chunks) {
-            v[i] = x[row + c];
-            if (OP == NVQ_IN_RMSNORM) gm[i] = gamma[c];  // (asked for here: one trip to memory less)
+            v[i] = load16(J.x, row + c);
             if (OP == NVQ_IN_RMSNORM) {
-                if (x2) v[i] = add_bf16x8(v[i], x2[row + c]);
-                if (h_out) h_out[row + c] = v[i];
+                gm[i] = load16(J.gamma, c);  // (asked for here: one trip to memory less)
+                if (x2) v[i] = add_bf16x8(v[i], load16(x2, row + c));
+                if (h_out) store16(J.h_out, row + c, v[i]);
                 part[c] = sumsq_bf16x8(v[i]);
             } else if (OP == NVQ_IN_SILU_MUL) {
-                v[i] = silu_mul_bf16x8(v[i], x2[row + c]);
+                v[i] = silu_mul_bf16x8(v[i], load16(x2, row + c));
             }
         }
     }
     if constexpr (OP == NVQ_IN_RMSNORM) {
         __syncthreads();
-        const float r = rms_scale(chunk_sums_in_norm_order(part, chunks, red[0]), K, eps);
+        const float r = rms_scale(chunk_sums_in_norm_order(part, chunks, red[0]), K, J.eps);
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const int c = (int)threadIdx.x + i * (int)blockDim.x;
@@ -246,7 +274,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
 #pragma unroll
         for (int i = 0; i < NCH; ++i) {
             const int c = (int)threadIdx.x + i * (int)blockDim.x;
-            if (c < chunks) xt[row + c] = v[i];
+            if (c < chunks) store16(J.xt, row + c, v[i]);
         }
         return;
     }
@@ -256,7 +284,7 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
 #pragma unroll
         for (int i = 0; i < NCH; ++i) a = fmaxf(a, chunk_absmax(v[i]));
         s = block_max(a, red[1]) / 127.0f;
-        if (threadIdx.x == 0) xscale[m] = s;
+        if (threadIdx.x == 0) store_word(J.xscale, m, s);
     }
     // four neighbouring lanes hold a group: chunks and blockDim.x are multiples of four
 #pragma unroll
@@ -265,11 +293,33 @@ __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(
         if (c >= chunks) continue;
         if (Q == 2) {
             s = over_group(chunk_absmax(v[i]), MaxOp()) / 127.0f;
-            if ((c & 3) == 0) xscale[(int64_t)m * G + (c >> 2)] = s;
+            if ((c & 3) == 0) store_word(J.xscale, (int64_t)m * G + (c >> 2), s);
         }
-        quant_chunk(v[i], s, c, reinterpret_cast<uint2 *>(xq + (int64_t)m * K),
-                    xgsum ? xgsum + (int64_t)m * G : nullptr);
+        int sum;
+        const uint2 q = quant8(v[i], s, &sum);
+        store_word(J.xq, row + c, (uint64_t)q.x | ((uint64_t)q.y << 32));
+        if (J.xgsum) {
+            sum = over_group(sum, AddOp());
+            if ((c & 3) == 0) store_word(J.xgsum, (int64_t)m * G + (c >> 2), sum);
+        }
     }
+}
+
+template <int Q, int NCH, int NP>
+__global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(PrepArgs<NP>) {
+    __shared__ float red[2][16];
+    __shared__ float part[kPrepThreads * NCH];
+    // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch)
+    const __attribute__((address_space(4))) PrepArgs<NP> &A =
+        *(const __attribute__((address_space(4))) PrepArgs<NP> *)__builtin_amdgcn_kernarg_segment_ptr();
+    const int second = NP > 1 && (int)blockIdx.x >= A.M ? 1 : 0, m = (int)blockIdx.x - (second ? A.M : 0);
+    const __attribute__((address_space(4))) PrepJob &J = A.job[second];
+    if (J.op == NVQ_IN_RMSNORM)
+        prep_token<NVQ_IN_RMSNORM, Q, NCH>(J, A.K, m, red, part);
+    else if (J.op == NVQ_IN_SILU_MUL)
+        prep_token<NVQ_IN_SILU_MUL, Q, NCH>(J, A.K, m, red, part);
+    else
+        prep_token<NVQ_IN_PLAIN, Q, NCH>(J, A.K, m, red, part);
 }
 
 template <bool PER_GROUP>
@@ -386,13 +436,41 @@ int launch_quant_act_group(const GroupPhase *tab, const uint16_t *jobs, int njob
     return NVQ_OK;
 }
 
+namespace {
+
+template <int Q, int NP>
+int prep_go(const PrepArgs<kMaxMerge> &all, hipStream_t st) {
+    PrepArgs<NP> a;
+    a.K = all.K;
+    a.M = all.M;
+    for (int i = 0; i < NP; ++i) a.job[i] = all.job[i];
+    const int chunks = a.K / 8;
+    const int nch = chunks <= kPrepThreads ? 1 : 2, per = (chunks + nch - 1) / nch;
+    const dim3 grid(NP * a.M), block((per + 63) / 64 * 64);
+    if (nch == 1)
+        hipLaunchKernelGGL((prep_token_kernel<Q, 1, NP>), grid, block, 0, st, a);
+    else
+        hipLaunchKernelGGL((prep_token_kernel<Q, 2, NP>), grid, block, 0, st, a);
+    NVQ_HIP_TRY(hipGetLastError());
+    return NVQ_OK;
+}
+
+template <int Q>
+int prep_jobs(const PrepArgs<kMaxMerge> &a, int jobs, hipStream_t st) {
+    return jobs == 2 ? prep_go<Q, 2>(a, st) : prep_go<Q, 1>(a, st);
+}
+
+}  // namespace
+
 int launch_quant_act(const uint16_t *x, int M, int K, int act_group, int8_t *xq, float *xscale,
                      int32_t *xgsum, hipStream_t st) {
     if (K <= kPrepMaxK) {
         nvq_linear e = {};
         e.x_bf16 = x;
         e.K = K;
-        return launch_prep(e, M, act_group, true, nullptr, xq, xscale, xgsum, st);
+        const nvq_linear *const layer = &e;
+        const PrepTarget to = {nullptr, xq, xscale, xgsum};
+        return launch_prep(&layer, &to, 1, M, act_group, true, st);
     }
     if (act_group == 0)
         hipLaunchKernelGGL(quant_act_kernel<false>, dim3(M), dim3(kQuantThreads), 0, st,
@@ -404,61 +482,53 @@ int launch_quant_act(const uint16_t *x, int M, int K, int act_group, int8_t *xq,
     return NVQ_OK;
 }
 
-namespace {
-
-template <int OP, int Q>
-int prep_go(const nvq_linear &e, int M, uint16_t *xt, int8_t *xq, float *xscale, int32_t *xgsum,
-            hipStream_t st) {
-    const int chunks = e.K / 8;
-    const int nch = chunks <= kPrepThreads ? 1 : 2, per = (chunks + nch - 1) / nch;
-    const dim3 grid(M), block((per + 63) / 64 * 64);
-    const uint4 *x = reinterpret_cast<const uint4 *>(e.x_bf16), *x2 = reinterpret_cast<const uint4 *>(e.x2_bf16);
-    const uint4 *gamma = reinterpret_cast<const uint4 *>(e.gamma_bf16);
-    uint4 *out = reinterpret_cast<uint4 *>(xt), *h = reinterpret_cast<uint4 *>(e.h_out_bf16);
-    if (nch == 1)
-        hipLaunchKernelGGL((prep_token_kernel<OP, Q, 1>), grid, block, 0, st, x, x2, gamma, e.eps, e.K, out, h,
-                           xq, xscale, xgsum);
-    else
-        hipLaunchKernelGGL((prep_token_kernel<OP, Q, 2>), grid, block, 0, st, x, x2, gamma, e.eps, e.K, out, h,
-                           xq, xscale, xgsum);
-    NVQ_HIP_TRY(hipGetLastError());
-    return NVQ_OK;
+// A layer whose K is beyond what one pass takes: step by step.
+static int prep_long(const nvq_linear &e, const PrepTarget &to, int M, int act_group, bool quant, hipStream_t st) {
+    const uint16_t *x = e.x_bf16;
+    if (e.in_op != NVQ_IN_PLAIN) {
+        const int t = e.in_op == NVQ_IN_RMSNORM
+                          ? launch_rms_norm(e.x_bf16, e.x2_bf16, e.gamma_bf16, e.eps, M, e.K, to.xt,
+                                            e.h_out_bf16, st)
+                          : launch_silu_mul(e.x_bf16, e.x2_bf16, M, e.K, to.xt, st);
+        if (t != NVQ_OK) return t;
+        x = to.xt;
+    }
+    return quant ? launch_quant_act(x, M, e.K, act_group, to.xq, to.xscale, to.xgsum, st) : NVQ_OK;
 }
 
-template <int OP>
-int prep_quant(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
-               float *xscale, int32_t *xgsum, hipStream_t st) {
-    if constexpr (OP == NVQ_IN_RMSNORM)  // (the others have launches of their own for that)
-        if (!quant) return prep_go<OP, 0>(e, M, xt, xq, xscale, xgsum, st);
-    if (act_group == 0) return prep_go<OP, 1>(e, M, xt, xq, xscale, xgsum, st);
-    return prep_go<OP, 2>(e, M, xt, xq, xscale, xgsum, st);
-}
-
-}  // namespace
-
-int launch_prep(const nvq_linear &e, int M, int act_group, bool quant, uint16_t *xt, int8_t *xq,
-                float *xscale, int32_t *xgsum, hipStream_t st) {
-    if (e.K > kPrepMaxK) {  // step by step
-        const uint16_t *x = e.x_bf16;
-        if (e.in_op != NVQ_IN_PLAIN) {
-            const int t = e.in_op == NVQ_IN_RMSNORM
-                              ? launch_rms_norm(e.x_bf16, e.x2_bf16, e.gamma_bf16, e.eps, M, e.K, xt,
-                                                e.h_out_bf16, st)
-                              : launch_silu_mul(e.x_bf16, e.x2_bf16, M, e.K, xt, st);
+int launch_prep(const nvq_linear *const *e, const PrepTarget *to, int n, int M, int act_group, bool quant,
+                hipStream_t st) {
+    PrepArgs<kMaxMerge> a = {};
+    a.K = e[0]->K;
+    a.M = M;
+    int jobs = 0;
+    for (int i = 0; i < n; ++i) {
+        const nvq_linear &l = *e[i];
+        if (l.K > kPrepMaxK) {
+            const int t = prep_long(l, to[i], M, act_group, quant, st);
             if (t != NVQ_OK) return t;
-            x = xt;
+            continue;
         }
-        return quant ? launch_quant_act(x, M, e.K, act_group, xq, xscale, xgsum, st) : NVQ_OK;
+        if (!quant && l.in_op == NVQ_IN_PLAIN) continue;
+        PrepJob &j = a.job[jobs++];
+        j.x = l.x_bf16;
+        j.x2 = l.in_op == NVQ_IN_PLAIN ? nullptr : l.x2_bf16;
+        j.gamma = l.gamma_bf16;
+        j.xt = to[i].xt;
+        j.h_out = l.in_op == NVQ_IN_RMSNORM ? l.h_out_bf16 : nullptr;
+        j.xq = to[i].xq;
+        j.xscale = to[i].xscale;
+        j.xgsum = to[i].xgsum;
+        j.eps = l.eps;
+        j.op = l.in_op;
     }
-    if (e.in_op == NVQ_IN_RMSNORM)
-        return prep_quant<NVQ_IN_RMSNORM>(e, M, act_group, quant, xt, xq, xscale, xgsum, st);
-    if (e.in_op == NVQ_IN_SILU_MUL) {
-        // without the codes nothing spans a token: one workgroup per 256 chunks instead
-        if (!quant) return launch_silu_mul(e.x_bf16, e.x2_bf16, M, e.K, xt, st);
-        return prep_quant<NVQ_IN_SILU_MUL>(e, M, act_group, quant, xt, xq, xscale, xgsum, st);
-    }
-    if (!quant) return NVQ_OK;
-    return prep_quant<NVQ_IN_PLAIN>(e, M, act_group, quant, xt, xq, xscale, xgsum, st);
+    if (jobs == 0) return NVQ_OK;
+    // without the codes nothing of a SiLU spans a token: one workgroup per 256 chunks instead
+    if (!quant && jobs == 1 && a.job[0].op == NVQ_IN_SILU_MUL)
+        return launch_silu_mul(static_cast<const uint16_t *>(a.job[0].x), static_cast<const uint16_t *>(a.job[0].x2), M,
+                               a.K, static_cast<uint16_t *>(a.job[0].xt), st);
+    if (!quant) return prep_jobs<0>(a, jobs, st);
+    return act_group == 0 ? prep_jobs<1>(a, jobs, st) : prep_jobs<2>(a, jobs, st);
 }
 
 }  // namespace nvq

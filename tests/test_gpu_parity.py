@@ -1095,6 +1095,74 @@ def test_prepared_inputs_equal_the_standalone_calls(M, group, K):
     dl.close()
 
 
+# Two phases that follow each other and do not depend on each other share their launches.  q (two
+# matrices) and o: independent; o and r: r reads what o wrote; r and w: w overwrites what r read;
+# five matrices on one input (two phases, one preparation) and one more phase; another K.  Sizes:
+# chains by columns and by groups, one and two row tiles per workgroup, ragged rows and K.
+@pytest.mark.parametrize("M,group,K,N", [(2, 0, 256, 40), (3, 32, 96, 33), (8, 0, 4096, 512), (8, 32, 1056, 4100),
+                                         (17, 0, 512, 9000), (32, 32, 288, 70), (5, 0, 16416, 24)])
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+def test_phases_that_share_a_launch_equal_single_calls(M, group, K, N, prec):
+    say("shared launches", M, group, K, N, prec)
+    dev = lambda t: t.to(DEV)
+    a, b = dev(act(9900 + K, M, K)), dev(act(9910 + K, M, K))
+    gamma = dev((1.0 + 0.1 * torch.randn(K, generator=torch.Generator().manual_seed(K))).to(torch.bfloat16))
+    w = {}
+
+    def layer(name, rows, k=K):
+        _, q, sc = packed(9920 + len(w) + k, rows, k)
+        w[name] = to_dev_packed(q, sc)
+        return dict(qweight=w[name][0], scales=w[name][1], precision=prec)
+
+    def out(rows, dt=torch.float32):
+        return torch.zeros((M, rows), dtype=dt, device=DEV)
+
+    c, over = a.clone(), b.clone()
+    K2 = K + 32
+    d = dev(act(9930 + K, M, K2))
+    h = torch.zeros_like(a)
+    norm = dict(x=a, x2=b, in_op=nvq.IN_RMSNORM, gamma=gamma, eps=1e-5, h_out=h)
+    entries = [dict(layer("q0", N), **norm, y=out(N)), dict(layer("q1", 16), **norm, y=out(16)),
+               dict(layer("o", K), x=c, y=out(K, torch.bfloat16))]
+    r_in = entries[2]["y"]
+    entries += [dict(layer("r", N), x=r_in, y=out(N)),
+                # (overwrites the input of the phase before it)
+                dict(layer("w", K), x=over, x2=a, in_op=nvq.IN_SILU_MUL, y=r_in),
+                dict(layer("k2", 48, K2), x=d, y=out(48))]
+    entries += [dict(layer("m%d" % i, N), x=b, y=out(N)) for i in range(5)]
+    entries += [dict(layer("last", N), x=c, x2=b, in_op=nvq.IN_SILU_MUL, y=out(N))]
+
+    def one(name, x):
+        if prec == nvq.W4A16:
+            return nvq.gemv_w4a16(*w[name], x)
+        xq, xs, gs = nvq.quant_act_i8(x, group)
+        return nvq.gemv_w4a8(*w[name], xq, xs, gs, group)
+
+    xn, hn = nvq.rms_norm(a, gamma, 1e-5, b)
+    o = one("o", c).to(torch.bfloat16)
+    want = [one("q0", xn), one("q1", xn), None, one("r", o),
+            one("w", nvq.silu_mul(over, a)).to(torch.bfloat16), one("k2", d)]
+    want += [one("m%d" % i, b) for i in range(5)] + [one("last", nvq.silu_mul(c, b))]
+    torch.cuda.synchronize()
+
+    def check(what):
+        torch.cuda.synchronize()
+        assert torch.equal(h, hn), what
+        for i, (e, y) in enumerate(zip(entries, want)):
+            if y is not None:
+                assert torch.equal(e["y"], y), (what, i, int((e["y"] != y).sum()))
+
+    dl = nvq.DecodeList(entries, M, group)
+    for rep in range(2):
+        dl.run_plan()
+        check("plan")
+    for e in entries:
+        e["y"].zero_()
+    dl.run_static()
+    check("static")
+    dl.close()
+
+
 def test_chain_of_blocks_with_transforms_in_one_launch():
     say("block chain with transforms")
     # two blocks at the 1B shapes, the second fed by the first (the residual add of the first
