@@ -21,10 +21,10 @@
 // Two kernels, which add the products of a slice of K in the same order:
 //  - tiles of 256 tokens x 256 rows ("wide", K a multiple of 256), whose waves dequantise
 //    a weight once per 256 tokens: the best rate, if the output has enough of them;
-//  - smaller tiles (second half of this file), 64 to 128 tokens x 32 to 256 rows, whose
+//  - smaller tiles (second half of this file), 32 to 128 tokens x 32 to 256 rows, whose
 //    waves share out rows and slices of K, for everything else.
 // gemm_choose weighs them by what they were measured to take; with it goes the order of the
-// additions (one, two or four slices of K), which therefore depends on the number of tokens.
+// additions (one, two, four or eight slices of K), which therefore depends on the number of tokens.
 #include "nvq_internal.h"
 
 #include <cstdlib>
@@ -444,9 +444,9 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
 }
 
 // ---- smaller tiles -----------------------------------------------------------
-// For outputs too small to give every compute unit a 256 x 256 tile: a workgroup of
-// four waves owns 32 TT tokens x 32 RT WN weight rows; WN waves lie side by side along
-// the rows (each 32 RT of them, all the tokens) and WK = 4 / WN share out K in blocks of
+// For outputs too small to give every compute unit a 256 x 256 tile: a workgroup of four or
+// eight waves owns 32 TT tokens x 32 RT WN weight rows; WN waves lie side by side along
+// the rows (each 32 RT of them, all the tokens) and WK share out K in blocks of
 // two pairs of groups (128 inputs), slice k the blocks k, k + WK, ...; the partial tiles
 // are added through LDS in slice order at the end.  As with the wide tiles everything
 // goes straight from global memory into LDS, 16 bytes per lane,
@@ -469,24 +469,33 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
 // 78 of the wide tiles (64 of them); 333 x 3072 x 3072: 17 against 69 of the 256 x 128
 // tiles that took these before; 48 x 2048 x 8192: 16 against 173.
 //
+// Eight waves instead of four, so that two share a SIMD, where that was measured to be faster: with
+// TAIL 128 x 256 and 128 x 128, whose addresses cost more instructions per load (1300 x 17280 x 2880:
+// 179 -> 159 us, 900 x 4288 x 2880 47 -> 40, 600 x 2880 x 8640 at 128 x 128 64.6 -> 57.0; without TAIL
+// a call alone gains 2-5 %, a prompt's calls one after the other, at the clock the power limit
+// leaves, nothing: 704 tokens of 3B 183 -> 187); and 32 x 32 with K in eight slices, for prompts
+// that four slices of 64 tokens leave on a quarter of the machine (48 x 2048 x 8192: 17.2 -> 13.8, 40 x
+// 4096 x 14336: 26.8 -> 21.9).  Not for the others: two waves that share rows dequantise them twice
+// (128 x 64 12.1 -> 14.0, 64 x 32 7.2 -> 8.9), and 32 rows per wave instead of 64 read the
+// activations twice from LDS (64 x 64 8.8 -> 9.5).
+//
 // Nibble -> weight: a nibble under the bits of the fp16 number 1024 is 1024 + n (in bits
 // 4-7: 1024 + 16 n), two per instruction, and a mixed-precision FMA takes the fp16 halves
 // as they are: (1024 + n) * s - 1032 * s, one rounding of a number that needs none (n - 8
 // has 4, s 11 significant bits).  17 instructions per 8 weights against 23 through bytes.
-constexpr int kTileWaves = 4;
-
-template <bool F32, int TT, int RT, int WN, bool TAIL>
-__global__ __launch_bounds__(kTileWaves * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
+template <bool F32, int TT, int RT, int WN, int WK, bool TAIL>
+__global__ __launch_bounds__(WN * WK * 64) __attribute__((amdgpu_waves_per_eu(WN * WK / 4, WN * WK / 4))) void
 gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char *__restrict__ sc,
                          int N, int G, const unsigned char *__restrict__ x, int M, int row_tiles,
                          int token_tiles, void *__restrict__ y) {
-    constexpr int WK = kTileWaves / WN;     // slices of K
+    constexpr int kWaves = WN * WK;
     constexpr int NM = TT * RT;           // MFMAs of a step (16 inputs per lane half)
     constexpr int kTokens = 32 * TT, kBufA = kTokens * 128;  // bytes of an activation buffer
     constexpr int NA = 4 * TT / WN;       // activation loads of a wave and pair
+    static_assert(NA * WN == 4 * TT && kWaves % 4 == 0, "whole instructions; waves on every SIMD");
     constexpr int kW = RT * 32 * 64;      // packed weights of a block
     constexpr int kS = RT * 512;          // scales of a block
-    constexpr int kLds = WK * 3 * kBufA + kTileWaves * (2 * kW + 2 * kS);
+    constexpr int kLds = WK * 3 * kBufA + kWaves * (2 * kW + 2 * kS);
     constexpr int kRegs = TT * RT * 16;   // result registers per lane
     constexpr int kScOps = TAIL ? 2 * RT : 2, kWOps = 2 * RT;
     constexpr int kEven = kWOps + kScOps + NA, kOdd = NA;  // loads of an even and an odd pair's list
@@ -620,7 +629,7 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     Nibbles nba, nbb;
     auto read_a = [&](uint32_t addr, uint4v (&v)[TT]) {
         asm volatile("ds_read_b128 %0, %1" : "=v"(v[0]) : "v"(addr));
-        asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(v[1]) : "v"(addr));
+        if (TT > 1) asm volatile("ds_read_b128 %0, %1 offset:4096" : "=v"(v[TT > 1 ? 1 : 0]) : "v"(addr));
         if (TT == 4) {
             asm volatile("ds_read_b128 %0, %1 offset:8192" : "=v"(v[TT - 2]) : "v"(addr));
             asm volatile("ds_read_b128 %0, %1 offset:12288" : "=v"(v[TT - 1]) : "v"(addr));
@@ -637,19 +646,32 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
                 asm volatile("ds_read_b32 %0, %1 offset:128" : "=v"(braw.h[RT - 1]) : "v"(saddr));
         }
     };
+    // (every register that is on its way is named by the wait: nothing of it moves before)
     auto arrived_a = [&](uint4v (&v)[TT]) {
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]));
-        if (TT == 4) asm volatile("" : "+v"(v[TT - 2]), "+v"(v[TT - 1]));
+        if constexpr (TT == 4)
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]));
+        else if constexpr (TT == 2)
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]));
+        else
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]));
     };
     auto arrived_b = [&](uint4v (&v)[TT]) {
-        if (RT == 2)
+        if constexpr (TT == 4 && RT == 2)
             asm volatile("s_waitcnt lgkmcnt(0)"
-                         : "+v"(v[0]), "+v"(v[1]), "+v"(braw.w[0]), "+v"(braw.w[RT - 1]),
-                           "+v"(braw.h[0]), "+v"(braw.h[RT - 1]));
-        else
+                         : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(braw.w[0]), "+v"(braw.w[1]),
+                           "+v"(braw.h[0]), "+v"(braw.h[1]));
+        else if constexpr (TT == 4)
+            asm volatile("s_waitcnt lgkmcnt(0)"
+                         : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3]), "+v"(braw.w[0]), "+v"(braw.h[0]));
+        else if constexpr (TT == 2 && RT == 2)
+            asm volatile("s_waitcnt lgkmcnt(0)"
+                         : "+v"(v[0]), "+v"(v[1]), "+v"(braw.w[0]), "+v"(braw.w[1]), "+v"(braw.h[0]), "+v"(braw.h[1]));
+        else if constexpr (TT == 2)
             asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(v[1]), "+v"(braw.w[0]), "+v"(braw.h[0]));
-        if (TT == 4) asm volatile("" : "+v"(v[TT - 2]), "+v"(v[TT - 1]));
+        else
+            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(v[0]), "+v"(braw.w[0]), "+v"(braw.h[0]));
     };
+    static_assert(RT == 1 || (RT == 2 && TT > 1), "the waits above");
     // row tile rt of the pair whose first group is g
     auto unpack = [&](Nibbles &nb, int rt, int g) {
 #pragma unroll
@@ -697,7 +719,10 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
                 acc[tt][rt], 0, 0, 0);
             if (i == 0) read_a(apos[nst] + nbuf, a[n]);
             if (extra == 1 && i == 0) read_b(waddr, saddr);
-            if (NM == 2 * RT)
+            if (NM == RT) {
+                dequant4(wc, nst, i, 0, bo[n][i]);
+                dequant4(wc, nst, i, 1, bo[n][i]);
+            } else if (NM == 2 * RT)
                 dequant4(wc, nst, i >> 1, i & 1, bo[n][i >> 1]);
             else if (!(i & 1))
                 dequant4(wc, nst, i >> 2, (i >> 1) & 1, bo[n][i >> 2]);
@@ -787,20 +812,21 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     // The partial tiles of the slices are added through LDS: of the WK waves with the same
     // rows, wave u owns registers u kMine .. and the others hand theirs over, four registers
     // (16 bytes) per lane at a time; the sum is taken in slice order.
-    constexpr int kMine = kRegs / WK;
+    constexpr int kOwners = WK < kRegs / 4 ? WK : kRegs / 4;  // waves that own a part, whole registers of 16 bytes
+    constexpr int kMine = kRegs / kOwners;
     constexpr int kOwnRt = kMine >= 16 * RT ? RT : 1;  // row tiles and tokens a wave owns
     constexpr int kOwnTok = kMine * 2 / kOwnRt;
-    constexpr int kRed = kTileWaves * kRegs * 256 / WK * (WK - 1), kOut = kMine * 128;
-    static_assert(kRed + kTileWaves * kOut <= kLds, "partial tiles and results fit");
+    constexpr int kRed = WN * kRegs * 256 * (WK - 1), kOut = kMine * 128;
+    static_assert(kRed + kWaves * kOut <= kLds, "partial tiles and results fit");
     float v[kMine];
     __syncthreads();  // every wave has left the loop
     if (WK > 1) {
         auto part = [&](int owner, int from) {  // where `from` leaves its part for `owner`
             const int slot = from < owner ? from : from - 1;
-            return reinterpret_cast<floatx4 *>(lds) + (((wn * WK + owner) * (WK - 1) + slot) * (kMine / 4)) * 64 + lane;
+            return reinterpret_cast<floatx4 *>(lds) + (((wn * kOwners + owner) * (WK - 1) + slot) * (kMine / 4)) * 64 + lane;
         };
 #pragma unroll
-        for (int u = 0; u < WK; ++u) {
+        for (int u = 0; u < kOwners; ++u) {
             if (u == wk) continue;
             floatx4 *const dst = part(u, wk);
 #pragma unroll
@@ -811,6 +837,7 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
             }
         }
         __syncthreads();
+        if (kOwners < WK && wk >= kOwners) return;
 #pragma unroll
         for (int i = 0; i < kMine; ++i) v[i] = 0.0f;
 #pragma unroll
@@ -855,8 +882,9 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
         }
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-        for (int i = 0; i < kOwnTok * kPieces / 64; ++i) {
+        for (int i = 0; i < (kOwnTok * kPieces + 63) / 64; ++i) {
             const int idx = i * 64 + lane;
+            if (kOwnTok * kPieces < 64 && idx >= kOwnTok * kPieces) break;
             const int tok = idx / kPieces, pos = idx % kPieces;
             const int c = pos ^ ((tok >> 2) & (kPieces - 1));
             const uint4v q = *reinterpret_cast<const uint4v *>(out + idx * 16);
@@ -873,18 +901,26 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     }
 }
 
-// The tiles a product can be cut into, and what they take (us, measured on one box): a
-// tile `fixed` and per pair of groups and slice `pair`, plus `busy` times the share of the
-// compute units that are at work (they share the L2 caches and the power).
+// The tiles a product can be cut into, and what a round of them takes (us): `fixed`, and per pair of
+// groups and slice `pair` plus `busy` times the share of the compute units that are at work (they
+// share the L2 caches and the power); `tail`: for kernels with TAIL.  Fitted to 456 products of 36
+// to 4096 tokens, 960 to 28672 rows and K from 960 to 14336 (4 to 13 % rms per kind).
+struct GemmCost {
+    float fixed, pair, busy;
+};
 struct GemmTile {
     int tokens, rows, slices;
-    float fixed, pair, busy;
+    GemmCost whole, tail;
     const char *name;  // for NVQ_GEMM_TILE
 };
 constexpr GemmTile kGemmTiles[] = {
-    {256, 256, 1, 4.0f, 1.34f, 0.25f, "wide"},   {128, 256, 1, 5.5f, 0.72f, 0.30f, "128x256"},
-    {128, 128, 2, 4.7f, 0.70f, 0.37f, "128x128"}, {128, 64, 2, 5.0f, 0.44f, 0.12f, "128x64"},
-    {64, 64, 4, 4.2f, 0.52f, 0.10f, "64x64"},     {64, 32, 4, 3.9f, 0.37f, 0.11f, "64x32"},
+    {256, 256, 1, {9.0f, 1.01f, 0.54f}, {}, "wide"},
+    {128, 256, 1, {6.4f, 0.65f, 0.33f}, {6.2f, 0.65f, 0.37f}, "128x256"},
+    {128, 128, 2, {6.9f, 0.69f, 0.28f}, {5.4f, 0.70f, 0.41f}, "128x128"},
+    {128, 64, 2, {4.7f, 0.46f, 0.16f}, {4.9f, 0.52f, 0.17f}, "128x64"},
+    {64, 64, 4, {4.5f, 0.57f, 0.10f}, {4.8f, 0.65f, 0.05f}, "64x64"},
+    {64, 32, 4, {3.1f, 0.49f, 0.01f}, {3.5f, 0.46f, 0.0f}, "64x32"},
+    {32, 32, 8, {2.8f, 0.72f, 0.0f}, {2.9f, 0.67f, 0.0f}, "32x32"},
 };
 constexpr int kGemmTileKinds = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
 
@@ -892,20 +928,23 @@ int64_t gemm_tiles(const GemmTile &k, int64_t N, int64_t M) {
     return ((N + k.rows - 1) / k.rows) * ((M + k.tokens - 1) / k.tokens);
 }
 
-// The kind of tile with the smallest estimated time: whole rounds of all compute units,
-// then the rest.  Between neighbouring kinds the estimates are within 15 % of what was
-// measured over 33 to 4096 tokens; where two are that close either will do.
-int gemm_choose(int64_t N, int64_t G, int64_t M, bool can_wide) {
+// The kind of tile with the smallest estimated time: whole rounds of all compute units, then the
+// rest, which has the caches and the power to itself.  Over those 456 products the choice costs 0.2 %
+// on average and 6 % at worst against the fastest kind (held out: the same); counting the rest at
+// the price of a full round it cost 3.7 % and up to 54 % (3300 x 2880 x 8640: 334 us, now 217; 2600
+// x 2048 x 8192: 147, now 107).
+int gemm_choose(int64_t N, int64_t G, int64_t M, bool can_wide, bool tail) {
     const int64_t cus = device_cu_count();
     int best = -1;
     double best_us = 0.0;
     for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i) {
         const GemmTile &k = kGemmTiles[i];
+        const GemmCost &c = tail ? k.tail : k.whole;
         const int64_t n = gemm_tiles(k, N, M), full = n / cus;
         const double part = (double)(n % cus) / (double)cus;
         const double steps = (double)(((G + 1) / 2 + k.slices - 1) / k.slices);
-        double us = (double)full * (k.fixed + steps * (k.pair + k.busy));
-        if (part > 0.0) us += k.fixed + steps * (k.pair + k.busy * (full ? 1.0 : part));
+        double us = (double)full * (c.fixed + steps * (c.pair + c.busy));
+        if (part > 0.0) us += c.fixed + steps * (c.pair + c.busy * part);
         if (best < 0 || us < best_us) {
             best = i;
             best_us = us;
@@ -914,16 +953,14 @@ int gemm_choose(int64_t N, int64_t G, int64_t M, bool can_wide) {
     return best;
 }
 
-template <bool F32, int TT, int RT, int WN>
-void launch_tile(bool tail, dim3 grid, hipStream_t st, const unsigned char *q, const unsigned char *s,
-                 int N, int G, const unsigned char *x, int M, int row_tiles, int token_tiles, void *y) {
-    const dim3 block(kTileWaves * 64);
-    if (tail)
-        hipLaunchKernelGGL((gemm_w4a16_tile_kernel<F32, TT, RT, WN, true>), grid, block, 0, st, q, s, N, G, x,
-                           M, row_tiles, token_tiles, y);
-    else
-        hipLaunchKernelGGL((gemm_w4a16_tile_kernel<F32, TT, RT, WN, false>), grid, block, 0, st, q, s, N, G,
-                           x, M, row_tiles, token_tiles, y);
+// Whether blocks of two pairs do not fit K, or the scales' words their alignment (TAIL).
+bool gemm_tail(int64_t G, const unsigned char *scales) { return (G & 3) != 0 || !aligned(scales, 4); }
+
+template <bool F32, int TT, int RT, int WN, int WK, bool TAIL>
+void launch_tile(dim3 grid, hipStream_t st, const unsigned char *q, const unsigned char *s, int N, int G,
+                 const unsigned char *x, int M, int row_tiles, int token_tiles, void *y) {
+    hipLaunchKernelGGL((gemm_w4a16_tile_kernel<F32, TT, RT, WN, WK, TAIL>), grid, dim3(WN * WK * 64), 0, st, q, s, N,
+                       G, x, M, row_tiles, token_tiles, y);
 }
 
 template <bool F32>
@@ -938,13 +975,23 @@ int launch_gemm(int kind, const unsigned char *q, const unsigned char *s, int N,
     } else {
         const int rt = (int)((N + (int64_t)k.rows - 1) / k.rows), tt = (M + k.tokens - 1) / k.tokens;
         const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
-        const bool tail = (G & 3) != 0 || !aligned(s, 4);
+        const bool tail = gemm_tail(G, s);
         switch (kind) {
-            case 1: launch_tile<F32, 4, 2, 4>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
-            case 2: launch_tile<F32, 4, 2, 2>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
-            case 3: launch_tile<F32, 4, 1, 2>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
-            case 4: launch_tile<F32, 2, 2, 1>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
-            default: launch_tile<F32, 2, 1, 1>(tail, grid, st, q, s, N, G, x, M, rt, tt, y); break;
+#define NVQ_TILE(TAIL_, TT_, RT_, WN_, WK_) launch_tile<F32, TT_, RT_, WN_, WK_, TAIL_>(grid, st, q, s, N, G, x, M, rt, tt, y)
+#define NVQ_TILES(TT_, RT_, WN_, WK_) \
+    if (tail) NVQ_TILE(true, TT_, RT_, WN_, WK_); else NVQ_TILE(false, TT_, RT_, WN_, WK_)
+            case 1:
+                if (tail) NVQ_TILE(true, 4, 1, 8, 1); else NVQ_TILE(false, 4, 2, 4, 1);
+                break;
+            case 2:
+                if (tail) NVQ_TILE(true, 4, 1, 4, 2); else NVQ_TILE(false, 4, 2, 2, 2);
+                break;
+            case 3: NVQ_TILES(4, 1, 2, 2); break;
+            case 4: NVQ_TILES(2, 2, 1, 4); break;
+            case 5: NVQ_TILES(2, 1, 1, 4); break;
+            default: NVQ_TILES(1, 1, 1, 8); break;
+#undef NVQ_TILES
+#undef NVQ_TILE
         }
     }
     NVQ_HIP_TRY(hipGetLastError());
@@ -971,13 +1018,13 @@ extern "C" int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, in
     // environment variable NVQ_GEMM_TILE (the name of a tile; "narrow" for 128x256) overrides
     // the choice where the kernel can run (the tests reach all of them on small shapes).
     const bool can_wide = (K % 256) == 0 && aligned(scales, 16);
-    int kind = gemm_choose(N, K / 32, M, can_wide);
+    const unsigned char *const sb = reinterpret_cast<const unsigned char *>(scales);
+    int kind = gemm_choose(N, K / 32, M, can_wide, gemm_tail(K / 32, sb));
     if (const char *force = getenv("NVQ_GEMM_TILE")) {
         if (strcmp(force, "narrow") == 0) force = "128x256";
         for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i)
             if (strcmp(force, kGemmTiles[i].name) == 0) kind = i;
     }
-    const unsigned char *const sb = reinterpret_cast<const unsigned char *>(scales);
     const unsigned char *const xb = reinterpret_cast<const unsigned char *>(x_bf16);
     if (y_dtype == NVQ_F32)
         return launch_gemm<true>(kind, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);

@@ -1532,6 +1532,30 @@ def test_gemm_w4a16_bits_with_a_tile_chosen_do_not_depend_on_the_batch(monkeypat
     assert torch.equal(whole["64x64"], whole["64x32"])
 
 
+# The tiles of eight waves.  32x32: K in eight slices (fewer blocks than slices, numbers that eight
+# cannot share evenly), half of the waves hand all of their sums over.  128x256 and 128x128 where K
+# is no whole number of blocks or the scales lie off their words: the same bits as the four waves of
+# the other case give, from the same weights at aligned addresses.
+@pytest.mark.parametrize("tile", ["32x32", "128x256", "128x128"])
+@pytest.mark.parametrize("M,N,K,off", [(1, 1, 32, 0), (33, 31, 96, 0), (32, 32, 1024, 1), (31, 33, 1152, 0),
+                                       (65, 129, 1056, 1), (48, 264, 2048, 1), (129, 270, 4160, 0)])
+def test_gemm_w4a16_tiles_of_eight_waves(tile, M, N, K, off, monkeypatch):
+    test_gemm_w4a16_small_tiles_match_oracle(tile, M, N, K, off, monkeypatch)
+    if K % 64 == 0:
+        test_gemm_w4a16_small_tiles_infinite_input(tile, K, monkeypatch)
+    _, q, s = packed(9186, N, K)
+    xd = act(9286, M, K).to(DEV)
+    qd, sd = to_dev_packed(q, s)
+    monkeypatch.setenv("NVQ_GEMM_TILE", tile)
+    whole = nvq.gemm_w4a16(qd, sd, xd)
+    last = nvq.gemm_w4a16(qd, sd, xd[M // 2:].contiguous())
+    buf = torch.zeros(sd.numel() + 1, dtype=sd.dtype, device=DEV)
+    buf[1:] = sd.flatten()
+    shifted = nvq.gemm_w4a16(qd, buf[1:].view(sd.shape), xd)
+    torch.cuda.synchronize()
+    assert torch.equal(whole[M // 2:], last) and torch.equal(whole, shifted)
+
+
 # An infinite activation in the last group of K: infinite results, NaN only where the weight is
 # zero (K that ends inside a block, an odd number of blocks, a single one).
 @pytest.mark.parametrize("tile", ["128x256", "128x128", "128x64", "64x64", "64x32"])
