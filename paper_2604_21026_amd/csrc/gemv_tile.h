@@ -66,12 +66,23 @@ __device__ __forceinline__ RowRef locate_row(SEGS &S, int row, int G) {
     return r;
 }
 
-// Rows per tile for a given groups-per-lane count: about eight 16-byte loads
-// per lane per tile.
 // Resident workgroups per compute unit of the batch-1 kernels (measured on a 295 MB
 // layer: 2 -> 3 workgroups 68 -> 60 us, 4 and 6 no better).
 constexpr int kM1WgPerCu = 3;
-constexpr int tile_rows(int gpl) { return gpl <= 1 ? 8 : gpl <= 2 ? 4 : gpl <= 4 ? 2 : 1; }
+
+// Rows per tile (1, 2, 4 or 8).  One while every row gets a team of its own that is resident: the
+// call is then one trip to memory by as many waves as there are rows (2048 x 2048, W4A16: 2.7 us
+// with one, 2.7, 3.6 and 5.3 with two, four and eight; 1024 x 3072 2.9 against 3.7 with two; cold
+// weights, W4A8, 2048 x 8192 4.5 against 4.6).  Beyond, with two to four groups per lane, two (4096
+// x 4096 4.4 against 4.8 with one and 4.7 with four, 14336 x 4096 9.0, 10.7 and 9.9, 28672 x 4096
+// 14.8, 19.8 and 15.8); with one, whose rows are a load each, as many as make every tile resident
+// (8192 x 2048 with four 4.5, with two 4.8; 128256 x 2048 with eight 42, with two 47).
+static inline int tile_rows(int gpl, int rows, int teams_per_wg) {
+    const int most = gpl == 1 ? 8 : gpl <= 4 ? 2 : 1, teams = device_cu_count() * kM1WgPerCu * teams_per_wg;
+    int u = 1;
+    while (u < most && (rows + u - 1) / u > teams) u *= 2;
+    return u;
+}
 
 // Whether a call whose sums are added in sixty-four chains (gemv_slice.h) goes to a kernel with
 // a wave per row instead of a workgroup per 16 rows.  Up to three tokens and few rows: the row

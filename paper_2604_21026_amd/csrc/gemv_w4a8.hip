@@ -30,12 +30,11 @@ __device__ __forceinline__ int block_dot_i8(const uint4 &w, const uint32_t (&x)[
     return acc;
 }
 
-template <int GPL, int LPR, bool PER_GROUP, bool DEBUG>
+template <int GPL, int LPR, int U, bool PER_GROUP, bool DEBUG>
 __global__ __launch_bounds__(256) void gemv_w4a8_m1_kernel(GemvSegs S, int G,
                                                            const uint4 *__restrict__ xq,
                                                            const float *__restrict__ xscale,
                                                            const int32_t *__restrict__ xgsum) {
-    constexpr int U = tile_rows(GPL);
     constexpr int TEAMS = 256 / LPR;
     const int lane = threadIdx.x % LPR;
     const int v = blockIdx.x * TEAMS + threadIdx.x / LPR;
@@ -43,25 +42,15 @@ __global__ __launch_bounds__(256) void gemv_w4a8_m1_kernel(GemvSegs S, int G,
     const int tiles = (S.total_rows + U - 1) / U;
 
     // Activation codes of the groups this lane owns, for the whole kernel.
-    uint32_t xr[GPL][8];
-    int neg8[GPL];
-    float xsg[GPL];
-    int gc[GPL];
+    int gc[GPL], sums[GPL];
     bool ok[GPL];
+    float xsg[GPL];
 #pragma unroll
     for (int i = 0; i < GPL; ++i) {
         const int g = i * LPR + lane;
         ok[i] = g < G;
         gc[i] = ok[i] ? g : 0;
-        const uint4 a = xq[gc[i] * 2], b = xq[gc[i] * 2 + 1];
-        const uint32_t t[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-        for (int d = 0; d < 8; ++d) xr[i][d] = ok[i] ? t[d] : 0u;
-        neg8[i] = ok[i] ? -8 * xgsum[gc[i]] : 0;
-        xsg[i] = PER_GROUP ? xscale[gc[i]] : 1.0f;
     }
-    const float xs = PER_GROUP ? 1.0f : xscale[0];
-
     uint4 wb[U][GPL];
     uint16_t sb[U][GPL];
     auto load_tile = [&](int t, uint4(&w)[U][GPL], uint16_t(&s)[U][GPL]) {
@@ -75,9 +64,32 @@ __global__ __launch_bounds__(256) void gemv_w4a8_m1_kernel(GemvSegs S, int G,
             }
         }
     };
-
+    // The first weights and the inputs make one trip to memory together.
     int t = v;
-    if (t < tiles) load_tile(t, wb, sb);
+    load_tile(t, wb, sb);
+    asm volatile("" ::: "memory");
+    uint4 xv[GPL][2];
+#pragma unroll
+    for (int i = 0; i < GPL; ++i) {
+        xv[i][0] = xq[gc[i] * 2];
+        xv[i][1] = xq[gc[i] * 2 + 1];
+        sums[i] = xgsum[gc[i]];
+        xsg[i] = PER_GROUP ? xscale[gc[i]] : 1.0f;
+    }
+    const float xs = PER_GROUP ? 1.0f : xscale[0];
+    asm volatile("" ::: "memory");
+
+    uint32_t xr[GPL][8];
+    int neg8[GPL];
+#pragma unroll
+    for (int i = 0; i < GPL; ++i) {
+        const uint4 a = xv[i][0], b = xv[i][1];
+        const uint32_t t8[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+        for (int d = 0; d < 8; ++d) xr[i][d] = ok[i] ? t8[d] : 0u;
+        neg8[i] = ok[i] ? -8 * sums[i] : 0;
+    }
+
     for (; t < tiles; t += V) {
         uint4 wn[U][GPL] = {};
         uint16_t sn[U][GPL] = {};
@@ -156,15 +168,14 @@ __global__ __launch_bounds__(256) void gemv_w4a8_row_kernel(
     }
 }
 
-template <int GPL, int LPR>
-static int launch_m1(const GemvSegs &S, int G, const int8_t *xq, const float *xscale,
-                     const int32_t *xgsum, bool per_group, bool debug, hipStream_t st) {
-    constexpr int U = tile_rows(GPL);
+template <int GPL, int LPR, int U>
+static int launch_m1_rows(const GemvSegs &S, int G, const int8_t *xq, const float *xscale,
+                          const int32_t *xgsum, bool per_group, bool debug, hipStream_t st) {
     const int tiles = (S.total_rows + U - 1) / U;
     const dim3 grid(gemv_grid(tiles, 256 / LPR, kM1WgPerCu)), block(256);
     const uint4 *x4 = reinterpret_cast<const uint4 *>(xq);
-#define NVQ_GO(PG, DBG)                                                                        \
-    hipLaunchKernelGGL((gemv_w4a8_m1_kernel<GPL, LPR, PG, DBG>), grid, block, 0, st, S, G, x4, \
+#define NVQ_GO(PG, DBG)                                                                           \
+    hipLaunchKernelGGL((gemv_w4a8_m1_kernel<GPL, LPR, U, PG, DBG>), grid, block, 0, st, S, G, x4, \
                        xscale, xgsum)
     if (per_group) {
         if (debug) NVQ_GO(true, true); else NVQ_GO(true, false);
@@ -174,6 +185,21 @@ static int launch_m1(const GemvSegs &S, int G, const int8_t *xq, const float *xs
 #undef NVQ_GO
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
+}
+
+template <int GPL, int LPR>
+static int launch_m1(const GemvSegs &S, int G, const int8_t *xq, const float *xscale,
+                     const int32_t *xgsum, bool per_group, bool debug, hipStream_t st) {
+    const int u = tile_rows(GPL, S.total_rows, 256 / LPR);
+#define NVQ_ROWS(u_) return launch_m1_rows<GPL, LPR, u_>(S, G, xq, xscale, xgsum, per_group, debug, st)
+    if constexpr (GPL == 1) {
+        if (u == 8) NVQ_ROWS(8);
+        if (u == 4) NVQ_ROWS(4);
+    }
+    if constexpr (GPL <= 4)
+        if (u == 2) NVQ_ROWS(2);
+    NVQ_ROWS(1);
+#undef NVQ_ROWS
 }
 
 int launch_gemv_w4a8(const GemvSegs &S, int K, const int8_t *xq, const float *xscale,

@@ -164,12 +164,39 @@ __device__ __forceinline__ float half_bits_to_float(uint16_t h) {
     return (float)v;
 }
 
-// Sum across the LPR lanes of an aligned lane group; every lane gets the sum.
+// op(value, value of lane i ^ D) without a trip through LDS, op symmetric.  D = 4 and 8 rotate
+// within sixteen lanes: for 8 that is the exchange, for 4 it is where lanes 8 apart agree.
+template <int D, typename T, typename OP>
+__device__ __forceinline__ T with_lane_xor(T v, OP op) {
+    static_assert(sizeof(T) == 4, "one register");
+    const uint32_t b = __builtin_bit_cast(uint32_t, v);
+    if constexpr (D >= 16) {
+        const auto r = D == 32 ? __builtin_amdgcn_permlane32_swap(b, b, false, false)
+                               : __builtin_amdgcn_permlane16_swap(b, b, false, false);
+        const uint32_t even = r[0], odd = r[1];  // (a bit cast of an element in place takes element 0)
+        return op(__builtin_bit_cast(T, even), __builtin_bit_cast(T, odd));
+    } else {
+        constexpr int kCtrl = D == 8 ? 0x128 : D == 4 ? 0x124 : D == 2 ? 0x4e : 0xb1;
+        return op(v, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(b, b, kCtrl, 0xf, 0xf, false)));
+    }
+}
+
+struct AddOp {
+    template <typename T>
+    __device__ T operator()(T a, T b) const { return a + b; }
+};
+
+// Sum across the LPR (64 or 32) lanes of an aligned lane group, those LPR / 2 apart first; every lane
+// gets the sum.
 template <int LPR>
 __device__ __forceinline__ float group_sum(float v) {
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    return v;
+    static_assert(LPR == 64 || LPR == 32, "");
+    if (LPR == 64) v = with_lane_xor<32>(v, AddOp());
+    v = with_lane_xor<16>(v, AddOp());
+    v = with_lane_xor<8>(v, AddOp());
+    v = with_lane_xor<4>(v, AddOp());
+    v = with_lane_xor<2>(v, AddOp());
+    return with_lane_xor<1>(v, AddOp());
 }
 
 __device__ __forceinline__ void store_out(void *y, int y_dtype, int64_t idx, float v) {

@@ -16,31 +16,9 @@ namespace nvq {
 
 constexpr int kQuantThreads = 256;
 
-// op(value, value of lane i ^ D) without a trip through LDS, op symmetric.  D = 4 and 8 rotate
-// within sixteen lanes: for 8 that is the exchange, for 4 it is where lanes 8 apart agree.
-template <int D, typename T, typename OP>
-__device__ __forceinline__ T with_lane_xor(T v, OP op) {
-    static_assert(sizeof(T) == 4, "one register");
-    const uint32_t b = __builtin_bit_cast(uint32_t, v);
-    if constexpr (D >= 16) {
-        const auto r = D == 32 ? __builtin_amdgcn_permlane32_swap(b, b, false, false)
-                               : __builtin_amdgcn_permlane16_swap(b, b, false, false);
-        const uint32_t even = r[0], odd = r[1];  // (a bit cast of an element in place takes element 0)
-        return op(__builtin_bit_cast(T, even), __builtin_bit_cast(T, odd));
-    } else {
-        constexpr int kCtrl = D == 8 ? 0x128 : D == 4 ? 0x124 : D == 2 ? 0x4e : 0xb1;
-        return op(v, __builtin_bit_cast(T, __builtin_amdgcn_update_dpp(b, b, kCtrl, 0xf, 0xf, false)));
-    }
-}
-
 struct MaxOp {
     __device__ float operator()(float a, float b) const { return fmaxf(a, b); }
 };
-struct AddOp {
-    template <typename T>
-    __device__ T operator()(T a, T b) const { return a + b; }
-};
-
 // Over the lanes of a wave, in every lane; in the order 32, 16, .. 1 apart.
 template <typename OP>
 __device__ __forceinline__ float over_wave(float a, OP op) {

@@ -223,6 +223,40 @@ def test_gemv_w4a8_acc_bit_exact_and_output(N, K, M, group):
     assert np_ref.rel_l2(y.cpu().numpy(), y_r) < 1e-5        # what fp32 accumulation gives
 
 
+# One token: rows per tile go with the rows of the call (one, two, and four and eight with a single
+# group per lane; teams of 64 and of 32 lanes, which a device of 256 compute units has 3072 and 6144
+# of).  A row's bits are those of a short call, on both sides of every step and past the last one;
+# tolerance against the oracle as above.
+@pytest.mark.parametrize("N,K", [(3072, 64), (3073, 2048), (6145, 160), (12289, 96), (24581, 64), (6145, 1024),
+                                 (24577, 1024), (49160, 1024), (3073, 4096), (7001, 2080), (6145, 3072),
+                                 (3075, 6176), (3073, 8192), (3100, 10240)])
+def test_one_token_rows_do_not_depend_on_the_tile(N, K):
+    say("one token, rows per tile", N, K)
+    rng = np.random.default_rng(3500 + N + K)
+    q = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+    s = rng.integers(0x1400, 0x2c00, (N, K // 32)).astype(np.uint16)
+    pick = np.unique(np.concatenate([[0, 1, 7, 8, 3071, N - 9, N - 2, N - 1], rng.integers(0, N, 24)]))
+    pick = pick[pick < N]
+    xh = act(3600 + K, 1, K)
+    (qd, sd), (qs, ss) = to_dev_packed(q, s), to_dev_packed(q[pick], s[pick])
+    y = nvq.gemv_w4a16(qd, sd, xh.to(DEV))[:, pick]
+    few = nvq.gemv_w4a16(qs, ss, xh.to(DEV))
+    torch.cuda.synchronize()
+    assert torch.equal(y, few)
+    assert np_ref.rel_l2(y.cpu().numpy(), oracle.gemv_w4a16(q[pick], s[pick], u16(xh))) < 1e-5
+    for group in (0, 32):
+        xq, xs, gs = oracle.quant_act_i8(u16(xh), group)
+        xqd, xsd, gsd = nvq.quant_act_i8(xh.to(DEV), group)
+        y, acc = nvq.gemv_w4a8(qd, sd, xqd, xsd, gsd, group, want_acc=True)
+        few = nvq.gemv_w4a8(qs, ss, xqd, xsd, gsd, group)
+        again = nvq.gemv_w4a8(qd, sd, xqd, xsd, gsd, group)
+        torch.cuda.synchronize()
+        want, acc_ref = oracle.gemv_w4a8(q[pick], s[pick], xq, xs, group, want_acc=True)
+        assert torch.equal(y[:, pick], few) and torch.equal(y, again)
+        assert np.array_equal(acc[:, pick].cpu().numpy(), acc_ref)
+        assert np_ref.rel_l2(few.cpu().numpy(), want) < 1e-5
+
+
 # The small-batch kernel behind the single calls: tokens at the edges of its three sizes, rows at
 # the edges of its tiles (16 rows; 32 from 12,288 rows on), K from one group on (fewer blocks of
 # eight groups than waves, blocks that end early by one to seven groups, odd numbers of groups),
