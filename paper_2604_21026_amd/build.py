@@ -1,4 +1,5 @@
-"""Build libnvq.so (gfx950 only) in-tree with hipcc.
+"""Build libnvq.so (gfx950 only) in-tree with hipcc, and _calls.so, the binding of the calls that
+count in latency, with the host compiler against torch's headers.
 
     python -m paper_2604_21026_amd.build [--force]
 
@@ -8,6 +9,7 @@ lands next to this file so that it travels with the source tree.
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -15,8 +17,11 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnvq.so")
+CALLS = os.path.join(HERE, "_calls.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+ROCM = os.path.dirname(os.path.dirname(HIPCC)) or "/opt/rocm"
+CXX = os.environ.get("CXX", "g++")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
     "-ffp-contract=off",
@@ -51,10 +56,28 @@ def _compile(src, force, extra):
     return obj
 
 
+def _build_calls(force):
+    src = os.path.join(CSRC, "binding.cpp")
+    if (not force and os.path.exists(CALLS)
+            and os.path.getmtime(CALLS) >= max(os.path.getmtime(src), _newest_header())):
+        return
+    import torch
+    from torch.utils import cpp_extension
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include"),
+                                           os.path.join(ROCM, "include")]
+    abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
+    subprocess.run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+                    "-D_GLIBCXX_USE_CXX11_ABI=%d" % abi] + ["-I" + i for i in inc] + [src, "-o", CALLS]
+                   + ["-L" + d for d in cpp_extension.library_paths()]
+                   + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
+
+
 def build(force: bool = False, extra=()) -> str:
     os.makedirs(OBJ, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
+        calls = ex.submit(_build_calls, force)
         objs = list(ex.map(lambda s: _compile(s, force, extra), sources()))
+        calls.result()
     subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs,
                    check=True)
     return LIB

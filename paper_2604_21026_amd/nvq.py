@@ -1,4 +1,5 @@
-"""Thin ctypes binding over libnvq.so (C ABI in include/nvq.h).
+"""Thin binding over libnvq.so (C ABI in include/nvq.h): ctypes, and csrc/binding.cpp for the calls
+whose latency counts.
 
 Argument marshalling only: torch supplies device memory and the current
 stream, every computation happens in the library's HIP kernels.  There is no
@@ -12,6 +13,7 @@ import torch
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libnvq.so")
+CALLS_PATH = os.path.join(HERE, "_calls.so")
 
 F32, BF16 = 0, 1
 W4A8, W4A16 = 0, 1
@@ -47,11 +49,23 @@ class Linear(C.Structure):
 
 
 _lib = None
+_calls = None  # csrc/binding.cpp, once the library is loaded
+
+
+def _load_calls(L):
+    """The calls that count in latency without ctypes; they know the library by its addresses."""
+    if not os.path.exists(CALLS_PATH):
+        raise FileNotFoundError(
+            "%s not found: build it with `python -m paper_2604_21026_amd.build`" % CALLS_PATH)
+    from . import _calls as calls
+    calls.bind(*(C.cast(f, C.c_void_p).value for f in
+                 (L.nvq_gemv_w4a16, L.nvq_gemv_w4a8, L.nvq_quant_act_i8, L.nvq_gemm_w4a16)))
+    return calls
 
 
 def lib() -> C.CDLL:
     """Load libnvq.so (built beforehand by paper_2604_21026_amd.build)."""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -97,6 +111,7 @@ def lib() -> C.CDLL:
               "nvq_stream_copy", "nvq_plan_create", "nvq_plan_run", "nvq_plan_info",
               "nvq_plan_status", "nvq_plan_trace"):
         getattr(L, f).restype = ci
+    _calls = _load_calls(L)
     _lib = L
     return L
 
@@ -193,9 +208,17 @@ def silu_mul(g: torch.Tensor, u: torch.Tensor) -> torch.Tensor:
 def quant_act_i8(x: torch.Tensor, act_group: int = 0, out=None):
     """x bf16 [M,K] -> xq i8 [M,K], xscale f32 [M] or [M,K/32], xgsum i32 [M,K/32]
     (`out`: the three tensors to write into, as returned by an earlier call)."""
-    M, K = x.shape
     if out is not None:
         xq, xs, gs = out
+        if _calls is not None:
+            status = _calls.quant_act_i8(x, act_group, xq, xs, gs)
+            if status is not None:  # (None: not the ordinary case)
+                if status:
+                    _check(status, "nvq_quant_act_i8")
+                return xq, xs, gs
+    M, K = x.shape
+    if out is not None:
+        pass
     else:
         xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
         xs = torch.empty((M,) if act_group == 0 else (M, K // 32), dtype=torch.float32,
@@ -207,6 +230,12 @@ def quant_act_i8(x: torch.Tensor, act_group: int = 0, out=None):
 
 
 def gemv_w4a16(qweight, scales, x, out_dtype=torch.float32, out: Optional[torch.Tensor] = None):
+    if out is not None and _calls is not None:
+        status = _calls.gemv_w4a16(qweight, scales, x, out)
+        if status is not None:  # (None: not the ordinary case)
+            if status:
+                _check(status, "nvq_gemv_w4a16")
+            return out
     N, K = qweight.shape[0], qweight.shape[1] * 2
     M = x.shape[0]
     if x.shape[1] != K or tuple(scales.shape) != (N, K // 32):
@@ -221,6 +250,12 @@ def gemv_w4a16(qweight, scales, x, out_dtype=torch.float32, out: Optional[torch.
 
 def gemm_w4a16(qweight, scales, x, out_dtype=torch.float32, out: Optional[torch.Tensor] = None):
     """Prefill / large-batch product: x bf16 [M,K] -> y [M,N] (weights rounded to bf16)."""
+    if out is not None and _calls is not None:
+        status = _calls.gemm_w4a16(qweight, scales, x, out)
+        if status is not None:  # (None: not the ordinary case)
+            if status:
+                _check(status, "nvq_gemm_w4a16")
+            return out
     N, K = qweight.shape[0], qweight.shape[1] * 2
     M = x.shape[0]
     if x.shape[1] != K or tuple(scales.shape) != (N, K // 32):
@@ -236,6 +271,12 @@ def gemm_w4a16(qweight, scales, x, out_dtype=torch.float32, out: Optional[torch.
 def gemv_w4a8(qweight, scales, xq, xscale, xgsum, act_group: int = 0,
               out_dtype=torch.float32, want_acc: bool = False,
               out: Optional[torch.Tensor] = None):
+    if out is not None and not want_acc and _calls is not None:
+        status = _calls.gemv_w4a8(qweight, scales, xq, xscale, xgsum, act_group, out)
+        if status is not None:  # (None: not the ordinary case)
+            if status:
+                _check(status, "nvq_gemv_w4a8")
+            return out
     N, K = qweight.shape[0], qweight.shape[1] * 2
     M = xq.shape[0]
     if xq.shape[1] != K or tuple(scales.shape) != (N, K // 32):

@@ -150,3 +150,19 @@ def test_binding_refuses_host_tensors():
     import torch
     with pytest.raises(ValueError):
         nvq.pack_int4(torch.zeros(4, 32))
+
+
+def test_the_binding_without_ctypes_leaves_unusual_calls_alone():
+    """Tensors that are not on a device, other types, too few arguments: None, so that the ordinary
+    way says what is wrong."""
+    import torch
+    nvq.lib()
+    q, s = torch.zeros((4, 32), dtype=torch.uint8), torch.zeros((4, 2), dtype=torch.int16)
+    x, y = torch.zeros((1, 64), dtype=torch.bfloat16), torch.zeros((1, 4))
+    calls = nvq._calls
+    assert calls.gemv_w4a16(q, s, x, y) is None and calls.gemm_w4a16(q, s, x, y) is None
+    assert calls.gemv_w4a16(q, s, x) is None and calls.gemv_w4a16(None, s, x, y) is None
+    assert calls.gemv_w4a8(q, s, x, y, y, 0, y) is None and calls.gemv_w4a8(q, s, x, y, y, "0", y) is None
+    assert calls.quant_act_i8(x, 0, q, y, s) is None and calls.quant_act_i8(x, 1 << 40, q, y, s) is None
+    with pytest.raises(ValueError, match="qweight must be a device tensor"):
+        nvq.gemv_w4a16(q, s, x, out=y)

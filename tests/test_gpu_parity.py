@@ -223,6 +223,63 @@ def test_gemv_w4a8_acc_bit_exact_and_output(N, K, M, group):
     assert np_ref.rel_l2(y.cpu().numpy(), y_r) < 1e-5        # what fp32 accumulation gives
 
 
+# The calls with an output given go through csrc/binding.cpp where everything is as expected: the same
+# bits as through ctypes, the same stream, and the same errors for what is not.
+def test_calls_without_ctypes_equal_those_through_it(monkeypatch):
+    M, N, K = 3, 70, 256
+    _, q, s = packed(3050, N, K)
+    qd, sd = to_dev_packed(q, s)
+    x = act(3051, M, K).to(DEV)
+    codes = [torch.empty_like(t) for t in nvq.quant_act_i8(x)]
+    fast, served = nvq._calls, []
+
+    class Counting:
+        def __getattr__(self, name):
+            def call(*args):
+                status = getattr(fast, name)(*args)
+                served.append((name, status))
+                return status
+            return call
+
+    def outputs():
+        ys = [torch.zeros((M, N), dtype=d, device=DEV) for d in (torch.float32, torch.bfloat16) for _ in range(3)]
+        xq, xs, gs = nvq.quant_act_i8(x, 0, out=[t.zero_() for t in codes])
+        for i in (0, 3):
+            assert nvq.gemv_w4a16(qd, sd, x, out=ys[i]) is ys[i]
+            assert nvq.gemv_w4a8(qd, sd, xq, xs, gs, out=ys[i + 1]) is ys[i + 1]
+            assert nvq.gemm_w4a16(qd, sd, x, out=ys[i + 2]) is ys[i + 2]
+        torch.cuda.synchronize()
+        return [t.clone() for t in codes] + ys
+
+    monkeypatch.setattr(nvq, "_calls", Counting())
+    a = outputs()
+    assert len(served) == 7 and all(status == 0 for _, status in served)
+    monkeypatch.setattr(nvq, "_calls", None)
+    b = outputs()
+    assert all(torch.equal(u, v) for u, v in zip(a, b))
+    # refused alike: types, strides, shapes, devices, what the library refuses, other numbers of tokens
+    y = torch.zeros((M, N), device=DEV)
+    xq, xs, gs = codes
+    wrong = [lambda: nvq.gemv_w4a16(qd, sd, x.float(), out=y), lambda: nvq.gemv_w4a16(qd, sd, x[:, :128], out=y),
+             lambda: nvq.gemv_w4a16(qd.cpu(), sd, x, out=y), lambda: nvq.gemv_w4a16(qd, sd[:, :4], x, out=y),
+             lambda: nvq.gemv_w4a16(qd, sd, x, out=y.to(torch.float16)), lambda: nvq.gemm_w4a16(qd, sd, x, out=y.t()),
+             lambda: nvq.gemv_w4a8(qd, sd, xq, xs, gs, 16, out=y), lambda: nvq.gemv_w4a8(qd, sd, xq.float(), xs, gs, out=y),
+             lambda: nvq.quant_act_i8(x, 7, out=codes), lambda: nvq.quant_act_i8(x[0], 0, out=codes),
+             lambda: nvq.gemv_w4a16(qd, sd, x.repeat(11, 1), out=torch.zeros((33, N), device=DEV))]
+    for i, call in enumerate(wrong):
+        said = []
+        for calls in (fast, None):
+            monkeypatch.setattr(nvq, "_calls", calls)
+            with pytest.raises((ValueError, nvq.NvqError)) as e:
+                call()
+            said.append((type(e.value), str(e.value)))
+        assert said[0] == said[1], i
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        assert fast.stream_handle() == side.cuda_stream == nvq._stream()
+    assert fast.stream_handle() == nvq._stream()
+
+
 # One token: rows per tile go with the rows of the call (one, two, and four and eight with a single
 # group per lane; teams of 64 and of 32 lanes, which a device of 256 compute units has 3072 and 6144
 # of).  A row's bits are those of a short call, on both sides of every step and past the last one;
