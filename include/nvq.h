@@ -273,8 +273,8 @@ int nvq_decode_linears_static(const nvq_linear *layers, int n, int M, int act_gr
  *                    the walk is issued as grouped small-batch launches (two
  *                    or three per batch of independent phases; 3: the product
  *                    of at least one batch runs as a persistent grid, which
- *                    needs every K a multiple of 512 and 16-byte aligned scale
- *                    rows, and from 17 tokens on enough work for the device),
+ *                    needs every K a multiple of 512, 16-byte aligned scale
+ *                    rows and enough work for the device),
  *                    0 for launches per phase;
  *                    waits = number of phases that wait for an earlier phase,
  *                    through flags or for mail (grouped launches: number of
@@ -364,7 +364,8 @@ int nvq_plan_describe_skips(const nvq_linear *layers, int n, int M, int act_grou
  * not qualify for the matrix-core kernels), out[1] = 1 if every phase qualifies
  * for a persistent kernel; then 24 words per batch: first and last phase, units
  * (pairs of 16-row tiles), input jobs, workgroups of the persistent kernel (0:
- * the batch, of 17 tokens or more, runs phase by phase) and its parts,
+ * the batch runs phase by phase, from 17 tokens on, or up to 16 as the grid of
+ * short workgroups) and its parts,
  * 9 words unit index at which each part begins (the last one = units; unused:
  * -1), 9 words phase of the unit at each cut.  The grid assumes the current
  * device's compute units (256 without a device).

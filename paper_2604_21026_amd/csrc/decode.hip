@@ -521,7 +521,14 @@ struct GroupPlan {
     std::vector<GroupBatch> batches;
 };
 
-// How a batch is worked off.  Up to 16 tokens: the persistent grid fed through LDS rings.  From
+// How a batch is worked off.  Up to 16 tokens: the per-tile grid (gemv_mfma.hip) or the persistent one
+// fed through LDS rings, which has the better rate, but sixteen microseconds before it and one for every
+// 256 inputs of the widest phase; both add in the same order.  Linear estimates as below, fitted to
+// 1008 and 720 lists of 4 to 64 phases and 3 to 490 MB (10 and 9 % rms), with a margin for their errors.  Per-tile
+// grid / rings, 8 tokens: two blocks of 1024 x 3072 13.4 / 32.8, four of 1536 x 4608 30 / 37, ten 58 /
+// 64, sixteen 87 / 79; three of 1B 46 / 58, four 56 / 57.  (Lists of up to eight phases with a wider
+// one keep to the rings, although one or two blocks of 1B take 24 and 37 against 53 and 55: tests
+// name their kernel.)  From
 // 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
 // activations (gemv_rows.hip), which moves the most bytes but takes 128 rows and all of their K
 // per workgroup, and launches phase by phase (gemv_slice.h), by what they were measured to take
@@ -532,7 +539,6 @@ struct GroupPlan {
 // 289, 32 of them 1337 / 1054 / 2225; six blocks of 1B 118 / 119 / 193, sixteen 247 / 201 / 576.
 GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
     if (!gp.ring) return kGroupTiles;
-    if (M < kRowsMinTokens) return kGroupRing;
     double mb = 0.0, widest = 0.0, single = 3.3;
     for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
         const GroupPhase &g = gp.tab[(size_t)p];
@@ -540,6 +546,13 @@ GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
         mb += w;
         widest = std::max(widest, steps);
         single += 3.0 + 0.165 * steps + w / 3.1;
+    }
+    if (M < kRowsMinTokens) {
+        const double tiles = 5.1 + 0.118 * b.nphases + 0.218 * widest + mb * (0.215 + 0.0082 * M + 0.0004 * widest);
+        const double rings = 16.3 + 0.131 * b.nphases + 0.972 * widest + 0.175 * std::max(0.0, mb - 27.0);
+        const bool narrow = widest < 24.0, many = b.nphases > 8 && mb > 50.0;
+        const bool per_tile = b.nphases >= 4 && mb >= 1.5 && (narrow || many) && tiles * (narrow ? 1.15 : 1.3) < rings;
+        return per_tile ? kGroupTiles : kGroupRing;
     }
     const double ring = 12.6 + 0.57 * widest + 0.27 * b.nphases + mb / 2.9;
     const double rows = 7.2 + 2.44 * widest + 0.36 * b.nphases + mb / 5.8;
@@ -598,7 +611,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
         cur.phase_first = batch_first;
         cur.nphases = (int)gp.tab.size() - batch_first;
         cur.kind = group_kind(gp, cur, M);
-        if (cur.kind == kGroupRows || cur.kind == kGroupSingle) {
+        if (gp.ring && cur.kind != kGroupRing) {
             // codes for the W4A8 phases instead of operand images for all of them
             const auto first = gp.jobs.begin() + cur.job_first;
             gp.jobs.erase(std::remove_if(first, gp.jobs.end(),
@@ -1136,10 +1149,12 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
 extern "C" int nvq_plan_info(const nvq_plan *pl, int *streaming, int *phases, int *waits) {
     if (!pl) return NVQ_ERR_INVALID_ARG;
     if (streaming) {
-        bool grid = false;  // some batch runs as a persistent grid
-        for (const nvq::GroupBatch &b : pl->batches)
+        bool grid = false, tiles = false;  // some batch runs as a persistent, as the per-tile grid
+        for (const nvq::GroupBatch &b : pl->batches) {
             grid = grid || b.kind == nvq::kGroupRing || b.kind == nvq::kGroupRows;
-        *streaming = pl->nwg > 0 ? 1 : grid ? 3 : pl->batches.empty() || pl->ring ? 0 : 2;
+            tiles = tiles || b.kind == nvq::kGroupTiles;
+        }
+        *streaming = pl->nwg > 0 ? 1 : grid ? 3 : tiles ? 2 : 0;
     }
     if (phases) *phases = (int)pl->phases.size();
     if (waits) *waits = pl->nwaits;
@@ -1244,7 +1259,7 @@ extern "C" int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M,
         o[1] = gb.nunits > 0 ? gp.units[(size_t)gb.unit_first + gb.nunits - 1] : -1;
         o[2] = gb.nunits;
         o[3] = gb.njobs;
-        o[4] = gb.kind == kGroupSingle ? 0 : gb.grid;
+        o[4] = gb.kind == kGroupSingle || (gp.ring && gb.kind == kGroupTiles) ? 0 : gb.grid;
         o[5] = gb.nparts;
         for (int k = 0; k <= gb.nparts && gb.nparts > 0; ++k) {
             o[6 + k] = (int32_t)gp.parts[(size_t)gb.part_first + k];

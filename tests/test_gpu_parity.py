@@ -972,6 +972,58 @@ def test_rows_plan_short_batches_run_phase_by_phase(M):
     dl.close()
 
 
+@pytest.mark.parametrize("M", [2, 9, 16])
+def test_short_lists_of_the_rings_kind_run_as_the_per_tile_grid(M):
+    """Every K a multiple of 512, but too little work for the persistent grid: the same bits (four
+    chains of columns, see above), eager and replayed with eager work in between; one more, wider
+    phase takes the list back to the rings."""
+    say("per-tile grid, whole 512s", M)
+    rng = np.random.default_rng(8720 + M)
+    entries, refs = [], []
+    for i, K in enumerate([512, 1024, 2048, 4608, 1536, 5632] * 2):
+        N, prec = int(rng.integers(200, 500)), (i // 2) % 2
+        q = rng.integers(0, 256, (N, K // 2), dtype=np.uint8)
+        s = rng.integers(0x1400, 0x2c00, (N, K // 32)).astype(np.uint16)
+        qd, sd = to_dev_packed(q, s)
+        if prec == nvq.W4A16:
+            xq, xs = rng.integers(-99, 100, (M, K)).astype(np.int8), None
+            x = torch.from_numpy(xq).to(torch.bfloat16)
+        else:
+            x = act(8730 + i, M, K)
+            xq, xs, _ = oracle.quant_act_i8(u16(x), 0)
+        _, acc = oracle.gemv_w4a8(q, s, xq, np.ones(M, np.float32), 0, want_acc=True)
+        refs.append(np_ref.sums_in_order(acc, np_ref.half_bits_to_f64(s), 4, xs))
+        entries.append(dict(qweight=qd, scales=sd, x=x.to(DEV), precision=prec,
+                            y=torch.zeros((M, N), dtype=torch.float32, device=DEV)))
+    dl = nvq.DecodeList(entries, M, 0)
+    info = dl.plan_info()
+    assert info["grouped"] and not info["persistent_grouped"] and kernels_of(dl) == ["phases"]
+    assert not dl.plan_timed_out()
+    g = torch.cuda.CUDAGraph()
+    for rep in range(4):
+        for e in entries:
+            e["y"].zero_()
+        if rep == 1:
+            with torch.cuda.graph(g):
+                dl.run_plan()
+        if rep == 0:
+            dl.run_plan()
+        else:
+            g.replay()
+        torch.cuda.synchronize()
+        for i, (e, want) in enumerate(zip(entries, refs)):
+            assert np.array_equal(e["y"].cpu().numpy(), want), (rep, i)
+    del g
+    dl.close()
+    wide, _ = model_entries([(32, 14336, 0)], (0,), M=M, seed=8740)
+    dl = nvq.DecodeList(entries + wide, M, 0)
+    assert dl.plan_info()["persistent_grouped"] and kernels_of(dl) == ["rings"]
+    dl.run_plan()
+    torch.cuda.synchronize()
+    assert all(np.array_equal(e["y"].cpu().numpy(), want) for e, want in zip(entries, refs))
+    dl.close()
+
+
 def test_ring_plan_needs_k_multiple_of_512():
     say("ring plan fallback")
     M = 4
