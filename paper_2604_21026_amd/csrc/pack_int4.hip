@@ -4,23 +4,25 @@
 // division so that a CPU implementation of the same rule gives the same bytes.
 //
 // Eight lanes own one group of 32 weights (one float4 each), so a wave reads
-// 1 KiB of consecutive weights per load, two loads in flight.  Lanes 0-3 of a
+// 1 KiB of consecutive weights per load, four loads in flight.  Lanes 0-3 of a
 // team hold the low nibbles of the 16 output bytes, lanes 4-7 the high nibbles;
 // the lanes exchange through the data-parallel moves of the vector ALU, and
-// lanes 0-3 store one dword each.
+// lanes 0-3 store one dword each.  (Four lanes per group, which need no exchange of nibbles, read
+// half lines per load: 50 us against 44.)
 //
-// The codes are those of an IEEE division, without dividing: v * (1 / s) differs
-// from v / s by less than 2^-19 (two roundings; |v / s| < 16: the fp16 scale is at
-// least half of absmax / 7), so the two round to the same integer unless the product lies
-// within 2^-16 of a tie, where the division decides.  The vector ALU is the bound,
-// with four divisions per lane far more so (14336 x 4096, packing and unpacking to bf16 in a
-// row: 77.7 us, now 67.9; by the trace 43 to 47 and 22).
+// The codes are those of an IEEE division, without dividing: v * rcp(s) differs from v / s by less
+// than 2^-18 (three roundings; |v / s| < 16: the fp16 scale is at least half of absmax / 7), so the two
+// round to the same integer unless the product lies within 2^-16 of a tie, where the division
+// decides.  Rounding (half to even) is an addition: the sum with 1.5 * 2^23 + 8 holds the code in its
+// low bits; clamping first gives the same, the bounds being integers.  The memory's mix of reads and
+// writes and the vector ALU bound it about equally: 14336 x 4096 50 us with two loads in flight, a full
+// reciprocal and conversions to integers, 45 with either change, 44 with both (6.2 TB/s).
 #include "nvq_internal.h"
 
 namespace nvq {
 
 typedef float pack_f32x4 __attribute__((ext_vector_type(4)));
-constexpr int kPackUnroll = 2;
+constexpr int kPackUnroll = 4;
 
 // The value of lane i ^ 1, i ^ 2, or 7 - i (within eight lanes).
 template <int CTRL>
@@ -55,26 +57,23 @@ __global__ __launch_bounds__(256) void pack_int4_kernel(const float4 *__restrict
         const _Float16 sh = (_Float16)s32;  // round to nearest even
         const float s = (float)sh;
         const bool live = (s != 0.0f) && !__builtin_isinf(s);
-        const float inv = 1.0f / s;
+        const float inv = __builtin_amdgcn_rcpf(s);
 
-        float r[4];
-        bool tie = false;
+        constexpr float kCode = 12582912.0f + 8.0f;  // 1.5 * 2^23 + 8
+        float t[4], off = 0.0f;  // off: the largest distance from an integer
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const float p = w[i][k] * inv;
-            r[k] = rintf(p);
-            tie = tie || fabsf(p - r[k]) > 0.5f - 0x1p-16f;
+            const float c = fminf(fmaxf(w[i][k] * inv, -8.0f), 7.0f);
+            t[k] = c + kCode;
+            off = fmaxf(off, fabsf(c - (t[k] - kCode)));
         }
-        if (tie) {
+        if (off > 0.5f - 0x1p-16f) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) r[k] = rintf(w[i][k] / s);
+            for (int k = 0; k < 4; ++k) t[k] = fminf(fmaxf(w[i][k] / s, -8.0f), 7.0f) + kCode;
         }
-        uint32_t mine = 0;
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const float c = fminf(fmaxf(r[k], -8.0f), 7.0f);
-            mine |= (uint32_t)((int)c + 8) << (8 * k);
-        }
+        // the lowest bytes of the four words
+        uint32_t mine = __builtin_amdgcn_perm(__float_as_uint(t[1]), __float_as_uint(t[0]), 0x0c0c0400u) |
+                        __builtin_amdgcn_perm(__float_as_uint(t[3]), __float_as_uint(t[2]), 0x04000c0cu);
         if (!live) mine = 0x08080808u;
         const uint32_t other = pack_dpp<kDppXor3>(pack_dpp<kDppMirror8>(mine));  // of lane i ^ 4
         if (valid[i]) {

@@ -125,6 +125,41 @@ def test_dequant_bf16_every_nibble_and_extreme_scales():
     assert np.array_equal(u16(out), oracle.dequant_bf16(q, s))
 
 
+# Packing: groups whose quotients are exact ties, lie a few units beside one, or reach the bounds,
+# scales from subnormal halves on, groups of zeros, the last group of a workgroup and of the matrix
+# (128 groups per workgroup): the oracle's bytes.
+@pytest.mark.parametrize("N,K", [(1, 32), (4, 1024), (43, 96), (65, 2048)])
+def test_pack_rounds_like_the_division(N, K):
+    rng = np.random.default_rng(2900 + N)
+    G = N * K // 32
+    W = rng.normal(0, 0.02, (G, 32)).astype(np.float32)
+    kind = np.arange(G) % 7
+    for g in range(G):
+        s = np.float32(np.float16(2.0 ** rng.integers(-14, 6) * (1 + rng.integers(0, 1024) / 1024)))
+        half = rng.integers(-15, 14, 32).astype(np.float32) * np.float32(0.5)
+        if kind[g] in (1, 2, 3):
+            W[g] = half * s
+            W[g, 0] = 7 * s                              # the scale comes out as s
+        if kind[g] == 2:
+            W[g] = np.nextafter(W[g], np.float32(np.inf))
+            W[g, 0] = 7 * s
+        if kind[g] == 3:
+            W[g] = W[g] * (1 + rng.integers(-3, 4, 32).astype(np.float32) * np.float32(2.0 ** -22))
+            W[g, 0] = 7 * s
+        if kind[g] == 4:
+            W[g] *= np.float32(10.0 ** rng.integers(-8, -3))
+        if kind[g] == 5:
+            W[g] *= np.float32(10.0 ** rng.integers(4, 7))
+        if kind[g] == 6:
+            W[g] = 0
+    W = W.reshape(N, K)
+    q_ref, s_ref = oracle.pack_int4(W)
+    q, s = nvq.pack_int4(torch.from_numpy(W).to(DEV))
+    torch.cuda.synchronize()
+    assert np.array_equal(s.cpu().numpy().view(np.uint16), s_ref)
+    assert np.array_equal(q.cpu().numpy(), q_ref)
+
+
 # ---- a2 activation quantisation ----------------------------------------------
 @pytest.mark.parametrize("M,K,group", [(1, 32, 0), (1, 2048, 0), (3, 3072, 0), (1, 4096, 0),
                                        (2, 8192, 0), (1, 14336, 0), (32, 4096, 0),
