@@ -47,6 +47,7 @@ struct Workspace {
     uint16_t *gimgs;    // [group_images]      phase of every operand image unit, batch after batch
     char *gquant;       // per-phase activation codes, scales and code sums
     uint32_t *mail;     // mailboxes of the streaming kernel (M = 1): tagged copies of outputs
+    size_t bytes_apart;  // without the second input, which phases that share a launch need
     size_t bytes;
 };
 
@@ -91,13 +92,15 @@ Workspace carve(void *base, int M, int n, const ListSizes &ls) {
     w.status = reinterpret_cast<uint32_t *>(take(256));
     take((size_t)(kFlagReplicas - 1) * kStreamMaxWg * 4);  // the other copies of the flags
     w.imgflags = reinterpret_cast<uint32_t *>(take((size_t)(n > 0 ? n : 1) * 4));
-    for (int i = 0; i < kMaxMerge; ++i) {
-        const size_t K = (size_t)(i == 0 ? maxK : ls.merged_K);
-        w.prep[i].xt = reinterpret_cast<uint16_t *>(take(ls.transforms ? M * K * 2 : 0));
-        w.prep[i].xq = reinterpret_cast<int8_t *>(take(M * K));
-        w.prep[i].xscale = reinterpret_cast<float *>(take(M * (K / 32) * 4));
-        w.prep[i].xgsum = reinterpret_cast<int32_t *>(take(M * (K / 32) * 4));
-    }
+    auto input = [&](size_t K) {
+        PrepTarget t;
+        t.xt = reinterpret_cast<uint16_t *>(take(ls.transforms ? M * K * 2 : 0));
+        t.xq = reinterpret_cast<int8_t *>(take(M * K));
+        t.xscale = reinterpret_cast<float *>(take(M * (K / 32) * 4));
+        t.xgsum = reinterpret_cast<int32_t *>(take(M * (K / 32) * 4));
+        return t;
+    };
+    w.prep[0] = input((size_t)maxK);
     w.tab = reinterpret_cast<StreamPhase *>(take((size_t)(n > 0 ? n : 1) * sizeof(StreamPhase)));
     w.dummy = take(1024);
     w.images = take(image_bytes);
@@ -112,6 +115,11 @@ Workspace carve(void *base, int M, int n, const ListSizes &ls) {
     w.gquant = take(M > 1 ? ls.group_quant : 0);
     w.mail = reinterpret_cast<uint32_t *>(
         take(M == 1 ? stream_mail_stride(ls.mail_words) * kMailReplicas * 4 : 0));
+    // last: which phases share a launch depends on M and on the operands, so a workspace sized for the
+    // same shapes at another M or for other operands may end here (see nvq_plan_create)
+    w.bytes_apart = off;
+    static_assert(kMaxMerge == 2, "one input besides the first");
+    w.prep[1] = input((size_t)ls.merged_K);
     w.bytes = off;
     return w;
 }
@@ -979,7 +987,7 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
         ls.merged_K = merged_K(layers, listed, walk_steps(layers, listed, M, act_group, false));
     }
     const Workspace ws = carve(workspace, M, n, ls);
-    if (workspace_bytes < ws.bytes) return NVQ_ERR_WORKSPACE;
+    if (workspace_bytes < ws.bytes_apart) return NVQ_ERR_WORKSPACE;
     nvq_plan *pl = new (std::nothrow) nvq_plan();
     if (!pl) return NVQ_ERR_UNSUPPORTED;
     pl->layers.assign(layers, layers + n);
@@ -989,7 +997,8 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
         delete pl;
         return NVQ_ERR_INVALID_ARG;
     }
-    pl->steps = walk_steps(pl->layers.data(), pl->phases, M, act_group, (flags & NVQ_PLAN_ORDERED) != 0);
+    pl->steps = walk_steps(pl->layers.data(), pl->phases, M, act_group,
+                           (flags & NVQ_PLAN_ORDERED) != 0 || workspace_bytes < ws.bytes);
     pl->ws = ws;
     pl->M = M;
     pl->act_group = act_group;

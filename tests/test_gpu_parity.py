@@ -1341,6 +1341,40 @@ def test_phases_that_share_a_launch_equal_single_calls(M, group, K, N, prec):
     dl.close()
 
 
+# Which phases share launches depends on the operands and on M, and the second input that these need
+# lies at the workspace's end: a workspace sized for the same shapes with the second phase behind the
+# first serves the independent list too, in launches of its own, with the same bits; a byte less than
+# that is refused.
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+def test_phases_that_could_share_a_launch_run_in_the_workspace_of_dependent_ones(prec):
+    say("workspace of dependent phases", prec)
+    M, K, N = 8, 1056, 80
+    a, b = act(9960, M, K).to(DEV), act(9961, M, K).to(DEV)
+    (_, q0, s0), (_, q1, s1) = packed(9962, K, K), packed(9963, N, K)
+    w = [to_dev_packed(q0, s0), to_dev_packed(q1, s1)]
+    y0, y1 = torch.zeros((M, K), dtype=torch.bfloat16, device=DEV), torch.zeros((M, N), device=DEV)
+
+    def entries(x1):
+        return [dict(qweight=w[0][0], scales=w[0][1], x=a, y=y0, precision=prec),
+                dict(qweight=w[1][0], scales=w[1][1], x=x1, y=y1, precision=prec)]
+
+    dl, behind = nvq.DecodeList(entries(b), M, 32), nvq.DecodeList(entries(y0), M, 32)
+    assert behind.workspace.numel() < dl.workspace.numel()
+    dl.run()
+    want = y0.clone(), y1.clone()
+    y0.zero_(), y1.zero_()
+    dl.workspace = guarded = torch.full_like(dl.workspace, 0x5a)
+    dl.workspace = guarded[:behind.workspace.numel()]
+    dl.run()
+    assert torch.equal(y0, want[0]) and torch.equal(y1, want[1])
+    assert bool((guarded[behind.workspace.numel():] == 0x5a).all())
+    dl.workspace = guarded[:behind.workspace.numel() - 1]
+    with pytest.raises(nvq.NvqError):
+        dl.run()
+    dl.close()
+    behind.close()
+
+
 def test_chain_of_blocks_with_transforms_in_one_launch():
     say("block chain with transforms")
     # two blocks at the 1B shapes, the second fed by the first (the residual add of the first
