@@ -15,14 +15,24 @@
 // round to the same integer unless the product lies within 2^-16 of a tie, where the division
 // decides.  Rounding (half to even) is an addition: the sum with 1.5 * 2^23 + 8 holds the code in its
 // low bits; clamping first gives the same, the bounds being integers.  The memory's mix of reads and
-// writes and the vector ALU bound it about equally: 14336 x 4096 50 us with two loads in flight, a full
-// reciprocal and conversions to integers, 45 with either change, 44 with both (6.2 TB/s).
+// writes and the vector ALU bound it about equally: 14336 x 4096 46.3 us with two loads in flight, a full
+// reciprocal and conversions to integers, 43.6 with four and neither, 42.1 (6.4 TB/s) in runs as below.
 #include "nvq_internal.h"
 
 namespace nvq {
 
 typedef float pack_f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPackUnroll = 4;
+constexpr int kPackXcds = 8;
+
+// First group of a workgroup's i-th load.  Workgroups b and b + 8 run on one XCD; a workgroup takes two
+// runs of 64 groups that lie eight apart, so that run r is written by XCD r mod 8: the one whose
+// workgroup of nvq_dequant_bf16 (64 groups each) reads it next, from its own L2.  (With 128 groups in a
+// row 4096 x 4096 packed and unpacked took 22.6 us, with two loads in flight, 64 in a row, 20.2.)
+__device__ __forceinline__ int64_t pack_first(int64_t b, int i) {
+    const int64_t run = b / kPackXcds * (2 * kPackXcds) + b % kPackXcds + (i >> 1) * kPackXcds;
+    return run * 64 + (i & 1) * 32;
+}
 
 // The value of lane i ^ 1, i ^ 2, or 7 - i (within eight lanes).
 template <int CTRL>
@@ -41,7 +51,7 @@ __global__ __launch_bounds__(256) void pack_int4_kernel(const float4 *__restrict
     pack_f32x4 w[kPackUnroll];
 #pragma unroll
     for (int i = 0; i < kPackUnroll; ++i) {
-        gid[i] = ((int64_t)blockIdx.x * kPackUnroll + i) * 32 + (threadIdx.x >> 3);
+        gid[i] = pack_first(blockIdx.x, i) + (threadIdx.x >> 3);
         valid[i] = gid[i] < total_groups;
         if (!valid[i]) gid[i] = total_groups - 1;  // keep the whole team in the exchange below
         w[i] = __builtin_nontemporal_load(reinterpret_cast<const pack_f32x4 *>(W) + gid[i] * 8 + sub);
@@ -93,7 +103,8 @@ extern "C" int nvq_pack_int4(const float *W, int64_t N, int64_t K, int group, ui
     if (!nvq::aligned(W, 16) || !nvq::aligned(qweight, 16) || !nvq::aligned(scales, 2))
         return NVQ_ERR_ALIGN;
     const int64_t groups = N * (K / 32);
-    const int64_t blocks = (groups + 32 * nvq::kPackUnroll - 1) / (32 * nvq::kPackUnroll);
+    constexpr int64_t kSpan = 32 * nvq::kPackUnroll * nvq::kPackXcds;  // groups of eight workgroups
+    const int64_t blocks = (groups + kSpan - 1) / kSpan * nvq::kPackXcds;
     if (blocks > 0x7fffffffLL) return NVQ_ERR_SHAPE;
     hipLaunchKernelGGL(nvq::pack_int4_kernel, dim3((unsigned)blocks), dim3(256), 0,
                        (hipStream_t)stream, reinterpret_cast<const float4 *>(W), groups,

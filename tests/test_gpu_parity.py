@@ -101,6 +101,22 @@ def test_pack_int4_edge_values():
     assert np_ref.unpack_codes(q.cpu().numpy())[0, :12].tolist() == [7, 2, 4, 0, 0, 2, -2, -4, 6, -6, 4, 6]
 
 
+# A workgroup packs two runs of 64 groups that lie eight runs apart: a last span of 1024 groups that
+# ends inside the first or the second run of a workgroup, or at an edge of either; nothing past the end.
+@pytest.mark.parametrize("G", [1, 63, 64, 65, 511, 512, 513, 577, 1023, 1024, 1025, 1537])
+def test_pack_runs_of_groups(G):
+    say("pack runs", G)
+    W, q_ref, s_ref = packed(3100 + G, G, 32)
+    Wd = W.to(DEV)
+    q = torch.full(((G + 2048) * 16,), 0xa5, dtype=torch.uint8, device=DEV)
+    s = torch.full((G + 2048,), 0x5a5a, dtype=torch.int16, device=DEV)
+    assert nvq.lib().nvq_pack_int4(Wd.data_ptr(), G, 32, 32, q.data_ptr(), s.data_ptr(), nvq._stream()) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(q[:G * 16].cpu().numpy().reshape(G, 16), q_ref)
+    assert np.array_equal(u16(s[:G]).reshape(s_ref.shape), s_ref)
+    assert bool((q[G * 16:] == 0xa5).all()) and bool((s[G:] == 0x5a5a).all())
+
+
 # ---- prefill path: dense bf16 weights ------------------------------------------
 @pytest.mark.parametrize("N,K", [(3, 32), (70, 2048), (257, 4096), (5, 14336), (1031, 1024)])
 def test_dequant_bf16_bit_exact(N, K):
