@@ -136,6 +136,16 @@ struct SlicePhase {
     uint32_t bf16;   // bit i: matrix i has bf16 results
     int32_t *dbg[DEBUG ? kMaxSeg : 1];
 };
+// What of a phase a workgroup keeps: where its rows are and their results go.
+template <bool DEBUG>
+struct SliceRows {
+    const uint4 *qw[kMaxSeg];
+    const uint16_t *sc[kMaxSeg];
+    void *y[kMaxSeg];
+    int row_end[kMaxSeg];
+    uint32_t bf16;
+    int32_t *dbg[DEBUG ? kMaxSeg : 1];
+};
 template <int NP, bool DEBUG>
 struct SliceArgs {
     SlicePhase<DEBUG> phase[NP];  // the first phase's workgroups come first
@@ -152,8 +162,8 @@ struct SliceRow {
     int N, n;
     bool bf16, valid;
 };
-template <bool DEBUG, class PHASE>
-__device__ __forceinline__ SliceRow slice_row(PHASE &P, int row, int G) {
+template <bool DEBUG>
+__device__ __forceinline__ SliceRow slice_row(const SliceRows<DEBUG> &P, int row, int G) {
     SliceRow r;
     r.valid = row < P.row_end[kMaxSeg - 1];
     if (!r.valid) row = P.row_end[kMaxSeg - 1] - 1;
@@ -164,16 +174,21 @@ __device__ __forceinline__ SliceRow slice_row(PHASE &P, int row, int G) {
     r.dbg = P.dbg[0];
     r.bf16 = (P.bf16 & 1u) != 0;
 #pragma unroll
-    for (int i = 1; i < kMaxSeg; ++i)
-        if (row >= P.row_end[i - 1]) {
-            first = P.row_end[i - 1];
-            end = P.row_end[i];
-            r.qw = P.qw[i];
-            r.sc = P.sc[i];
-            r.y = P.y[i];
-            if (DEBUG) r.dbg = P.dbg[DEBUG ? i : 0];
-            r.bf16 = (P.bf16 >> i & 1u) != 0;
-        }
+    for (int i = 1; i < kMaxSeg; ++i) {
+        const uint4 *const qw = P.qw[i];
+        const uint16_t *const sc = P.sc[i];
+        void *const y = P.y[i];
+        int32_t *const dbg = P.dbg[DEBUG ? i : 0];
+        const int from = P.row_end[i - 1], to = P.row_end[i];
+        const bool in = row >= from;
+        first = in ? from : first;
+        end = in ? to : end;
+        r.qw = in ? qw : r.qw;
+        r.sc = in ? sc : r.sc;
+        r.y = in ? y : r.y;
+        r.dbg = in ? dbg : r.dbg;
+        r.bf16 = in ? (P.bf16 >> i & 1u) != 0 : r.bf16;
+    }
     r.N = end - first;
     r.n = row - first;
     r.qw += (int64_t)r.n * G;
@@ -204,22 +219,40 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     typedef const __attribute__((address_space(4))) uint32_t CWord;
     // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch)
     CPhase *phase = (CPhase *)__builtin_amdgcn_kernarg_segment_ptr();
-    auto all_lines = [&] {
-        CWord *a = (CWord *)phase;
-        const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[sizeof(SlicePhase<DEBUG>) / 4 - 1];
-        asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3));
-    };
-    all_lines();
     int unit = (int)blockIdx.x;
-    if (NP > 1 && unit >= phase->units) {
-        unit -= phase->units;
-        ++phase;
-        all_lines();
+    if (NP > 1) {
+        CWord *a = (CWord *)phase;
+        constexpr int kNext = sizeof(SlicePhase<DEBUG>) / 4;
+        const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[kNext], l4 = a[kNext + 16], l5 = a[NP * kNext - 1];
+        const int units = phase->units;
+        asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3), "s"(l4), "s"(l5), "s"(units));
+        if (unit >= units) {
+            unit -= units;
+            ++phase;
+        }
     }
-    CPhase &S = *phase;
+    // A copy in scalar registers that the compiler takes for values of its own: it would select among
+    // the fields' addresses and load again, once in front of the first weights and once in front of
+    // every store (with a scale per group, W4A8: 9361 x 7232 at 25 tokens 35.1 us, so 32.3, 29039 x 544 at
+    // 16 27.4 and 24.7; four 8B blocks as a chain at 8 tokens 196 and 190, four of 3B at 4 147 and 139).
+    SliceRows<DEBUG> S;
+#pragma unroll
+    for (int i = 0; i < kMaxSeg; ++i) {
+        S.qw[i] = phase->qw[i];
+        S.sc[i] = phase->sc[i];
+        S.y[i] = phase->y[i];
+        S.row_end[i] = phase->row_end[i];
+        if (DEBUG || i == 0) S.dbg[DEBUG ? i : 0] = phase->dbg[DEBUG ? i : 0];
+    }
+    S.bf16 = phase->bf16;
     const int G = phase->G, M = phase->M;
     const char *const xin = phase->x;
     const float *const xscale = phase->xscale;
+    static_assert(kMaxSeg == 4, "the registers named here");
+    asm volatile("" : "+s"(S.qw[0]), "+s"(S.qw[1]), "+s"(S.qw[2]), "+s"(S.qw[3]), "+s"(S.sc[0]), "+s"(S.sc[1]),
+                 "+s"(S.sc[2]), "+s"(S.sc[3]));
+    asm volatile("" : "+s"(S.y[0]), "+s"(S.y[1]), "+s"(S.y[2]), "+s"(S.y[3]), "+s"(S.row_end[0]),
+                 "+s"(S.row_end[1]), "+s"(S.row_end[2]), "+s"(S.row_end[3]), "+s"(S.bf16));
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 15, kb = lane >> 4;
