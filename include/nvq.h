@@ -154,7 +154,9 @@ int nvq_silu_mul_bf16(const uint16_t *g, const uint16_t *u, int M, int K, uint16
  *   NVQ_IN_PLAIN     the layer reads x_bf16
  *   NVQ_IN_RMSNORM   the layer reads nvq_rms_norm_bf16(x_bf16, x2_bf16, gamma_bf16, eps)
  *                    (x2_bf16 may be NULL; with x2_bf16 the sum x + x2 goes to
- *                    h_out_bf16 if that is not NULL: the updated residual stream)
+ *                    h_out_bf16 if that is not NULL: the updated residual stream.
+ *                    Without x2_bf16 pass NULL: launches per phase store x in
+ *                    h_out_bf16, the persistent kernel nothing)
  *   NVQ_IN_SILU_MUL  the layer reads nvq_silu_mul_bf16(x_bf16, x2_bf16)
  */
 enum { NVQ_IN_PLAIN = 0, NVQ_IN_RMSNORM = 1, NVQ_IN_SILU_MUL = 2 };

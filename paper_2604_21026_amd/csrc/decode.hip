@@ -236,9 +236,10 @@ struct Range {
 bool overlap(const Range &a, const Range &b) { return a.lo < b.hi && b.lo < a.hi; }
 
 // What a phase reads (input, second operand and norm weights) and what it
-// writes (every layer's output, the residual sum).
+// writes (every layer's output, the residual sum; `launched`: also an h_out without x2, which is no
+// output of the phase, but which the input launch of launches per phase stores).
 void phase_ranges(const nvq_linear *L, const Phase &ph, int M, std::vector<Range> *in,
-                  std::vector<Range> *out) {
+                  std::vector<Range> *out, bool launched = false) {
     const nvq_linear &e0 = L[ph.first];
     const size_t xbytes = (size_t)M * e0.K * 2;
     in->push_back({(uintptr_t)e0.x_bf16, (uintptr_t)e0.x_bf16 + xbytes});
@@ -246,7 +247,7 @@ void phase_ranges(const nvq_linear *L, const Phase &ph, int M, std::vector<Range
         if (e0.x2_bf16) in->push_back({(uintptr_t)e0.x2_bf16, (uintptr_t)e0.x2_bf16 + xbytes});
         if (e0.gamma_bf16)
             in->push_back({(uintptr_t)e0.gamma_bf16, (uintptr_t)e0.gamma_bf16 + (size_t)e0.K * 2});
-        if (e0.in_op == NVQ_IN_RMSNORM && e0.x2_bf16 && e0.h_out_bf16)
+        if (e0.in_op == NVQ_IN_RMSNORM && (e0.x2_bf16 || launched) && e0.h_out_bf16)
             out->push_back({(uintptr_t)e0.h_out_bf16, (uintptr_t)e0.h_out_bf16 + xbytes});
     }
     for (int k = 0; k < ph.count; ++k) {
@@ -273,18 +274,11 @@ int check_phase_hazards(const nvq_linear *L, const std::vector<Phase> &phases, i
     return NVQ_OK;
 }
 
-// The order the persistent kernel takes the phases in (batch 1).  A phase that
-// reads what its predecessor writes starts with everybody waiting for the
-// predecessor's slowest wave and for the results to travel.  Where the phase
-// after it conflicts with neither of the two, that one goes first: the waves
-// that are done early then have work, and the wait has passed when they get
-// there.  (A decode step whose attention runs elsewhere has one such phase per
-// block, the o projection.)  Phases that do not conflict may run in any order,
-// so every result is what the list's own order gives.
-bool phases_conflict(const nvq_linear *L, const Phase &a, const Phase &b, int M) {
+// Whether phases that follow each other depend on each other (`launched`: see phase_ranges).
+bool phases_conflict(const nvq_linear *L, const Phase &a, const Phase &b, int M, bool launched = false) {
     std::vector<Range> ain, aout, bin, bout;
-    phase_ranges(L, a, M, &ain, &aout);
-    phase_ranges(L, b, M, &bin, &bout);
+    phase_ranges(L, a, M, &ain, &aout, launched);
+    phase_ranges(L, b, M, &bin, &bout, launched);
     for (const Range &y : aout) {
         for (const Range &x : bin)
             if (overlap(y, x)) return true;
@@ -307,7 +301,8 @@ struct WalkStep {
 // with the same K and precision: a launch costs 1.7 us before it does anything, and one phase's
 // workgroups alone leave compute units idle.  In a decode step whose attention runs elsewhere that
 // is q/k/v with o: 8192 x 3072 as one product and one input launch 10.7 us, as two each 18.9.
-// Dependent phases, and with `ordered` all, stay apart.
+// Dependent phases, and with `ordered` all, stay apart; so do phases one of which reads or overwrites
+// what the other's input launch stores (see phase_ranges).
 std::vector<WalkStep> walk_steps(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
                                  bool ordered) {
     std::vector<WalkStep> out;
@@ -317,7 +312,7 @@ std::vector<WalkStep> walk_steps(const nvq_linear *L, const std::vector<Phase> &
             const nvq_linear &a = L[phases[p].first], &b = L[phases[p + 1].first];
             if (a.K == b.K && a.precision == b.precision &&
                 gemv_slice_merges(make_segs(L, phases[p]), make_segs(L, phases[p + 1]), a.K, M, a.precision, act_group) &&
-                !phases_conflict(L, phases[p], phases[p + 1], M))
+                !phases_conflict(L, phases[p], phases[p + 1], M, true))
                 s.count = 2;
         }
         out.push_back(s);
@@ -394,6 +389,14 @@ int walk_per_phase(const nvq_linear *L, const std::vector<Phase> &phases, const 
     return NVQ_OK;
 }
 
+// The order the persistent kernel takes the phases in (batch 1).  A phase that
+// reads what its predecessor writes starts with everybody waiting for the
+// predecessor's slowest wave and for the results to travel.  Where the phase
+// after it conflicts with neither of the two, that one goes first: the waves
+// that are done early then have work, and the wait has passed when they get
+// there.  (A decode step whose attention runs elsewhere has one such phase per
+// block, the o projection.)  Phases that do not conflict may run in any order,
+// so every result is what the list's own order gives.
 void schedule_phases(const nvq_linear *L, std::vector<Phase> *phases, int M, bool ordered) {
     if (M != 1 || ordered) return;
     std::vector<Phase> &ph = *phases;

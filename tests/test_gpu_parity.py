@@ -1357,6 +1357,39 @@ def test_phases_that_share_a_launch_equal_single_calls(M, group, K, N, prec):
     dl.close()
 
 
+# Launches per phase store h_out without x2 as well: the phase behind reads it, or its input is what
+# the next one stores, so neither pair shares a launch.
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+@pytest.mark.parametrize("M", [2, 8, 32])
+def test_residual_outputs_without_a_second_input_are_ordered(M, prec):
+    say("h_out without x2", M, prec)
+    K, N = 1056, 80
+    (_, q0, s0), (_, q1, s1) = packed(9970, N, K), packed(9971, N, K)
+    w = [to_dev_packed(q0, s0), to_dev_packed(q1, s1)]
+    x, old = act(9972, M, K).to(DEV), act(9973, M, K).to(DEV)
+    gamma = torch.ones(K, dtype=torch.bfloat16, device=DEV)
+    h, y = torch.empty_like(x), [torch.zeros((M, N), device=DEV) for _ in range(2)]
+    norm = dict(qweight=w[0][0], scales=w[0][1], x=x, in_op=nvq.IN_RMSNORM, gamma=gamma, eps=1e-5, h_out=h, y=y[0],
+                precision=prec)
+    plain = dict(qweight=w[1][0], scales=w[1][1], x=h, y=y[1], precision=prec)
+
+    def one(i, v):
+        if prec == nvq.W4A16:
+            return nvq.gemv_w4a16(*w[i], v)
+        xq, xs, gs = nvq.quant_act_i8(v, 32)
+        return nvq.gemv_w4a8(*w[i], xq, xs, gs, 32)
+
+    normed = one(0, nvq.rms_norm(x, gamma, 1e-5)[0])
+    for entries, read in (([norm, plain], x), ([plain, norm], old)):
+        dl = nvq.DecodeList(entries, M, 32)
+        for run in (dl.run_plan, dl.run_static):
+            h.copy_(old)
+            run()
+            torch.cuda.synchronize()
+            assert torch.equal(h, x) and torch.equal(y[0], normed) and torch.equal(y[1], one(1, read))
+        dl.close()
+
+
 # Which phases share launches depends on the operands and on M, and the second input that these need
 # lies at the workspace's end: a workspace sized for the same shapes with the second phase behind the
 # first serves the independent list too, in launches of its own, with the same bits; a byte less than

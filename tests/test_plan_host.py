@@ -432,3 +432,32 @@ def test_lists_the_persistent_small_batch_kernel_does_not_take():
     assert not ring and len(batches) == 1          # K is no multiple of 512
     ring, batches = nvq.plan_describe_batches([linear(a, 128, 4128, x, M=4)], 4)
     assert not ring and batches == []              # K % 128 != 0: launches per phase
+
+
+# ---- launches per phase: which neighbours may share them ----------------------------
+def workspace_bytes(layers, M, act_group=0):
+    arr = (nvq.Linear * len(layers))(*layers)
+    return nvq.lib().nvq_decode_workspace_bytes(arr, len(layers), M, act_group)
+
+
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+def test_a_residual_output_without_a_second_input_keeps_neighbours_apart(prec):
+    """Launches per phase store h_out also where there is no x2.  Neighbours that read, overwrite or are
+    overwritten by it must not share launches: their workspace then needs no second input."""
+    M, K, N = 8, 1024, 96
+    a = Arena()
+    x, x2, h, gamma = (a.take(M * K * 2) for _ in range(4))
+    norm = dict(in_op=nvq.IN_RMSNORM, gamma=gamma, eps=1e-5)
+    lin = lambda x_, rows=N, **kw: linear(a, rows, K, x_, prec=prec, M=M, **kw)
+    out = a.take(M * K * 2)
+    apart = workspace_bytes([lin(x, K, y=out, y_f32=False, **norm), lin(out)], M)
+    assert workspace_bytes([lin(x, h_out=h, **norm), lin(x2)], M) > apart           # nothing shared
+    assert workspace_bytes([lin(x, h_out=h, **norm), lin(h)], M) == apart           # read behind
+    assert workspace_bytes([lin(x, h_out=h, **norm), lin(h + 64)], M) == apart      # in part
+    assert workspace_bytes([lin(x), lin(x2, h_out=x, **norm)], M) == apart          # input overwritten
+    assert workspace_bytes([lin(x, K, y=h, y_f32=False), lin(x2, h_out=h, **norm)], M) == apart
+    assert workspace_bytes([lin(x, h_out=h, **norm), lin(x2, h_out=h, **norm)], M) == apart
+    assert workspace_bytes([lin(x, h_out=h, **norm), lin(x2, K, y=h, y_f32=False)], M) == apart
+    # lists that were accepted stay accepted: such an h_out over its own phase's input
+    L, words = [lin(x, h_out=x, **norm)], (nvq.C.c_int32 * 64)()
+    assert nvq.lib().nvq_plan_describe((nvq.Linear * 1)(*L), 1, M, 0, 0, 256, words, 64) == 0
