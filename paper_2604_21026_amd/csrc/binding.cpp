@@ -2,8 +2,8 @@
 // nvq.gemv_w4a16 and its like spend 2.8 us in Python on shapes, types and the stream (2048 x 2048 at one
 // token: 6.4 us a call, of which the launch takes 3.6 and the kernel 2.7).
 //
-// Only the ordinary case is served here: tensors of the expected types on a device, contiguous,
-// with fitting shapes.  For everything else a function returns None and the caller takes its own
+// Only the ordinary case is served here: tensors (no subclasses, which may say themselves where their
+// data is) of the expected types on a device, contiguous, with fitting shapes.  For everything else a function returns None and the caller takes its own
 // way, which names what is wrong.  The library's entry points are handed over by address (bind);
 // a call returns their status.
 #include <Python.h>
@@ -23,7 +23,7 @@ decltype(&nvq_gemm_w4a16) g_gemm_w4a16;
 
 // A contiguous device tensor of that type; dims < 0: any shape.
 const at::Tensor *device_tensor(PyObject *o, at::ScalarType type, int64_t dims) {
-    if (!THPVariable_Check(o)) return nullptr;
+    if (!THPVariable_CheckExact(o)) return nullptr;
     const at::Tensor &t = THPVariable_Unpack(o);
     if (!t.defined() || !t.is_cuda() || t.scalar_type() != type || !t.is_contiguous()) return nullptr;
     if (dims >= 0 && t.dim() != dims) return nullptr;
@@ -134,7 +134,7 @@ PyObject *quant_act_i8(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const at::Tensor *x = device_tensor(a[0], at::kBFloat16, 2);
     if (!x || x->size(0) > INT32_MAX || x->size(1) > INT32_MAX) return none();
     for (int i = 2; i < 5; ++i)
-        if (!THPVariable_Check(a[i]) || !THPVariable_Unpack(a[i]).is_cuda()) return none();
+        if (!THPVariable_CheckExact(a[i]) || !THPVariable_Unpack(a[i]).is_cuda()) return none();
     const uint16_t *const xp = static_cast<const uint16_t *>(x->data_ptr());
     int8_t *const q = static_cast<int8_t *>(THPVariable_Unpack(a[2]).data_ptr());
     float *const s = static_cast<float *>(THPVariable_Unpack(a[3]).data_ptr());

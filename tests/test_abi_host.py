@@ -166,3 +166,25 @@ def test_the_binding_without_ctypes_leaves_unusual_calls_alone():
     assert calls.quant_act_i8(x, 0, q, y, s) is None and calls.quant_act_i8(x, 1 << 40, q, y, s) is None
     with pytest.raises(ValueError, match="qweight must be a device tensor"):
         nvq.gemv_w4a16(q, s, x, out=y)
+
+
+def test_the_binding_without_ctypes_leaves_subclasses_of_tensors_alone():
+    """A subclass may say itself where its data is: the ordinary way asks it."""
+    import torch
+    nvq.lib()
+
+    class Own(torch.Tensor):
+        @staticmethod
+        def __new__(cls, shape, dtype):
+            return torch.Tensor._make_wrapper_subclass(cls, shape, dtype=dtype, device="cuda")
+
+        __torch_dispatch__ = classmethod(lambda cls, func, types, args=(), kwargs=None: NotImplemented)
+
+    q, s = Own((4, 32), torch.uint8), Own((4, 2), torch.int16)
+    x, y = Own((1, 64), torch.bfloat16), Own((1, 4), torch.float32)
+    xq, xs, gs = Own((1, 64), torch.int8), Own((1,), torch.float32), Own((1, 2), torch.int32)
+    assert q.is_cuda and q.is_contiguous()
+    calls = nvq._calls
+    assert calls.gemv_w4a16(q, s, x, y) is None and calls.gemm_w4a16(q, s, x, y) is None
+    assert calls.gemv_w4a8(q, s, xq, xs, gs, 0, y) is None
+    assert calls.quant_act_i8(x, 0, xq, xs, gs) is None
