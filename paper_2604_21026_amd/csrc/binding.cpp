@@ -30,14 +30,20 @@ const at::Tensor *device_tensor(PyObject *o, at::ScalarType type, int64_t dims) 
     return &t;
 }
 
-// The output of a product, and its type for the library.
-const at::Tensor *output_tensor(PyObject *o, int *y_dtype) {
-    if (const at::Tensor *t = device_tensor(o, at::kFloat, -1)) {
+// The same with room for n values.
+const at::Tensor *device_room(PyObject *o, at::ScalarType type, int64_t n) {
+    const at::Tensor *const t = device_tensor(o, type, -1);
+    return t && t->numel() >= n ? t : nullptr;
+}
+
+// The output of a product (n results), and its type for the library.
+const at::Tensor *output_tensor(PyObject *o, int64_t n, int *y_dtype) {
+    if (const at::Tensor *t = device_room(o, at::kFloat, n)) {
         *y_dtype = NVQ_F32;
         return t;
     }
     *y_dtype = NVQ_BF16;
-    return device_tensor(o, at::kBFloat16, -1);
+    return device_room(o, at::kBFloat16, n);
 }
 
 struct Weights {
@@ -75,9 +81,11 @@ PyObject *product_w4a16(PyObject *const *a, Py_ssize_t n) {
     Weights w;
     int y_dtype;
     if (n != 4 || !weights(a[0], a[1], &w)) return none();
-    const at::Tensor *x = device_tensor(a[2], at::kBFloat16, 2), *y = output_tensor(a[3], &y_dtype);
-    if (!x || !y || x->size(1) != w.K || x->size(0) > INT32_MAX) return none();
+    const at::Tensor *const x = device_tensor(a[2], at::kBFloat16, 2);
+    if (!x || x->size(1) != w.K || x->size(0) > INT32_MAX) return none();
     const int64_t M = x->size(0);
+    const at::Tensor *const y = output_tensor(a[3], M * w.N, &y_dtype);
+    if (!y) return none();
     const uint16_t *const xp = static_cast<const uint16_t *>(x->data_ptr());
     void *const yp = y->data_ptr(), *const st = current_stream();
     if (GEMM) return status_of([&] { return g_gemm_w4a16(w.q, w.s, w.N, w.K, xp, M, yp, y_dtype, st); });
@@ -112,10 +120,14 @@ PyObject *gemv_w4a8(PyObject *, PyObject *const *a, Py_ssize_t n) {
     Weights w;
     int y_dtype, group;
     if (n != 7 || !weights(a[0], a[1], &w) || !small_int(a[5], &group)) return none();
-    const at::Tensor *xq = device_tensor(a[2], at::kChar, 2), *xs = device_tensor(a[3], at::kFloat, -1),
-                     *gs = device_tensor(a[4], at::kInt, -1), *y = output_tensor(a[6], &y_dtype);
-    if (!xq || !xs || !gs || !y || xq->size(1) != w.K || xq->size(0) > INT32_MAX) return none();
+    const at::Tensor *const xq = device_tensor(a[2], at::kChar, 2);
+    if (!xq || xq->size(1) != w.K || xq->size(0) > INT32_MAX) return none();
     const int M = (int)xq->size(0);
+    const int64_t groups = M * (w.K / 32);
+    const at::Tensor *const xs = device_room(a[3], at::kFloat, group == 32 ? groups : M),
+                     *const gs = device_room(a[4], at::kInt, M <= 3 ? groups : 0),  // (read for up to three tokens)
+                     *const y = output_tensor(a[6], M * w.N, &y_dtype);
+    if (!xs || !gs || !y) return none();
     const int8_t *const xp = static_cast<const int8_t *>(xq->data_ptr());
     const float *const sp = static_cast<const float *>(xs->data_ptr());
     const int32_t *const gp = static_cast<const int32_t *>(gs->data_ptr());
@@ -133,12 +145,15 @@ PyObject *quant_act_i8(PyObject *, PyObject *const *a, Py_ssize_t n) {
     if (n != 5 || !small_int(a[1], &group)) return none();
     const at::Tensor *x = device_tensor(a[0], at::kBFloat16, 2);
     if (!x || x->size(0) > INT32_MAX || x->size(1) > INT32_MAX) return none();
-    for (int i = 2; i < 5; ++i)
-        if (!THPVariable_CheckExact(a[i]) || !THPVariable_Unpack(a[i]).is_cuda()) return none();
+    const int64_t M = x->size(0), groups = M * (x->size(1) / 32);
+    const at::Tensor *const xq = device_room(a[2], at::kChar, M * x->size(1)),
+                     *const xs = device_room(a[3], at::kFloat, group == 32 ? groups : M),
+                     *const gs = device_room(a[4], at::kInt, groups);
+    if (!xq || !xs || !gs) return none();
     const uint16_t *const xp = static_cast<const uint16_t *>(x->data_ptr());
-    int8_t *const q = static_cast<int8_t *>(THPVariable_Unpack(a[2]).data_ptr());
-    float *const s = static_cast<float *>(THPVariable_Unpack(a[3]).data_ptr());
-    int32_t *const g = static_cast<int32_t *>(THPVariable_Unpack(a[4]).data_ptr());
+    int8_t *const q = static_cast<int8_t *>(xq->data_ptr());
+    float *const s = static_cast<float *>(xs->data_ptr());
+    int32_t *const g = static_cast<int32_t *>(gs->data_ptr());
     void *const st = current_stream();
     return status_of([&] { return g_quant_act_i8(xp, (int)x->size(0), (int)x->size(1), group, q, s, g, st); });
     END_HANDLE_TH_ERRORS

@@ -137,14 +137,22 @@ def _stream() -> int:
     return _raw_stream(torch.cuda.current_device())
 
 
-def _dev(t: torch.Tensor, dtype, name: str) -> int:
+def _dev(t: torch.Tensor, dtype, name: str, n: int = 0) -> int:
+    """The address of a contiguous device tensor of that type with room for n values."""
     if not t.is_cuda:
         raise ValueError("%s must be a device tensor" % name)
     if t.dtype != dtype:
         raise ValueError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
+    if t.numel() < n:
+        raise ValueError("%s has %d values, %d are needed" % (name, t.numel(), n))
     return t.data_ptr()
+
+
+def _space(t: torch.Tensor, nbytes: int, name: str) -> int:
+    """The address of a contiguous device tensor of any type with room for that many bytes."""
+    return _dev(t, t.dtype, name, -(-nbytes // t.element_size()))
 
 
 def _y_dtype(dtype) -> int:
@@ -217,15 +225,16 @@ def quant_act_i8(x: torch.Tensor, act_group: int = 0, out=None):
                     _check(status, "nvq_quant_act_i8")
                 return xq, xs, gs
     M, K = x.shape
-    if out is not None:
-        pass
-    else:
+    if out is None:
         xq = torch.empty((M, K), dtype=torch.int8, device=x.device)
         xs = torch.empty((M,) if act_group == 0 else (M, K // 32), dtype=torch.float32,
                          device=x.device)
         gs = torch.empty((M, K // 32), dtype=torch.int32, device=x.device)
-    _check(lib().nvq_quant_act_i8(_dev(x, torch.bfloat16, "x"), M, K, act_group, xq.data_ptr(),
-                                  xs.data_ptr(), gs.data_ptr(), _stream()), "nvq_quant_act_i8")
+    G = K // 32
+    _check(lib().nvq_quant_act_i8(_dev(x, torch.bfloat16, "x"), M, K, act_group,
+                                  _space(xq, M * K, "xq"),
+                                  _space(xs, 4 * M * (G if act_group == 32 else 1), "xscale"),
+                                  _space(gs, 4 * M * G, "xgsum"), _stream()), "nvq_quant_act_i8")
     return xq, xs, gs
 
 
@@ -243,7 +252,7 @@ def gemv_w4a16(qweight, scales, x, out_dtype=torch.float32, out: Optional[torch.
     y = out if out is not None else torch.empty((M, N), dtype=out_dtype, device=x.device)
     _check(lib().nvq_gemv_w4a16(_dev(qweight, torch.uint8, "qweight"),
                                 _dev(scales, torch.int16, "scales"), N, K,
-                                _dev(x, torch.bfloat16, "x"), M, _dev(y, y.dtype, "y"),
+                                _dev(x, torch.bfloat16, "x"), M, _dev(y, y.dtype, "y", M * N),
                                 _y_dtype(y.dtype), _stream()), "nvq_gemv_w4a16")
     return y
 
@@ -263,7 +272,7 @@ def gemm_w4a16(qweight, scales, x, out_dtype=torch.float32, out: Optional[torch.
     y = out if out is not None else torch.empty((M, N), dtype=out_dtype, device=x.device)
     _check(lib().nvq_gemm_w4a16(_dev(qweight, torch.uint8, "qweight"),
                                 _dev(scales, torch.int16, "scales"), N, K,
-                                _dev(x, torch.bfloat16, "x"), M, _dev(y, y.dtype, "y"),
+                                _dev(x, torch.bfloat16, "x"), M, _dev(y, y.dtype, "y", M * N),
                                 _y_dtype(y.dtype), _stream()), "nvq_gemm_w4a16")
     return y
 
@@ -278,17 +287,19 @@ def gemv_w4a8(qweight, scales, xq, xscale, xgsum, act_group: int = 0,
                 _check(status, "nvq_gemv_w4a8")
             return out
     N, K = qweight.shape[0], qweight.shape[1] * 2
-    M = xq.shape[0]
-    if xq.shape[1] != K or tuple(scales.shape) != (N, K // 32):
+    M, G = xq.shape[0], K // 32
+    if xq.shape[1] != K or tuple(scales.shape) != (N, G):
         raise ValueError("shape mismatch")
     y = out if out is not None else torch.empty((M, N), dtype=out_dtype, device=xq.device)
     acc = (torch.empty((M, N, K // 32), dtype=torch.int32, device=xq.device)
            if want_acc else None)
     _check(lib().nvq_gemv_w4a8(_dev(qweight, torch.uint8, "qweight"),
                                _dev(scales, torch.int16, "scales"), N, K,
-                               _dev(xq, torch.int8, "xq"), _dev(xscale, torch.float32, "xscale"),
-                               _dev(xgsum, torch.int32, "xgsum"), act_group, M,
-                               _dev(y, y.dtype, "y"), _y_dtype(y.dtype),
+                               _dev(xq, torch.int8, "xq"),
+                               _dev(xscale, torch.float32, "xscale", M * (G if act_group == 32 else 1)),
+                               # (read for up to three tokens)
+                               _dev(xgsum, torch.int32, "xgsum", M * G if M <= 3 else 0), act_group, M,
+                               _dev(y, y.dtype, "y", M * N), _y_dtype(y.dtype),
                                acc.data_ptr() if want_acc else None, _stream()),
            "nvq_gemv_w4a8")
     return (y, acc) if want_acc else y

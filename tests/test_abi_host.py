@@ -168,10 +168,9 @@ def test_the_binding_without_ctypes_leaves_unusual_calls_alone():
         nvq.gemv_w4a16(q, s, x, out=y)
 
 
-def test_the_binding_without_ctypes_leaves_subclasses_of_tensors_alone():
-    """A subclass may say itself where its data is: the ordinary way asks it."""
+def pretended():
+    """A class of tensors that say they are on a device, and have no memory."""
     import torch
-    nvq.lib()
 
     class Own(torch.Tensor):
         @staticmethod
@@ -180,6 +179,14 @@ def test_the_binding_without_ctypes_leaves_subclasses_of_tensors_alone():
 
         __torch_dispatch__ = classmethod(lambda cls, func, types, args=(), kwargs=None: NotImplemented)
 
+    return Own
+
+
+def test_the_binding_without_ctypes_leaves_subclasses_of_tensors_alone():
+    """A subclass may say itself where its data is: the ordinary way asks it."""
+    import torch
+    nvq.lib()
+    Own = pretended()
     q, s = Own((4, 32), torch.uint8), Own((4, 2), torch.int16)
     x, y = Own((1, 64), torch.bfloat16), Own((1, 4), torch.float32)
     xq, xs, gs = Own((1, 64), torch.int8), Own((1,), torch.float32), Own((1, 2), torch.int32)
@@ -188,3 +195,33 @@ def test_the_binding_without_ctypes_leaves_subclasses_of_tensors_alone():
     assert calls.gemv_w4a16(q, s, x, y) is None and calls.gemm_w4a16(q, s, x, y) is None
     assert calls.gemv_w4a8(q, s, xq, xs, gs, 0, y) is None
     assert calls.quant_act_i8(x, 0, xq, xs, gs) is None
+
+
+def test_tensors_that_are_too_small_are_refused():
+    """Outputs kept from a call with fewer tokens or rows, a scale per token where one per group is
+    read: the library gets addresses only, so the binding looks at the sizes."""
+    import torch
+    Own = pretended()
+    M, N, K = 3, 5, 64
+    q, s, x = Own((N, K // 2), torch.uint8), Own((N, 2), torch.int16), Own((M, K), torch.bfloat16)
+    xq, xs, gs = Own((M, K), torch.int8), Own((M, 2), torch.float32), Own((M, 2), torch.int32)
+    y = Own((M, N), torch.float32)
+    for call in (nvq.gemv_w4a16, nvq.gemm_w4a16):
+        with pytest.raises(ValueError, match="y has 10 values, 15 are needed"):
+            call(q, s, x, out=Own((2, N), torch.float32))
+    with pytest.raises(ValueError, match="y has 14 values"):
+        nvq.gemv_w4a8(q, s, xq, xs, gs, 32, out=Own((14,), torch.bfloat16))
+    with pytest.raises(ValueError, match="xscale has 3 values, 6 are needed"):
+        nvq.gemv_w4a8(q, s, xq, Own((M,), torch.float32), gs, 32, out=y)
+    with pytest.raises(ValueError, match="xgsum has 4 values, 6 are needed"):
+        nvq.gemv_w4a8(q, s, xq, xs, Own((2, 2), torch.int32), 0, out=y)
+    few = {"xq": Own((2, K), torch.int8), "xscale": Own((2,), torch.float32), "xgsum": Own((5,), torch.int32)}
+    for i, (name, t) in enumerate(few.items()):
+        out = [xq, xs, gs]
+        out[i] = t
+        with pytest.raises(ValueError, match="%s has %d values" % (name, t.numel())):
+            nvq.quant_act_i8(x, 0, out=out)
+    with pytest.raises(ValueError, match="xscale has 6 values, 24 are needed"):
+        nvq.quant_act_i8(x, 32, out=[xq, Own((M, 2), torch.int8), gs])
+    with pytest.raises(ValueError, match="xgsum must be a device tensor"):
+        nvq.quant_act_i8(x, 0, out=[xq, xs, torch.zeros((M, 2), dtype=torch.int32)])

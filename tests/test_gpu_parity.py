@@ -331,6 +331,43 @@ def test_calls_without_ctypes_equal_those_through_it(monkeypatch):
     assert fast.stream_handle() == nvq._stream()
 
 
+# Outputs and scales that are too small are refused both ways, and nothing is written; larger ones, and
+# code sums that more than three tokens do not read, are taken.
+def test_calls_look_at_the_sizes_of_outputs_and_scales(monkeypatch):
+    M, N, K = 4, 70, 256
+    _, q, s = packed(3060, N, K)
+    qd, sd = to_dev_packed(q, s)
+    x = act(3061, M, K).to(DEV)
+    codes = {g: nvq.quant_act_i8(x, g) for g in (0, 32)}
+    y = torch.full((M * N + 64,), 7.0, device=DEV)
+    few = y[:M * N - 1]
+    fast = nvq._calls
+    xq, xs, gs = codes[32]
+    kept = [torch.full_like(t, 3) for t in (xq, xs, gs)]
+    wrong = [lambda: nvq.gemv_w4a16(qd, sd, x, out=few), lambda: nvq.gemm_w4a16(qd, sd, x, out=few),
+             lambda: nvq.gemv_w4a8(qd, sd, xq, xs, gs, 32, out=few),
+             lambda: nvq.gemv_w4a8(qd, sd, xq, codes[0][1], gs, 32, out=y),
+             lambda: nvq.gemv_w4a8(qd, sd, xq[:1], xs[:1], gs[:1, :7].contiguous(), 32, out=y),
+             lambda: nvq.quant_act_i8(x, 32, out=[kept[0][1:], kept[1], kept[2]]),
+             lambda: nvq.quant_act_i8(x, 32, out=[kept[0], kept[1][1:], kept[2]]),
+             lambda: nvq.quant_act_i8(x, 0, out=[kept[0], kept[1], kept[2][1:]]),
+             lambda: nvq.quant_act_i8(x, 0, out=[kept[0].t(), kept[1], kept[2]])]
+    for i, call in enumerate(wrong):
+        for calls in (fast, None):
+            monkeypatch.setattr(nvq, "_calls", calls)
+            with pytest.raises(ValueError):
+                call()
+    torch.cuda.synchronize()
+    assert bool((y == 7).all()) and all(bool((t == 3).all()) for t in kept)
+    want = nvq.gemv_w4a8(qd, sd, xq, xs, gs, 32)
+    for calls in (fast, None):
+        monkeypatch.setattr(nvq, "_calls", calls)
+        y.fill_(7.0)
+        assert nvq.gemv_w4a8(qd, sd, xq, xs, gs[:1], 32, out=y) is y
+        torch.cuda.synchronize()
+        assert torch.equal(y[:M * N].view(M, N), want) and bool((y[M * N:] == 7).all())
+
+
 # One token: rows per tile go with the rows of the call (one, two, and four and eight with a single
 # group per lane; teams of 64 and of 32 lanes, which a device of 256 compute units has 3072 and 6144
 # of).  A row's bits are those of a short call, on both sides of every step and past the last one;
