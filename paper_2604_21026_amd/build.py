@@ -58,18 +58,23 @@ def _compile(src, force, extra):
 
 def _build_calls(force):
     src = os.path.join(CSRC, "binding.cpp")
-    if (not force and os.path.exists(CALLS)
+    import torch
+    # what the file was built for, besides the sources
+    made_for, stamp = "torch %s python %s\n" % (torch.__version__, sys.version), os.path.join(OBJ, "calls.stamp")
+    if (not force and os.path.exists(CALLS) and os.path.exists(stamp) and open(stamp).read() == made_for
             and os.path.getmtime(CALLS) >= max(os.path.getmtime(src), _newest_header())):
         return
-    import torch
     from torch.utils import cpp_extension
-    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROOT, "include"),
-                                           os.path.join(ROCM, "include")]
+    inc = cpp_extension.include_paths() + [sysconfig.get_paths()["include"], os.path.join(ROCM, "include")]
     abi = int(torch._C._GLIBCXX_USE_CXX11_ABI)
-    subprocess.run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-w", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
-                    "-D_GLIBCXX_USE_CXX11_ABI=%d" % abi] + ["-I" + i for i in inc] + [src, "-o", CALLS]
+    subprocess.run([CXX, "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM",
+                    "-D_GLIBCXX_USE_CXX11_ABI=%d" % abi, '-DNVQ_TORCH_VERSION="%s"' % torch.__version__,
+                    "-I" + os.path.join(ROOT, "include")]
+                   + [a for i in inc for a in ("-isystem", i)] + [src, "-o", CALLS]
                    + ["-L" + d for d in cpp_extension.library_paths()]
                    + ["-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"], check=True)
+    with open(stamp, "w") as f:
+        f.write(made_for)
 
 
 def build(force: bool = False, extra=()) -> str:
@@ -77,9 +82,9 @@ def build(force: bool = False, extra=()) -> str:
     with ThreadPoolExecutor(max_workers=min(8, os.cpu_count() or 1)) as ex:
         calls = ex.submit(_build_calls, force)
         objs = list(ex.map(lambda s: _compile(s, force, extra), sources()))
-        calls.result()
-    subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs,
-                   check=True)
+        subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs,
+                       check=True)
+        calls.result()  # (last: the library works without it)
     return LIB
 
 

@@ -201,4 +201,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__calls() {
+    PyObject *const m = PyModule_Create(&module);
+    // (the caller leaves a module alone that was built for another torch)
+    if (m && PyModule_AddStringConstant(m, "torch_version", NVQ_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -3,10 +3,12 @@ whose latency counts.
 
 Argument marshalling only: torch supplies device memory and the current
 stream, every computation happens in the library's HIP kernels.  There is no
-fallback: if libnvq.so is missing, loading fails with an error.
+fallback: if libnvq.so is missing, loading fails with an error.  Without a
+_calls.so that fits this torch every call goes through ctypes, with a warning.
 """
 import ctypes as C
 import os
+import warnings
 from typing import List, Optional, Sequence
 
 import torch
@@ -49,15 +51,20 @@ class Linear(C.Structure):
 
 
 _lib = None
-_calls = None  # csrc/binding.cpp, once the library is loaded
+_calls = None  # csrc/binding.cpp, once the library is loaded, or None
 
 
 def _load_calls(L):
-    """The calls that count in latency without ctypes; they know the library by its addresses."""
-    if not os.path.exists(CALLS_PATH):
-        raise FileNotFoundError(
-            "%s not found: build it with `python -m paper_2604_21026_amd.build`" % CALLS_PATH)
-    from . import _calls as calls
+    """The calls that count in latency without ctypes; they know the library by its addresses.  None,
+    with a warning, where they are missing or were built for another torch."""
+    try:
+        from . import _calls as calls
+        if calls.torch_version != str(torch.__version__):
+            raise ImportError("built for torch %s" % calls.torch_version)
+    except ImportError as e:
+        warnings.warn("%s cannot be used (%s): calls go through ctypes, which costs 2 to 3 us each; "
+                      "build it with `python -m paper_2604_21026_amd.build`" % (CALLS_PATH, e))
+        return None
     calls.bind(*(C.cast(f, C.c_void_p).value for f in
                  (L.nvq_gemv_w4a16, L.nvq_gemv_w4a8, L.nvq_quant_act_i8, L.nvq_gemm_w4a16)))
     return calls

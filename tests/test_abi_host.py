@@ -225,3 +225,54 @@ def test_tensors_that_are_too_small_are_refused():
         nvq.quant_act_i8(x, 32, out=[xq, Own((M, 2), torch.int8), gs])
     with pytest.raises(ValueError, match="xgsum must be a device tensor"):
         nvq.quant_act_i8(x, 0, out=[xq, xs, torch.zeros((M, 2), dtype=torch.int32)])
+
+
+def load_anew(monkeypatch):
+    monkeypatch.setattr(nvq, "_lib", None)
+    monkeypatch.setattr(nvq, "_calls", None)
+    return nvq.lib()
+
+
+def test_the_library_loads_without_the_native_calls(monkeypatch):
+    """A missing binding, or one built for another torch, costs its latency and nothing else."""
+    import sys
+
+    import paper_2604_21026_amd as package
+    nvq.lib()
+    calls = package._calls
+    with monkeypatch.context() as m:
+        m.setattr(calls, "torch_version", "1.0")
+        with pytest.warns(UserWarning, match="built for torch 1.0"):
+            assert load_anew(m).nvq_status_string(0) == b"ok" and nvq._calls is None
+    with monkeypatch.context() as m:
+        m.delattr(package, "_calls")
+        m.setitem(sys.modules, package.__name__ + "._calls", None)
+        with pytest.warns(UserWarning, match="calls go through ctypes"):
+            assert load_anew(m).nvq_status_string(0) == b"ok" and nvq._calls is None
+    with monkeypatch.context() as m:
+        load_anew(m)
+        assert nvq._calls is calls
+
+
+def test_the_native_calls_are_built_again_for_another_torch(monkeypatch, tmp_path):
+    import torch
+
+    from paper_2604_21026_amd import build
+    built = []
+
+    def run(cmd, **kw):
+        built.append(cmd)
+        open(build.CALLS, "w").close()
+
+    monkeypatch.setattr(build, "OBJ", str(tmp_path))
+    monkeypatch.setattr(build, "CALLS", str(tmp_path / "_calls.so"))
+    monkeypatch.setattr(build.subprocess, "run", run)
+    build._build_calls(False)
+    build._build_calls(False)
+    assert len(built) == 1
+    monkeypatch.setattr(torch, "__version__", "1.0")
+    build._build_calls(False)
+    assert len(built) == 2
+    build._build_calls(False)
+    build._build_calls(True)
+    assert len(built) == 3
