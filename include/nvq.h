@@ -223,7 +223,13 @@ typedef struct nvq_linear {
  * and phase, ~0.4 MB for 129 phases); a plan does that once.  At M = 1 the
  * workspace also reserves that table for the largest grid (13312 bytes per
  * phase).
- * nvq_decode_workspace_bytes returns 0 for invalid arguments.
+ * nvq_decode_workspace_bytes looks at the list alone (no device is touched) and
+ * returns 0 for invalid arguments.  At M > 1 its result has room at the end for
+ * a second input: launches per phase let two phases that follow each other share
+ * their launches if they have the same K and precision and do not depend on each
+ * other.  A workspace that was sized for a list of the same shapes in which all
+ * such neighbours depend on each other is accepted too; phases then share no
+ * launches (the same results, more launches).
  * The persistent kernels wait for each other with bounded spins; a wait that
  * gives up (the grid was not co-resident, say because another stream held
  * compute units) sets a status word in the workspace and leaves the outputs

@@ -54,7 +54,7 @@ struct Workspace {
 // Sizes that depend on the layer list (upper bounds: every entry its own phase).
 struct ListSizes {
     int maxK;
-    int merged_K;        // largest K of phases that share a launch with another, or 0
+    int merged_K;        // largest K of phases that may share a launch with another, or 0
     size_t image_bytes;  // activation images of the streaming kernel (M = 1)
     size_t group_units;  // 16-row tiles of all entries (M > 1)
     size_t group_quant;  // codes + scales + code sums of all W4A8 entries (M > 1)
@@ -115,8 +115,8 @@ Workspace carve(void *base, int M, int n, const ListSizes &ls) {
     w.gquant = take(M > 1 ? ls.group_quant : 0);
     w.mail = reinterpret_cast<uint32_t *>(
         take(M == 1 ? stream_mail_stride(ls.mail_words) * kMailReplicas * 4 : 0));
-    // last: which phases share a launch depends on M and on the operands, so a workspace sized for the
-    // same shapes at another M or for other operands may end here (see nvq_plan_create)
+    // last: which phases may share a launch depends on the operands, so a workspace sized for the same
+    // shapes with other operands may end here (see nvq_plan_create)
     w.bytes_apart = off;
     static_assert(kMaxMerge == 2, "one input besides the first");
     w.prep[1] = input((size_t)ls.merged_K);
@@ -189,17 +189,18 @@ bool same_transform(const nvq_linear &a, const nvq_linear &b) {
            a.h_out_bf16 == b.h_out_bf16;
 }
 
+// The phase that begins with entry i.
+Phase phase_at(const nvq_linear *L, int n, int i) {
+    int j = i + 1;
+    while (j < n && j - i < kMaxSeg && L[j].x_bf16 == L[i].x_bf16 && L[j].K == L[i].K &&
+           L[j].precision == L[i].precision && same_transform(L[i], L[j]))
+        ++j;
+    return {i, j - i};
+}
+
 std::vector<Phase> group_phases(const nvq_linear *L, int n) {
     std::vector<Phase> out;
-    int i = 0;
-    while (i < n) {
-        int j = i + 1;
-        while (j < n && j - i < kMaxSeg && L[j].x_bf16 == L[i].x_bf16 && L[j].K == L[i].K &&
-               L[j].precision == L[i].precision && same_transform(L[i], L[j]))
-            ++j;
-        out.push_back({i, j - i});
-        i = j;
-    }
+    for (int i = 0; i < n; i += out.back().count) out.push_back(phase_at(L, n, i));
     return out;
 }
 
@@ -234,12 +235,22 @@ struct Range {
     uintptr_t lo, hi;
 };
 bool overlap(const Range &a, const Range &b) { return a.lo < b.hi && b.lo < a.hi; }
+// Those of a phase: three operands, or the outputs of its layers and the residual sum.
+struct Ranges {
+    Range r[kMaxSeg + 1];
+    int n = 0;
+    void push_back(const Range &v) { r[n++] = v; }
+    void erase(int i) {
+        for (--n; i < n; ++i) r[i] = r[i + 1];
+    }
+    const Range *begin() const { return r; }
+    const Range *end() const { return r + n; }
+};
 
 // What a phase reads (input, second operand and norm weights) and what it
 // writes (every layer's output, the residual sum; `launched`: also an h_out without x2, which is no
 // output of the phase, but which the input launch of launches per phase stores).
-void phase_ranges(const nvq_linear *L, const Phase &ph, int M, std::vector<Range> *in,
-                  std::vector<Range> *out, bool launched = false) {
+void phase_ranges(const nvq_linear *L, const Phase &ph, int M, Ranges *in, Ranges *out, bool launched = false) {
     const nvq_linear &e0 = L[ph.first];
     const size_t xbytes = (size_t)M * e0.K * 2;
     in->push_back({(uintptr_t)e0.x_bf16, (uintptr_t)e0.x_bf16 + xbytes});
@@ -262,13 +273,13 @@ void phase_ranges(const nvq_linear *L, const Phase &ph, int M, std::vector<Range
 // reads, or another of its outputs.
 int check_phase_hazards(const nvq_linear *L, const std::vector<Phase> &phases, int M) {
     for (const Phase &ph : phases) {
-        std::vector<Range> in, out;
+        Ranges in, out;
         phase_ranges(L, ph, M, &in, &out);
-        for (size_t a = 0; a < out.size(); ++a) {
+        for (int a = 0; a < out.n; ++a) {
             for (const Range &r : in)
-                if (overlap(out[a], r)) return NVQ_ERR_INVALID_ARG;
-            for (size_t b = a + 1; b < out.size(); ++b)
-                if (overlap(out[a], out[b])) return NVQ_ERR_INVALID_ARG;
+                if (overlap(out.r[a], r)) return NVQ_ERR_INVALID_ARG;
+            for (int b = a + 1; b < out.n; ++b)
+                if (overlap(out.r[a], out.r[b])) return NVQ_ERR_INVALID_ARG;
         }
     }
     return NVQ_OK;
@@ -276,7 +287,7 @@ int check_phase_hazards(const nvq_linear *L, const std::vector<Phase> &phases, i
 
 // Whether phases that follow each other depend on each other (`launched`: see phase_ranges).
 bool phases_conflict(const nvq_linear *L, const Phase &a, const Phase &b, int M, bool launched = false) {
-    std::vector<Range> ain, aout, bin, bout;
+    Ranges ain, aout, bin, bout;
     phase_ranges(L, a, M, &ain, &aout, launched);
     phase_ranges(L, b, M, &bin, &bout, launched);
     for (const Range &y : aout) {
@@ -291,6 +302,25 @@ bool phases_conflict(const nvq_linear *L, const Phase &a, const Phase &b, int M,
     return false;
 }
 
+// Whether two phases that follow each other may share launches: the same K and precision, and neither
+// reads or overwrites what the other, or its input launch, stores.
+bool may_share(const nvq_linear *L, const Phase &a, const Phase &b, int M) {
+    return M > 1 && L[a.first].K == L[b.first].K && L[a.first].precision == L[b.first].precision &&
+           !phases_conflict(L, a, b, M, true);
+}
+
+// Largest K of phases that may share launches with a neighbour, or 0.  Which of them do depends on the
+// device (gemv_slice_merges); the size of a workspace does not, and computing it allocates nothing.
+int merged_K(const nvq_linear *L, int n, int M) {
+    int k = 0;
+    for (int i = 0; i < n;) {
+        const Phase a = phase_at(L, n, i);
+        i += a.count;
+        if (i < n && may_share(L, a, phase_at(L, n, i), M)) k = std::max(k, L[a.first].K);
+    }
+    return k;
+}
+
 // Phases that are launched together.
 struct WalkStep {
     int first, count;
@@ -301,18 +331,16 @@ struct WalkStep {
 // with the same K and precision: a launch costs 1.7 us before it does anything, and one phase's
 // workgroups alone leave compute units idle.  In a decode step whose attention runs elsewhere that
 // is q/k/v with o: 8192 x 3072 as one product and one input launch 10.7 us, as two each 18.9.
-// Dependent phases, and with `ordered` all, stay apart; so do phases one of which reads or overwrites
-// what the other's input launch stores (see phase_ranges).
+// Dependent phases, and with `ordered` all, stay apart.
 std::vector<WalkStep> walk_steps(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
                                  bool ordered) {
     std::vector<WalkStep> out;
     for (size_t p = 0; p < phases.size(); ++p) {
         WalkStep s = {(int)p, 1};
-        if (!ordered && M > 1 && p + 1 < phases.size()) {
-            const nvq_linear &a = L[phases[p].first], &b = L[phases[p + 1].first];
-            if (a.K == b.K && a.precision == b.precision &&
-                gemv_slice_merges(make_segs(L, phases[p]), make_segs(L, phases[p + 1]), a.K, M, a.precision, act_group) &&
-                !phases_conflict(L, phases[p], phases[p + 1], M, true))
+        if (!ordered && p + 1 < phases.size()) {
+            const nvq_linear &a = L[phases[p].first];
+            if (may_share(L, phases[p], phases[p + 1], M) &&
+                gemv_slice_merges(make_segs(L, phases[p]), make_segs(L, phases[p + 1]), a.K, M, a.precision, act_group))
                 s.count = 2;
         }
         out.push_back(s);
@@ -322,7 +350,7 @@ std::vector<WalkStep> walk_steps(const nvq_linear *L, const std::vector<Phase> &
 }
 
 // Largest K of the steps of two phases, or 0.
-int merged_K(const nvq_linear *L, const std::vector<Phase> &phases, const std::vector<WalkStep> &steps) {
+int steps_K(const nvq_linear *L, const std::vector<Phase> &phases, const std::vector<WalkStep> &steps) {
     int k = 0;
     for (const WalkStep &s : steps)
         if (s.count > 1) k = std::max(k, L[phases[(size_t)s.first].first].K);
@@ -475,15 +503,15 @@ std::vector<int> phase_deps(const nvq_linear *L, const std::vector<Phase> &phase
                             bool ordered, const std::vector<PhaseLinks> *links = nullptr) {
     const size_t P = phases.size();
     std::vector<int> deps(P, -1);
-    std::vector<std::vector<Range>> xin(P), yout(P);  // what a phase reads and writes
+    std::vector<Ranges> xin(P), yout(P);  // what a phase reads and writes
     for (size_t p = 0; p < P; ++p) {
         phase_ranges(L, phases[p], M, &xin[p], &yout[p]);
         if (!links) continue;
         const nvq_linear &e0 = L[phases[p].first];
         auto drop = [&](const uint16_t *operand) {
-            for (size_t i = 0; i < xin[p].size(); ++i)
-                if (xin[p][i].lo == (uintptr_t)operand) {
-                    xin[p].erase(xin[p].begin() + (long)i);
+            for (int i = 0; i < xin[p].n; ++i)
+                if (xin[p].r[i].lo == (uintptr_t)operand) {
+                    xin[p].erase(i);
                     return;
                 }
         };
@@ -970,8 +998,7 @@ extern "C" size_t nvq_decode_workspace_bytes(const nvq_linear *layers, int n, in
                                              int act_group) {
     nvq::ListSizes ls;
     if (nvq::check_layers(layers, n, M, act_group, &ls) != NVQ_OK) return 0;
-    const std::vector<nvq::Phase> phases = nvq::group_phases(layers, n);
-    ls.merged_K = nvq::merged_K(layers, phases, nvq::walk_steps(layers, phases, M, act_group, false));
+    ls.merged_K = nvq::merged_K(layers, n, M);
     return nvq::carve(nullptr, M, n, ls).bytes;
 }
 
@@ -985,10 +1012,7 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
     const int rc = check_layers(layers, n, M, act_group, &ls);
     if (rc != NVQ_OK) return rc;
     if (!workspace || !aligned(workspace, 256)) return NVQ_ERR_WORKSPACE;
-    {
-        const std::vector<Phase> listed = group_phases(layers, n);
-        ls.merged_K = merged_K(layers, listed, walk_steps(layers, listed, M, act_group, false));
-    }
+    ls.merged_K = merged_K(layers, n, M);
     const Workspace ws = carve(workspace, M, n, ls);
     if (workspace_bytes < ws.bytes_apart) return NVQ_ERR_WORKSPACE;
     nvq_plan *pl = new (std::nothrow) nvq_plan();
@@ -1373,7 +1397,7 @@ extern "C" int nvq_decode_linears_static(const nvq_linear *layers, int n, int M,
     // the part of the workspace that launches per phase use; phases share launches if there is room
     // for both inputs
     std::vector<WalkStep> steps = walk_steps(layers, phases, M, act_group, false);
-    const int slot_K[kMaxMerge] = {ls.maxK, merged_K(layers, phases, steps)};
+    const int slot_K[kMaxMerge] = {ls.maxK, steps_K(layers, phases, steps)};
     Workspace ws = {};
     size_t off[kMaxMerge][4], bytes = 0;
     for (int i = 0; i < kMaxMerge; ++i) {

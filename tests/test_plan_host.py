@@ -461,3 +461,28 @@ def test_a_residual_output_without_a_second_input_keeps_neighbours_apart(prec):
     # lists that were accepted stay accepted: such an h_out over its own phase's input
     L, words = [lin(x, h_out=x, **norm)], (nvq.C.c_int32 * 64)()
     assert nvq.lib().nvq_plan_describe((nvq.Linear * 1)(*L), 1, M, 0, 0, 256, words, 64) == 0
+
+
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+@pytest.mark.parametrize("M,group,K,N", [(2, 32, 96, 33), (3, 32, 96, 33), (2, 0, 16416, 24), (8, 0, 4096, 512),
+                                         (32, 32, 288, 70)])
+def test_the_workspace_has_room_for_a_second_input_whatever_the_device(M, group, K, N, prec):
+    """Which phases share launches depends on the device's compute units too (a few rows and up to three
+    tokens go to another kernel).  The size does not: it has room for any two neighbours of the same K
+    and precision that do not depend on each other, however many rows they have."""
+    def pair(rows, x2, **kw):
+        return [linear(a, K, K, x, y=y, y_f32=False, prec=prec, M=M),
+                linear(a, rows, kw.get("K2", K), x2, prec=kw.get("prec2", prec), M=M)]
+
+    a = Arena()
+    x, other, y = (a.take(M * (K + 32) * 2) for _ in range(3))
+    round_up = lambda v: (v + 255) // 256 * 256
+    second = round_up(M * K) + 2 * round_up(M * K // 32 * 4)
+    apart = workspace_bytes(pair(N, y), M, group)
+    assert workspace_bytes(pair(N, other), M, group) == apart + second
+    assert workspace_bytes(pair(N + 20000, other), M, group) - workspace_bytes(pair(N + 20000, y), M, group) == second
+    assert workspace_bytes(pair(N, other), 1, group) == workspace_bytes(pair(N, y), 1, group)
+    # another K or precision never shares: as large as if the second depended on the first
+    for kw in (dict(K2=K + 32), dict(prec2=1 - prec)):
+        dependent = workspace_bytes(pair(N, y, **kw), M, group)
+        assert workspace_bytes(pair(N, other, **kw), M, group) == dependent
