@@ -380,6 +380,16 @@ int nvq_plan_describe_skips(const nvq_linear *layers, int n, int M, int act_grou
  */
 int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M, int act_group, int flags,
                               int32_t *out, int out_words);
+/*
+ * nvq_plan_describe_steps -- likewise the launches per phase (what a plan runs
+ * that is neither the batch-1 persistent kernel nor grouped, and what
+ * nvq_decode_linears_static runs if its scratch has room): out[0] = steps, then
+ * 2 words per step: its first phase, and its phases (2: they share their input
+ * and product launches).  Which phases share depends on the current device's
+ * compute units (256 without a device).
+ */
+int nvq_plan_describe_steps(const nvq_linear *layers, int n, int M, int act_group, int flags,
+                            int32_t *out, int out_words);
 void nvq_plan_destroy(nvq_plan *plan);
 
 /*

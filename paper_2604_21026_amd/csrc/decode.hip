@@ -1305,6 +1305,25 @@ extern "C" int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M,
     return NVQ_OK;
 }
 
+extern "C" int nvq_plan_describe_steps(const nvq_linear *layers, int n, int M, int act_group, int flags,
+                                       int32_t *out, int out_words) {
+    using namespace nvq;
+    if (!out || out_words < 1 || (flags & ~NVQ_PLAN_ORDERED)) return NVQ_ERR_INVALID_ARG;
+    ListSizes ls;
+    const int rc = check_layers(layers, n, M, act_group, &ls);
+    if (rc != NVQ_OK) return rc;
+    const std::vector<Phase> phases = group_phases(layers, n);
+    if (check_phase_hazards(layers, phases, M) != NVQ_OK) return NVQ_ERR_INVALID_ARG;
+    const std::vector<WalkStep> steps = walk_steps(layers, phases, M, act_group, (flags & NVQ_PLAN_ORDERED) != 0);
+    if ((size_t)out_words < 1 + 2 * steps.size()) return NVQ_ERR_WORKSPACE;
+    *out++ = (int32_t)steps.size();
+    for (const WalkStep &s : steps) {
+        *out++ = s.first;
+        *out++ = s.count;
+    }
+    return NVQ_OK;
+}
+
 extern "C" int nvq_plan_trace(nvq_plan *pl, uint64_t *buf, size_t bytes) {
     if (!pl) return NVQ_ERR_INVALID_ARG;
     const size_t one = (size_t)pl->nphase * nvq::kStreamTraceSlots * 8;

@@ -29,7 +29,7 @@ EXPORTS = (
     "nvq_decode_status", "nvq_decode_linears_static",
     "nvq_plan_create", "nvq_plan_run", "nvq_plan_info", "nvq_plan_status", "nvq_plan_trace",
     "nvq_plan_destroy", "nvq_plan_describe", "nvq_plan_describe_batches",
-    "nvq_plan_describe_skips",
+    "nvq_plan_describe_skips", "nvq_plan_describe_steps",
     "nvq_dequant_bf16", "nvq_gemm_w4a16", "nvq_rms_norm_bf16", "nvq_silu_mul_bf16", "nvq_precision_from_scores", "nvq_token_norms", "nvq_mcap_scores", "nvq_stream_read", "nvq_stream_copy",
 )
 
@@ -106,6 +106,7 @@ def lib() -> C.CDLL:
     L.nvq_plan_describe.argtypes = [vp, ci, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_describe_batches.argtypes = [vp, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_describe_skips.argtypes = [vp, ci, ci, ci, ci, ci, vp, sz, vp]
+    L.nvq_plan_describe_steps.argtypes = [vp, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_destroy.restype = None
     L.nvq_precision_from_scores.argtypes = [vp, ci, C.c_double, C.c_double, vp]
     L.nvq_token_norms.argtypes = [vp, ci, vp, ci, ci, ci, vp, vp]
@@ -431,6 +432,17 @@ def plan_describe_batches(linears: Sequence[Linear], M: int, ordered: bool = Fal
                         parts=nparts, cuts=list(o[6:6 + nparts + 1]),
                         cut_phases=list(o[15:15 + nparts + 1])))
     return bool(out[1]), res
+
+
+def plan_describe_steps(linears: Sequence[Linear], M: int, act_group: int = 0, ordered: bool = False):
+    """Host-side planning of launches per phase (no device needed): [(first phase, phases)] of the
+    steps; two phases share their launches."""
+    n = len(linears)
+    arr = (Linear * max(n, 1))(*linears)
+    out = (C.c_int32 * (1 + 2 * n))()
+    _check(lib().nvq_plan_describe_steps(C.byref(arr), n, M, act_group, PLAN_ORDERED if ordered else 0, out,
+                                         1 + 2 * n), "nvq_plan_describe_steps")
+    return [(out[1 + 2 * i], out[2 + 2 * i]) for i in range(out[0])]
 
 
 DESCRIBE_FIELDS = ("first", "count", "wait", "publish", "rows", "rows_base", "rows_extra",

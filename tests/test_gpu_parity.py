@@ -1329,7 +1329,8 @@ def test_prepared_inputs_equal_the_standalone_calls(M, group, K):
 # Two phases that follow each other and do not depend on each other share their launches.  q (two
 # matrices) and o: independent; o and r: r reads what o wrote; r and w: w overwrites what r read;
 # five matrices on one input (two phases, one preparation) and one more phase; another K.  Sizes:
-# chains by columns and by groups, one and two row tiles per workgroup, ragged rows and K.
+# chains by columns and by groups, one and two row tiles per workgroup, ragged rows and K.  (Three
+# tokens and few rows go to a kernel that takes one phase at a time.)
 @pytest.mark.parametrize("M,group,K,N", [(2, 0, 256, 40), (3, 32, 96, 33), (8, 0, 4096, 512), (8, 32, 1056, 4100),
                                          (17, 0, 512, 9000), (32, 32, 288, 70), (5, 0, 16416, 24)])
 @pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
@@ -1384,6 +1385,9 @@ def test_phases_that_share_a_launch_equal_single_calls(M, group, K, N, prec):
                 assert torch.equal(e["y"], y), (what, i, int((e["y"] != y).sum()))
 
     dl = nvq.DecodeList(entries, M, group)
+    steps = nvq.plan_describe_steps([dl.arr[i] for i in range(dl.n)], M, group)
+    assert [first for first, count in steps if count == 2] == ([] if M == 3 else [0, 5])
+    assert dl.plan_info() == dict(streaming=False, grouped=False, persistent_grouped=False, phases=8, waits=0)
     for rep in range(2):
         dl.run_plan()
         check("plan")

@@ -458,6 +458,10 @@ def test_a_residual_output_without_a_second_input_keeps_neighbours_apart(prec):
     assert workspace_bytes([lin(x, K, y=h, y_f32=False), lin(x2, h_out=h, **norm)], M) == apart
     assert workspace_bytes([lin(x, h_out=h, **norm), lin(x2, h_out=h, **norm)], M) == apart
     assert workspace_bytes([lin(x, h_out=h, **norm), lin(x2, K, y=h, y_f32=False)], M) == apart
+    steps = lambda *layers: nvq.plan_describe_steps(list(layers), M)
+    assert steps(lin(x, h_out=h, **norm), lin(x2)) == [(0, 2)]
+    assert steps(lin(x, h_out=h, **norm), lin(h)) == [(0, 1), (1, 1)]
+    assert steps(lin(x), lin(x2, h_out=x, **norm)) == [(0, 1), (1, 1)]
     # lists that were accepted stay accepted: such an h_out over its own phase's input
     L, words = [lin(x, h_out=x, **norm)], (nvq.C.c_int32 * 64)()
     assert nvq.lib().nvq_plan_describe((nvq.Linear * 1)(*L), 1, M, 0, 0, 256, words, 64) == 0
@@ -486,3 +490,30 @@ def test_the_workspace_has_room_for_a_second_input_whatever_the_device(M, group,
     for kw in (dict(K2=K + 32), dict(prec2=1 - prec)):
         dependent = workspace_bytes(pair(N, y, **kw), M, group)
         assert workspace_bytes(pair(N, other, **kw), M, group) == dependent
+
+
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+def test_neighbours_that_share_launches(prec):
+    """Two at a time, of the same K and precision, that do not depend on each other and are added in the
+    same order; five layers on one input are two phases; not at one token and not in an ordered plan."""
+    M, K = 8, 1024
+    a = Arena()
+    xs = [a.take(32 * K * 2) for _ in range(6)]
+    lin = lambda x, rows=96, **kw: linear(a, rows, kw.pop("K", K), x, prec=kw.pop("prec", prec), M=32, **kw)
+    steps = nvq.plan_describe_steps
+    three = [lin(xs[0]), lin(xs[1]), lin(xs[2])]
+    assert steps(three, M) == [(0, 2), (2, 1)] and steps(three + [lin(xs[3])], 17) == [(0, 2), (2, 2)]
+    assert steps(three, M, ordered=True) == steps(three, 1) == [(0, 1), (1, 1), (2, 1)]
+    assert steps([lin(xs[0], K=K // 2), lin(xs[1])], M) == [(0, 1), (1, 1)]
+    assert steps([lin(xs[0], prec=1 - prec), lin(xs[1])], M) == [(0, 1), (1, 1)]
+    assert steps([lin(xs[0]) for _ in range(5)], M) == [(0, 2)]
+    y = a.take(32 * K * 2)
+    assert steps([lin(xs[0], K, y=y, y_f32=False), lin(y), lin(xs[1])], M) == [(0, 1), (1, 2)]
+    # K no whole number of columns: sixty-four chains whatever the rows
+    assert steps([lin(xs[0], K=96), lin(xs[1], 20000, K=96)], M) == [(0, 2)]
+    # long K: sixteen chains for few rows, eight for many
+    assert steps([lin(xs[0], K=4096), lin(xs[1], 20000, K=4096)], M) == [(0, 1), (1, 1)]
+    # few rows and up to three tokens: a wave per row, where the order of the additions allows
+    assert steps([lin(xs[0], K=96), lin(xs[1], K=96)], 3) == [(0, 1), (1, 1)]
+    assert nvq.lib().nvq_plan_describe_steps((nvq.Linear * 3)(*three), 3, M, 0, 0, (nvq.C.c_int32 * 4)(), 4) == 6
+    assert nvq.lib().nvq_plan_describe_steps((nvq.Linear * 3)(*three), 3, M, 0, 7, (nvq.C.c_int32 * 9)(), 9) == 1
