@@ -281,8 +281,11 @@ int nvq_decode_linears_static(const nvq_linear *layers, int n, int M, int act_gr
  *                    the walk is issued as grouped small-batch launches (two
  *                    or three per batch of independent phases; 3: the product
  *                    of at least one batch runs as a persistent grid, which
- *                    needs every K a multiple of 512, 16-byte aligned scale
- *                    rows and enough work for the device),
+ *                    needs every K a multiple of 512 and 16-byte aligned scale
+ *                    rows, and is taken by estimates of its time; up to 16 tokens
+ *                    also by batches of fewer than four phases, of less than 1.5
+ *                    MB of weights, or of up to eight phases or 50 MB with one of
+ *                    K >= 6144, whatever the estimates),
  *                    0 for launches per phase;
  *                    waits = number of phases that wait for an earlier phase,
  *                    through flags or for mail (grouped launches: number of

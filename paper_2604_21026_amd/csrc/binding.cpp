@@ -3,9 +3,10 @@
 // token: 6.4 us a call, of which the launch takes 3.6 and the kernel 2.7).
 //
 // Only the ordinary case is served here: tensors (no subclasses, which may say themselves where their
-// data is) of the expected types on a device, contiguous, with fitting shapes.  For everything else a function returns None and the caller takes its own
-// way, which names what is wrong.  The library's entry points are handed over by address (bind);
-// a call returns their status.
+// data is) of the expected types on a device, contiguous, with fitting shapes and room for what is
+// written and read.  For everything else a function returns None and the caller takes its own way, which
+// names what is wrong.  The library's entry points are handed over by address (bind); a call returns their
+// status.
 #include <Python.h>
 
 #include <c10/hip/HIPStream.h>

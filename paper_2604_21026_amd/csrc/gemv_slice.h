@@ -217,7 +217,8 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
 
     typedef const __attribute__((address_space(4))) SlicePhase<DEBUG> CPhase;
     typedef const __attribute__((address_space(4))) uint32_t CWord;
-    // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch)
+    // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch; it is
+    // the kernel's only parameter, so the segment begins with it)
     CPhase *phase = (CPhase *)__builtin_amdgcn_kernarg_segment_ptr();
     int unit = (int)blockIdx.x;
     if (NP > 1) {

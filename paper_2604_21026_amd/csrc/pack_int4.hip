@@ -28,7 +28,9 @@ constexpr int kPackXcds = 8;
 // First group of a workgroup's i-th load.  Workgroups b and b + 8 run on one XCD; a workgroup takes two
 // runs of 64 groups that lie eight apart, so that run r is written by XCD r mod 8: the one whose
 // workgroup of nvq_dequant_bf16 (64 groups each) reads it next, from its own L2.  (With 128 groups in a
-// row 4096 x 4096 packed and unpacked took 22.6 us, with two loads in flight, 64 in a row, 20.2.)
+// row 4096 x 4096 packed and unpacked took 22.6 us, with two loads in flight, 64 in a row, 20.2: passes
+// repeated over the same buffers; a first pass over new ones gains nothing.  That workgroups go to XCDs in
+// turn is what was observed: where they do not, the bytes are the same and the gain is gone.)
 __device__ __forceinline__ int64_t pack_first(int64_t b, int i) {
     const int64_t run = b / kPackXcds * (2 * kPackXcds) + b % kPackXcds + (i >> 1) * kPackXcds;
     return run * 64 + (i & 1) * 32;

@@ -287,7 +287,8 @@ template <int Q, int NCH, int NP>
 __global__ __launch_bounds__(kPrepThreads) void prep_token_kernel(PrepArgs<NP>) {
     __shared__ float red[2][16];
     __shared__ float part[kPrepThreads * NCH];
-    // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch)
+    // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch; it is
+    // the kernel's only parameter, so the segment begins with it)
     const __attribute__((address_space(4))) PrepArgs<NP> &A =
         *(const __attribute__((address_space(4))) PrepArgs<NP> *)__builtin_amdgcn_kernarg_segment_ptr();
     const int second = NP > 1 && (int)blockIdx.x >= A.M ? 1 : 0, m = (int)blockIdx.x - (second ? A.M : 0);
