@@ -47,17 +47,18 @@ __device__ __forceinline__ float chunk_absmax(const uint4 &v) {
 }
 
 // The codes of eight values with scale s, packed, and their sum.  One division per scale instead
-// of one per value (some ten instructions each): t = x * fl(1 / s) is within 2^-15 of the
-// quotient fl(x / s) (|x / s| <= 127: two roundings of 2^-24 relative, and the quotient's own),
-// so unless t lies within 2^-14 of a half-integer rounding t gives the integer that rounding
-// the quotient gives.  Where one of the eight does, and where the scale is too small for its
-// reciprocal, the lane divides.
+// of one per value (some ten instructions each): t = x * fl(1 / s), corrected once by its exact remainder,
+// is the quotient fl(x / s) to the bit for every bf16 x of at most the maximum that s = fl(amax / 127)
+// comes from (all 128 significands of amax with all 128 of x; tests/test_quant_by_reciprocal.py).
+// Without a branch: x / s lies on a tie for every x = amax / 2, so that nearly every wave had some lane
+// that divided where only values near a tie were divided (a scale per group, 8 x 2048: 2.5 us, with a
+// division per value 2.1, now 1.9; a list of ten phases through the rings, 3 tokens: 52.8, 48.1, now 47.1).
+// Where the scale is too small for that, zero or infinite, the lane divides.
 __device__ __forceinline__ uint2 quant8(const uint4 &v, float s, int *sum) {
     const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-    const bool by_reciprocal = s >= 0x1p-100f;
+    const bool by_reciprocal = s >= 0x1p-90f && s < 0x1p127f;
     const float inv_s = by_reciprocal ? 1.0f / s : 0.0f;
     float x[8], r[8];
-    bool redo = !by_reciprocal;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         x[2 * i] = bf16_bits_to_float(w[i] & 0xffffu);
@@ -66,10 +67,9 @@ __device__ __forceinline__ uint2 quant8(const uint4 &v, float s, int *sum) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float t = x[i] * inv_s;
-        r[i] = rintf(t);
-        redo = redo || fabsf(t - r[i]) > 0.5f - 0x1p-14f;
+        r[i] = rintf(fmaf(fmaf(-t, s, x[i]), inv_s, t));
     }
-    if (redo) {
+    if (!by_reciprocal) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) r[i] = s != 0.0f ? rintf(x[i] / s) : 0.0f;
     }

@@ -153,7 +153,7 @@ def _dev(t: torch.Tensor, dtype, name: str, n: int = 0) -> int:
         raise ValueError("%s must be %s, got %s" % (name, dtype, t.dtype))
     if not t.is_contiguous():
         raise ValueError("%s must be contiguous" % name)
-    if t.numel() < n:
+    if n and t.numel() < n:
         raise ValueError("%s has %d values, %d are needed" % (name, t.numel(), n))
     return t.data_ptr()
 

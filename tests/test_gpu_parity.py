@@ -274,6 +274,30 @@ def test_gemv_w4a8_acc_bit_exact_and_output(N, K, M, group):
     assert np_ref.rel_l2(y.cpu().numpy(), y_r) < 1e-5        # what fp32 accumulation gives
 
 
+# Every significand of a value under every significand of the maximum, down to quotients that round to
+# zero: the codes of the division.
+@pytest.mark.parametrize("group", [0, 32])
+@pytest.mark.parametrize("first", [0, 32, 64, 96])
+def test_quant_act_every_pair_of_significands(first, group):
+    say("quant significands", first, group)
+    sig = (1 + np.arange(128, dtype=np.float32) / 128)
+    x = np.zeros((32, 128 * 10 // 31 + 1, 32), np.float32)
+    vals = np.concatenate([sig * np.float32(2.0 ** -e) for e in range(10)])
+    vals = np.resize(vals, x.shape[1] * 31).reshape(x.shape[1], 31)
+    x[:, :, 1:] = vals * np.where(np.arange(31) % 2, -1, 1).astype(np.float32)
+    amax = sig[first:first + 32, None] * np.float32(2)  # above every value
+    x[:, :, 0] = amax
+    s = amax / np.float32(127)
+    want = np.rint(x / s[:, :, None]).astype(np.int8).reshape(32, -1)
+    xb = torch.from_numpy(x.reshape(32, -1)).to(torch.bfloat16)
+    assert np.array_equal(xb.float().numpy(), x.reshape(32, -1))
+    xq, xs, gs = nvq.quant_act_i8(xb.to(DEV), group)
+    torch.cuda.synchronize()
+    assert np.array_equal(xq.cpu().numpy(), want)
+    assert bool((xs.cpu().reshape(32, -1) == torch.from_numpy(s)).all())
+    assert np.array_equal(gs.cpu().numpy(), want.reshape(32, -1, 32).sum(2, dtype=np.int32))
+
+
 # The calls with an output given go through csrc/binding.cpp where everything is as expected: the same
 # bits as through ctypes, the same stream, and the same errors for what is not.
 def test_calls_without_ctypes_equal_those_through_it(monkeypatch):
