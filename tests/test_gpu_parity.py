@@ -101,8 +101,8 @@ def test_pack_int4_edge_values():
     assert np_ref.unpack_codes(q.cpu().numpy())[0, :12].tolist() == [7, 2, 4, 0, 0, 2, -2, -4, 6, -6, 4, 6]
 
 
-# A workgroup packs two runs of 64 groups that lie eight runs apart: a last span of 1024 groups that
-# ends inside the first or the second run of a workgroup, or at an edge of either; nothing past the end.
+# Small matrices (a run of 64 groups per workgroup): ends inside a run or at its edge, one and many
+# workgroups; nothing past the end.
 @pytest.mark.parametrize("G", [1, 63, 64, 65, 511, 512, 513, 577, 1023, 1024, 1025, 1537])
 def test_pack_runs_of_groups(G):
     say("pack runs", G)
@@ -141,9 +141,36 @@ def test_dequant_bf16_every_nibble_and_extreme_scales():
     assert np.array_equal(u16(out), oracle.dequant_bf16(q, s))
 
 
+# Up to eight workgroups of 64 groups per compute unit pack with two loads in flight, beyond that with
+# four, in spans of 1024 groups: the line (of a device with 256 compute units), and ends inside the first
+# and the second run of a workgroup and at the edges of both.  Ties and their neighbours among the groups.
+@pytest.mark.parametrize("over", [0, 1, 63, 64, 511, 513, 577, 1024, 1025])
+def test_pack_with_two_and_four_loads(over):
+    G = 64 * 8 * torch.cuda.get_device_properties(0).multi_processor_count + over
+    say("pack two and four loads", G)
+    rng = np.random.default_rng(3200)
+    W = rng.normal(0, 0.02, (997, 32)).astype(np.float32)
+    s = (2.0 ** rng.integers(-14, 6, 997) * (1 + rng.integers(0, 1024, 997) / 1024)).astype(np.float16).astype(np.float32)
+    half = rng.integers(-15, 14, (997, 32)).astype(np.float32) * np.float32(0.5) * s[:, None]
+    beside = half * (1 + rng.integers(-3, 4, half.shape).astype(np.float32) * np.float32(2.0 ** -22))
+    kind = np.arange(997) % 4
+    W[kind == 1], W[kind == 2] = half[kind == 1], beside[kind == 2]
+    W[kind % 3 != 0, 0] = (7 * s)[kind % 3 != 0]
+    q_ref, s_ref = oracle.pack_int4(W)
+    at = np.arange(G) % 997
+    q = torch.full(((G + 2048) * 16,), 0xa5, dtype=torch.uint8, device=DEV)
+    sc = torch.full((G + 2048,), 0x5a5a, dtype=torch.int16, device=DEV)
+    Wd = torch.from_numpy(W).to(DEV)[torch.from_numpy(at).to(DEV)].contiguous()
+    assert nvq.lib().nvq_pack_int4(Wd.data_ptr(), G, 32, 32, q.data_ptr(), sc.data_ptr(), nvq._stream()) == 0
+    torch.cuda.synchronize()
+    assert np.array_equal(q[:G * 16].cpu().numpy().reshape(G, 16), q_ref.reshape(997, 16)[at])
+    assert np.array_equal(u16(sc[:G]).reshape(G), s_ref.reshape(997)[at])
+    assert bool((q[G * 16:] == 0xa5).all()) and bool((sc[G:] == 0x5a5a).all())
+
+
 # Packing: groups whose quotients are exact ties, lie a few units beside one, or reach the bounds,
 # scales from subnormal halves on, groups of zeros, the last group of a workgroup and of the matrix
-# (128 groups per workgroup): the oracle's bytes.
+# (64 groups per workgroup): the oracle's bytes.
 @pytest.mark.parametrize("N,K", [(1, 32), (4, 1024), (43, 96), (65, 2048)])
 def test_pack_rounds_like_the_division(N, K):
     rng = np.random.default_rng(2900 + N)
