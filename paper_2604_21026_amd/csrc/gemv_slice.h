@@ -122,35 +122,37 @@ struct SliceBlock {
 // launch.  So they are few, there are two phases only where a launch has two, and the kernel asks
 // for all lines of a phase together (one after the other, where they are needed, the last of
 // them, where the results go, was waited for when everything else was done; W4A16, 4096 x 4096 at 8
-// tokens: 5.1 us against 4.5).
-template <bool DEBUG>
+// tokens: 5.1 us against 4.5).  SEGS: room for kMaxSeg matrices, or for the one of a single call, which
+// then has fewer lines of them and no matrix to select for its rows and results (W4A16, 16 tokens: 4096 x
+// 4096 4.6 us with four, 4.2 with one, 5000 x 96 3.8 and 3.1; 3 tokens, 300 x 1024 2.7 and 2.5).
+template <int SEGS, bool DEBUG>
 struct SlicePhase {
-    const uint4 *qw[kMaxSeg];
-    const uint16_t *sc[kMaxSeg];
-    void *y[kMaxSeg];
-    int row_end[kMaxSeg];  // of matrices that are not there: as the last one's
+    const uint4 *qw[SEGS];
+    const uint16_t *sc[SEGS];
+    void *y[SEGS];
+    int row_end[SEGS];  // of matrices that are not there: as the last one's
     const char *x;
     const float *xscale;
     int G, M;
     int units;       // workgroups
     uint32_t bf16;   // bit i: matrix i has bf16 results
-    int32_t *dbg[DEBUG ? kMaxSeg : 1];
+    int32_t *dbg[DEBUG ? SEGS : 1];
 };
 // What of a phase a workgroup keeps: where its rows are and their results go.
-template <bool DEBUG>
+template <int SEGS, bool DEBUG>
 struct SliceRows {
-    const uint4 *qw[kMaxSeg];
-    const uint16_t *sc[kMaxSeg];
-    void *y[kMaxSeg];
-    int row_end[kMaxSeg];
+    const uint4 *qw[SEGS];
+    const uint16_t *sc[SEGS];
+    void *y[SEGS];
+    int row_end[SEGS];
     uint32_t bf16;
-    int32_t *dbg[DEBUG ? kMaxSeg : 1];
+    int32_t *dbg[DEBUG ? SEGS : 1];
 };
-template <int NP, bool DEBUG>
+template <int NP, int SEGS, bool DEBUG>
 struct SliceArgs {
-    SlicePhase<DEBUG> phase[NP];  // the first phase's workgroups come first
+    SlicePhase<SEGS, DEBUG> phase[NP];  // the first phase's workgroups come first
 };
-static_assert(sizeof(SlicePhase<false>) == 152 && kMaxMerge == 2, "three lines; one comparison finds a workgroup's phase");
+static_assert(sizeof(SlicePhase<kMaxSeg, false>) == 152 && kMaxMerge == 2, "three lines; one comparison finds a workgroup's phase");
 
 // A row of a phase (past the last one: the last one again, not valid).  Selected, not indexed, as in
 // locate_row.
@@ -162,11 +164,11 @@ struct SliceRow {
     int N, n;
     bool bf16, valid;
 };
-template <bool DEBUG>
-__device__ __forceinline__ SliceRow slice_row(const SliceRows<DEBUG> &P, int row, int G) {
+template <int SEGS, bool DEBUG>
+__device__ __forceinline__ SliceRow slice_row(const SliceRows<SEGS, DEBUG> &P, int row, int G) {
     SliceRow r;
-    r.valid = row < P.row_end[kMaxSeg - 1];
-    if (!r.valid) row = P.row_end[kMaxSeg - 1] - 1;
+    r.valid = row < P.row_end[SEGS - 1];
+    if (!r.valid) row = P.row_end[SEGS - 1] - 1;
     int first = 0, end = P.row_end[0];
     r.qw = P.qw[0];
     r.sc = P.sc[0];
@@ -174,7 +176,7 @@ __device__ __forceinline__ SliceRow slice_row(const SliceRows<DEBUG> &P, int row
     r.dbg = P.dbg[0];
     r.bf16 = (P.bf16 & 1u) != 0;
 #pragma unroll
-    for (int i = 1; i < kMaxSeg; ++i) {
+    for (int i = 1; i < SEGS; ++i) {
         const uint4 *const qw = P.qw[i];
         const uint16_t *const sc = P.sc[i];
         void *const y = P.y[i];
@@ -196,8 +198,8 @@ __device__ __forceinline__ SliceRow slice_row(const SliceRows<DEBUG> &P, int row
     return r;
 }
 
-template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, bool DEBUG>
-__global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>) {
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, int SEGS, bool DEBUG>
+__global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, DEBUG>) {
     typedef Act<PREC> A;
     typedef SliceBlock<PREC, PG, TOK, RT, NG, SCB> B;
     constexpr bool TAIL = SCB != 16;
@@ -215,15 +217,16 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     constexpr int kRed = kByGroup ? W * C * kRedStride * 4 : V * kTile * 256;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing > kRed ? kRing : kRed];
 
-    typedef const __attribute__((address_space(4))) SlicePhase<DEBUG> CPhase;
+    typedef const __attribute__((address_space(4))) SlicePhase<SEGS, DEBUG> CPhase;
     typedef const __attribute__((address_space(4))) uint32_t CWord;
     // (through the segment's pointer: indexed as a parameter the struct would be copied to scratch; it is
     // the kernel's only parameter, so the segment begins with it)
     CPhase *phase = (CPhase *)__builtin_amdgcn_kernarg_segment_ptr();
     int unit = (int)blockIdx.x;
-    if (NP > 1) {
+    if constexpr (NP > 1) {
+        static_assert(SEGS == kMaxSeg, "the lines asked for here");
         CWord *a = (CWord *)phase;
-        constexpr int kNext = sizeof(SlicePhase<DEBUG>) / 4;
+        constexpr int kNext = sizeof(SlicePhase<SEGS, DEBUG>) / 4;
         const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[kNext], l4 = a[kNext + 16], l5 = a[NP * kNext - 1];
         const int units = phase->units;
         asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3), "s"(l4), "s"(l5), "s"(units));
@@ -236,9 +239,9 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     // the fields' addresses and load again, once in front of the first weights and once in front of
     // every store (with a scale per group, W4A8: 9361 x 7232 at 25 tokens 35.1 us, so 32.3, 29039 x 544 at
     // 16 27.4 and 24.7; four 8B blocks as a chain at 8 tokens 196 and 190, four of 3B at 4 147 and 139).
-    SliceRows<DEBUG> S;
+    SliceRows<SEGS, DEBUG> S;
 #pragma unroll
-    for (int i = 0; i < kMaxSeg; ++i) {
+    for (int i = 0; i < SEGS; ++i) {
         S.qw[i] = phase->qw[i];
         S.sc[i] = phase->sc[i];
         S.y[i] = phase->y[i];
@@ -249,11 +252,15 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     const int G = phase->G, M = phase->M;
     const char *const xin = phase->x;
     const float *const xscale = phase->xscale;
-    static_assert(kMaxSeg == 4, "the registers named here");
-    asm volatile("" : "+s"(S.qw[0]), "+s"(S.qw[1]), "+s"(S.qw[2]), "+s"(S.qw[3]), "+s"(S.sc[0]), "+s"(S.sc[1]),
-                 "+s"(S.sc[2]), "+s"(S.sc[3]));
-    asm volatile("" : "+s"(S.y[0]), "+s"(S.y[1]), "+s"(S.y[2]), "+s"(S.y[3]), "+s"(S.row_end[0]),
-                 "+s"(S.row_end[1]), "+s"(S.row_end[2]), "+s"(S.row_end[3]), "+s"(S.bf16));
+    static_assert(SEGS == 1 || (SEGS == 4 && kMaxSeg == 4), "the registers named here");
+    if constexpr (SEGS == 4) {
+        asm volatile("" : "+s"(S.qw[0]), "+s"(S.qw[1]), "+s"(S.qw[2]), "+s"(S.qw[3]), "+s"(S.sc[0]), "+s"(S.sc[1]),
+                     "+s"(S.sc[2]), "+s"(S.sc[3]));
+        asm volatile("" : "+s"(S.y[0]), "+s"(S.y[1]), "+s"(S.y[2]), "+s"(S.y[3]), "+s"(S.row_end[0]),
+                     "+s"(S.row_end[1]), "+s"(S.row_end[2]), "+s"(S.row_end[3]), "+s"(S.bf16));
+    } else {
+        asm volatile("" : "+s"(S.qw[0]), "+s"(S.sc[0]), "+s"(S.y[0]), "+s"(S.row_end[0]), "+s"(S.bf16));
+    }
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 15, kb = lane >> 4;
@@ -271,7 +278,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     for (int j = 0; j < 2; ++j) wc[j] = (lane % NG) ^ (((kWRows * j + lane / NG) / (16 / NG)) % NG);
 #pragma unroll
     for (int j = 0; j < B::kWOps; ++j)
-        wsrc[j] = reinterpret_cast<const char *>(slice_row<DEBUG>(S, row0 + kWRows * j + lane / NG, G).qw) +
+        wsrc[j] = reinterpret_cast<const char *>(slice_row(S, row0 + kWRows * j + lane / NG, G).qw) +
                   (TAIL ? 0 : 16 * wc[j & 1]);
     constexpr int kRows = 16 * RT;
     int sg[B::kScOps];  // first group of the lane's word
@@ -279,7 +286,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     for (int k = 0; k < B::kScOps; ++k) {
         const int word = k * 64 + lane;
         sg[k] = SCB == 16 ? 0 : (word / kRows * (SCB / 2)) % NG;
-        ssrc[k] = reinterpret_cast<const char *>(slice_row<DEBUG>(S, row0 + word % kRows, G).sc);
+        ssrc[k] = reinterpret_cast<const char *>(slice_row(S, row0 + word % kRows, G).sc);
     }
     // activations: 2 or 4 tokens per instruction, pieces permuted against each other
     constexpr int kPieces = B::kPieces;
@@ -478,7 +485,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
             }
         };
         auto dump = [&](const typename A::offset_t &raw, int i, int r, int mt) {
-            const SliceRow o = slice_row<DEBUG>(S, row0 + 16 * r + n, G);
+            const SliceRow o = slice_row(S, row0 + 16 * r + n, G);
             if (!o.valid || !o.dbg || g0 + i >= G) return;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
@@ -557,7 +564,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
 #undef NVQ_RD128
 
     auto store = [&](int row, int m, float sum) {
-        const SliceRow o = slice_row<DEBUG>(S, row, G);
+        const SliceRow o = slice_row(S, row, G);
         if (o.valid && m < M) store_global(o.y, o.bf16 ? NVQ_BF16 : NVQ_F32, (int64_t)m * o.N + o.n, sum);
     };
     __syncthreads();  // the blocks' LDS is free
@@ -627,14 +634,14 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, DEBUG>
     }
 }
 
-template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, bool DEBUG>
+template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, int SEGS, bool DEBUG>
 int slice_launch(const SliceWork &w, int G, int M, hipStream_t st) {
-    SliceArgs<NP, DEBUG> a = {};
+    SliceArgs<NP, SEGS, DEBUG> a = {};
     int units = 0;
     for (int i = 0; i < NP; ++i) {
-        SlicePhase<DEBUG> &p = a.phase[i];
+        SlicePhase<SEGS, DEBUG> &p = a.phase[i];
         const GemvSegs &S = *w.segs[i];
-        for (int k = 0; k < kMaxSeg; ++k) {
+        for (int k = 0; k < SEGS; ++k) {
             const bool there = k < S.nseg;
             p.row_end[k] = there ? S.row_end[k] : S.total_rows;
             if (!there) continue;
@@ -651,7 +658,7 @@ int slice_launch(const SliceWork &w, int G, int M, hipStream_t st) {
         p.units = (S.total_rows + 16 * RT - 1) / (16 * RT);
         units += p.units;
     }
-    hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, W, NG, V, SCB, NP, DEBUG>), dim3(units), dim3(W * 64), 0,
+    hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, W, NG, V, SCB, NP, SEGS, DEBUG>), dim3(units), dim3(W * 64), 0,
                        st, a);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
@@ -659,9 +666,12 @@ int slice_launch(const SliceWork &w, int G, int M, hipStream_t st) {
 
 template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, bool DEBUG = false>
 int slice_go(const SliceWork &w, int G, int M, hipStream_t st) {
-    if constexpr (!DEBUG)  // (the walk asks for no accumulators)
-        if (w.n == 2) return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 2, false>(w, G, M, st);
-    return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 1, DEBUG>(w, G, M, st);
+    if constexpr (!DEBUG) {  // (only a single call asks for accumulators)
+        if (w.n == 2) return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 2, kMaxSeg, false>(w, G, M, st);
+        if (w.segs[0]->nseg > 1)
+            return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 1, kMaxSeg, false>(w, G, M, st);
+    }
+    return slice_launch<PREC, PG, TOK, RT, W, NG, V, SCB, 1, 1, DEBUG>(w, G, M, st);
 }
 
 // Whether a phase has more than two row tiles per compute unit.
