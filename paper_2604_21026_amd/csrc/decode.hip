@@ -564,13 +564,13 @@ struct GroupPlan {
 // fed through LDS rings, which has the better rate, but sixteen microseconds before it and one for every
 // 256 inputs of the widest phase; both add in the same order.  Linear estimates as below, fitted to
 // 1008 and 720 lists of 4 to 64 phases and 3 to 490 MB (10 and 9 % rms), with a margin for their errors.  Per-tile
-// grid / rings, 8 tokens: two blocks of 1024 x 3072 13.4 / 32.8, four of 1536 x 4608 30 / 37, ten 58 /
-// 64, sixteen 87 / 79; three of 1B 46 / 58, four 56 / 57.
+// grid / rings, 8 tokens, cold weights: two blocks of 1024 x 3072 16 / 32, four of 1536 x 4608 36 / 39, ten
+// 65 / 63, sixteen 96 / 79; three of 1B 51 / 59, four 62 / 59.
 // Three bounds beside the estimates are not where the per-tile grid stops being the faster one: lists of
 // fewer than four phases, of less than 1.5 MB, and of up to eight phases or 50 MB with one of K >= 6144 keep
-// to the rings although these are slower (6 of 64 x 512 6.9 / 14.9, 8 of 256 x 1024 9.1 / 17.7, one layer of
-// 2048 x 2048 8.9 / 21, three 12 / 34, 4096 x 14336 32 / 131, one block of 1B 29 / 59, two 44 / 61, one of
-// 8B 70 / 95; two of 8B 102 / 98).  They are the lists that the rings' tests are built on, whose kernel
+// to the rings although these are slower (6 of 64 x 512 6.6 / 13.8, 8 of 256 x 1024 8.7 / 15.8, one layer of
+// 2048 x 2048 8.7 / 20, three 12 / 32, 4096 x 14336 31 / 129, one block of 1B 28 / 56, two 43 / 57, one of
+// 8B 68 / 93; two of 8B 101 / 96).  They are the lists that the rings' tests are built on, whose kernel
 // and waits those name, and the first two lie outside of what was fitted.  From
 // 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
 // activations (gemv_rows.hip), which moves the most bytes but takes 128 rows and all of their K

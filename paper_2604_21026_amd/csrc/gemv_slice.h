@@ -27,7 +27,8 @@
 // What bounds it: neither memory nor arithmetic alone.  28672 x 4096 at 8 tokens takes 16.5
 // (W4A8) to 18.8 us (W4A16), 3.5 to 4 TB/s; the per-tile grid that loaded straight into
 // registers took 25 and 31.  The vector ALUs are busy half of the time (16 to 18 instructions
-// per 16 x 16 x 32 product), the matrix cores a sixth.  The sixty-four chains cost registers
+// per 16 x 16 x 32 product where a row's matrix is one of four, 13.5 to 16 in a launch of one matrix), the
+// matrix cores a sixth.  The sixty-four chains cost registers
 // and a longer way through LDS: with a scale per group 16384 x 3072 takes 10.1 us at 4 tokens
 // (8.6 in one chain per wave; a wave per row, which served these calls before, 18.7), 28672 x
 // 4096 20, 27 and 57 us at 8, 16 and 32 tokens (that: 63, 111 and 202).  Two to four blocks in

@@ -139,7 +139,7 @@ __device__ __forceinline__ void quant_token(const uint4 *__restrict__ x, int K, 
 // codes.  The grid is a handful of workgroups, so what it costs is its launch (1.7 us) and a
 // chain of memory, exchange and barrier latencies: one trip to memory (the norm's weights are
 // asked for with the input), lane exchanges that do not pass through LDS, and one division per
-// scale.  By the trace 3.9 us for norm and quantisation of 8 x 4096 and 4.5 for SiLU and
+// scale.  By the trace 3.7 us for norm and quantisation of 8 x 4096 and 4.4 for SiLU and
 // quantisation of 8 x 14336 (4.3 and 6.2 with two trips, exchanges through LDS and a division
 // per value).
 // Q: 0 = the transformed bf16 values (xt), 1 = codes with a scale per token, 2 = codes with a
