@@ -188,7 +188,7 @@ def dequant_bf16_into(qweight: torch.Tensor, scales: torch.Tensor, out: torch.Te
     if tuple(out.shape) != (N, K):
         raise ValueError("out: shape mismatch")
     _check(lib().nvq_dequant_bf16(_dev(qweight, torch.uint8, "qweight"),
-                                  _dev(scales, torch.int16, "scales"), N, K,
+                                  _dev(scales, torch.int16, "scales", N * (K // 32)), N, K,
                                   _dev(out, torch.bfloat16, "out"), _stream()), "nvq_dequant_bf16")
     return out
 
@@ -205,8 +205,8 @@ def rms_norm(x: torch.Tensor, gamma: torch.Tensor, eps: float, res: Optional[tor
     out = torch.empty_like(x)
     h = torch.empty_like(x) if res is not None else None
     _check(lib().nvq_rms_norm_bf16(_dev(x, torch.bfloat16, "x"),
-                                   _dev(res, torch.bfloat16, "res") if res is not None else None,
-                                   _dev(gamma, torch.bfloat16, "gamma"), float(eps), M, K,
+                                   _dev(res, torch.bfloat16, "res", M * K) if res is not None else None,
+                                   _dev(gamma, torch.bfloat16, "gamma", K), float(eps), M, K,
                                    out.data_ptr(), h.data_ptr() if h is not None else None,
                                    _stream()), "nvq_rms_norm_bf16")
     return out, h
@@ -216,8 +216,9 @@ def silu_mul(g: torch.Tensor, u: torch.Tensor) -> torch.Tensor:
     """g, u bf16 [M,K] -> bf16(silu(g) * u)."""
     M, K = g.shape
     out = torch.empty_like(g)
-    _check(lib().nvq_silu_mul_bf16(_dev(g, torch.bfloat16, "g"), _dev(u, torch.bfloat16, "u"), M, K,
-                                   out.data_ptr(), _stream()), "nvq_silu_mul_bf16")
+    _check(lib().nvq_silu_mul_bf16(_dev(g, torch.bfloat16, "g"),
+                                   _dev(u, torch.bfloat16, "u", M * K), M, K, out.data_ptr(),
+                                   _stream()), "nvq_silu_mul_bf16")
     return out
 
 
@@ -337,8 +338,9 @@ class DecodeList:
                 raise ValueError("entry %d: h_out shape mismatch" % i)
             if gamma is not None and tuple(gamma.shape) != (K,):
                 raise ValueError("entry %d: gamma shape mismatch" % i)
-            self.arr[i] = Linear(_dev(q, torch.uint8, "qweight"), _dev(s, torch.int16, "scales"),
-                                 N, K, _dev(x, torch.bfloat16, "x"), _dev(y, y.dtype, "y"),
+            self.arr[i] = Linear(_dev(q, torch.uint8, "qweight"),
+                                 _dev(s, torch.int16, "scales", N * (K // 32)), N, K,
+                                 _dev(x, torch.bfloat16, "x"), _dev(y, y.dtype, "y"),
                                  _y_dtype(y.dtype), int(e["precision"]), op,
                                  float(e.get("eps", 0.0)),
                                  _dev(x2, torch.bfloat16, "x2") if x2 is not None else None,

@@ -199,7 +199,7 @@ def test_the_binding_without_ctypes_leaves_subclasses_of_tensors_alone():
 
 def test_tensors_that_are_too_small_are_refused():
     """Outputs kept from a call with fewer tokens or rows, a scale per token where one per group is
-    read: the library gets addresses only, so the binding looks at the sizes."""
+    read, another matrix's scales: the library gets addresses only, so the binding looks at the sizes."""
     import torch
     Own = pretended()
     M, N, K = 3, 5, 64
@@ -223,6 +223,11 @@ def test_tensors_that_are_too_small_are_refused():
             nvq.quant_act_i8(x, 0, out=out)
     with pytest.raises(ValueError, match="xscale has 6 values, 24 are needed"):
         nvq.quant_act_i8(x, 32, out=[xq, Own((M, 2), torch.int8), gs])
+    bf16 = lambda *shape: Own(shape, torch.bfloat16)
+    with pytest.raises(ValueError, match="scales has 8 values, 10 are needed"):
+        nvq.dequant_bf16_into(q, Own((4, 2), torch.int16), bf16(N, K))
+    with pytest.raises(ValueError, match="scales has 8 values, 10 are needed"):
+        nvq.DecodeList([dict(qweight=q, scales=Own((4, 2), torch.int16), x=x, y=y, precision=0)], M)
     with pytest.raises(ValueError, match="xgsum must be a device tensor"):
         nvq.quant_act_i8(x, 0, out=[xq, xs, torch.zeros((M, 2), dtype=torch.int32)])
 
