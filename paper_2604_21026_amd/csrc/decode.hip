@@ -14,6 +14,7 @@
 // tokens of shapes the matrix-core kernel takes, as two launches per batch of
 // mutually independent phases (one grid quantises, one multiplies).
 #include <algorithm>
+#include <cmath>
 #include <mutex>
 #include <new>
 #include <vector>
@@ -548,6 +549,7 @@ struct GroupBatch {
     int unit_first, nunits;  // range in the unit list
     int img_first, nimg;     // range in the image unit list
     int part_first, nparts;  // the batch's table in the part list (2 * (nparts + 1) words)
+    int order;               // the order of its phases there (see order_phases), or -1
     int grid;                // workgroups of the persistent kernel
     int phase_first, nphases;  // phases of the batch
     GroupKind kind;
@@ -556,7 +558,7 @@ struct GroupPlan {
     bool ring;  // the persistent kernel serves the list: every phase has a job and an operand image
     std::vector<GroupPhase> tab;
     std::vector<uint16_t> jobs, units, imgs;
-    std::vector<uint32_t> parts;  // per batch: nparts + 1 unit cuts, then the phases at the cuts
+    std::vector<uint32_t> parts;  // per batch: nparts + 1 unit cuts, the phases at the cuts, the order
     std::vector<GroupBatch> batches;
 };
 
@@ -573,13 +575,17 @@ struct GroupPlan {
 // 8B 68 / 93; two of 8B 101 / 96).  They are the lists that the rings' tests are built on, whose kernel
 // and waits those name, and the first two lie outside of what was fitted.  From
 // 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
-// activations (gemv_rows.hip), which moves the most bytes but takes 128 rows and all of their K
-// per workgroup, and launches phase by phase (gemv_slice.h), by what they were measured to take
-// (us; MB of weights, phases, the largest K): 186 lists of 1 to 128 phases and 0.1 to 3900 MB
-// fit within 13, 17 and 10 % (rms), and the choice costs 0.8 % on average, 20 % at worst (6
-// phases, 44 MB: 56 us, with the rings 47).  Where the lines lie, rings / rows / phases: 4096 x
-// 14336 alone 30 / 107 / 20; one block of 8B 79 / 156 / 64, two 135 / 169 / 138, four 193 / 177 /
-// 289, 32 of them 1337 / 1054 / 2225; six blocks of 1B 118 / 119 / 193, sixteen 247 / 201 / 576.
+// activations (gemv_rows.hip), and launches phase by phase (gemv_slice.h), by what they were measured to
+// take (us; MB of weights, phases, the largest K): 123 lists of 4 to 64 phases and 2 to 980 MB, where
+// the choice costs 2 % on average.  A list takes the second as long as its widest phase takes a
+// workgroup, which keeps a group of rows for all of K, or as long as its bytes do, whichever is longer,
+// and a fifth more where both are equal (the fourth powers).  Rings / rows / phases: one block of 8B
+// 76 / 124 / 61, two 131 / 135 / 127, four 185 / 147 / 244, eight 353 / 252 / 480; two blocks of 1B
+// 61 / 75 / 66, six 110 / 87 / 185, sixteen 229 / 138 / 485; four of 1536 x 4608 47 / 41 / 99.
+// The tenth more and the two bounds: few and small phases go up and down with how they fall to the
+// workgroups (20 phases, 8 MB: 23 with the rings, 27; 16 phases, 7 MB: 20 and 17), and wide lists of
+// less than 400 MB keep to the rings, whose tests name them, although three blocks of 8B would take
+// 143 instead of 169.
 GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
     if (!gp.ring) return kGroupTiles;
     double mb = 0.0, widest = 0.0, single = 3.3;
@@ -598,7 +604,9 @@ GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
         return per_tile ? kGroupTiles : kGroupRing;
     }
     const double ring = 12.6 + 0.57 * widest + 0.27 * b.nphases + mb / 2.9;
-    const double rows = 7.2 + 2.44 * widest + 0.36 * b.nphases + mb / 5.8;
+    const double longest = 9.0 + 2.15 * widest, bytes = 10.0 + 0.2 * b.nphases + mb / 4.45;
+    const bool enough = mb >= 5.0 && (mb >= 400.0 || widest < 48.0);
+    const double rows = enough ? 1.1 * std::pow(std::pow(longest, 4) + std::pow(bytes, 4), 0.25) : 1e30;
     return single < std::min(ring, rows) ? kGroupSingle : ring <= rows ? kGroupRing : kGroupRows;
 }
 
@@ -633,6 +641,33 @@ void cut_batch(GroupPlan &gp, GroupBatch &b, int M) {
     gp.parts.insert(gp.parts.end(), phase.begin(), phase.end());
 }
 
+// The order in which the workgroups of a part take its phases (gemv_rows.hip), those with the largest K
+// first: a workgroup keeps a group of units for all of K (128 rows of 14336 inputs about 100 us), and
+// those that begin one last are waited for (16 blocks of 8B, 32 tokens: 466 us, as they stand in the list 520).
+// nparts + 1 indices into what follows, then the phases of every part; a phase that the cut
+// divides is in both.  Fits the room for the parts of as many batches as the list has phases.
+void order_phases(GroupPlan &gp, GroupBatch &b) {
+    b.order = -1;
+    if (b.nphases < 3 || b.nparts <= 0) return;
+    std::vector<uint32_t> begin, phases;
+    for (int t = 0; t < b.nparts; ++t) {
+        const int from = (int)gp.parts[(size_t)(b.part_first + t)], to = (int)gp.parts[(size_t)(b.part_first + t + 1)];
+        begin.push_back((uint32_t)phases.size());
+        for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
+            const GroupPhase &g = gp.tab[(size_t)p];
+            if (g.unit_begin < to && g.unit_begin + g.unit_count > from) phases.push_back((uint32_t)p);
+        }
+        std::stable_sort(phases.begin() + begin.back(), phases.end(),
+                         [&](uint32_t p, uint32_t q) { return gp.tab[p].G > gp.tab[q].G; });
+    }
+    begin.push_back((uint32_t)phases.size());
+    b.order = (int)gp.parts.size();
+    gp.parts.insert(gp.parts.end(), begin.begin(), begin.end());
+    gp.parts.insert(gp.parts.end(), phases.begin(), phases.end());
+    static_assert(2 * (kRingMaxParts + 1) + kRingMaxParts + 1 + kRingMaxParts + 2 <= 3 * 2 * (kRingMaxParts + 1),
+                  "three phases have the room");
+}
+
 GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
                      bool ordered, const Workspace &ws) {
     GroupPlan gp;
@@ -664,7 +699,10 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
             gp.imgs.resize((size_t)cur.img_first);
             cur.nimg = 0;
         }
-        if (cur.kind == kGroupRows) cur.grid = rows_grid(cur.nunits, cur.nparts);
+        if (cur.kind == kGroupRows) {
+            cur.grid = rows_grid(cur.nunits, cur.nparts);
+            order_phases(gp, cur);
+        }
         gp.batches.push_back(cur);
     };
     for (size_t p = 0; p < phases.size(); ++p) {
@@ -1165,7 +1203,8 @@ extern "C" int nvq_plan_run(nvq_plan *pl, void *stream) {
                     uint32_t *const tickets = pl->ws.status + 16;
                     rc = launch_quant_act_group(pl->ws.gtab, jobs, b.njobs, pl->M, tickets, st);
                     if (rc == NVQ_OK)
-                        rc = launch_gemv_rows(pl->ws.gtab, parts, b.nparts, b.grid, pl->M, tickets, st);
+                        rc = launch_gemv_rows(pl->ws.gtab, parts, b.nparts,
+                                              b.order < 0 ? nullptr : pl->ws.gteams + b.order, b.grid, pl->M, tickets, st);
                     break;
                 }
                 case kGroupSingle:

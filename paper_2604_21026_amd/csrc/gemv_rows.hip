@@ -2,11 +2,10 @@
 // grid (plans whose K are all multiples of 512).  Paper: the W4A8 / W4A16 kernel
 // descriptions; the arithmetic is that of mfma_act.h.
 //
-// With two token tiles 32 weight rows need 3.6 times their own bytes of bf16 activations,
-// and the L2 caches deliver about 10 TB/s to all compute units together: a kernel whose
-// waves each fetch their own (the ring kernel, which serves up to 16 tokens and shorter lists)
-// stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with 32 rows
-// of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
+// With two token tiles 32 weight rows need 3.6 times their own bytes of bf16 activations, and a
+// kernel whose waves each fetch their own (the ring kernel, which serves up to 16 tokens and shorter
+// lists) stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with
+// 32 rows of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
 // through LDS, and no sums cross the waves.  K advances by 256 inputs (a whole 128-byte
 // line of a row); per step a wave asks for its quarter of the next step's activations (two
 // buffers) and, once the current step's weights and scales are in registers, for its next
@@ -16,14 +15,18 @@
 //
 // The batch is cut into parts, one per XCD (the compute units of an XCD advance through
 // the phases together, so that the activations they all read stay in their L2); the
-// workgroups of a part take its groups of four units first come first served from a
-// counter, which the quantisation launch in front has cleared.
+// workgroups of a part take its groups of four units, the phases with the largest K first, first come
+// first served from a counter, which the quantisation launch in front has cleared.
 //
-// What bounds it: 8B layers at 32 tokens take 1,133 us (3.9 TB/s; 1,124 with the sums of a
-// result in one chain, 1,480 with the ring kernel); without the loads 820-870, without the products 1,030, so either alone comes
-// close and the two overlap by half.  Eight waves and 256 rows per workgroup are as fast
-// on long lists and 15 % slower on short ones; 64 rows per wave 4 % slower, two steps of
-// weights in flight with two thirds of the waves 15 %.
+// What bounds it: 8B layers at 32 tokens take 1,040 us (4.3 TB/s), 25 of them the quantisation.
+// Without the loads 700, without the products 960: memory, whose queue runs dry while a workgroup waits for
+// a step, crosses the barrier and copies its weights.  What brought it there from 1,133: the phases in the order of
+// their K (see order_phases; 60 us), two steps' scales per load (16 bytes of a row per load were a
+// request each, 20), the matrix core and the vector instructions interleaved unit by unit with
+// addresses that need no arithmetic per group (from 92 vector instructions per KiB of weights to 75), a
+// higher priority for the waves that ask for operands (10).  Not faster: two steps of weights in flight with
+// four barriers per step (the activations in quarters, for the room: 1,140), eight waves per workgroup, weights
+// loaded into registers (they spill), plain loads of the weights (2.5 %).
 #include <type_traits>
 
 #include "gemv_tile.h"
@@ -40,24 +43,46 @@ typedef const __attribute__((address_space(4))) uint32_t CWord;
 
 constexpr int kRowsWaves = 4;      // waves per workgroup = units per group
 constexpr int kRowsWgPerCu = 3;
+constexpr int kRowsBlock = 4096;   // a block of activations: 128 bytes of 32 tokens
+constexpr int kRowsA = 4 * kRowsBlock;  // a buffer: a step's 256 inputs as bf16 (codes fill half of it)
 constexpr int kRowsW = 2 * 2048;   // a wave's weights of a step: 32 rows x 128 bytes
-constexpr int kRowsSlot = kRowsW + 512;  // and its scales, 16 bytes per row
+constexpr int kRowsSc = 1024;      // and the scales of two, 32 bytes per row
 
+// A part of the batch: the units begin .. begin + units - 1, phase by phase, in the order given or as they
+// stand in the batch.
+struct RowsPart {
+    CWord *order;  // its phases, or null
+    int first;     // its first phase
+    int begin, units;
+};
 // A bundle: up to four consecutive units of one phase.
 struct RowsBundle {
     int p;            // phase
     int unit, count;  // first unit (of the phase) and how many
-    int next;         // unit of the batch after the bundle
+    int next;         // unit of the part after the bundle
     int end;          // end of the group of units it belongs to
+    int at, base;     // the phase's place in the order, units of the part before it
 };
 
-__device__ __forceinline__ RowsBundle rows_bundle(CGroup *tab, int p, int u, int end) {
+// The bundle that unit u of the part begins, not before `from`'s phase.
+__device__ __forceinline__ RowsBundle rows_bundle(CGroup *tab, const RowsPart &P, const RowsBundle &from, int u, int end) {
     RowsBundle b;
-    while (u >= tab[p].unit_begin + tab[p].unit_count) ++p;  // phases have units
-    const int phase_end = tab[p].unit_begin + tab[p].unit_count;
-    b.p = p;
-    b.unit = u - tab[p].unit_begin;
-    b.next = end < phase_end ? end : phase_end;
+    b.at = from.at;
+    b.base = from.base;
+    while (true) {  // (u is a unit of the part)
+        b.p = P.order ? (int)P.order[b.at] : P.first + b.at;
+        const int lo = tab[b.p].unit_begin, hi = lo + tab[b.p].unit_count;
+        const int from_unit = lo < P.begin ? P.begin : lo;
+        const int to_unit = hi < P.begin + P.units ? hi : P.begin + P.units;
+        const int phase_end = b.base + (to_unit - from_unit);
+        if (u < phase_end) {
+            b.unit = from_unit - lo + (u - b.base);
+            b.next = end < phase_end ? end : phase_end;
+            break;
+        }
+        b.base = phase_end;
+        ++b.at;
+    }
     b.count = b.next - u;
     b.end = end;
     return b;
@@ -75,27 +100,28 @@ struct RowsSource {
 
 __global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu(3))) void
 gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict__ part_tab_, int nparts,
-                 int M, uint32_t *__restrict__ tickets) {
-    constexpr int MT = 2, R = 2;   // token tiles, row tiles of a wave
-    constexpr int kA = 32 * 512;  // an activation buffer (bf16; codes fill half of it)
-    constexpr int kASlice = 16 / kRowsWaves;  // loads of a wave and step, bf16 (codes: half)
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kA + kRowsWaves * kRowsSlot];
+                 const uint32_t *__restrict__ order_, int M, uint32_t *__restrict__ tickets) {
+    constexpr int MT = 2, R = 2;  // token tiles, row tiles of a wave
+    constexpr int kWaveLds = kRowsW + kRowsSc;
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kRowsA + kRowsWaves * kWaveLds];
     __shared__ int ticket_word;
     CGroup *tab = (CGroup *)tab_;
     CWord *part_tab = (CWord *)part_tab_;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int n = lane & 15, kb = lane >> 4;
-    unsigned char *const slot = lds + 2 * kA + w * kRowsSlot;
+    unsigned char *const slot = lds + 2 * kRowsA + w * kWaveLds;
 
     const int part = (int)blockIdx.x % nparts;
-    const int part_end = (int)part_tab[part + 1];
     const int part_wgs = ((int)gridDim.x - 1 - part) / nparts + 1;
-    const int part_begin = (int)part_tab[part];
-    // the group of ticket t: units part_begin + 4 t .. + 3
+    RowsPart P;
+    P.begin = (int)part_tab[part];
+    P.units = (int)part_tab[part + 1] - P.begin;
+    P.order = order_ ? (CWord *)order_ + nparts + 1 + ((CWord *)order_)[part] : nullptr;
+    P.first = (int)part_tab[nparts + 1 + part];
+    // the group of ticket t: units 4 t .. + 3 of the part
     int t = (int)blockIdx.x / nparts;
-    if (part_begin + t * kRowsWaves >= part_end) return;
-    auto group_end = [&](int first) { return first + kRowsWaves < part_end ? first + kRowsWaves : part_end; };
+    if (t * kRowsWaves >= P.units) return;
+    auto group_end = [&](int first) { return first + kRowsWaves < P.units ? first + kRowsWaves : P.units; };
 
     auto source = [&](const RowsBundle &b) {
         RowsSource s;
@@ -113,71 +139,81 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
         s.whole = e.valid && e.n == o.n + 31 && e.y == o.y;
         return s;
     };
-    // the wave's share of step c's activations: whole lines of 2 (bf16) or 4 (codes) tokens
-    // per load, a token's pieces permuted by its number
+
+    // The lane's number, opaque: what follows from it is made anew where it is used.  Kept, it would cost
+    // registers across the whole loop, and a spill's reload waits for every load in flight.
+    auto fresh_lane = [&]() {
+        uint32_t l = threadIdx.x & 63;
+        asm volatile("" : "+v"(l));
+        return l;
+    };
+
+    // The wave's share of step c's activations: a block is 128 bytes of every token, four tokens' 64
+    // bytes per load; W4A16 has four blocks in a step, W4A8 two.
     auto issue_a = [&](const RowsSource &s, int c, int buf) {
         const bool codes = s.precision == NVQ_W4A8;
-        unsigned char *const dst = lds + buf * kA;
+        const int lane = (int)fresh_lane();
+        const uint32_t row = (uint32_t)(s.G * (codes ? 32 : 64));
+        const int block = codes ? w >> 1 : w;
+        const char *src = s.a + (size_t)c * (codes ? 256 : 512) + block * 128;
+        unsigned char *const dst = lds + buf * kRowsA + block * kRowsBlock;
+        const uint32_t piece = 16u * (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
 #pragma unroll
-        for (int j = 0; j < kASlice; ++j) {
-            if (codes && j >= kASlice / 2) continue;
-            const int i = (codes ? kASlice / 2 : kASlice) * w + j;
-            const int m = codes ? 4 * i + (lane >> 4) : 2 * i + (lane >> 5);
-            const int p = codes ? (lane & 15) ^ (m & 15) : (lane & 31) ^ (m & 15);
-            const uint32_t row = (uint32_t)(s.G * (codes ? 32 : 64));
-            const char *src = s.a + (size_t)c * (codes ? 256 : 512) +
-                              ((uint32_t)(m < M ? m : M - 1) * row + 16u * (uint32_t)p);
-            __builtin_amdgcn_global_load_lds((const void *)src, (rows_lds_ptr)(dst + i * 1024), 16, 0, 0);
+        for (int j = 0; j < 4; ++j) {
+            if (codes && (j >> 1) != (w & 1)) continue;
+            const int m = 16 * (j >> 1) + (lane >> 2);
+            __builtin_amdgcn_global_load_lds(
+                (const void *)(src + ((uint32_t)(m < M ? m : M - 1) * row + piece + 64u * (uint32_t)(j & 1))),
+                (rows_lds_ptr)(dst + j * 1024), 16, 0, 0);
         }
     };
     // Weights, load j: rows 8 j .. + 7 of the wave's 32, lane l piece (l % 8) ^ (row / 2 % 8)
-    // of row l / 8; scales: 16 bytes of row l.
+    // of row l / 8.
     auto issue_w = [&](const RowsSource &s, int c) {
         if (!s.active) return;
-        int lane = threadIdx.x & 63;  // (opaque, see the result store)
-        asm volatile("" : "+v"(lane));
-        const int wrow = lane >> 3;
+        const int wrow = (int)fresh_lane() >> 3, piece = (int)fresh_lane() & 7;
         const uint32_t row_bytes = (uint32_t)s.G * 16;  // a multiple of 256
-        const uint32_t lo = (uint32_t)wrow * row_bytes + 16u * (uint32_t)((lane & 7) ^ (wrow >> 1));
         if (s.whole) {
+            const uint32_t lo = (uint32_t)wrow * row_bytes + 16u * (uint32_t)(piece ^ (wrow >> 1));
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 __builtin_amdgcn_global_load_lds(
                     (const void *)(s.w + ((size_t)c * 128 + (size_t)(8 * j) * row_bytes) + ((j & 1) ? lo ^ 64u : lo)),
                     (rows_lds_ptr)(slot + j * 1024), 16, 0, 2);
-            if (lane < 32)
-                __builtin_amdgcn_global_load_lds((const void *)(s.s + (size_t)c * 16 + (uint32_t)lane * (uint32_t)s.G * 2u),
-                                                 (rows_lds_ptr)(slot + kRowsW), 16, 0, 0);
-            return;
+        } else {
+            CGroup &P = tab[s.p];
+            for (int j = 0; j < 4; ++j) {
+                const char *row = reinterpret_cast<const char *>(locate_row(P.segs, s.row0 + 8 * j + wrow, s.G).qw);
+                const int pc = piece ^ ((4 * j + (wrow >> 1)) & 7);
+                __builtin_amdgcn_global_load_lds((const void *)(row + (size_t)c * 128 + 16 * pc),
+                                                 (rows_lds_ptr)(slot + j * 1024), 16, 0, 2);
+            }
         }
-        CGroup &P = tab[s.p];
-        for (int j = 0; j < 4; ++j) {
-            const char *row = reinterpret_cast<const char *>(locate_row(P.segs, s.row0 + 8 * j + wrow, s.G).qw);
-            const int pc = (lane & 7) ^ ((4 * j + (wrow >> 1)) & 7);
-            __builtin_amdgcn_global_load_lds((const void *)(row + (size_t)c * 128 + 16 * pc),
-                                             (rows_lds_ptr)(slot + j * 1024), 16, 0, 2);
-        }
-        const char *srow = reinterpret_cast<const char *>(locate_row(P.segs, s.row0 + (lane & 31), s.G).sc);
-        if (lane < 32)
-            __builtin_amdgcn_global_load_lds((const void *)(srow + (size_t)c * 16), (rows_lds_ptr)(slot + kRowsW), 16,
-                                             0, 0);
+    };
+    // Scales of steps c and c + 1 (c even): 32 bytes of every row, in two pieces.
+    auto issue_s = [&](const RowsSource &s, int c) {
+        if (!s.active) return;
+        const uint32_t l = fresh_lane(), row = l >> 1, piece = l & 1;
+        const char *a;
+        if (s.whole)
+            a = s.s + ((size_t)c * 16 + (row * (uint32_t)s.G * 2u + 16u * piece));
+        else
+            a = reinterpret_cast<const char *>(locate_row(tab[s.p].segs, s.row0 + (int)row, s.G).sc) + (size_t)c * 16 +
+                16 * piece;
+        __builtin_amdgcn_global_load_lds((const void *)a, (rows_lds_ptr)(slot + kRowsW), 16, 0, 0);
     };
 
     // The lane's places.  Weights: dword kb of piece i of row n, piece i at position i ^ (n / 2
-    // % 8); activations: W4A16 half a piece twice (pieces 4 i + 2 h + kb / 2 of half a step), W4A8
-    // a dword twice (pieces 2 i + h), piece p at position p ^ n.  The permutations leave the
-    // rest of an address alone: another piece is one xor away.
+    // % 8).  Activations, [tile][half line][token][position], piece p of a half line at position
+    // p ^ (n / 4): W4A16 half a piece twice (pieces 4 g + 2 h + kb / 2 of a block), W4A8 a dword
+    // twice (pieces 2 g + h).
     const uint32_t at = (uint32_t)(uintptr_t)slot, abase = (uint32_t)(uintptr_t)lds;
-    const uint32_t wpos = at + n * 128 + 16 * ((n >> 1) & 7) + 4 * kb;
-    const uint32_t spos = at + kRowsW + 16 * n;
-    const uint32_t apos16 = abase + n * 512 + 16 * ((kb >> 1) ^ n) + 8 * (kb & 1);
-    const uint32_t apos8 = abase + n * 256 + 16 * n + 4 * kb;
 
     // A result's sum in three levels: the eight groups of a step, eight steps, all of K.  (One
     // chain over all of K had up to twice the error of the four that the kernel for up to 16 tokens
     // adds, registers for four would be 64; this is closer than those, at any K, for 2 % more
     // vector instructions.)
-    float f[R][MT][4], total[R][MT][4];
+    float f[R][MT][4], total[R][MT][4], sums[R][MT][4];
     auto clear = [&](float (&v)[R][MT][4]) {
 #pragma unroll
         for (int r = 0; r < R; ++r)
@@ -195,102 +231,28 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                 for (int jj = 0; jj < 4; ++jj) to[r][mt][jj] += v[r][mt][jj];
     };
 
+#define NVQ_RD2(dst_, addr_) asm volatile("ds_read2st64_b32 %0, %1 offset0:0 offset1:8" : "=v"(dst_) : "v"(addr_))
+#define NVQ_RD128(dst_, addr_, off_) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD64(dst_, addr_, off_) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
-    // The products of a step, group by group; the activations of a group are read from LDS
-    // while the one before it is multiplied.
-    auto products = [&](auto prec, uint32_t abuf, const uint32_t (&q)[R][8], const uint32_t (&sc)[R][4]) {
-        constexpr int PREC = decltype(prec)::value;
-        typedef Act<PREC> A;
-        float part[R][MT][4];
-        uint2v a2[2][PREC == NVQ_W4A8 ? 1 : MT][2];
-        uint32_t a1[2][PREC == NVQ_W4A8 ? MT : 1][2];
-        auto read = [&](int g) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const uint32_t pos = abuf ^ (uint32_t)(PREC == NVQ_W4A8 ? 16 * (2 * g + h) : 16 * (4 * g + 2 * h));
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    if (PREC == NVQ_W4A8)
-                        NVQ_RD32(a1[g & 1][mt][h], pos, mt * 16 * 256);
-                    else
-                        NVQ_RD64(a2[g & 1][mt][h], pos, mt * 16 * 512);
-                }
-            }
-        };
-        read(0);
-#pragma unroll
-        for (int g = 0; g < 8; ++g) {
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                if (PREC == NVQ_W4A8)
-                    asm volatile("" : "+v"(a1[g & 1][mt][0]), "+v"(a1[g & 1][mt][1]));
-                else
-                    asm volatile("" : "+v"(a2[g & 1][mt][0]), "+v"(a2[g & 1][mt][1]));
-            }
-            if (g < 7) read(g + 1);
-            __builtin_amdgcn_sched_barrier(0);
-            typename A::operand act[MT];
-            typename A::offset_t off[MT];
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                if constexpr (PREC == NVQ_W4A8) {
-                    act[mt] = (long)((uint64_t)a1[g & 1][mt][0] | ((uint64_t)a1[g & 1][mt][1] << 32));
-                } else {
-                    const uint4v v = {a2[g & 1][mt][0].x, a2[g & 1][mt][0].y, a2[g & 1][mt][1].x, a2[g & 1][mt][1].y};
-                    act[mt] = __builtin_bit_cast(bf16x8, v);
-                }
-                if (PREC == NVQ_W4A16) off[mt] = A::offset(act[mt]);
-            }
-            // W4A8: no correction, the weights enter as 16 (n - 8): the nibble in the high half of
-            // its byte, its top bit flipped (the factor leaves with the activation scale)
-            if constexpr (PREC == NVQ_W4A8) off[0] = off[MT - 1] = int4v{0, 0, 0, 0};
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                const float sw = half_bits_to_float((uint16_t)(sc[r][g >> 1] >> (16 * (g & 1))));
-                typename A::operand wt;
-                if constexpr (PREC == NVQ_W4A8) {
-                    const uint32_t v = q[r][g] ^ 0x88888888u;
-                    wt = (long)((uint64_t)((v << 4) & 0xf0f0f0f0u) | ((uint64_t)(v & 0xf0f0f0f0u) << 32));
-                } else {
-                    wt = A::weights(q[r][g]);
-                }
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    int4v raw;
-                    const float4v p = A::product(act[mt], wt, off[mt], raw);
-#pragma unroll
-                    for (int jj = 0; jj < 4; ++jj)
-                        part[r][mt][jj] = g > 0 ? fmaf(sw, p[jj], part[r][mt][jj]) : sw * p[jj];
-                    // (here and now: the compiler would gather the additions of a step at its end and keep
-                    // the products until then)
-                    asm volatile("" : "+v"(part[r][mt][0]), "+v"(part[r][mt][1]), "+v"(part[r][mt][2]),
-                                 "+v"(part[r][mt][3]));
-                }
-            }
-        }
-        add(f, part);
-    };
-
-    const int first = part_begin + t * kRowsWaves;
-    RowsBundle cur = rows_bundle(tab, (int)part_tab[nparts + 1 + part], first, group_end(first));
+    const int first = t * kRowsWaves;
+    RowsBundle cur = rows_bundle(tab, P, RowsBundle{}, first, group_end(first));
     RowsSource src = source(cur);
     int buf = 0;
     issue_a(src, 0, 0);
+    issue_s(src, 0);
     issue_w(src, 0);
     while (true) {
-        const int G = src.G, steps = G >> 3;
-        const bool active = src.active, codes = src.precision == NVQ_W4A8;
+        const int steps = src.G >> 3;
+        const bool active = src.active;
         const bool last_of_group = cur.next >= cur.end;
         bool more = false;
         RowsBundle nxt = cur;
         int drawn = 0;
-        clear(f);
-        clear(total);
-        for (int c = 0; c < steps; ++c) {
-            // this step's operands have arrived; everyone has left the other buffer
+        uint2v q[8];   // the two row tiles' weights of a step
+        uint4v sc[R];  // and their scales
+        // The start of step c: its operands have arrived; everyone has left the other buffer.
+        auto begin = [&](int c) {
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
             if (c == 1 && last_of_group && w == 0 && lane == 0) ticket_word = drawn;
             __syncthreads();
@@ -303,46 +265,174 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                 int u = cur.next, e = cur.end;
                 if (last_of_group) {
                     t = part_wgs + __builtin_amdgcn_readfirstlane(ticket_word);
-                    u = part_begin + t * kRowsWaves;
+                    u = t * kRowsWaves;
                     e = group_end(u);
                 }
-                more = u < part_end;
+                more = u < P.units;
                 if (more) {
-                    nxt = rows_bundle(tab, cur.p, u, e);
+                    nxt = rows_bundle(tab, P, cur, u, e);
                     src = source(nxt);  // from here on the next bundle's
                     issue_a(src, 0, buf ^ 1);
                 }
             }
-            uint32_t q[R][8], sc[R][4];
+            const uint32_t l = fresh_lane(), n = l & 15, kb = l >> 4;
+            const uint32_t wpos = at + n * 128 + 16 * ((n >> 1) & 7) + 4 * kb, spos = at + kRowsW + 32 * n + 16 * (c & 1);
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
+            for (int i = 0; i < 8; ++i) NVQ_RD2(q[i], wpos ^ (16 * i));
 #pragma unroll
-                for (int r = 0; r < R; ++r) NVQ_RD32(q[r][i], wpos ^ (16 * i), r * 2048);
-#pragma unroll
-            for (int r = 0; r < R; ++r)
-#pragma unroll
-                for (int k = 0; k < 4; ++k) NVQ_RD32(sc[r][k], spos, r * 256 + 4 * k);
+            for (int r = 0; r < R; ++r) NVQ_RD128(sc[r], spos, r * 512);
             asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 #pragma unroll
-            for (int r = 0; r < R; ++r) {
+            for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(q[i]));
 #pragma unroll
-                for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(q[r][i]));
+            for (int r = 0; r < R; ++r) asm volatile("" : "+v"(sc[r]));
+            if (c + 1 < steps || more) {
+                const int next = c + 1 < steps ? c + 1 : 0;
+                if (c & 1) issue_s(src, next);
+                issue_w(src, next);
+            }
+        };
+        auto bundle = [&](auto prec) {
+            constexpr int PREC = decltype(prec)::value;
+            // groups in a block of activations (whose places are the same but for a constant)
+            constexpr int kGroups = PREC == NVQ_W4A8 ? 4 : 2;
+            typedef Act<PREC> A;
+            constexpr int kMatrix = 0x8, kVector = 0x2;
+            uint32_t pos[4];
+            uint2v a2[2][PREC == NVQ_W4A8 ? 1 : MT][2];
+            uint32_t a1[2][PREC == NVQ_W4A8 ? MT : 1][2];
+            typename A::operand wt[2];
+            typename A::offset_t off[MT], p[2][MT];
+            auto places = [&]() {
+                const uint32_t l = fresh_lane(), n = l & 15, kb = l >> 4;
+                const uint32_t p0 = abase + buf * kRowsA + n * 64 +
+                                    (PREC == NVQ_W4A8 ? 16 * (n >> 2) + 4 * kb : 16 * ((kb >> 1) ^ (n >> 2)) + 8 * (kb & 1));
 #pragma unroll
-                for (int k = 0; k < 4; ++k) asm volatile("" : "+v"(sc[r][k]));
+                for (int i = 0; i < 4; ++i) pos[i] = p0 ^ (uint32_t)(PREC == NVQ_W4A8 ? 16 * i : 32 * (i & 1));
+            };
+            auto read = [&](int i) {  // the activations of group i
+                const int g = i % kGroups, block = i / kGroups * kRowsBlock;
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        if (PREC == NVQ_W4A8)
+                            NVQ_RD32(a1[i & 1][mt][h], pos[2 * (g & 1) + h], block + mt * 2048 + (g >> 1) * 1024);
+                        else
+                            NVQ_RD64(a2[i & 1][mt][h], pos[h], block + mt * 2048 + g * 1024);
+                    }
+            };
+            auto arrived = [&](int i) {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    if (PREC == NVQ_W4A8)
+                        asm volatile("" : "+v"(a1[i & 1][mt][0]), "+v"(a1[i & 1][mt][1]));
+                    else
+                        asm volatile("" : "+v"(a2[i & 1][mt][0]), "+v"(a2[i & 1][mt][1]));
+                }
+            };
+            auto activation = [&](int i, int mt) {
+                if constexpr (PREC == NVQ_W4A8) {
+                    return (long)((uint64_t)a1[i & 1][mt][0] | ((uint64_t)a1[i & 1][mt][1] << 32));
+                } else {
+                    const uint4v v = {a2[i & 1][mt][0].x, a2[i & 1][mt][0].y, a2[i & 1][mt][1].x, a2[i & 1][mt][1].y};
+                    return __builtin_bit_cast(bf16x8, v);
+                }
+            };
+            // W4A8: no correction, the weights enter as 16 (n - 8): the nibble in the high half of
+            // its byte, its top bit flipped (the factor leaves with the activation scale)
+            auto unpack = [&](int u) {
+                const uint32_t v = q[u >> 1][u & 1];
+                if constexpr (PREC == NVQ_W4A8) {
+                    const uint32_t lo = ((v << 4) & 0xf0f0f0f0u) ^ 0x80808080u, hi = (v & 0xf0f0f0f0u) ^ 0x80808080u;
+                    wt[u & 1] = (long)((uint64_t)lo | ((uint64_t)hi << 32));
+                } else {
+                    wt[u & 1] = A::weights(v);
+                }
+            };
+            auto multiply = [&](int u) {
+                const int i = u >> 1;
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    if (PREC == NVQ_W4A8)
+                        off[mt] = typename A::offset_t{0, 0, 0, 0};
+                    else if ((u & 1) == 0)
+                        off[mt] = A::offset(activation(i, mt));
+                }
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) p[u & 1][mt] = A::multiply(activation(i, mt), wt[u & 1], off[mt]);
+            };
+            auto scale_add = [&](int u) {
+                const int i = u >> 1, r = u & 1;
+                const float sw = half_bits_to_float((uint16_t)(sc[r][i >> 1] >> (16 * (i & 1))));
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) {
+                    const float4v v = A::value(p[u & 1][mt]);
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+                        sums[r][mt][jj] = i > 0 ? fmaf(sw, v[jj], sums[r][mt][jj]) : sw * v[jj];
+                }
+            };
+            // Unit u of a step is row tile u % 2 of group u / 2.  While the matrix core works on it, the one before
+            // is scaled and added and the next one's weights are unpacked, a few instructions behind
+            // every product: the wave waits neither for a product nor for the matrix core.
+            auto units = [&]() {
+#pragma unroll
+                for (int u = 0; u < 16; ++u) {
+                    const int i = u >> 1;
+                    if ((u & 1) == 0) {
+                        __builtin_amdgcn_sched_barrier(0);
+                        arrived(i);
+                        if (i < 7) read(i + 1);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    multiply(u);
+                    if (u > 0) scale_add(u - 1);
+                    if (u < 15) unpack(u + 1);
+                    if (PREC == NVQ_W4A16 && (u & 1) == 0) {
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            __builtin_amdgcn_sched_group_barrier(kMatrix, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(kVector, 4, 0);
+                        }
+                    } else {
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            __builtin_amdgcn_sched_group_barrier(kMatrix, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(kVector, PREC == NVQ_W4A16 ? 7 : 9, 0);
+                        }
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            };
+            for (int c = 0; c < steps; ++c) {
+                // (ahead of the waves that multiply: what it asks for takes longest)
+                __builtin_amdgcn_s_setprio(2);
+                begin(c);
+                __builtin_amdgcn_s_setprio(0);
+                if (active) {
+                    places();
+                    read(0);
+                    unpack(0);
+                    units();
+                    scale_add(15);
+                    add(f, sums);
+                    if ((c & 7) == 7) {
+                        add(total, f);
+                        clear(f);
+                    }
+                }
+                buf ^= 1;
             }
-            if (c + 1 < steps || more) issue_w(src, c + 1 < steps ? c + 1 : 0);
-            if (active) {
-                if (codes)
-                    products(std::integral_constant<int, NVQ_W4A8>(), apos8 + buf * kA, q, sc);
-                else
-                    products(std::integral_constant<int, NVQ_W4A16>(), apos16 + buf * kA, q, sc);
-            }
-            if ((c & 7) == 7) {
-                add(total, f);
-                clear(f);
-            }
-            buf ^= 1;
-        }
+        };
+        clear(f);
+        clear(total);
+        const bool codes = src.precision == NVQ_W4A8;
+        if (codes)
+            bundle(std::integral_constant<int, NVQ_W4A8>());
+        else
+            bundle(std::integral_constant<int, NVQ_W4A16>());
         add(total, f);
         if (active) {
             CGroup &P = tab[cur.p];
@@ -360,7 +450,7 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                 }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
-                const RowRef o = locate_row(P.segs, ((cur.unit + w) * R + r) * 16 + n, G);
+                const RowRef o = locate_row(P.segs, ((cur.unit + w) * R + r) * 16 + n, 0);
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -374,6 +464,8 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
         if (!more) break;
         cur = nxt;
     }
+#undef NVQ_RD2
+#undef NVQ_RD128
 #undef NVQ_RD32
 #undef NVQ_RD64
 }
@@ -386,11 +478,11 @@ int rows_grid(int nunits, int nparts) {
     return groups < cap ? groups : cap;
 }
 
-int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, int grid, int M,
-                     uint32_t *tickets, hipStream_t st) {
+int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, const uint32_t *order, int grid,
+                     int M, uint32_t *tickets, hipStream_t st) {
     if (nparts <= 0 || grid <= 0) return NVQ_OK;
-    hipLaunchKernelGGL(gemv_rows_kernel, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, M,
-                       tickets);
+    hipLaunchKernelGGL(gemv_rows_kernel, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, order,
+                       M, tickets);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }

@@ -1055,6 +1055,36 @@ def test_rows_plan_draws_tickets_and_replays():
     dl.close()
 
 
+# The workgroups of a part take its phases by their K: one and two phases (as they stand), and several of
+# rising K, divided by the cuts or smaller than a group of units.
+@pytest.mark.parametrize("shapes,mbytes", [([], 300), ([(4999, 3072, 1)], 150),
+                                           ([(40000, 512, 0), (30, 1024, 1), (129, 1536, 2), (7000, 2048, 3),
+                                             (3, 2560, 4), (2500, 4096, 5)], 60)])
+def test_rows_plan_results_do_not_depend_on_the_order_of_the_phases(shapes, mbytes):
+    say("rows plan, order of the phases", shapes)
+    M = 29
+    bulk = bulk_layer(M, mbytes)
+    entries, host = model_entries(shapes, (1, 0)[:max(1, len(shapes) // 3)], M=M, seed=8655)
+    ran = []
+    for turn in (1, -1):
+        dl = nvq.DecodeList((entries[:3] + [bulk[0]] + entries[3:])[::turn], M, 0)
+        assert kernels_of(dl) == ["rows"]
+        dl.run_plan()
+        torch.cuda.synchronize()
+        check_bulk(bulk, M)
+        ran.append([e["y"].clone() for e in entries + [bulk[0]]])
+        dl.close()
+        for e in entries:
+            e["y"].zero_()
+    assert all(torch.equal(a, b) for a, b in zip(*ran))
+    rng = np.random.default_rng(3)
+    for y, h in zip(ran[0], host):
+        N = y.shape[1]
+        pick = np.unique(np.concatenate([[0, N - 1, N // 2], rng.integers(0, N, 24)]))
+        sub = dict(h, qweight=h["qweight"][pick], scales=h["scales"][pick])
+        assert np_ref.rel_l2(y.cpu().numpy()[:, pick], oracle.decode_linears([sub], M, 0)[0]) < 1e-5
+
+
 @pytest.mark.parametrize("M,kernel", [(2, "rings"), (16, "rings"), (17, "rings"), (32, "rings"), (17, "rows"),
                                       (32, "rows")])
 def test_grid_sums_are_added_in_the_stated_order(M, kernel):
