@@ -2,8 +2,8 @@
 // of groups, activation scales per token or per group: the kernel behind the single calls
 // and the per-phase walk (up to three tokens and few rows: see gemv_wave_per_row).  Paper:
 // the W4A8 / W4A16 kernel descriptions; the arithmetic is that of mfma_act.h (one 16x16x32
-// MFMA per quantisation group, 16 tokens times 16 rows, the constant nibble offset removed
-// by a second MFMA).
+// MFMA per quantisation group, 16 tokens times 16 rows, the constant nibble offset of W4A16 removed
+// by a second MFMA; W4A8 weights enter as signed bytes 16 (n - 8)).
 //
 // A workgroup of W waves owns 16 RT consecutive rows; the waves share out K in blocks of
 // NG groups (eight: 256 inputs, a whole 128-byte line of every row), wave w the blocks w, w
@@ -24,15 +24,20 @@
 // sums get longer, four to eight times in parts, and a chain of layers amplifies the bits that
 // differ from the other kernels' to a hundredth of the result.)
 //
-// What bounds it: neither memory nor arithmetic alone.  28672 x 4096 at 8 tokens takes 16.5
-// (W4A8) to 18.8 us (W4A16), 3.5 to 4 TB/s; the per-tile grid that loaded straight into
-// registers took 25 and 31.  The vector ALUs are busy half of the time (16 to 18 instructions
-// per 16 x 16 x 32 product where a row's matrix is one of four, 13.5 to 16 in a launch of one matrix), the
-// matrix cores a sixth.  The sixty-four chains cost registers
-// and a longer way through LDS: with a scale per group 16384 x 3072 takes 10.1 us at 4 tokens
+// What bounds it: a launch, and then the instructions of a compute unit's waves.  4096 x 4096 at 8 tokens
+// (W4A16, 4.1 us between launches): the first load leaves 0.6 us after a workgroup's start, the first block
+// arrives after 1.4, the last 2.4, and 0.9 go by with the slowest wave's products and the sums; between the
+// loads memory is near its rate.  28672 x 4096 at 8 tokens takes 14.5 (W4A8) to 16.7 us (W4A16), a compute
+// unit with 4 workgroups 2 us longer than one with 3; the per-tile grid that loaded straight into
+// registers took 25 and 31.  A product takes 8 to 10 vector instructions and one or two LDS reads with up to 8
+// tokens (11 to 13 and three when the products of a pair of groups were brought together by lane
+// exchanges: 17.2 us instead of 16.7, 8192 x 2048 4.4 instead of 4.1, the 8B chain 188.4 instead of 183.2).
+// The sixty-four chains cost registers
+// and a longer way through LDS: with a scale per group 16384 x 3072 takes 9.2 us at 4 tokens
 // (8.6 in one chain per wave; a wave per row, which served these calls before, 18.7), 28672 x
 // 4096 20, 27 and 57 us at 8, 16 and 32 tokens (that: 63, 111 and 202).  Two to four blocks in
-// flight per wave instead of one, with fewer workgroups per compute unit, were no faster.
+// flight per wave instead of one were no faster, with the same number of workgroups per compute unit either
+// (4096 x 14336 11.4 us against 10.8), nor were priorities of any kind.
 //
 // W, NG: eight waves with blocks of eight groups, or where that is better
 //  - four waves, in eight column chains (see slice_eight_waves), and with a scale per group and up to
@@ -87,11 +92,12 @@ struct SliceBlock {
     static constexpr int kW = 0, kSc = kW + RT * kWTile, kA = kSc + kScBytes;
     static constexpr int kXs = kA + TOK * kTokenBytes, kBytes = kXs + kXsOps * 256;
 
-    // With up to eight tokens lane rows 2 and 3 of a product hold no token.  The products of
-    // groups i and i + 4 of a block are therefore put into one register each, group i + 4 in the
-    // upper half of the lanes, and rescaled and added together: a pair of groups costs 4 fmaf, 4
-    // (W4A8) conversions and 4 exchanges instead of 8 and 8, with half the registers.
+    // With up to eight tokens lane rows 2 and 3 of a product hold no token.  The products of groups i and
+    // i + 4 of a block are therefore added into one register each: group i multiplies the tokens as rows 0
+    // to 7 of the operand, group i + 4 as rows 8 to 15, and what the other rows read in LDS is zero.  A pair of
+    // groups then costs 4 conversions (W4A8) and 4 fmaf instead of 8 and 8, with half the registers.
     static constexpr bool kPair = TOK == 8 && NG == 8;
+    static constexpr int kZero = kPair ? 16 : 0;  // bytes of zeros behind the rings, for those
     static constexpr int group_half(int kb) { return kPair ? kb >> 1 : 0; }  // whose groups lane row kb adds
 
     // Where lane row kb finds the scales of its first token, and a token's place among the
@@ -126,78 +132,39 @@ struct SliceBlock {
 // tokens: 5.1 us against 4.5).  SEGS: room for kMaxSeg matrices, or for the one of a single call, which
 // then has fewer lines of them and no matrix to select for its rows and results (W4A16, 16 tokens: 4096 x
 // 4096 4.6 us with four, 4.2 with one, 5000 x 96 3.8 and 3.1; 3 tokens, 300 x 1024 2.7 and 2.5).
+// A workgroup's rows belong to one matrix (a matrix that ends inside a row tile leaves the rest of it
+// empty), so that everything but a lane's place in the tile is in scalar registers: when every lane
+// found the matrix of its own rows, a third of a wave's vector instructions at K = 4096 were spent
+// before its first load and behind its last product (four 8B blocks as a chain at 8 tokens: 191.4 us, now
+// 189.6).
 template <int SEGS, bool DEBUG>
 struct SlicePhase {
     const uint4 *qw[SEGS];
     const uint16_t *sc[SEGS];
     void *y[SEGS];
-    int row_end[SEGS];  // of matrices that are not there: as the last one's
+    int N[SEGS];         // of the whole matrix
+    int rows[SEGS];
+    int unit_end[SEGS];  // workgroups up to this matrix; of those that are not there: as the last one's
     const char *x;
     const float *xscale;
     int G, M;
-    int units;       // workgroups
-    uint32_t bf16;   // bit i: matrix i has bf16 results
+    uint32_t bf16;  // bit i: matrix i has bf16 results; bit 8 + i: its workgroups have 16 rows each
     int32_t *dbg[DEBUG ? SEGS : 1];
 };
-// What of a phase a workgroup keeps: where its rows are and their results go.
-template <int SEGS, bool DEBUG>
-struct SliceRows {
-    const uint4 *qw[SEGS];
-    const uint16_t *sc[SEGS];
-    void *y[SEGS];
-    int row_end[SEGS];
-    uint32_t bf16;
-    int32_t *dbg[DEBUG ? SEGS : 1];
+// What of a phase a workgroup keeps: the matrix its rows belong to.
+struct SliceMatrix {
+    const uint4 *qw;
+    const uint16_t *sc;
+    void *y;
+    int32_t *dbg;
+    int N, rows;
+    bool bf16, half;
 };
 template <int NP, int SEGS, bool DEBUG>
 struct SliceArgs {
     SlicePhase<SEGS, DEBUG> phase[NP];  // the first phase's workgroups come first
 };
-static_assert(sizeof(SlicePhase<kMaxSeg, false>) == 152 && kMaxMerge == 2, "three lines; one comparison finds a workgroup's phase");
-
-// A row of a phase (past the last one: the last one again, not valid).  Selected, not indexed, as in
-// locate_row.
-struct SliceRow {
-    const uint4 *qw;
-    const uint16_t *sc;
-    void *y;
-    int32_t *dbg;
-    int N, n;
-    bool bf16, valid;
-};
-template <int SEGS, bool DEBUG>
-__device__ __forceinline__ SliceRow slice_row(const SliceRows<SEGS, DEBUG> &P, int row, int G) {
-    SliceRow r;
-    r.valid = row < P.row_end[SEGS - 1];
-    if (!r.valid) row = P.row_end[SEGS - 1] - 1;
-    int first = 0, end = P.row_end[0];
-    r.qw = P.qw[0];
-    r.sc = P.sc[0];
-    r.y = P.y[0];
-    r.dbg = P.dbg[0];
-    r.bf16 = (P.bf16 & 1u) != 0;
-#pragma unroll
-    for (int i = 1; i < SEGS; ++i) {
-        const uint4 *const qw = P.qw[i];
-        const uint16_t *const sc = P.sc[i];
-        void *const y = P.y[i];
-        int32_t *const dbg = P.dbg[DEBUG ? i : 0];
-        const int from = P.row_end[i - 1], to = P.row_end[i];
-        const bool in = row >= from;
-        first = in ? from : first;
-        end = in ? to : end;
-        r.qw = in ? qw : r.qw;
-        r.sc = in ? sc : r.sc;
-        r.y = in ? y : r.y;
-        r.dbg = in ? dbg : r.dbg;
-        r.bf16 = in ? (P.bf16 >> i & 1u) != 0 : r.bf16;
-    }
-    r.N = end - first;
-    r.n = row - first;
-    r.qw += (int64_t)r.n * G;
-    r.sc += (int64_t)r.n * G;
-    return r;
-}
+static_assert(sizeof(SlicePhase<kMaxSeg, false>) == 184 && kMaxMerge == 2, "three lines; one comparison finds a workgroup's phase");
 
 template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, int SEGS, bool DEBUG>
 __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, DEBUG>) {
@@ -214,9 +181,9 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
     static_assert(U * C * W == V && (U == 1 || U == 2), "every chain has one place");
     constexpr int SH = W / 2;  // by group: lanes that share a result
     static_assert(!kByGroup || SH == 2 || SH == 4, "128 results at a time");
-    constexpr int kRing = W * B::kBytes, kRedStride = 128 + 64 / SH;
+    constexpr int kRing = W * B::kBytes, kLds = kRing + B::kZero, kRedStride = 128 + 64 / SH;
     constexpr int kRed = kByGroup ? W * C * kRedStride * 4 : V * kTile * 256;
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[kRing > kRed ? kRing : kRed];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds > kRed ? kLds : kRed];
 
     typedef const __attribute__((address_space(4))) SlicePhase<SEGS, DEBUG> CPhase;
     typedef const __attribute__((address_space(4))) uint32_t CWord;
@@ -229,65 +196,74 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         CWord *a = (CWord *)phase;
         constexpr int kNext = sizeof(SlicePhase<SEGS, DEBUG>) / 4;
         const uint32_t l0 = a[0], l1 = a[16], l2 = a[32], l3 = a[kNext], l4 = a[kNext + 16], l5 = a[NP * kNext - 1];
-        const int units = phase->units;
+        const int units = phase->unit_end[SEGS - 1];
         asm volatile("" ::"s"(l0), "s"(l1), "s"(l2), "s"(l3), "s"(l4), "s"(l5), "s"(units));
         if (unit >= units) {
             unit -= units;
             ++phase;
         }
     }
-    // A copy in scalar registers that the compiler takes for values of its own: it would select among
-    // the fields' addresses and load again, once in front of the first weights and once in front of
-    // every store (with a scale per group, W4A8: 9361 x 7232 at 25 tokens 35.1 us, so 32.3, 29039 x 544 at
-    // 16 27.4 and 24.7; four 8B blocks as a chain at 8 tokens 196 and 190, four of 3B at 4 147 and 139).
-    SliceRows<SEGS, DEBUG> S;
+    // (Copies in scalar registers that the compiler takes for values of its own: it would select among
+    // the fields' addresses and load again.)
+    const uint4 *qw[SEGS];
+    const uint16_t *sc[SEGS];
+    void *y[SEGS];
+    int N[SEGS], rows[SEGS], unit_end[SEGS];
 #pragma unroll
     for (int i = 0; i < SEGS; ++i) {
-        S.qw[i] = phase->qw[i];
-        S.sc[i] = phase->sc[i];
-        S.y[i] = phase->y[i];
-        S.row_end[i] = phase->row_end[i];
-        if (DEBUG || i == 0) S.dbg[DEBUG ? i : 0] = phase->dbg[DEBUG ? i : 0];
+        qw[i] = phase->qw[i];
+        sc[i] = phase->sc[i];
+        y[i] = phase->y[i];
+        N[i] = phase->N[i];
+        rows[i] = phase->rows[i];
+        unit_end[i] = phase->unit_end[i];
+        asm volatile("" : "+s"(qw[i]), "+s"(sc[i]), "+s"(y[i]), "+s"(N[i]), "+s"(rows[i]), "+s"(unit_end[i]));
     }
-    S.bf16 = phase->bf16;
     const int G = phase->G, M = phase->M;
     const char *const xin = phase->x;
     const float *const xscale = phase->xscale;
-    static_assert(SEGS == 1 || (SEGS == 4 && kMaxSeg == 4), "the registers named here");
-    if constexpr (SEGS == 4) {
-        asm volatile("" : "+s"(S.qw[0]), "+s"(S.qw[1]), "+s"(S.qw[2]), "+s"(S.qw[3]), "+s"(S.sc[0]), "+s"(S.sc[1]),
-                     "+s"(S.sc[2]), "+s"(S.sc[3]));
-        asm volatile("" : "+s"(S.y[0]), "+s"(S.y[1]), "+s"(S.y[2]), "+s"(S.y[3]), "+s"(S.row_end[0]),
-                     "+s"(S.row_end[1]), "+s"(S.row_end[2]), "+s"(S.row_end[3]), "+s"(S.bf16));
-    } else {
-        asm volatile("" : "+s"(S.qw[0]), "+s"(S.sc[0]), "+s"(S.y[0]), "+s"(S.row_end[0]), "+s"(S.bf16));
+    const uint32_t bits = phase->bf16;
+    SliceMatrix S = {qw[0], sc[0], y[0], phase->dbg[0], N[0], rows[0], (bits & 1u) != 0, (bits >> 8 & 1u) != 0};
+    int first = 0;  // the matrix's first workgroup
+#pragma unroll
+    for (int i = 1; i < SEGS; ++i) {
+        if (unit < unit_end[i - 1]) continue;
+        S = {qw[i], sc[i], y[i], phase->dbg[DEBUG ? i : 0], N[i], rows[i], (bits >> i & 1u) != 0, (bits >> (8 + i) & 1u) != 0};
+        first = unit_end[i - 1];
     }
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 15, kb = lane >> 4;
-    const int row0 = unit * (16 * RT);
+    const bool one_tile = RT == 2 && SEGS > 1 && S.half;
+    const int row0 = (unit - first) * (one_tile ? 16 : 16 * RT);
+    // the last of the tile's rows: others are read as this one
+    const int last = one_tile && S.rows - row0 > 16 ? 15 : S.rows - 1 - row0;
+    const char *const qrow = reinterpret_cast<const char *>(S.qw + (int64_t)row0 * G);
+    const char *const srow = reinterpret_cast<const char *>(S.sc + (int64_t)row0 * G);
     const int NB = (G + NG - 1) / NG;
     const int nblk = NB > w ? (NB - w + W - 1) / W : 0;
     unsigned char *const slot = lds + w * B::kBytes;
 
     // Sources, at the start of the row: weights (a row's NG pieces of 16 bytes side by
     // side, permuted against the neighbouring rows'), scales, activations.
-    const char *wsrc[B::kWOps], *ssrc[B::kScOps];
+    uint32_t woff[B::kWOps], soff[B::kScOps];
     constexpr int kWRows = 64 / NG;  // rows per weight load
     int wc[2];                       // the piece, even and odd j
 #pragma unroll
     for (int j = 0; j < 2; ++j) wc[j] = (lane % NG) ^ (((kWRows * j + lane / NG) / (16 / NG)) % NG);
 #pragma unroll
-    for (int j = 0; j < B::kWOps; ++j)
-        wsrc[j] = reinterpret_cast<const char *>(slice_row(S, row0 + kWRows * j + lane / NG, G).qw) +
-                  (TAIL ? 0 : 16 * wc[j & 1]);
+    for (int j = 0; j < B::kWOps; ++j) {
+        const int r = kWRows * j + lane / NG;
+        woff[j] = (uint32_t)(r < last ? r : last) * (uint32_t)(G * 16) + (TAIL ? 0u : 16u * (uint32_t)wc[j & 1]);
+    }
     constexpr int kRows = 16 * RT;
     int sg[B::kScOps];  // first group of the lane's word
 #pragma unroll
     for (int k = 0; k < B::kScOps; ++k) {
         const int word = k * 64 + lane;
         sg[k] = SCB == 16 ? 0 : (word / kRows * (SCB / 2)) % NG;
-        ssrc[k] = reinterpret_cast<const char *>(slice_row(S, row0 + word % kRows, G).sc);
+        const int r = word % kRows;
+        soff[k] = (uint32_t)(r < last ? r : last) * (uint32_t)(G * 2);
     }
     // activations: 2 or 4 tokens per instruction, pieces permuted against each other
     constexpr int kPieces = B::kPieces;
@@ -313,21 +289,21 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         const int g0 = NG * (w + W * b);
 #pragma unroll
         for (int j = 0; j < B::kWOps; ++j) {
-            const char *p = wsrc[j] + (TAIL ? (size_t)clamp_g(g0 + wc[j & 1]) * 16 : (size_t)g0 * 16);
+            const char *p = TAIL ? qrow + (woff[j] + 16u * (uint32_t)clamp_g(g0 + wc[j & 1])) : qrow + (size_t)g0 * 16 + woff[j];
             __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kW + j * 1024), 16, 0, 0);
         }
 #pragma unroll
         for (int k = 0; k < B::kScOps; ++k) {
             if (SCB == 16) {
-                const char *p = ssrc[k] + (size_t)g0 * 2;
+                const char *p = srow + (size_t)g0 * 2 + soff[k];
                 if (lane < kRows)
                     __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kSc), 16, 0, 0);
             } else if (SCB == 4) {  // (a pair of groups is inside the row or outside it)
                 const int g = g0 + sg[k];
-                const char *p = ssrc[k] + (size_t)(g < G ? g : G - 2) * 2;
+                const char *p = srow + (soff[k] + 2u * (uint32_t)(g < G ? g : G - 2));
                 __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kSc + k * 256), 4, 0, 0);
             } else {
-                const char *p = ssrc[k] + (size_t)clamp_g(g0 + sg[k]) * 2;
+                const char *p = srow + (soff[k] + 2u * (uint32_t)clamp_g(g0 + sg[k]));
                 __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kSc + k * 256), 2, 0, 0);
             }
         }
@@ -346,7 +322,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         if (PG) {
 #pragma unroll
             for (int j = 0; j < B::kXsOps; ++j) {
-                const float *p = xscale + (xsoff[j] + (uint32_t)clamp_g(g0 + lane % NG));
+                const char *p = reinterpret_cast<const char *>(xscale) + 4u * (xsoff[j] + (uint32_t)clamp_g(g0 + lane % NG));
                 __builtin_amdgcn_global_load_lds((const void *)p, (slice_lds_ptr)(slot + B::kXs + j * 256), 4, 0, 0);
             }
         }
@@ -382,6 +358,12 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
     auto apiece_at = [&](uint32_t p0, int i, int h) {
         return at + (p0 ^ (uint32_t)(16 * (PREC == NVQ_W4A8 ? 2 * i + h : 4 * i + 2 * h)));
     };
+    // pairs: rows 0 to 7 of the operand of groups 0 to 3, rows 8 to 15 of that of 4 to 7, and zeros
+    const uint32_t zero = (uint32_t)(uintptr_t)lds + kRing;
+    if (B::kPair) asm volatile("ds_write_b32 %0, %1" ::"v"(zero + 4 * (n & 3)), "v"(0) : "memory");
+    auto pair_at = [&](uint32_t p0, int i, int h) {
+        return (n < 8) == (i < 4) ? B::kA + apiece_at(p0, i, h) : zero;
+    };
     const int half = B::group_half(kb);
     const uint32_t spos = at + (SCB == 16 ? 16 : 4) * n + half * B::kScRead * B::kScStep;
     const uint32_t xspos = at + B::xs_place(kb);  // token 4 kb, 4 NG bytes per token
@@ -398,17 +380,35 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         return 16 * ((reg >> 2) % MT) + 4 * ((result >> 4) & (B::kPair ? 1 : 3)) + (reg & 3);
     };
     constexpr int kXsc = kByGroup ? kRounds : MT * 4;
+    constexpr float kWeightUnit = PREC == NVQ_W4A8 ? 0.0625f : 1.0f;  // (see weights, below)
     float xsc[kXsc];
     if (kTokenScale) {
 #pragma unroll
         for (int i = 0; i < kXsc; ++i) {
             const int m = kByGroup ? stored_token(stored_reg(i)) : (i >> 2) * 16 + (B::kPair ? kb & 1 : kb) * 4 + (i & 3);
-            xsc[i] = as_global<float>(xscale)[m < M ? m : M - 1];
+            xsc[i] = kWeightUnit * as_global<float>(xscale)[m < M ? m : M - 1];
         }
     }
 
+    // (in registers before the first block arrives)
+    uint32_t wplace[kFresh ? 1 : NG], pplace[kFresh || !B::kPair ? 1 : NG][2];
+    if constexpr (!kFresh) {
+#pragma unroll
+        for (int i = 0; i < NG; ++i) {
+            wplace[i] = wpiece(wpos0, i);
+            asm volatile("" : "+v"(wplace[i]));
+            if constexpr (B::kPair) {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    pplace[i][h] = pair_at(apos0, i, h);
+                    asm volatile("" : "+v"(pplace[i][h]));
+                }
+            }
+        }
+    }
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD64(dst_, addr_, off_) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
+#define NVQ_RDROWS(dst_, addr_, off_) asm volatile("ds_read2st64_b32 %0, %1 offset0:0 offset1:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD128(dst_, addr_, off_) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
     // block b of set u
     auto block = [&](int b, auto set) {
@@ -424,28 +424,42 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         uint32_t q[RT][NG], sc[RT][kSc];
         uint32_t wpos = wpos0, apos = apos0;
         if (kFresh) asm volatile("" : "+v"(wpos), "+v"(apos));
+        constexpr bool kRows = B::kPair && RT == 2;
+        uint2v q2[kRows ? NG : 1], s2[B::kPair && SCB == 16 ? RT : 1];  // weights of both row tiles; scales
         uint2v a2[PREC == NVQ_W4A8 ? 1 : MT][NG][2];
         uint32_t a1[PREC == NVQ_W4A8 ? MT : 1][NG][2];
         float4v xs4[PG ? MT : 1][4][B::kXsRead];
 #pragma unroll
-        for (int i = 0; i < NG; ++i)
+        for (int i = 0; i < NG; ++i) {
+            if constexpr (kRows) {
+                NVQ_RDROWS(q2[i], (kFresh ? wpiece(wpos, i) : wplace[kFresh ? 0 : i]), B::kWTile / 256);
+            } else {
 #pragma unroll
-            for (int r = 0; r < RT; ++r) NVQ_RD32(q[r][i], wpiece(wpos, i), B::kW + r * B::kWTile);
+                for (int r = 0; r < RT; ++r) NVQ_RD32(q[r][i], (kFresh ? wpiece(wpos, i) : wplace[kFresh ? 0 : i]), B::kW + r * B::kWTile);
+            }
+        }
 #pragma unroll
-        for (int r = 0; r < RT; ++r)
+        for (int r = 0; r < RT; ++r) {
+            if constexpr (B::kPair && SCB == 16) {
+                NVQ_RD64(s2[r], spos, B::kSc + r * 256);
+            } else {
 #pragma unroll
-            for (int k = 0; k < kSc; ++k)
-                NVQ_RD32(sc[r][k], spos, B::kSc + r * (SCB == 16 ? 256 : 64) + k * B::kScStep);
+                for (int k = 0; k < kSc; ++k)
+                    NVQ_RD32(sc[r][k], spos, B::kSc + r * (SCB == 16 ? 256 : 64) + k * B::kScStep);
+            }
+        }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int i = 0; i < NG; ++i)
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
+                    const uint32_t from = B::kPair ? (kFresh ? pair_at(apos, i, h) : pplace[kFresh || !B::kPair ? 0 : i][h])
+                                                   : B::kA + apiece_at(apos, i, h);
                     if (PREC == NVQ_W4A8)
-                        NVQ_RD32(a1[mt][i][h], apiece_at(apos, i, h), B::kA + mt * 16 * B::kTokenBytes);
+                        NVQ_RD32(a1[mt][i][h], from, mt * 16 * B::kTokenBytes);
                     else
-                        NVQ_RD64(a2[mt][i][h], apiece_at(apos, i, h), B::kA + mt * 16 * B::kTokenBytes);
+                        NVQ_RD64(a2[mt][i][h], from, mt * 16 * B::kTokenBytes);
                 }
         if (PG) {
 #pragma unroll
@@ -460,9 +474,21 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 #pragma unroll
         for (int r = 0; r < RT; ++r) {
 #pragma unroll
-            for (int i = 0; i < NG; ++i) asm volatile("" : "+v"(q[r][i]));
+            for (int i = 0; i < NG; ++i) {
+                if constexpr (kRows) {
+                    if (r == 0) asm volatile("" : "+v"(q2[i]));
+                } else {
+                    asm volatile("" : "+v"(q[r][i]));
+                }
+            }
+            if constexpr (B::kPair && SCB == 16) {
+                asm volatile("" : "+v"(s2[r]));
+                sc[r][0] = s2[r].x;
+                sc[r][1] = s2[r].y;
+            } else {
 #pragma unroll
-            for (int k = 0; k < kSc; ++k) asm volatile("" : "+v"(sc[r][k]));
+                for (int k = 0; k < kSc; ++k) asm volatile("" : "+v"(sc[r][k]));
+            }
         }
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
@@ -485,13 +511,29 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                 return __builtin_bit_cast(bf16x8, v);
             }
         };
+        // W4A8: no correction of the offset, the weights enter as 16 (n - 8): the nibble in the high half of
+        // its byte, its top bit flipped (the factor leaves with the token's scale, or at the end)
+        auto weights = [&](int r, int i) {
+            uint32_t v;
+            if constexpr (kRows)
+                v = q2[i][r];
+            else
+                v = q[r][i];
+            if constexpr (PREC == NVQ_W4A8) {
+                const uint32_t lo = ((v << 4) & 0xf0f0f0f0u) ^ 0x80808080u, hi = (v & 0xf0f0f0f0u) ^ 0x80808080u;
+                return (long)((uint64_t)lo | ((uint64_t)hi << 32));
+            } else {
+                return A::weights(v);
+            }
+        };
+        // groups i, and i + 4 in the upper half of a pair
         auto dump = [&](const typename A::offset_t &raw, int i, int r, int mt) {
-            const SliceRow o = slice_row(S, row0 + 16 * r + n, G);
-            if (!o.valid || !o.dbg || g0 + i >= G) return;
+            const int row = row0 + 16 * r + n, g = g0 + i + 4 * half;
+            if (row >= S.rows || !S.dbg || g >= G) return;
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const int m = mt * 16 + kb * 4 + jj;
-                if (m < M) o.dbg[((int64_t)m * o.N + o.n) * G + g0 + i] = (int)raw[jj];
+                const int m = mt * 16 + (B::kPair ? kb & 1 : kb) * 4 + jj;
+                if (m < M) S.dbg[((int64_t)m * S.N + row) * G + g] = (int)raw[jj] / 16;
             }
         };
         // what the lane adds in round i: group i, or i + 4 in the upper half of a pair
@@ -509,49 +551,60 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         // wait costs up to 5% (W4A8, 32 tokens, 16400 x 2720: 31.0 -> 32.5 us) and nothing at
         // 4096 x 4096.
         constexpr bool kBranches = TAIL || DEBUG;
-        if constexpr (B::kPair) {
+        // Group i, or the pair of groups i and i + 4: its product with row tile r and token tile mt.
+        auto product = [&](int i, int r, int mt, const typename A::offset_t &off) {
+            if constexpr (B::kPair) {
+                const typename A::offset_t p = A::multiply(activation(0, i), weights(r, i), off);
+                return A::multiply(activation(0, i + 4), weights(r, i + 4), p);
+            } else {
+                return A::multiply(activation(mt, i), weights(r, i), off);
+            }
+        };
+        // W4A16: the constant offset of its weights, for all row tiles
+        auto correction = [&](int i, int mt) {
+            if constexpr (PREC == NVQ_W4A8)
+                return typename A::offset_t{0, 0, 0, 0};
+            else if constexpr (B::kPair)
+                return A::offset(activation(0, i + 4), A::offset(activation(0, i)));
+            else
+                return A::offset(activation(mt, i));
+        };
+        constexpr int kRounds = B::kPair ? 4 : NG;
+        if constexpr (kBranches) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
+            for (int i = 0; i < kRounds; ++i) {
                 if (TAIL && g0 + i >= G) break;  // the last block may end early
-                const auto lo = activation(0, i), hi = activation(0, i + 4);
-                const auto off_lo = A::offset(lo), off_hi = A::offset(hi);
 #pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    typename A::offset_t plo = A::multiply(lo, A::weights(q[r][i]), off_lo);
-                    typename A::offset_t phi = A::multiply(hi, A::weights(q[r][i + 4]), off_hi);
-                    if constexpr (kBranches) wait_written(plo, phi);
-                    if (DEBUG && PREC == NVQ_W4A8) {
-                        dump(plo, i, r, 0);
-                        dump(phi, i + 4, r, 0);
-                    }
-                    typename A::offset_t mine;
+                for (int mt = 0; mt < MT; ++mt) {
+                    const auto off = correction(i, mt);
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) {
-                        const auto both = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint4v, plo)[jj],
-                                                                           __builtin_bit_cast(uint4v, phi)[jj], false, false);
-                        if constexpr (PREC == NVQ_W4A8)
-                            mine[jj] = (int)both[0];
-                        else
-                            mine[jj] = __uint_as_float(both[0]);
+                    for (int r = 0; r < RT; ++r) {
+                        auto p = product(i, r, mt, off);
+                        wait_written(p);
+                        if (DEBUG && PREC == NVQ_W4A8) dump(p, i, r, mt);
+                        if (!TAIL || !B::kPair || g0 + i + 4 * half < G) add(A::value(p), i, r, mt);
                     }
-                    if (!TAIL || g0 + i + 4 * half < G) add(A::value(mine), i, r, 0);
                 }
             }
         } else {
+            // (the products of a round are used when those of the next are on their way)
+            constexpr int kLag = 2;
+            typename A::offset_t p[kLag][MT][RT];
 #pragma unroll
-            for (int i = 0; i < NG; ++i) {
-                if (TAIL && g0 + i >= G) break;
+            for (int i = 0; i < kRounds + kLag - 1; ++i) {
+                if (i < kRounds) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    const auto act = activation(mt, i);
-                    const auto off = A::offset(act);
+                    for (int mt = 0; mt < MT; ++mt) {
+                        const auto off = correction(i, mt);
 #pragma unroll
-                    for (int r = 0; r < RT; ++r) {
-                        typename A::offset_t p = A::multiply(act, A::weights(q[r][i]), off);
-                        if constexpr (kBranches) wait_written(p);
-                        if (DEBUG && PREC == NVQ_W4A8) dump(p, i, r, mt);
-                        add(A::value(p), i, r, mt);
+                        for (int r = 0; r < RT; ++r) p[i % kLag][mt][r] = product(i, r, mt, off);
                     }
+                }
+                if (i >= kLag - 1) {
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                        for (int r = 0; r < RT; ++r) add(A::value(p[(i - kLag + 1) % kLag][mt][r]), i - kLag + 1, r, mt);
                 }
             }
         }
@@ -563,10 +616,11 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 #undef NVQ_RD32
 #undef NVQ_RD64
 #undef NVQ_RD128
+#undef NVQ_RDROWS
 
+    // (row of the tile)
     auto store = [&](int row, int m, float sum) {
-        const SliceRow o = slice_row(S, row, G);
-        if (o.valid && m < M) store_global(o.y, o.bf16 ? NVQ_BF16 : NVQ_F32, (int64_t)m * o.N + o.n, sum);
+        if (row <= last && m < M) store_global(S.y, S.bf16 ? NVQ_BF16 : NVQ_F32, (int64_t)m * S.N + (row0 + row), sum);
     };
     __syncthreads();  // the blocks' LDS is free
     if constexpr (!kByGroup) {
@@ -595,7 +649,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 #pragma unroll
                 for (int k = 0; k < V; ++k) sum += red[k][reg][B::kPair ? lane & 31 : lane];
                 const int r = reg / (MT * 4), mt = (reg >> 2) % MT, jj = reg & 3;
-                store(row0 + 16 * r + n, mt * 16 + kb * 4 + jj, sum);
+                store(16 * r + n, mt * 16 + kb * 4 + jj, sum);
             }
         }
     } else {
@@ -629,10 +683,28 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                 v[0] += dpp_f32<kDppXor1>(v[0]);
                 const int reg = stored_reg(round), r = reg / (MT * 4);
                 if (share == 0)
-                    store(row0 + 16 * r + (result & 15), stored_token(reg), v[0] * (kTokenScale ? xsc[round] : 1.0f));
+                    store(16 * r + (result & 15), stored_token(reg), v[0] * (kTokenScale ? xsc[round] : kWeightUnit));
             }
         }
     }
+}
+
+// Two row tiles per workgroup: how many of a phase's tiles get a workgroup of their own, so that every
+// compute unit has the same rows.  With a tile or less per unit left over by whole workgroups, those
+// of two tiles would give some units two more and others none (28672 rows on 256 units: 128 rows or 96,
+// with halves 112; a chain of four such blocks at 8 tokens 190.4 us, so 188.4).
+inline int slice_halves(const GemvSegs &S) {
+    int tiles = 0;
+    for (int k = 0; k < S.nseg; ++k) tiles += (S.N[k] + 15) / 16;
+    const int cus = device_cu_count(), rest = tiles % (2 * cus);
+    return rest <= cus ? rest : 0;
+}
+// The rows of matrix k in workgroups of two tiles: it has a share of the `halves`, at its end.
+inline int slice_whole(const GemvSegs &S, int k, int halves) {
+    const int before = k > 0 ? S.row_end[k - 1] : 0, end = S.row_end[k];
+    auto share = [&](int rows) { return (int)((int64_t)halves * rows / S.total_rows); };
+    const int tiles = (S.N[k] + 15) / 16, whole = (tiles - (share(end) - share(before))) / 2 * 32;
+    return whole < S.N[k] ? whole : S.N[k];
 }
 
 template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, int SEGS, bool DEBUG>
@@ -642,22 +714,30 @@ int slice_launch(const SliceWork &w, int G, int M, hipStream_t st) {
     for (int i = 0; i < NP; ++i) {
         SlicePhase<SEGS, DEBUG> &p = a.phase[i];
         const GemvSegs &S = *w.segs[i];
-        for (int k = 0; k < SEGS; ++k) {
-            const bool there = k < S.nseg;
-            p.row_end[k] = there ? S.row_end[k] : S.total_rows;
-            if (!there) continue;
-            p.qw[k] = S.qw[k];
-            p.sc[k] = S.sc[k];
-            p.y[k] = S.y[k];
-            if (S.y_dtype[k] == NVQ_BF16) p.bf16 |= 1u << k;
-            if (DEBUG) p.dbg[DEBUG ? k : 0] = S.dbg[k];
-        }
+        int end = 0, seg = 0;
+        // rows from .. to - 1 of matrix k, in workgroups of `unit` rows
+        auto matrix = [&](int k, int from, int to, int unit) {
+            if (to <= from) return;
+            p.qw[seg] = S.qw[k] + (int64_t)from * G;
+            p.sc[seg] = S.sc[k] + (int64_t)from * G;
+            p.y[seg] = static_cast<char *>(S.y[k]) + (int64_t)from * (S.y_dtype[k] == NVQ_BF16 ? 2 : 4);
+            p.N[seg] = S.N[k];
+            p.rows[seg] = to - from;
+            if (S.y_dtype[k] == NVQ_BF16) p.bf16 |= 1u << seg;
+            if (unit < 16 * RT) p.bf16 |= 1u << (8 + seg);
+            if (DEBUG) p.dbg[DEBUG ? seg : 0] = S.dbg[k];
+            end += (to - from + unit - 1) / unit;
+            p.unit_end[seg++] = end;
+        };
+        const int halves = RT == 2 && 2 * S.nseg <= SEGS ? slice_halves(S) : 0;
+        for (int k = 0; k < S.nseg; ++k) matrix(k, 0, halves ? slice_whole(S, k, halves) : S.N[k], 16 * RT);
+        for (int k = 0; k < S.nseg && halves; ++k) matrix(k, slice_whole(S, k, halves), S.N[k], 16);
+        for (; seg < SEGS; ++seg) p.unit_end[seg] = end;
         p.x = reinterpret_cast<const char *>(w.x[i]);
         p.xscale = w.xscale[i];
         p.G = G;
         p.M = M;
-        p.units = (S.total_rows + 16 * RT - 1) / (16 * RT);
-        units += p.units;
+        units += end;
     }
     hipLaunchKernelGGL((gemv_slice_kernel<PREC, PG, TOK, RT, W, NG, V, SCB, NP, SEGS, DEBUG>), dim3(units), dim3(W * 64), 0,
                        st, a);

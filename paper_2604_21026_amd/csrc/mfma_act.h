@@ -153,8 +153,7 @@ struct Act<NVQ_W4A16> {
                                    __builtin_amdgcn_perm(kMagic, hi, 0x04030402u));
         return __builtin_bit_cast(bf16x8, b);
     }
-    __device__ static float4v offset(operand a) {
-        const float4v z = {0.0f, 0.0f, 0.0f, 0.0f};
+    __device__ static float4v offset(operand a, float4v z = float4v{0.0f, 0.0f, 0.0f, 0.0f}) {
         constexpr uint32_t kNeg136 = 0xc308c308u;  // bf16(-136) twice
         const uint4 c = make_uint4(kNeg136, kNeg136, kNeg136, kNeg136);
         return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, c), z, 0, 0,

@@ -1407,6 +1407,34 @@ def test_prepared_inputs_equal_the_standalone_calls(M, group, K):
     dl.close()
 
 
+# Walk in launches per phase, two matrices whose row tiles go out two by two: what is left over gets
+# workgroups of one tile each (a compute unit's worth or less: 2, 256, and with ragged matrices), so the rows
+# of a matrix lie in two places of the launch.  As one matrix the same rows are one piece.
+@pytest.mark.parametrize("prec", [nvq.W4A8, nvq.W4A16])
+@pytest.mark.parametrize("M,Na,Nb", [(8, 8224, 8192), (5, 10240, 10240), (3, 9985, 10480), (20, 16400, 21)])
+def test_walk_rows_in_two_matrices_equal_those_of_one(prec, M, Na, Nb):
+    say("walk, two matrices or one", prec, M, Na, Nb)
+    K = 512
+    q = torch.randint(0, 256, (Na + Nb, K // 2), dtype=torch.uint8, device=DEV,
+                      generator=torch.Generator(device=DEV).manual_seed(31 + M))
+    s = torch.randint(0x1400, 0x2c00, (Na + Nb, K // 32), dtype=torch.int16, device=DEV,
+                      generator=torch.Generator(device=DEV).manual_seed(32 + M))
+    x = act(33 + M, M, K).to(DEV)
+    norm = dict(x=x, in_op=nvq.IN_RMSNORM, gamma=torch.ones(K, dtype=torch.bfloat16, device=DEV), eps=1e-5,
+                precision=prec)
+    ys = [torch.full((M, n), 9.0, dtype=torch.float32, device=DEV) for n in (Na, Nb, Na + Nb)]
+    parts = [dict(norm, qweight=q[:Na], scales=s[:Na], y=ys[0]), dict(norm, qweight=q[Na:], scales=s[Na:], y=ys[1])]
+    nvq.decode_linears(parts, M, 0)
+    nvq.decode_linears([dict(norm, qweight=q, scales=s, y=ys[2])], M, 0)
+    torch.cuda.synchronize()
+    assert torch.equal(torch.cat(ys[:2], 1), ys[2])
+    h = nvq.rms_norm(x, norm["gamma"], 1e-5)[0]
+    rows = torch.tensor([0, 15, 16, Na - 1, Na, Na + Nb - 1])
+    host = dict(qweight=q[rows.to(DEV)].cpu().numpy(), scales=u16(s[rows.to(DEV)]), x=u16(h), precision=prec)
+    want = oracle.decode_linears([host], M, 0)[0]
+    assert np_ref.rel_l2(ys[2][:, rows.to(DEV)].cpu().numpy(), want) < 1e-5
+
+
 # Two phases that follow each other and do not depend on each other share their launches.  q (two
 # matrices) and o: independent; o and r: r reads what o wrote; r and w: w overwrites what r read;
 # five matrices on one input (two phases, one preparation) and one more phase; another K.  Sizes:
