@@ -142,13 +142,14 @@ struct SlicePhase {
     const uint4 *qw[SEGS];
     const uint16_t *sc[SEGS];
     void *y[SEGS];
-    int N[SEGS];         // of the whole matrix
-    int rows[SEGS];
-    int unit_end[SEGS];  // workgroups up to this matrix; of those that are not there: as the last one's
     const char *x;
     const float *xscale;
+    int N[SEGS];  // of the whole matrix
     int G, M;
     uint32_t bf16;  // bit i: matrix i has bf16 results; bit 8 + i: its workgroups have 16 rows each
+    // (with one matrix all that is read lies in one line)
+    int rows[SEGS];      // of it here
+    int unit_end[SEGS];  // workgroups up to this matrix; of those that are not there: as the last one's
     int32_t *dbg[DEBUG ? SEGS : 1];
 };
 // What of a phase a workgroup keeps: the matrix its rows belong to.
@@ -215,9 +216,10 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         sc[i] = phase->sc[i];
         y[i] = phase->y[i];
         N[i] = phase->N[i];
-        rows[i] = phase->rows[i];
-        unit_end[i] = phase->unit_end[i];
-        asm volatile("" : "+s"(qw[i]), "+s"(sc[i]), "+s"(y[i]), "+s"(N[i]), "+s"(rows[i]), "+s"(unit_end[i]));
+        asm volatile("" : "+s"(qw[i]), "+s"(sc[i]), "+s"(y[i]), "+s"(N[i]));
+        rows[i] = SEGS > 1 ? phase->rows[i] : N[i];
+        unit_end[i] = SEGS > 1 ? phase->unit_end[i] : 0;
+        if (SEGS > 1) asm volatile("" : "+s"(rows[i]), "+s"(unit_end[i]));
     }
     const int G = phase->G, M = phase->M;
     const char *const xin = phase->x;
@@ -234,7 +236,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int n = lane & 15, kb = lane >> 4;
-    const bool one_tile = RT == 2 && SEGS > 1 && S.half;
+    const bool one_tile = RT == 2 && TOK == 8 && SEGS > 1 && S.half;
     const int row0 = (unit - first) * (one_tile ? 16 : 16 * RT);
     // the last of the tile's rows: others are read as this one
     const int last = one_tile && S.rows - row0 > 16 ? 15 : S.rows - 1 - row0;
@@ -386,17 +388,18 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 #pragma unroll
         for (int i = 0; i < kXsc; ++i) {
             const int m = kByGroup ? stored_token(stored_reg(i)) : (i >> 2) * 16 + (B::kPair ? kb & 1 : kb) * 4 + (i & 3);
-            xsc[i] = kWeightUnit * as_global<float>(xscale)[m < M ? m : M - 1];
+            xsc[i] = as_global<float>(xscale)[m < M ? m : M - 1];
         }
     }
 
-    // (in registers before the first block arrives)
+    // (up to eight tokens in registers before the first block arrives; with more the compiler's own choice is
+    // up to 4 % faster)
     uint32_t wplace[kFresh ? 1 : NG], pplace[kFresh || !B::kPair ? 1 : NG][2];
     if constexpr (!kFresh) {
 #pragma unroll
         for (int i = 0; i < NG; ++i) {
             wplace[i] = wpiece(wpos0, i);
-            asm volatile("" : "+v"(wplace[i]));
+            if (TOK == 8) asm volatile("" : "+v"(wplace[i]));
             if constexpr (B::kPair) {
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
@@ -570,7 +573,17 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                 return A::offset(activation(mt, i));
         };
         constexpr int kRounds = B::kPair ? 4 : NG;
-        if constexpr (kBranches) {
+        if constexpr (PREC == NVQ_W4A8 && MT * RT == 1 && !kBranches) {
+            // the products of a round are used when those of the next are on their way (3072 x 8192 at 16 tokens
+            // 6.5 us, so 6.3; with more tiles there are enough of them)
+            typename A::offset_t p = product(0, 0, 0, correction(0, 0));
+#pragma unroll
+            for (int i = 0; i < kRounds; ++i) {
+                const typename A::offset_t now = p;
+                if (i + 1 < kRounds) p = product(i + 1, 0, 0, correction(i + 1, 0));
+                add(A::value(now), i, 0, 0);
+            }
+        } else {
 #pragma unroll
             for (int i = 0; i < kRounds; ++i) {
                 if (TAIL && g0 + i >= G) break;  // the last block may end early
@@ -579,32 +592,11 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                     const auto off = correction(i, mt);
 #pragma unroll
                     for (int r = 0; r < RT; ++r) {
-                        auto p = product(i, r, mt, off);
-                        wait_written(p);
+                        typename A::offset_t p = product(i, r, mt, off);
+                        if constexpr (kBranches) wait_written(p);
                         if (DEBUG && PREC == NVQ_W4A8) dump(p, i, r, mt);
                         if (!TAIL || !B::kPair || g0 + i + 4 * half < G) add(A::value(p), i, r, mt);
                     }
-                }
-            }
-        } else {
-            // (the products of a round are used when those of the next are on their way)
-            constexpr int kLag = 2;
-            typename A::offset_t p[kLag][MT][RT];
-#pragma unroll
-            for (int i = 0; i < kRounds + kLag - 1; ++i) {
-                if (i < kRounds) {
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) {
-                        const auto off = correction(i, mt);
-#pragma unroll
-                        for (int r = 0; r < RT; ++r) p[i % kLag][mt][r] = product(i, r, mt, off);
-                    }
-                }
-                if (i >= kLag - 1) {
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                        for (int r = 0; r < RT; ++r) add(A::value(p[(i - kLag + 1) % kLag][mt][r]), i - kLag + 1, r, mt);
                 }
             }
         }
@@ -630,7 +622,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const float xs = kTokenScale ? xsc[kByGroup ? 0 : mt * 4 + jj] : 1.0f;
+                const float xs = kTokenScale ? kWeightUnit * xsc[kByGroup ? 0 : mt * 4 + jj] : 1.0f;
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -683,7 +675,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                 v[0] += dpp_f32<kDppXor1>(v[0]);
                 const int reg = stored_reg(round), r = reg / (MT * 4);
                 if (share == 0)
-                    store(16 * r + (result & 15), stored_token(reg), v[0] * (kTokenScale ? xsc[round] : kWeightUnit));
+                    store(16 * r + (result & 15), stored_token(reg), v[0] * (kTokenScale ? kWeightUnit * xsc[round] : kWeightUnit));
             }
         }
     }
@@ -692,7 +684,9 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 // Two row tiles per workgroup: how many of a phase's tiles get a workgroup of their own, so that every
 // compute unit has the same rows.  With a tile or less per unit left over by whole workgroups, those
 // of two tiles would give some units two more and others none (28672 rows on 256 units: 128 rows or 96,
-// with halves 112; a chain of four such blocks at 8 tokens 190.4 us, so 188.4).
+// with halves 112; a chain of four such blocks at 8 tokens 190.4 us, so 188.4).  Up to eight tokens: a workgroup
+// of one tile multiplies as much as one of two, which is what counts beyond (two 8B blocks, W4A16, 16 tokens:
+// 105 us, with halves 108).
 inline int slice_halves(const GemvSegs &S) {
     int tiles = 0;
     for (int k = 0; k < S.nseg; ++k) tiles += (S.N[k] + 15) / 16;
@@ -729,7 +723,7 @@ int slice_launch(const SliceWork &w, int G, int M, hipStream_t st) {
             end += (to - from + unit - 1) / unit;
             p.unit_end[seg++] = end;
         };
-        const int halves = RT == 2 && 2 * S.nseg <= SEGS ? slice_halves(S) : 0;
+        const int halves = RT == 2 && TOK == 8 && 2 * S.nseg <= SEGS ? slice_halves(S) : 0;
         for (int k = 0; k < S.nseg; ++k) matrix(k, 0, halves ? slice_whole(S, k, halves) : S.N[k], 16 * RT);
         for (int k = 0; k < S.nseg && halves; ++k) matrix(k, slice_whole(S, k, halves), S.N[k], 16);
         for (; seg < SEGS; ++seg) p.unit_end[seg] = end;
