@@ -48,43 +48,38 @@ constexpr int kRowsA = 4 * kRowsBlock;  // a buffer: a step's 256 inputs as bf16
 constexpr int kRowsW = 2 * 2048;   // a wave's weights of a step: 32 rows x 128 bytes
 constexpr int kRowsSc = 1024;      // and the scales of two, 32 bytes per row
 
-// A part of the batch: the units begin .. begin + units - 1, phase by phase, in the order given or as they
-// stand in the batch.
+// A part of the batch: the units begin .. end - 1, in groups of up to four of one phase, phase by phase in
+// the order given or as they stand in the batch.  (Groups across phases made a workgroup of four small
+// phases keep all of K four times: 32 phases of up to 8192 rows and 14 x 512 inputs 118 us.)
 struct RowsPart {
-    CWord *order;  // its phases, or null
-    int first;     // its first phase
-    int begin, units;
+    CWord *order;  // its phases, or null: first, first + 1, ...
+    int first, phases;
+    int begin, end;
 };
 // A bundle: up to four consecutive units of one phase.
 struct RowsBundle {
     int p;            // phase
-    int unit, count;  // first unit (of the phase) and how many
-    int next;         // unit of the part after the bundle
-    int end;          // end of the group of units it belongs to
-    int at, base;     // the phase's place in the order, units of the part before it
+    int unit, count;  // first unit (of the phase) and how many; none: the part has no such group
+    int at, base;     // the phase's place in the order, groups of the part before it
 };
 
-// The bundle that unit u of the part begins, not before `from`'s phase.
-__device__ __forceinline__ RowsBundle rows_bundle(CGroup *tab, const RowsPart &P, const RowsBundle &from, int u, int end) {
-    RowsBundle b;
-    b.at = from.at;
-    b.base = from.base;
-    while (true) {  // (u is a unit of the part)
+// Group t of the part, not before `from`'s phase.
+__device__ __forceinline__ RowsBundle rows_bundle(CGroup *tab, const RowsPart &P, const RowsBundle &from, int t) {
+    RowsBundle b = from;
+    b.count = 0;
+    for (; b.at < P.phases; ++b.at) {
         b.p = P.order ? (int)P.order[b.at] : P.first + b.at;
         const int lo = tab[b.p].unit_begin, hi = lo + tab[b.p].unit_count;
-        const int from_unit = lo < P.begin ? P.begin : lo;
-        const int to_unit = hi < P.begin + P.units ? hi : P.begin + P.units;
-        const int phase_end = b.base + (to_unit - from_unit);
-        if (u < phase_end) {
-            b.unit = from_unit - lo + (u - b.base);
-            b.next = end < phase_end ? end : phase_end;
+        const int first = lo < P.begin ? P.begin : lo, units = (hi < P.end ? hi : P.end) - first;
+        const int groups = (units + kRowsWaves - 1) / kRowsWaves;  // (none, if units < 0)
+        if (t < b.base + groups) {
+            const int u = (t - b.base) * kRowsWaves;
+            b.unit = first - lo + u;
+            b.count = units - u < kRowsWaves ? units - u : kRowsWaves;
             break;
         }
-        b.base = phase_end;
-        ++b.at;
+        b.base += groups > 0 ? groups : 0;
     }
-    b.count = b.next - u;
-    b.end = end;
     return b;
 }
 
@@ -115,14 +110,16 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
     const int part_wgs = ((int)gridDim.x - 1 - part) / nparts + 1;
     RowsPart P;
     P.begin = (int)part_tab[part];
-    P.units = (int)part_tab[part + 1] - P.begin;
-    P.order = order_ ? (CWord *)order_ + nparts + 1 + ((CWord *)order_)[part] : nullptr;
+    P.end = (int)part_tab[part + 1];
     P.first = (int)part_tab[nparts + 1 + part];
-    // the group of ticket t: units 4 t .. + 3 of the part
-    int t = (int)blockIdx.x / nparts;
-    if (t * kRowsWaves >= P.units) return;
-    auto group_end = [&](int first) { return first + kRowsWaves < P.units ? first + kRowsWaves : P.units; };
-
+    P.phases = (int)part_tab[nparts + 1 + part + 1] + 1 - P.first;
+    P.order = nullptr;
+    if (order_) {
+        CWord *const order = (CWord *)order_;
+        P.order = order + nparts + 1 + order[part];
+        P.phases = (int)(order[part + 1] - order[part]);
+    }
+    int t = (int)blockIdx.x / nparts;  // the group
     auto source = [&](const RowsBundle &b) {
         RowsSource s;
         CGroup &P = tab[b.p];
@@ -235,8 +232,8 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
 #define NVQ_RD128(dst_, addr_, off_) asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD32(dst_, addr_, off_) asm volatile("ds_read_b32 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
 #define NVQ_RD64(dst_, addr_, off_) asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(dst_) : "v"(addr_), "n"(off_))
-    const int first = t * kRowsWaves;
-    RowsBundle cur = rows_bundle(tab, P, RowsBundle{}, first, group_end(first));
+    RowsBundle cur = rows_bundle(tab, P, RowsBundle{}, t);
+    if (cur.count == 0) return;
     RowsSource src = source(cur);
     int buf = 0;
     issue_a(src, 0, 0);
@@ -245,7 +242,6 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
     while (true) {
         const int steps = src.G >> 3;
         const bool active = src.active;
-        const bool last_of_group = cur.next >= cur.end;
         bool more = false;
         RowsBundle nxt = cur;
         int drawn = 0;
@@ -254,23 +250,17 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
         // The start of step c: its operands have arrived; everyone has left the other buffer.
         auto begin = [&](int c) {
             __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
-            if (c == 1 && last_of_group && w == 0 && lane == 0) ticket_word = drawn;
+            if (c == 1 && w == 0 && lane == 0) ticket_word = drawn;
             __syncthreads();
-            if (c == 0 && last_of_group && w == 0 && lane == 0)  // read at the next step's barrier
+            if (c == 0 && w == 0 && lane == 0)  // read at the next step's barrier
                 drawn = (int)__hip_atomic_fetch_add(&tickets[part], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (c + 1 < steps) {
                 issue_a(src, c + 1, buf ^ 1);
             } else {
-                // the bundle after this one: the rest of the group, or the next ticket's
-                int u = cur.next, e = cur.end;
-                if (last_of_group) {
-                    t = part_wgs + __builtin_amdgcn_readfirstlane(ticket_word);
-                    u = t * kRowsWaves;
-                    e = group_end(u);
-                }
-                more = u < P.units;
+                t = part_wgs + __builtin_amdgcn_readfirstlane(ticket_word);
+                nxt = rows_bundle(tab, P, cur, t);
+                more = nxt.count > 0;
                 if (more) {
-                    nxt = rows_bundle(tab, P, cur, u, e);
                     src = source(nxt);  // from here on the next bundle's
                     issue_a(src, 0, buf ^ 1);
                 }
