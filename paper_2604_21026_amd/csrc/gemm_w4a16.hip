@@ -455,7 +455,12 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
 //  - a wave's packed weights of a block (64 bytes per row, two buffers; an instruction
 //    covers 16 rows: loaded by the lane that needs them it touches 32 lines, which took a
 //    third of the time),
-//  - its scales of a block (two buffers; 4 bytes per row and pair),
+//  - its scales of a block (two buffers; 4 bytes per row and pair, or 2 per row and group with
+//    TAIL; a row's lie with neighbouring lanes, since what a load costs is the lines that its lanes
+//    touch: with each row's in 64 lines of two loads a 48-token prompt waited as long for 6 % of the
+//    bytes as for the weights.  48 x 2048 x 2048: 6.2 -> 5.4 us, 48 x 2048 x 8192 12.9 -> 11.4; with TAIL
+//    48 x 2048 x 8224 12.4 -> 11.9, but 100 x 8192 x 2880 in 128 x 64 17.7 -> 18.1: with four token
+//    tiles TAIL keeps a lane's own scales),
 // in the wide kernel's permuted order, and everything besides the MFMAs is dealt between
 // them.  TAIL: the number of groups is no multiple of four (a block then ends past the
 // row: the last group again, with scale 0) or the scales are not aligned to 4 bytes.
@@ -494,10 +499,11 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     constexpr int NA = 4 * TT / WN;       // activation loads of a wave and pair
     static_assert(NA * WN == 4 * TT && kWaves % 4 == 0, "whole instructions; waves on every SIMD");
     constexpr int kW = RT * 32 * 64;      // packed weights of a block
-    constexpr int kS = RT * 512;          // scales of a block
+    constexpr int kS = TAIL ? RT * 512 : RT * 256;  // scales of a block
     constexpr int kLds = WK * 3 * kBufA + kWaves * (2 * kW + 2 * kS);
     constexpr int kRegs = TT * RT * 16;   // result registers per lane
-    constexpr int kScOps = TAIL ? 2 * RT : 2, kWOps = 2 * RT;
+    constexpr bool kNear = !TAIL || TT < 4;  // neighbouring lanes load the scales of one row
+    constexpr int kScOps = TAIL ? 2 * RT : RT, kWOps = 2 * RT;
     constexpr int kEven = kWOps + kScOps + NA, kOdd = NA;  // loads of an even and an odd pair's list
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds];
 
@@ -541,17 +547,17 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     const unsigned char *const qbase = qw + (size_t)n0 * (size_t)(G * 16);
     const unsigned char *const sbase = sc + (size_t)n0 * (size_t)(G * 2);
     const int qc = (lane & 3) ^ ((lane >> 4) & 3);
-    uint32_t qo[2 * RT], so[RT];
+    uint32_t qo[2 * RT], so[kScOps];
 #pragma unroll
     for (int j = 0; j < 2 * RT; ++j) {
         const int r = 16 * j + (lane >> 2);
         qo[j] = (uint32_t)(n0 + r < N ? r : N - 1 - n0) * (uint32_t)(G * 16) + (TAIL ? 0u : 16u * (uint32_t)qc);
     }
 #pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-        // TAIL: per row tile, the lane's own scale; else lane = row, both scales of a pair
-        const int r = TAIL ? rt * 32 + li : (RT == 2 ? lane : li);
-        so[rt] = (uint32_t)(n0 + r < N ? r : N - 1 - n0) * (uint32_t)(G * 2);
+    for (int k = 0; k < kScOps; ++k) {
+        // lane l the scales of pair l % 2 of row l / 2; TAIL: of group l % 4 of row l / 4, or its own of pair k / RT
+        const int r = !TAIL ? 32 * k + (lane >> 1) : kNear ? 16 * k + (lane >> 2) : 32 * (k % RT) + li;
+        so[k] = (uint32_t)(n0 + r < N ? r : N - 1 - n0) * (uint32_t)(G * 2) + (TAIL ? 0u : 4u * (uint32_t)(lane & 1));
     }
     const int last = nblk > 0 ? nblk - 1 : 0;
     auto group_of = [&](int b) { return 4 * (wk + WK * (b < last ? b : last)); };  // first group of block b
@@ -576,11 +582,10 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     auto issue_s1 = [&](int b, int sel, int k) {
         const int g0 = group_of(b);
         if (TAIL) {
-            const int pp = k / RT, rt = k % RT;
-            const unsigned char *src = sbase + (so[rt] + 2u * (uint32_t)clamp_g(g0 + 2 * pp + lb));
+            const unsigned char *src = sbase + (so[k] + 2u * (uint32_t)clamp_g(g0 + (kNear ? lane & 3 : 2 * (k / RT) + lb)));
             __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_ptr)(bs + sel * kS + k * 256), 2, 0, 0);
         } else {
-            const unsigned char *src = sbase + (size_t)(g0 + 2 * k) * 2 + so[0];
+            const unsigned char *src = sbase + (size_t)g0 * 2 + so[k];
             __builtin_amdgcn_global_load_lds((const void *)src, (lds_void_ptr)(bs + sel * kS + k * 256), 4, 0, 0);
         }
     };
@@ -609,7 +614,7 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
 #pragma unroll
     for (int st = 0; st < 4; ++st) apos[st] = xa0 + li * 128 + 16 * ((4 * lb + st) ^ ((li >> 1) & 7));
     const uint32_t bwpos = (uint32_t)(uintptr_t)bw + li * 64 + 16 * (lb ^ ((li >> 2) & 3));
-    const uint32_t bspos = (uint32_t)(uintptr_t)bs + 4 * (TAIL ? lane : li);
+    const uint32_t bspos = (uint32_t)(uintptr_t)bs + (!TAIL ? 8 * li : kNear ? 16 * li + 4 * lb : 4 * lane);
     uint32_t mask_lo = 0x000f000fu, mask_hi = 0x00f000f0u, magic = 0x64006400u;
     asm("" : "+s"(mask_lo));
     asm("" : "+s"(mask_hi));
@@ -640,10 +645,10 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
         if (RT == 2) asm volatile("ds_read_b128 %0, %1 offset:2048" : "=v"(braw.w[RT - 1]) : "v"(waddr));
         asm volatile("ds_read_b32 %0, %1" : "=v"(braw.h[0]) : "v"(saddr));
         if (RT == 2) {
-            if (TAIL)
-                asm volatile("ds_read_b32 %0, %1 offset:256" : "=v"(braw.h[RT - 1]) : "v"(saddr));
+            if (TAIL && kNear)
+                asm volatile("ds_read_b32 %0, %1 offset:512" : "=v"(braw.h[RT - 1]) : "v"(saddr));
             else
-                asm volatile("ds_read_b32 %0, %1 offset:128" : "=v"(braw.h[RT - 1]) : "v"(saddr));
+                asm volatile("ds_read_b32 %0, %1 offset:256" : "=v"(braw.h[RT - 1]) : "v"(saddr));
         }
     };
     // (every register that is on its way is named by the wait: nothing of it moves before)
@@ -776,7 +781,7 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
         const int q_ = 2 * b + (odd_);                                                             \
         const int nsel_ = (odd_) ? wsel ^ 1 : wsel; /* weight buffer of the next pair */           \
         const uint32_t waddr_ = (bwpos + nsel_ * kW) ^ ((odd_) ? 0 : 32);                          \
-        const uint32_t saddr_ = bspos + nsel_ * kS + ((odd_) ? 0 : (TAIL ? RT * 256 : 256));       \
+        const uint32_t saddr_ = bspos + nsel_ * kS + ((odd_) ? 0 : !TAIL ? 4 : kNear ? 8 : RT * 256); \
         const int gnext_ = (odd_) ? group_of(b + 1) : group_of(b) + 2;                             \
         const int nxt_ = cur + kBufA == 3 * kBufA ? 0 : cur + kBufA;                                  \
         step(0, cur, nb, 1, 0, 0, 0, nnb, 0, q_ - 1, (odd_), 1, wsel, xa + prv);                   \
@@ -930,7 +935,8 @@ int64_t gemm_tiles(const GemmTile &k, int64_t N, int64_t M) {
 
 // The kind of tile with the smallest estimated time: whole rounds of all compute units, then the
 // rest, which has the caches and the power to itself.  Over those 456 products the choice costs 0.2 %
-// on average and 6 % at worst against the fastest kind (held out: the same); counting the rest at
+// on average and 6 % at worst against the fastest kind (held out: the same; with the scales of 480
+// products of up to 500 tokens since loaded in fewer lines 0.1 % and 3 %); counting the rest at
 // the price of a full round it cost 3.7 % and up to 54 % (3300 x 2880 x 8640: 334 us, now 217; 2600
 // x 2048 x 8192: 147, now 107).
 int gemm_choose(int64_t N, int64_t G, int64_t M, bool can_wide, bool tail) {
