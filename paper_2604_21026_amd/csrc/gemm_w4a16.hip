@@ -488,6 +488,8 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
 // 4-7: 1024 + 16 n), two per instruction, and a mixed-precision FMA takes the fp16 halves
 // as they are: (1024 + n) * s - 1032 * s, one rounding of a number that needs none (n - 8
 // has 4, s 11 significant bits).  17 instructions per 8 weights against 23 through bytes.
+constexpr int kBand = 4;
+
 template <bool F32, int TT, int RT, int WN, int WK, bool TAIL>
 __global__ __launch_bounds__(WN * WK * 64) __attribute__((amdgpu_waves_per_eu(WN * WK / 4, WN * WK / 4))) void
 gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char *__restrict__ sc,
@@ -507,13 +509,22 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     constexpr int kEven = kWOps + kScOps + NA, kOdd = NA;  // loads of an even and an odd pair's list
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds];
 
-    // Tiles are numbered along the tokens first; workgroup b runs on XCD b % 8 and takes
-    // one of that XCD's eighth of the numbers, so that the tiles of a row range are worked
-    // off on one XCD and its weights are fetched into one L2.
+    // Tiles are numbered along the tokens first, in bands of kBand token tiles; workgroup b runs on
+    // XCD b % 8 and takes one of that XCD's eighth of the numbers, so that its 32 workgroups share
+    // a few token tiles and a few row ranges in their L2.  Without the bands an XCD's workgroups all
+    // read other activations where there are 32 token tiles: 128 x 64 then waited for the memory behind
+    // L2 (4096 tokens, 2560 rows, K = 8192: 372 us, 203 with bands of 4; 128 x 128 212 -> 185, 128 x
+    // 256 224 -> 222).  Bands of 8: within 2 %; 2 and 16: up to 4 and 7 % slower.
     const int tiles = row_tiles * token_tiles, per_xcd = (tiles + 7) >> 3;
     const int tile = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (tile >= tiles) return;
-    const int row_tile = tile / token_tiles, token_tile = tile % token_tiles;
+    int band0 = 0, width = token_tiles, in_band = tile;
+    if (token_tiles > kBand) {
+        band0 = tile / (row_tiles * kBand) * kBand;
+        width = token_tiles - band0 < kBand ? token_tiles - band0 : kBand;
+        in_band = tile - row_tiles * band0;
+    }
+    const int row_tile = in_band / width, token_tile = band0 + in_band % width;
 
     const int t = threadIdx.x, lane = t & 63;
     const int w = __builtin_amdgcn_readfirstlane(t >> 6);
