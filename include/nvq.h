@@ -421,14 +421,16 @@ int nvq_dequant_bf16(const uint8_t *qweight, const uint16_t *scales, int64_t N, 
  * and are not in nvq_gemv_w4a16.
  * Two kernels: tiles of 256 tokens x 256 rows (K % 256 == 0, scales 16-byte
  * aligned), and smaller tiles down to 32 x 32 whose waves may split K; the one
- * with the smallest estimated time runs.
+ * with the smallest estimated time runs, or, where a product ends a little past
+ * whole rounds of all compute units, two launches: those rounds, and the rest
+ * of the rows or tokens in smaller tiles.
  * The order of the additions, hence the last bits of an fp32 result, is the
  * tile's: K in one piece (wide and 128x256, which agree to the bit), in two
  * (128x128, 128x64), in four (64x64, 64x32) or in eight (32x32).  As the choice looks at M, N, K
  * and the device's compute units, a token's result may differ in its last bits
  * between a prompt worked off at once and in pieces.  The environment variable
  * NVQ_GEMM_TILE = wide | 128x256 (or narrow) | 128x128 | 128x64 | 64x64 |
- * 64x32 | 32x32 (read by every call) takes that tile where the kernel can run; with it
+ * 64x32 | 32x32 (read by every call) takes that tile alone where the kernel can run; with it
  * a token's bits do not depend on M or on the other tokens.  On an MI355X the 8B
  * block's projections at 4096 tokens (q+k+v, o, gate+up, down as one launch
  * each) run at 1.1-1.2 PFLOP/s, 47 % of the bf16 matrix peak; the paper's own

@@ -85,7 +85,7 @@ template <bool F32>
 __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char *__restrict__ sc,
                        int N, int G, const unsigned char *__restrict__ x, int M,
-                       void *__restrict__ y) {
+                       void *__restrict__ y, int ldy) {
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kWideLds];
     unsigned char *const xa = lds;
     const int t = threadIdx.x, lane = t & 63;
@@ -420,7 +420,7 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
             const uint4 v = *reinterpret_cast<const uint4 *>(out + tok * 128 + pos * 16);
             const int m = m0 + tok, n = nb0 + c * 8;
             if (m < M && n < N)
-                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(y) + (size_t)m * N + n) = v;
+                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(y) + (size_t)m * ldy + n) = v;
         }
         return;
     }
@@ -434,9 +434,9 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
                 const int m = m0 + tt * 32 + 8 * (r >> 2) + 4 * lb + (r & 3);
                 if (m < M && n < N) {
                     if (F32)
-                        reinterpret_cast<float *>(y)[(size_t)m * N + n] = acc[tt][rt][r];
+                        reinterpret_cast<float *>(y)[(size_t)m * ldy + n] = acc[tt][rt][r];
                     else
-                        reinterpret_cast<uint16_t *>(y)[(size_t)m * N + n] =
+                        reinterpret_cast<uint16_t *>(y)[(size_t)m * ldy + n] =
                             float_to_bf16_bits(acc[tt][rt][r]);
                 }
             }
@@ -494,7 +494,7 @@ template <bool F32, int TT, int RT, int WN, int WK, bool TAIL>
 __global__ __launch_bounds__(WN * WK * 64) __attribute__((amdgpu_waves_per_eu(WN * WK / 4, WN * WK / 4))) void
 gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char *__restrict__ sc,
                          int N, int G, const unsigned char *__restrict__ x, int M, int row_tiles,
-                         int token_tiles, void *__restrict__ y) {
+                         int token_tiles, void *__restrict__ y, int ldy) {
     constexpr int kWaves = WN * WK;
     constexpr int NM = TT * RT;           // MFMAs of a step (16 inputs per lane half)
     constexpr int kTokens = 32 * TT, kBufA = kTokens * 128;  // bytes of an activation buffer
@@ -906,21 +906,22 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
             const uint4v q = *reinterpret_cast<const uint4v *>(out + idx * 16);
             const int m = mo + tok, n = no + c * 8;
             if (m < M && n < N)
-                *reinterpret_cast<uint4v *>(reinterpret_cast<uint16_t *>(y) + (size_t)m * N + n) = q;
+                *reinterpret_cast<uint4v *>(reinterpret_cast<uint16_t *>(y) + (size_t)m * ldy + n) = q;
         }
         return;
     }
 #pragma unroll
     for (int i = 0; i < kMine; ++i) {
         const int m = mo + token_of(i), n = no + ((i >> 4) % kOwnRt) * 32 + li;
-        if (m < M && n < N) store_out(y, F32 ? NVQ_F32 : NVQ_BF16, (int64_t)m * N + n, v[i]);
+        if (m < M && n < N) store_out(y, F32 ? NVQ_F32 : NVQ_BF16, (int64_t)m * ldy + n, v[i]);
     }
 }
 
-// The tiles a product can be cut into, and what a round of them takes (us): `fixed`, and per pair of
-// groups and slice `pair` plus `busy` times the share of the compute units that are at work (they
-// share the L2 caches and the power); `tail`: for kernels with TAIL.  Fitted to 456 products of 36
-// to 4096 tokens, 960 to 28672 rows and K from 960 to 14336 (4 to 13 % rms per kind).
+// The tiles a product can be cut into, and what a launch of them takes (us): kGemmLaunch, and for each
+// round of all compute units `fixed` and per pair of groups and slice `pair` plus `busy` times the
+// share of the compute units that are at work (they share the L2 caches and the power); `tail`: for
+// kernels with TAIL.  Fitted to 480 products of 36 to 4096 tokens, 512 to 28672 rows and K from 960 to
+// 14336 (2.5 to 4.6 % rms per kind).
 struct GemmCost {
     float fixed, pair, busy;
 };
@@ -930,41 +931,93 @@ struct GemmTile {
     const char *name;  // for NVQ_GEMM_TILE
 };
 constexpr GemmTile kGemmTiles[] = {
-    {256, 256, 1, {9.0f, 1.01f, 0.54f}, {}, "wide"},
-    {128, 256, 1, {6.4f, 0.65f, 0.33f}, {6.2f, 0.65f, 0.37f}, "128x256"},
-    {128, 128, 2, {6.9f, 0.69f, 0.28f}, {5.4f, 0.70f, 0.41f}, "128x128"},
-    {128, 64, 2, {4.7f, 0.46f, 0.16f}, {4.9f, 0.52f, 0.17f}, "128x64"},
-    {64, 64, 4, {4.5f, 0.57f, 0.10f}, {4.8f, 0.65f, 0.05f}, "64x64"},
-    {64, 32, 4, {3.1f, 0.49f, 0.01f}, {3.5f, 0.46f, 0.0f}, "64x32"},
-    {32, 32, 8, {2.8f, 0.72f, 0.0f}, {2.9f, 0.67f, 0.0f}, "32x32"},
+    {256, 256, 1, {9.96f, 0.959f, 0.575f}, {}, "wide"},
+    {128, 256, 1, {5.02f, 0.693f, 0.256f}, {4.10f, 0.642f, 0.408f}, "128x256"},
+    {128, 128, 2, {4.81f, 0.681f, 0.276f}, {3.14f, 0.679f, 0.414f}, "128x128"},
+    {128, 64, 2, {2.98f, 0.450f, 0.145f}, {3.00f, 0.503f, 0.164f}, "128x64"},
+    {64, 64, 4, {3.11f, 0.518f, 0.144f}, {3.07f, 0.566f, 0.147f}, "64x64"},
+    {64, 32, 4, {2.16f, 0.378f, 0.087f}, {2.17f, 0.375f, 0.083f}, "64x32"},
+    {32, 32, 8, {2.21f, 0.475f, 0.115f}, {2.19f, 0.442f, 0.146f}, "32x32"},
 };
+constexpr double kGemmLaunch = 2.5, kGemmSplitGain = 0.925;
 constexpr int kGemmTileKinds = (int)(sizeof(kGemmTiles) / sizeof(kGemmTiles[0]));
 
-int64_t gemm_tiles(const GemmTile &k, int64_t N, int64_t M) {
-    return ((N + k.rows - 1) / k.rows) * ((M + k.tokens - 1) / k.tokens);
+// n / d up, for d a power of two
+int64_t up_div(int64_t n, int d) { return (n + d - 1) >> __builtin_ctz((unsigned)d); }
+
+int64_t gemm_tiles(const GemmTile &k, int64_t N, int64_t M) { return up_div(N, k.rows) * up_div(M, k.tokens); }
+
+// A round with this share of the compute units at work.
+double gemm_round(const GemmTile &k, int64_t G, bool tail, double share) {
+    const GemmCost &c = tail ? k.tail : k.whole;
+    return c.fixed + (double)up_div((G + 1) / 2, k.slices) * (c.pair + c.busy * share);
 }
 
-// The kind of tile with the smallest estimated time: whole rounds of all compute units, then the
-// rest, which has the caches and the power to itself.  Over those 456 products the choice costs 0.2 %
-// on average and 6 % at worst against the fastest kind (held out: the same; with the scales of 480
-// products of up to 500 tokens since loaded in fewer lines 0.1 % and 3 %); counting the rest at
-// the price of a full round it cost 3.7 % and up to 54 % (3300 x 2880 x 8640: 334 us, now 217; 2600
-// x 2048 x 8192: 147, now 107).
-int gemm_choose(int64_t N, int64_t G, int64_t M, bool can_wide, bool tail) {
-    const int64_t cus = device_cu_count();
+// (a narrow division where it will do: a call makes up to a few dozen)
+int64_t whole_rounds(int64_t tiles, int64_t cus) {
+    return tiles <= 0xffffffffll ? (int64_t)((uint32_t)tiles / (uint32_t)cus) : tiles / cus;
+}
+
+// Estimated time of a launch: whole rounds of all compute units, then the rest, which has the caches and
+// the power to itself.
+double gemm_cost(const GemmTile &k, int64_t N, int64_t G, int64_t M, int64_t cus, bool tail) {
+    const int64_t n = gemm_tiles(k, N, M), full = whole_rounds(n, cus);
+    double us = kGemmLaunch + (double)full * gemm_round(k, G, tail, 1.0);
+    if (n > full * cus) us += gemm_round(k, G, tail, (double)(n - full * cus) / (double)cus);
+    return us;
+}
+
+// The kind of tile with the smallest estimated time.  Over those 480 products the choice costs 0.05 %
+// on average and 3.6 % at worst against the fastest kind; counting the rest at the price of a full
+// round it cost 3.7 % and up to 54 %.
+int gemm_choose(int64_t N, int64_t G, int64_t M, int64_t cus, bool can_wide, bool tail, double *us) {
     int best = -1;
-    double best_us = 0.0;
+    for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i) {
+        const double t = gemm_cost(kGemmTiles[i], N, G, M, cus, tail);
+        if (best < 0 || t < *us) {
+            best = i;
+            *us = t;
+        }
+    }
+    return best;
+}
+
+// A product as one launch of tiles, or as two: the whole rounds of one kind, and the rest of the rows or
+// of the tokens in the kind that is best for what is left.
+struct GemmPlan {
+    int kind;
+    int64_t rows, tokens;  // of the first launch
+    int rest;              // kind of the second; < 0: none
+};
+
+// Large tiles are the cheaper ones per product, but their last round takes a whole round's time however
+// few compute units it keeps busy: smaller tiles fill the chip with what is left.  Two launches where
+// they are estimated 8 % faster: of 138 such products (100 to 4096 tokens) 12 % faster on average, the
+// worst 5 % slower (333 x 6144 x 14336: 86.2 -> 90.9 us; 6000 x 3072 x 3072: 148 -> 112, 3072 x 6144 x
+// 4096: 188 -> 151, 1300 x 3072 x 4096: 57 -> 44, 4096 x 6144 x 4096: 199 -> 188).  From an
+// estimate of 2 % on: 6 % on average, but 28 of 271 lost 3 to 10 %.  Cuts elsewhere than at the end
+// of the whole rounds, all of them tried with the estimate, gain 0.2 % more.
+GemmPlan gemm_plan(int64_t N, int64_t G, int64_t M, int64_t cus, bool can_wide, bool tail) {
+    double one = 0.0;
+    GemmPlan best = {gemm_choose(N, G, M, cus, can_wide, tail, &one), N, M, -1};
+    double best_us = kGemmSplitGain * one;
     for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i) {
         const GemmTile &k = kGemmTiles[i];
-        const GemmCost &c = tail ? k.tail : k.whole;
-        const int64_t n = gemm_tiles(k, N, M), full = n / cus;
-        const double part = (double)(n % cus) / (double)cus;
-        const double steps = (double)(((G + 1) / 2 + k.slices - 1) / k.slices);
-        double us = (double)full * (c.fixed + steps * (c.pair + c.busy));
-        if (part > 0.0) us += c.fixed + steps * (c.pair + c.busy * part);
-        if (best < 0 || us < best_us) {
-            best = i;
-            best_us = us;
+        const int64_t full = whole_rounds(gemm_tiles(k, N, M), cus);
+        // (what is left takes at least another launch)
+        if (full == 0 || 2 * kGemmLaunch + (double)full * gemm_round(k, G, tail, 1.0) >= best_us) continue;
+        for (int by_rows = 0; by_rows < 2; ++by_rows) {
+            const int64_t across = by_rows ? up_div(M, k.tokens) : up_div(N, k.rows);
+            const int64_t first = full * cus / across * (by_rows ? k.rows : k.tokens);
+            if (first == 0 || first >= (by_rows ? N : M)) continue;
+            const int64_t n1 = by_rows ? first : N, m1 = by_rows ? M : first;
+            double us = 0.0;
+            const int rest = gemm_choose(by_rows ? N - n1 : N, G, by_rows ? M : M - m1, cus, can_wide, tail, &us);
+            us += gemm_cost(k, n1, G, m1, cus, tail);
+            if (us < best_us) {
+                best_us = us;
+                best = {i, n1, m1, rest};
+            }
         }
     }
     return best;
@@ -975,26 +1028,25 @@ bool gemm_tail(int64_t G, const unsigned char *scales) { return (G & 3) != 0 || 
 
 template <bool F32, int TT, int RT, int WN, int WK, bool TAIL>
 void launch_tile(dim3 grid, hipStream_t st, const unsigned char *q, const unsigned char *s, int N, int G,
-                 const unsigned char *x, int M, int row_tiles, int token_tiles, void *y) {
+                 const unsigned char *x, int M, int row_tiles, int token_tiles, void *y, int ldy) {
     hipLaunchKernelGGL((gemm_w4a16_tile_kernel<F32, TT, RT, WN, WK, TAIL>), grid, dim3(WN * WK * 64), 0, st, q, s, N,
-                       G, x, M, row_tiles, token_tiles, y);
+                       G, x, M, row_tiles, token_tiles, y, ldy);
 }
 
 template <bool F32>
-int launch_gemm(int kind, const unsigned char *q, const unsigned char *s, int N, int G,
-                const unsigned char *x, int M, void *y, hipStream_t st) {
+void launch_gemm(int kind, const unsigned char *q, const unsigned char *s, int N, int G,
+                 const unsigned char *x, int M, void *y, int ldy, hipStream_t st) {
     const GemmTile &k = kGemmTiles[kind];
     const int64_t tiles = gemm_tiles(k, N, M);
-    if (tiles > (int64_t)0x7ffffff8) return NVQ_ERR_SHAPE;
     if (kind == 0) {
         hipLaunchKernelGGL(gemm_w4a16_wide_kernel<F32>, dim3((unsigned)tiles), dim3(kGemmThreads), 0, st, q, s,
-                           N, G, x, M, y);
+                           N, G, x, M, y, ldy);
     } else {
         const int rt = (int)((N + (int64_t)k.rows - 1) / k.rows), tt = (M + k.tokens - 1) / k.tokens;
         const dim3 grid((unsigned)((tiles + 7) / 8 * 8));
         const bool tail = gemm_tail(G, s);
         switch (kind) {
-#define NVQ_TILE(TAIL_, TT_, RT_, WN_, WK_) launch_tile<F32, TT_, RT_, WN_, WK_, TAIL_>(grid, st, q, s, N, G, x, M, rt, tt, y)
+#define NVQ_TILE(TAIL_, TT_, RT_, WN_, WK_) launch_tile<F32, TT_, RT_, WN_, WK_, TAIL_>(grid, st, q, s, N, G, x, M, rt, tt, y, ldy)
 #define NVQ_TILES(TT_, RT_, WN_, WK_) \
     if (tail) NVQ_TILE(true, TT_, RT_, WN_, WK_); else NVQ_TILE(false, TT_, RT_, WN_, WK_)
             case 1:
@@ -1010,6 +1062,20 @@ int launch_gemm(int kind, const unsigned char *q, const unsigned char *s, int N,
 #undef NVQ_TILES
 #undef NVQ_TILE
         }
+    }
+}
+
+template <bool F32>
+int launch_plan(const GemmPlan &p, const unsigned char *q, const unsigned char *s, int N, int G,
+                const unsigned char *x, int M, void *y, hipStream_t st) {
+    const int n1 = (int)p.rows, m1 = (int)p.tokens;
+    launch_gemm<F32>(p.kind, q, s, n1, G, x, m1, y, N, st);
+    if (p.rest >= 0) {
+        const bool by_rows = n1 < N;
+        const size_t n0 = by_rows ? n1 : 0, m0 = by_rows ? 0 : m1;
+        launch_gemm<F32>(p.rest, q + n0 * (size_t)(G * 16), s + n0 * (size_t)(G * 2), N - (int)n0, G,
+                         x + m0 * (size_t)(G * 64), M - (int)m0,
+                         static_cast<unsigned char *>(y) + (m0 * (size_t)N + n0) * (F32 ? 4 : 2), N, st);
     }
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
@@ -1036,14 +1102,24 @@ extern "C" int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, in
     // the choice where the kernel can run (the tests reach all of them on small shapes).
     const bool can_wide = (K % 256) == 0 && aligned(scales, 16);
     const unsigned char *const sb = reinterpret_cast<const unsigned char *>(scales);
-    int kind = gemm_choose(N, K / 32, M, can_wide, gemm_tail(K / 32, sb));
+    const bool tail = gemm_tail(K / 32, sb);
+    const int64_t cus = device_cu_count();
+    GemmPlan plan = gemm_plan(N, K / 32, M, cus, can_wide, tail);
     if (const char *force = getenv("NVQ_GEMM_TILE")) {
         if (strcmp(force, "narrow") == 0) force = "128x256";
         for (int i = can_wide ? 0 : 1; i < kGemmTileKinds; ++i)
-            if (strcmp(force, kGemmTiles[i].name) == 0) kind = i;
+            if (strcmp(force, kGemmTiles[i].name) == 0) plan = {i, N, M, -1};
     }
+    // a grid holds so many workgroups
+    auto fits = [](int kind, int64_t n, int64_t m) { return gemm_tiles(kGemmTiles[kind], n, m) <= (int64_t)0x7ffffff8; };
+    if (plan.rest >= 0 && !(fits(plan.kind, plan.rows, plan.tokens) &&
+                            fits(plan.rest, plan.rows < N ? N - plan.rows : N, plan.rows < N ? M : M - plan.tokens))) {
+        double us;
+        plan = {gemm_choose(N, K / 32, M, cus, can_wide, tail, &us), N, M, -1};
+    }
+    if (!fits(plan.kind, plan.rows, plan.tokens)) return NVQ_ERR_SHAPE;
     const unsigned char *const xb = reinterpret_cast<const unsigned char *>(x_bf16);
     if (y_dtype == NVQ_F32)
-        return launch_gemm<true>(kind, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
-    return launch_gemm<false>(kind, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
+        return launch_plan<true>(plan, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
+    return launch_plan<false>(plan, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
 }

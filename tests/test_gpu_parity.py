@@ -1976,6 +1976,34 @@ def test_gemm_w4a16_bands_of_token_tiles(tile, tiles, monkeypatch):
     test_gemm_w4a16_small_tiles_match_oracle(tile, (tiles - 1) * tokens + 1, 2 * rows + 8, 160, 0, monkeypatch)
 
 
+# Products that end a little past a whole round of all compute units go in two launches, split by
+# rows (the first three at 256 units) or by tokens: rows no multiple of 8, K that ends inside a block,
+# scales off their alignment, the two parts of different kinds.  Nothing outside of the result is
+# written.  Tolerance as above.
+@pytest.mark.parametrize("M,N,K,off", [(2049, 4104, 800, 0), (2049, 4133, 800, 1), (2049, 2056, 2048, 0),
+                                       (1300, 3079, 2080, 0), (1281, 3079, 2048, 0), (2049, 2117, 2048, 1)])
+def test_gemm_w4a16_in_two_launches(M, N, K, off):
+    say("gemm in two launches", M, N, K, off)
+    _, q, s = packed(9300 + N, N, K)
+    xh = act(9400 + K, M, K)
+    want = oracle.gemm_w4a16_dense(q, s, u16(xh))
+    qd, sd = to_dev_packed(q, s)
+    buf = torch.zeros(sd.numel() + off, dtype=sd.dtype, device=DEV)
+    buf[off:] = sd.flatten()
+    sd = buf[off:].view(sd.shape)
+    y = {}
+    for dt in (torch.float32, torch.bfloat16):
+        out = torch.full((M + 2, N), float("nan"), dtype=dt, device=DEV)
+        nvq.gemm_w4a16(qd, sd, xh.to(DEV), out=out[1:-1])
+        torch.cuda.synchronize()
+        assert out[0].isnan().all() and out[-1].isnan().all()
+        y[dt] = out[1:-1]
+    err = np_ref.rel_l2(y[torch.float32].cpu().numpy(), want)
+    say("  rel l2", err)
+    assert err < 1e-5
+    assert torch.equal(y[torch.bfloat16], y[torch.float32].to(torch.bfloat16))
+
+
 # An infinite activation in the last group of K: infinite results, NaN only where the weight is
 # zero (K that ends inside a block, an odd number of blocks, a single one).
 @pytest.mark.parametrize("tile", ["128x256", "128x128", "128x64", "64x64", "64x32"])
