@@ -18,12 +18,12 @@
 // workgroups of a part take its groups of four units, the phases with the largest K first, first come
 // first served from a counter, which the quantisation launch in front has cleared.
 //
-// What bounds it: 8B layers at 32 tokens take 1,040 us (4.3 TB/s), 25 of them the quantisation.
+// What bounds it: 8B layers at 32 tokens take 1,021 us (4.1 TB/s), 20 of them the quantisation.
 // Without the loads 700, without the products 960: memory, whose queue runs dry while a workgroup waits for
 // a step, crosses the barrier and copies its weights.  What brought it there from 1,133: the phases in the order of
 // their K (see order_phases; 60 us), two steps' scales per load (16 bytes of a row per load were a
 // request each, 20), the matrix core and the vector instructions interleaved unit by unit with
-// addresses that need no arithmetic per group (from 92 vector instructions per KiB of weights to 75), a
+// addresses that need no arithmetic per group (from 92 vector instructions per KiB of weights to 89), a
 // higher priority for the waves that ask for operands (10).  Not faster: two steps of weights in flight with
 // four barriers per step (the activations in quarters, for the room: 1,140), eight waves per workgroup, weights
 // loaded into registers (they spill), plain loads of the weights (2.5 %).
