@@ -562,8 +562,8 @@ struct GroupPlan {
     std::vector<GroupBatch> batches;
 };
 
-// How a batch is worked off.  Up to 16 tokens: the per-tile grid (gemv_mfma.hip) or the persistent one
-// fed through LDS rings, which has the better rate, but sixteen microseconds before it and one for every
+// How a batch is worked off.  Up to 16 tokens: the per-tile grid (gemv_mfma.hip), the persistent one
+// whose waves share the activations (gemv_rows.hip) or the one fed through LDS rings, which has the better rate, but sixteen microseconds before it and one for every
 // 256 inputs of the widest phase; both add in the same order.  Linear estimates as below, fitted to
 // 1008 and 720 lists of 4 to 64 phases and 3 to 490 MB (10 and 9 % rms), with a margin for their errors.  Per-tile
 // grid / rings, 8 tokens, cold weights: two blocks of 1024 x 3072 16 / 32, four of 1536 x 4608 36 / 39, ten
@@ -573,7 +573,13 @@ struct GroupPlan {
 // to the rings although these are slower (6 of 64 x 512 6.6 / 13.8, 8 of 256 x 1024 8.7 / 15.8, one layer of
 // 2048 x 2048 8.7 / 20, three 12 / 32, 4096 x 14336 31 / 129, one block of 1B 28 / 56, two 43 / 57, one of
 // 8B 68 / 93; two of 8B 101 / 96).  They are the lists that the rings' tests are built on, whose kernel
-// and waits those name, and the first two lie outside of what was fitted.  From
+// and waits those name, and the first two lie outside of what was fitted.  The grid of shared activations is
+// for lists beyond those and 20 MB, and up to 500 MB: whole models keep to the rings, whose tests name them
+// too, although it is the faster one there (the step of 8B at 2, 8 and 16 tokens 798, 897, 985 through the
+// rings, 719, 790, 886).  It is estimated as below (10 % rms over 109 lists).  Per-tile grid / rings / rows:
+// 8 tokens, five blocks of 3072 x 8192 103 / 84 / 88, eight 151 / 112 / 106; four of 8B 174 / 132 / 117; twelve of 1B
+// 144 / 113 / 98, of 1024 x 3072 39 / 51 / 42, sixteen 48 / 61 / 44; 2 tokens, four of 8B 152 / 128 / 113; 16
+// tokens 202 / 138 / 119.  From
 // 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
 // activations (gemv_rows.hip), and launches phase by phase (gemv_slice.h), by what they were measured to
 // take (us; MB of weights, phases, the largest K): 123 lists of 4 to 64 phases and 2 to 980 MB, where
@@ -596,17 +602,23 @@ GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
         widest = std::max(widest, steps);
         single += 3.0 + 0.165 * steps + w / 3.1;
     }
-    if (M < kRowsMinTokens) {
+    // the grid of gemv_rows.hip: as long as the widest phase or as the bytes take, and what both together cost
+    auto rows_us = [&](double longest, double bytes) {
+        return 1.1 * std::pow(std::pow(longest, 4) + std::pow(bytes, 4), 0.25);
+    };
+    if (M <= 16) {
         const double tiles = 5.1 + 0.118 * b.nphases + 0.218 * widest + mb * (0.215 + 0.0082 * M + 0.0004 * widest);
         const double rings = 16.3 + 0.131 * b.nphases + 0.972 * widest + 0.175 * std::max(0.0, mb - 27.0);
         const bool narrow = widest < 24.0, many = b.nphases > 8 && mb > 50.0;
         const bool per_tile = b.nphases >= 4 && mb >= 1.5 && (narrow || many) && tiles * (narrow ? 1.15 : 1.3) < rings;
+        const double rows = rows_us(5.9 + 1.79 * widest, 10.5 + 0.113 * b.nphases + mb / (5.77 - 0.065 * M));
+        const bool between = mb <= 500.0 && (many || (narrow && b.nphases >= 4 && mb >= 20.0));
+        if (between && rows < (per_tile ? tiles : rings)) return kGroupRows;
         return per_tile ? kGroupTiles : kGroupRing;
     }
     const double ring = 12.6 + 0.57 * widest + 0.27 * b.nphases + mb / 2.9;
-    const double longest = 9.0 + 2.15 * widest, bytes = 10.0 + 0.2 * b.nphases + mb / 4.45;
     const bool enough = mb >= 5.0 && (mb >= 400.0 || widest < 48.0);
-    const double rows = enough ? 1.1 * std::pow(std::pow(longest, 4) + std::pow(bytes, 4), 0.25) : 1e30;
+    const double rows = enough ? rows_us(9.0 + 2.15 * widest, 10.0 + 0.2 * b.nphases + mb / 4.45) : 1e30;
     return single < std::min(ring, rows) ? kGroupSingle : ring <= rows ? kGroupRing : kGroupRows;
 }
 
@@ -700,7 +712,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
             cur.nimg = 0;
         }
         if (cur.kind == kGroupRows) {
-            cur.grid = rows_grid(cur.nunits, cur.nparts);
+            cur.grid = rows_grid(cur.nunits, cur.nparts, M);
             order_phases(gp, cur);
         }
         gp.batches.push_back(cur);

@@ -1,9 +1,9 @@
-// Small batches of 17 to 32 tokens through many independent phases as one persistent
+// Small batches of 2 to 32 tokens through many independent phases as one persistent
 // grid (plans whose K are all multiples of 512).  Paper: the W4A8 / W4A16 kernel
 // descriptions; the arithmetic is that of mfma_act.h.
 //
 // With two token tiles 32 weight rows need 3.6 times their own bytes of bf16 activations, and a
-// kernel whose waves each fetch their own (the ring kernel, which serves up to 16 tokens and shorter
+// kernel whose waves each fetch their own (the ring kernel, which serves shorter
 // lists) stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with
 // 32 rows of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
 // through LDS, and no sums cross the waves.  K advances by 256 inputs (a whole 128-byte
@@ -11,7 +11,9 @@
 // buffers) and, once the current step's weights and scales are in registers, for its next
 // weights, all straight from global memory into LDS; one barrier per step says that the
 // activations have arrived and that the other buffer is free.  Three workgroups share a
-// compute unit.
+// compute unit, four where one token tile does (36 KiB of LDS): up to 16 tokens the rings wait for
+// their sums across waves and for the operand images made beforehand: four blocks of 8B at 2, 8 and 16 tokens
+// 128, 132 and 138 us there, 113, 117 and 119 here.
 //
 // The batch is cut into parts, one per XCD (the compute units of an XCD advance through
 // the phases together, so that the activations they all read stay in their L2); the
@@ -42,9 +44,7 @@ typedef const __attribute__((address_space(4))) GroupPhase CGroup;
 typedef const __attribute__((address_space(4))) uint32_t CWord;
 
 constexpr int kRowsWaves = 4;      // waves per workgroup = units per group
-constexpr int kRowsWgPerCu = 3;
-constexpr int kRowsBlock = 4096;   // a block of activations: 128 bytes of 32 tokens
-constexpr int kRowsA = 4 * kRowsBlock;  // a buffer: a step's 256 inputs as bf16 (codes fill half of it)
+constexpr int rows_per_cu(int mt) { return mt == 2 ? 3 : 4; }  // workgroups, for mt token tiles
 constexpr int kRowsW = 2 * 2048;   // a wave's weights of a step: 32 rows x 128 bytes
 constexpr int kRowsSc = 1024;      // and the scales of two, 32 bytes per row
 
@@ -93,10 +93,14 @@ struct RowsSource {
     bool whole;         // its 32 rows follow each other in memory (one matrix, none missing)
 };
 
-__global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu(3))) void
+// MT: tiles of 16 tokens
+template <int MT>
+__global__ __launch_bounds__(kRowsWaves * 64) __attribute__((amdgpu_waves_per_eu(rows_per_cu(MT)))) void
 gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict__ part_tab_, int nparts,
                  const uint32_t *__restrict__ order_, int M, uint32_t *__restrict__ tickets) {
-    constexpr int MT = 2, R = 2;  // token tiles, row tiles of a wave
+    constexpr int R = 2;  // row tiles of a wave
+    constexpr int kRowsBlock = 2048 * MT;   // a block of activations: 128 bytes of every token
+    constexpr int kRowsA = 4 * kRowsBlock;  // a buffer: a step's 256 inputs as bf16 (codes fill half of it)
     constexpr int kWaveLds = kRowsW + kRowsSc;
     __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * kRowsA + kRowsWaves * kWaveLds];
     __shared__ int ticket_word;
@@ -156,8 +160,8 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
         unsigned char *const dst = lds + buf * kRowsA + block * kRowsBlock;
         const uint32_t piece = 16u * (uint32_t)((lane & 3) ^ ((lane >> 4) & 3));
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (codes && (j >> 1) != (w & 1)) continue;
+        for (int j = 0; j < 2 * MT; ++j) {
+            if (codes && (MT == 2 ? j >> 1 : j) != (w & 1)) continue;
             const int m = 16 * (j >> 1) + (lane >> 2);
             __builtin_amdgcn_global_load_lds(
                 (const void *)(src + ((uint32_t)(m < M ? m : M - 1) * row + piece + 64u * (uint32_t)(j & 1))),
@@ -207,9 +211,9 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
     const uint32_t at = (uint32_t)(uintptr_t)slot, abase = (uint32_t)(uintptr_t)lds;
 
     // A result's sum in three levels: the eight groups of a step, eight steps, all of K.  (One
-    // chain over all of K had up to twice the error of the four that the kernel for up to 16 tokens
-    // adds, registers for four would be 64; this is closer than those, at any K, for 2 % more
-    // vector instructions.)
+    // chain over all of K had up to twice the error of the four that the ring kernel adds, registers
+    // for four would be 64; for 2 % more vector instructions this is as close as those at K = 2048 (rms of
+    // W4A8 results against 64 bits 6.4e-8, there 6.3e-8) and closer beyond: K = 14336 8.5e-8, there 1.5e-7.)
     float f[R][MT][4], total[R][MT][4], sums[R][MT][4];
     auto clear = [&](float (&v)[R][MT][4]) {
 #pragma unroll
@@ -463,16 +467,21 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
 }  // namespace
 
 // A workgroup per group of units (every part may end with a smaller one), at most what is resident.
-int rows_grid(int nunits, int nparts) {
-    const int groups = (nunits + kRowsWaves - 1) / kRowsWaves + nparts, cap = kRowsWgPerCu * device_cu_count();
+int rows_grid(int nunits, int nparts, int M) {
+    const int groups = (nunits + kRowsWaves - 1) / kRowsWaves + nparts;
+    const int cap = rows_per_cu(M > 16 ? 2 : 1) * device_cu_count();
     return groups < cap ? groups : cap;
 }
 
 int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, const uint32_t *order, int grid,
                      int M, uint32_t *tickets, hipStream_t st) {
     if (nparts <= 0 || grid <= 0) return NVQ_OK;
-    hipLaunchKernelGGL(gemv_rows_kernel, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, order,
-                       M, tickets);
+    if (M > 16)
+        hipLaunchKernelGGL(gemv_rows_kernel<2>, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, order,
+                           M, tickets);
+    else
+        hipLaunchKernelGGL(gemv_rows_kernel<1>, dim3(grid), dim3(kRowsWaves * 64), 0, st, tab, part_tab, nparts, order,
+                           M, tickets);
     NVQ_HIP_TRY(hipGetLastError());
     return NVQ_OK;
 }

@@ -1120,6 +1120,29 @@ def test_grid_sums_are_added_in_the_stated_order(M, kernel):
     dl.close()
 
 
+# The same up to 16 tokens, one token tile: one and several tokens, every token there is room for; phases of
+# several matrices whose boundaries fall inside a unit, fewer rows than a unit (tolerance as with the rings), and
+# the order of the sums.
+@pytest.mark.parametrize("M,bits,mbytes", [(2, (0, 1), 300), (7, (1, 0), 300), (16, (0, 1, 1), 120)])
+def test_rows_plan_up_to_16_tokens(M, bits, mbytes):
+    say("rows plan up to 16 tokens", M, bits)
+    entries, host = model_entries([s for s in RING_SHAPES if s[1] != 14336], bits, M=M, seed=8600)
+    ys_ref = oracle.decode_linears(host, M, 0)
+    bulk = bulk_layer(M, mbytes)
+    dl = nvq.DecodeList(entries[:5] + [bulk[0]] + entries[5:], M, 0)
+    assert dl.plan_info()["persistent_grouped"] and kernels_of(dl) == ["rows"]
+    for rep in range(3):
+        for e in entries:
+            e["y"].zero_()
+        dl.run_plan()
+        torch.cuda.synchronize()
+        for e, y_r in zip(entries, ys_ref):
+            assert np_ref.rel_l2(e["y"].cpu().numpy(), y_r) < 1e-5, rep
+        check_bulk(bulk, M)
+    dl.close()
+    test_grid_sums_are_added_in_the_stated_order(M, "rows")
+
+
 @pytest.mark.parametrize("M", [17, 32])
 def test_rows_plan_short_batches_run_phase_by_phase(M):
     """Forced order: every phase is a batch of its own, too small for the persistent grid."""
