@@ -448,6 +448,17 @@ int nvq_dequant_bf16(const uint8_t *qweight, const uint16_t *scales, int64_t N, 
  */
 int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, int64_t N, int64_t K,
                    const uint16_t *x_bf16, int64_t M, void *y, int y_dtype, void *stream);
+/*
+ * nvq_gemm_describe -- the launches that such a product takes, without touching
+ * a device (for inspection and tests; of scales and y only the alignment is
+ * looked at).  out (host, out_words int32): [0] launches, then 7 words per
+ * launch: tokens and rows of its tiles, its first row and rows, its first token
+ * and tokens, and the bytes a lane stores at a time (16: eight bf16 results).
+ * The current device's compute units count (256 without a device).  Errors as
+ * there, NVQ_ERR_WORKSPACE if out is too small.
+ */
+int nvq_gemm_describe(const uint16_t *scales, int64_t N, int64_t K, int64_t M, const void *y, int y_dtype,
+                      int32_t *out, int out_words);
 
 /*
  * Calibration statistics of the paper's Algorithm 1 (Monte Carlo activation

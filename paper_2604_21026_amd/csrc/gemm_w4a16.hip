@@ -81,6 +81,12 @@ constexpr int kWideLds = 3 * kWideBuf + 4 * 2 * (kWideBw + kWideBs);
 // s_waitcnt immediate that waits for vmcnt <= n only
 constexpr int wide_vmcnt(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0f70; }
 
+// Whether bf16 results leave as 16 bytes per lane: N rows of a launch, ldy from token to token.  (A launch of
+// part of the rows can have whole eights of them where the result's rows are no multiple of 16 bytes apart.)
+__host__ __device__ inline bool gemm_whole_stores(int N, int ldy, const void *y) {
+    return ((N | ldy) & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0;
+}
+
 template <bool F32>
 __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char *__restrict__ sc,
@@ -389,7 +395,7 @@ gemm_w4a16_wide_kernel(const unsigned char *__restrict__ qw, const unsigned char
 
     // Result tile: lane (j, b) holds weight row j; register r holds token
     // 8 * (r / 4) + 4 * b + r % 4 of a 32 x 32 tile.
-    if (!F32 && (N & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0) {
+    if (!F32 && gemm_whole_stores(N, ldy, y)) {
         // bf16 results pass through LDS (free now), so that they leave as whole
         // 128-byte lines, 16 bytes per lane, instead of 2 bytes per lane: a wave's
         // 256 tokens x 64 rows in 32 KiB, a row of 128 bytes per token with its
@@ -885,7 +891,7 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     const int mo = m0 + (k0 / (16 * RT)) * 32 + 2 * (k0 & 15);
     const int no = row_tile * (32 * RT * WN) + wn * (32 * RT) + (kOwnRt == RT ? 0 : ((k0 >> 4) % RT) * 32);
     auto token_of = [&](int i) { return (i / (16 * kOwnRt)) * 32 + 8 * ((i & 15) >> 2) + 4 * lb + (i & 3); };
-    if (!F32 && (N & 7) == 0 && (reinterpret_cast<uintptr_t>(y) & 15) == 0) {
+    if (!F32 && gemm_whole_stores(N, ldy, y)) {
         // bf16 results leave as 16 bytes per lane, whole lines where a wave owns 64 rows: through
         // LDS, pieces permuted as in the wide kernel; the wave reads back what it wrote itself
         constexpr int kPieces = kOwnRt * 4;
@@ -1081,28 +1087,17 @@ int launch_plan(const GemmPlan &p, const unsigned char *q, const unsigned char *
     return NVQ_OK;
 }
 
-}  // namespace
+bool gemm_sizes(int64_t N, int64_t K, int64_t M) {
+    return N > 0 && M > 0 && K > 0 && (K % 32) == 0 && K <= NVQ_MAX_K && N <= (1 << 24) && M <= (1 << 24);
+}
 
-}  // namespace nvq
-
-extern "C" int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, int64_t N, int64_t K,
-                              const uint16_t *x_bf16, int64_t M, void *y, int y_dtype,
-                              void *stream) {
-    using namespace nvq;
-    if (!qweight || !scales || !x_bf16 || !y) return NVQ_ERR_INVALID_ARG;
-    if (y_dtype != NVQ_F32 && y_dtype != NVQ_BF16) return NVQ_ERR_INVALID_ARG;
-    if (N <= 0 || M <= 0 || K <= 0 || (K % 32) != 0 || K > NVQ_MAX_K || N > (1 << 24) ||
-        M > (1 << 24))
-        return NVQ_ERR_SHAPE;
-    if (!aligned(qweight, 16) || !aligned(scales, 2) || !aligned(x_bf16, 16) ||
-        !aligned(y, y_dtype == NVQ_F32 ? 4 : 2))
-        return NVQ_ERR_ALIGN;
+// The launches of a product of such sizes.
+int gemm_launches(int64_t N, int64_t K, int64_t M, const uint16_t *scales, GemmPlan *out) {
     // The wide tiles take whole blocks of K and move 16 bytes of scales at a time.  The
     // environment variable NVQ_GEMM_TILE (the name of a tile; "narrow" for 128x256) overrides
     // the choice where the kernel can run (the tests reach all of them on small shapes).
     const bool can_wide = (K % 256) == 0 && aligned(scales, 16);
-    const unsigned char *const sb = reinterpret_cast<const unsigned char *>(scales);
-    const bool tail = gemm_tail(K / 32, sb);
+    const bool tail = gemm_tail(K / 32, reinterpret_cast<const unsigned char *>(scales));
     const int64_t cus = device_cu_count();
     GemmPlan plan = gemm_plan(N, K / 32, M, cus, can_wide, tail);
     if (const char *force = getenv("NVQ_GEMM_TILE")) {
@@ -1118,8 +1113,56 @@ extern "C" int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, in
         plan = {gemm_choose(N, K / 32, M, cus, can_wide, tail, &us), N, M, -1};
     }
     if (!fits(plan.kind, plan.rows, plan.tokens)) return NVQ_ERR_SHAPE;
+    *out = plan;
+    return NVQ_OK;
+}
+
+}  // namespace
+
+}  // namespace nvq
+
+extern "C" int nvq_gemm_w4a16(const uint8_t *qweight, const uint16_t *scales, int64_t N, int64_t K,
+                              const uint16_t *x_bf16, int64_t M, void *y, int y_dtype,
+                              void *stream) {
+    using namespace nvq;
+    if (!qweight || !scales || !x_bf16 || !y) return NVQ_ERR_INVALID_ARG;
+    if (y_dtype != NVQ_F32 && y_dtype != NVQ_BF16) return NVQ_ERR_INVALID_ARG;
+    if (!gemm_sizes(N, K, M)) return NVQ_ERR_SHAPE;
+    if (!aligned(qweight, 16) || !aligned(scales, 2) || !aligned(x_bf16, 16) ||
+        !aligned(y, y_dtype == NVQ_F32 ? 4 : 2))
+        return NVQ_ERR_ALIGN;
+    GemmPlan plan;
+    const int rc = gemm_launches(N, K, M, scales, &plan);
+    if (rc != NVQ_OK) return rc;
+    const unsigned char *const sb = reinterpret_cast<const unsigned char *>(scales);
     const unsigned char *const xb = reinterpret_cast<const unsigned char *>(x_bf16);
     if (y_dtype == NVQ_F32)
         return launch_plan<true>(plan, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
     return launch_plan<false>(plan, qweight, sb, (int)N, (int)(K / 32), xb, (int)M, y, (hipStream_t)stream);
+}
+
+extern "C" int nvq_gemm_describe(const uint16_t *scales, int64_t N, int64_t K, int64_t M, const void *y, int y_dtype,
+                                 int32_t *out, int out_words) {
+    using namespace nvq;
+    if (!out || (y_dtype != NVQ_F32 && y_dtype != NVQ_BF16)) return NVQ_ERR_INVALID_ARG;
+    if (!gemm_sizes(N, K, M)) return NVQ_ERR_SHAPE;
+    if (!aligned(scales, 2) || !aligned(y, y_dtype == NVQ_F32 ? 4 : 2)) return NVQ_ERR_ALIGN;
+    GemmPlan plan;
+    const int rc = gemm_launches(N, K, M, scales, &plan);
+    if (rc != NVQ_OK) return rc;
+    const int launches = plan.rest < 0 ? 1 : 2;
+    if (out_words < 1 + 7 * launches) return NVQ_ERR_WORKSPACE;
+    *out++ = launches;
+    const bool by_rows = plan.rows < N;
+    for (int i = 0; i < launches; ++i) {
+        const GemmTile &k = kGemmTiles[i == 0 ? plan.kind : plan.rest];
+        const int64_t n0 = i > 0 && by_rows ? plan.rows : 0, m0 = i > 0 && !by_rows ? plan.tokens : 0;
+        const int64_t n = i == 0 ? plan.rows : N - n0, m = i == 0 ? plan.tokens : M - m0;
+        const int size = y_dtype == NVQ_F32 ? 4 : 2;
+        const char *const at = static_cast<const char *>(y) + (m0 * N + n0) * size;
+        const int64_t words[7] = {k.tokens, k.rows, n0, n, m0, m,
+                                  y_dtype == NVQ_BF16 && gemm_whole_stores((int)n, (int)N, at) ? 16 : size};
+        for (int64_t w : words) *out++ = (int32_t)w;
+    }
+    return NVQ_OK;
 }

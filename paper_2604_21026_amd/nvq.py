@@ -30,7 +30,7 @@ EXPORTS = (
     "nvq_plan_create", "nvq_plan_run", "nvq_plan_info", "nvq_plan_status", "nvq_plan_trace",
     "nvq_plan_destroy", "nvq_plan_describe", "nvq_plan_describe_batches",
     "nvq_plan_describe_skips", "nvq_plan_describe_steps",
-    "nvq_dequant_bf16", "nvq_gemm_w4a16", "nvq_rms_norm_bf16", "nvq_silu_mul_bf16", "nvq_precision_from_scores", "nvq_token_norms", "nvq_mcap_scores", "nvq_stream_read", "nvq_stream_copy",
+    "nvq_dequant_bf16", "nvq_gemm_w4a16", "nvq_gemm_describe", "nvq_rms_norm_bf16", "nvq_silu_mul_bf16", "nvq_precision_from_scores", "nvq_token_norms", "nvq_mcap_scores", "nvq_stream_read", "nvq_stream_copy",
 )
 
 
@@ -87,6 +87,7 @@ def lib() -> C.CDLL:
     L.nvq_pack_int4.argtypes = [vp, i64, i64, ci, vp, vp, vp]
     L.nvq_dequant_bf16.argtypes = [vp, vp, i64, i64, vp, vp]
     L.nvq_gemm_w4a16.argtypes = [vp, vp, i64, i64, vp, i64, vp, ci, vp]
+    L.nvq_gemm_describe.argtypes = [vp, i64, i64, i64, vp, ci, vp, ci]
     L.nvq_rms_norm_bf16.argtypes = [vp, vp, vp, C.c_float, ci, ci, vp, vp, vp]
     L.nvq_silu_mul_bf16.argtypes = [vp, vp, ci, ci, vp, vp]
     L.nvq_quant_act_i8.argtypes = [vp, ci, ci, ci, vp, vp, vp, vp]
@@ -414,6 +415,15 @@ class DecodeList:
             self.close()
         except Exception:
             pass
+
+
+def gemm_describe(M: int, N: int, K: int, dtype=torch.float32, scales_at: int = 0, y_at: int = 0):
+    """The launches of gemm_w4a16 for M tokens, N rows and K inputs (no device needed): [dict per launch].
+    scales_at, y_at: addresses, of which the alignment is looked at."""
+    out = (C.c_int32 * 15)()
+    _check(lib().nvq_gemm_describe(scales_at, N, K, M, y_at, _y_dtype(dtype), out, 15), "nvq_gemm_describe")
+    names = ("tile_tokens", "tile_rows", "first_row", "rows", "first_token", "tokens", "store_bytes")
+    return [dict(zip(names, out[1 + 7 * i:8 + 7 * i])) for i in range(out[0])]
 
 
 def plan_describe_batches(linears: Sequence[Linear], M: int, ordered: bool = False):

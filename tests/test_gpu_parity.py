@@ -2027,6 +2027,28 @@ def test_gemm_w4a16_in_two_launches(M, N, K, off):
     assert torch.equal(y[torch.bfloat16], y[torch.float32].to(torch.bfloat16))
 
 
+# Cut by rows, the result itself begins at a whole 16 bytes but its rows are 2 and 8 bytes off: the same bits as the
+# fp32 results rounded, nothing outside.
+@pytest.mark.parametrize("M,N,K", [(2049, 4133, 800), (227, 4196, 11040)])
+def test_gemm_w4a16_in_two_launches_rows_no_whole_16_bytes(M, N, K):
+    say("gemm in two launches, ragged rows", M, N, K)
+    ws = (torch.randint(0, 256, (N, K // 2), dtype=torch.uint8, device=DEV,
+                        generator=torch.Generator(device=DEV).manual_seed(9500 + N)),
+          torch.randint(0x1400, 0x2c00, (N, K // 32), dtype=torch.int16, device=DEV,
+                        generator=torch.Generator(device=DEV).manual_seed(9600 + N)))
+    x = act(9700 + K, M, K).to(DEV)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        parts = nvq.gemm_describe(M, N, K, dtype=torch.bfloat16)
+        assert len(parts) == 2 and parts[1]["first_row"] > 0 and {p["store_bytes"] for p in parts} == {2}
+    want = nvq.gemm_w4a16(*ws, x, out=torch.empty((M, N), dtype=torch.float32, device=DEV)).to(torch.bfloat16)
+    flat = torch.full((M * N + 16,), float("nan"), dtype=torch.bfloat16, device=DEV)
+    y = flat[8:8 + M * N].view(M, N)
+    assert y.data_ptr() % 16 == 0
+    nvq.gemm_w4a16(*ws, x, out=y)
+    torch.cuda.synchronize()
+    assert torch.equal(y, want) and flat[:8].isnan().all() and flat[-8:].isnan().all()
+
+
 # An infinite activation in the last group of K: infinite results, NaN only where the weight is
 # zero (K that ends inside a block, an odd number of blocks, a single one).
 @pytest.mark.parametrize("tile", ["128x256", "128x128", "128x64", "64x64", "64x32"])
