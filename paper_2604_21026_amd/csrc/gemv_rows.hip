@@ -335,7 +335,7 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                 }
             };
             // W4A8: no correction, the weights enter as 16 (n - 8): the nibble in the high half of
-            // its byte, its top bit flipped (the factor leaves with the activation scale)
+            // its byte, its top bit flipped (the factor leaves with the result)
             auto unpack = [&](int u) {
                 const uint32_t v = q[u >> 1][u & 1];
                 if constexpr (PREC == NVQ_W4A8) {
@@ -435,12 +435,13 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
             int kb = lane >> 4, n = lane & 15;
             asm volatile("" : "+v"(kb), "+v"(n));
             float xs[MT][4];  // per-token activation scale of the lane's results (W4A8)
+            const float unit = codes ? 0.0625f : 1.0f;  // (on the sum: scales may be as small as they like)
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int jj = 0; jj < 4; ++jj) {
                     const int m = mt * 16 + kb * 4 + jj;
-                    xs[mt][jj] = codes && m < M ? 0.0625f * as_global<float>(P.xscale)[m] : 1.0f;
+                    xs[mt][jj] = codes && m < M ? as_global<float>(P.xscale)[m] : 1.0f;
                 }
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -451,7 +452,7 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                     for (int jj = 0; jj < 4; ++jj) {
                         const int m = mt * 16 + kb * 4 + jj;
                         if (o.valid && m < M)
-                            store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, total[r][mt][jj] * xs[mt][jj]);
+                            store_global(o.y, o.y_dtype, (int64_t)m * o.N + o.n, (unit * total[r][mt][jj]) * xs[mt][jj]);
                     }
             }
         }

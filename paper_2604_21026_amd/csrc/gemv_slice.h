@@ -167,8 +167,13 @@ struct SliceArgs {
 };
 static_assert(sizeof(SlicePhase<kMaxSeg, false>) == 184 && kMaxMerge == 2, "three lines; one comparison finds a workgroup's phase");
 
+// Two workgroups of eight waves per compute unit with a scale per group and 16 tokens: 128 registers, which
+// the compiler would pass by two.
+constexpr int slice_min_waves(bool pg, int tok, int scb, bool debug) { return pg && tok == 16 && scb >= 4 && !debug ? 4 : 1; }
+
 template <int PREC, bool PG, int TOK, int RT, int W, int NG, int V, int SCB, int NP, int SEGS, bool DEBUG>
-__global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, DEBUG>) {
+__global__ __launch_bounds__(W * 64) __attribute__((amdgpu_waves_per_eu(slice_min_waves(PG, TOK, SCB, DEBUG)))) void
+gemv_slice_kernel(SliceArgs<NP, SEGS, DEBUG>) {
     typedef Act<PREC> A;
     typedef SliceBlock<PREC, PG, TOK, RT, NG, SCB> B;
     constexpr bool TAIL = SCB != 16;
@@ -382,7 +387,14 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         return 16 * ((reg >> 2) % MT) + 4 * ((result >> 4) & (B::kPair ? 1 : 3)) + (reg & 3);
     };
     constexpr int kXsc = kByGroup ? kRounds : MT * 4;
-    constexpr float kWeightUnit = PREC == NVQ_W4A8 ? 0.0625f : 1.0f;  // (see weights, below)
+    // W4A8 weights enter as 16 (n - 8) (see weights, below).  The factor leaves with a scale per token on the
+    // chain's sum (in the scale it would cost bits of those below 2^-122); with a scale per group before that:
+    // left in the chains it would overflow for results beyond 2^124.  There a product starts at the bits
+    // of 786432.0f, whose last place is a sixteenth, so that what it ends at is a float that is
+    // one subtraction from the product, no more than a conversion costs.  (For a scale per token too it
+    // would cost four registers, and with 8 waves and 8 tokens a sixth of the waves.)
+    constexpr float kWeightUnit = kTokenScale ? 0.0625f : 1.0f;
+    constexpr int kStart = PG ? 0x49400000 : 0;
     float xsc[kXsc];
     if (kTokenScale) {
 #pragma unroll
@@ -515,7 +527,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
             }
         };
         // W4A8: no correction of the offset, the weights enter as 16 (n - 8): the nibble in the high half of
-        // its byte, its top bit flipped (the factor leaves with the token's scale, or at the end)
+        // its byte, its top bit flipped (see kWeightUnit)
         auto weights = [&](int r, int i) {
             uint32_t v;
             if constexpr (kRows)
@@ -536,7 +548,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
                 const int m = mt * 16 + (B::kPair ? kb & 1 : kb) * 4 + jj;
-                if (m < M) S.dbg[((int64_t)m * S.N + row) * G + g] = (int)raw[jj] / 16;
+                if (m < M) S.dbg[((int64_t)m * S.N + row) * G + g] = ((int)raw[jj] - kStart) / 16;
             }
         };
         // what the lane adds in round i: group i, or i + 4 in the upper half of a pair
@@ -566,11 +578,17 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         // W4A16: the constant offset of its weights, for all row tiles
         auto correction = [&](int i, int mt) {
             if constexpr (PREC == NVQ_W4A8)
-                return typename A::offset_t{0, 0, 0, 0};
+                return typename A::offset_t{kStart, kStart, kStart, kStart};
             else if constexpr (B::kPair)
                 return A::offset(activation(0, i + 4), A::offset(activation(0, i)));
             else
                 return A::offset(activation(mt, i));
+        };
+        auto value = [&](const typename A::offset_t &p) {
+            if constexpr (PG)
+                return __builtin_bit_cast(float4v, p) - 786432.0f;
+            else
+                return A::value(p);
         };
         constexpr int kRounds = B::kPair ? 4 : NG;
         if constexpr (PREC == NVQ_W4A8 && MT * RT == 1 && !kBranches) {
@@ -581,7 +599,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
             for (int i = 0; i < kRounds; ++i) {
                 const typename A::offset_t now = p;
                 if (i + 1 < kRounds) p = product(i + 1, 0, 0, correction(i + 1, 0));
-                add(A::value(now), i, 0, 0);
+                add(value(now), i, 0, 0);
             }
         } else {
 #pragma unroll
@@ -595,7 +613,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                         typename A::offset_t p = product(i, r, mt, off);
                         if constexpr (kBranches) wait_written(p);
                         if (DEBUG && PREC == NVQ_W4A8) dump(p, i, r, mt);
-                        if (!TAIL || !B::kPair || g0 + i + 4 * half < G) add(A::value(p), i, r, mt);
+                        if (!TAIL || !B::kPair || g0 + i + 4 * half < G) add(value(p), i, r, mt);
                     }
                 }
             }
@@ -622,7 +640,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj) {
-                const float xs = kTokenScale ? kWeightUnit * xsc[kByGroup ? 0 : mt * 4 + jj] : 1.0f;
+                const float xs = kTokenScale ? xsc[kByGroup ? 0 : mt * 4 + jj] : 1.0f;
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
@@ -630,7 +648,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
 #pragma unroll
                         for (int r = 0; r < RT; ++r)
                             red[C * (w + W * u) + c + half * (C / 2)][(r * MT + mt) * 4 + jj][B::kPair ? lane & 31 : lane] =
-                                f[u][c][r][mt][jj] * xs;
+                                (kWeightUnit * f[u][c][r][mt][jj]) * xs;
             }
         __syncthreads();
 #pragma unroll
@@ -675,7 +693,7 @@ __global__ __launch_bounds__(W * 64) void gemv_slice_kernel(SliceArgs<NP, SEGS, 
                 v[0] += dpp_f32<kDppXor1>(v[0]);
                 const int reg = stored_reg(round), r = reg / (MT * 4);
                 if (share == 0)
-                    store(16 * r + (result & 15), stored_token(reg), v[0] * (kTokenScale ? kWeightUnit * xsc[round] : kWeightUnit));
+                    store(16 * r + (result & 15), stored_token(reg), (kWeightUnit * v[0]) * (kTokenScale ? xsc[round] : 1.0f));
             }
         }
     }

@@ -915,6 +915,26 @@ def test_streaming_plan_orders_dependent_phases():
     dl.close()
 
 
+# Activation scales of the smallest and largest normal numbers: the results are those of ordinary scales times
+# a power of two, to the bit (chains of columns, 16 and 8, and of groups; a scale per token and per group).  The
+# weights' scales are large, so that sums at the lower end are far from the numbers with fewer bits.
+@pytest.mark.parametrize("M", [2, 8, 13, 29])
+@pytest.mark.parametrize("group", [0, 32])
+@pytest.mark.parametrize("N,K", [(160, 4096), (20000, 1024), (100, 1312), (96, 2752)])
+def test_w4a8_scales_of_any_size(M, group, N, K):
+    say("w4a8, scales of any size", M, group, N, K)
+    rng = np.random.default_rng(8900 + M + K)
+    q = torch.from_numpy(rng.integers(0, 256, (N, K // 2), dtype=np.uint8)).to(DEV)
+    s = torch.from_numpy(rng.integers(0x5400, 0x6c00, (N, K // 32)).astype(np.int16)).to(DEV)
+    xq, xs, gs = nvq.quant_act_i8(act(8950 + M, M, K).to(DEV), group)
+    xs = 1.0 + torch.rand(xs.shape, device=DEV, generator=torch.Generator(device=DEV).manual_seed(M))
+    y = nvq.gemv_w4a8(q, s, xq, xs, gs, group)
+    top = 126 - int(np.ceil(np.log2(y.abs().max().item())))
+    for power in (-124, top):
+        got = nvq.gemv_w4a8(q, s, xq, xs * 2.0 ** power, gs, group)
+        assert got.isfinite().all() and torch.equal(got.double(), y.double() * 2.0 ** power), power
+
+
 # ---- grouped small-batch walker (2..32 tokens on the matrix cores) -------------------
 def kernels_of(dl, ordered=False):
     """Per batch of a plan that is issued in batches: what it runs on (see nvq_plan_describe_batches;
@@ -1083,6 +1103,30 @@ def test_rows_plan_results_do_not_depend_on_the_order_of_the_phases(shapes, mbyt
         pick = np.unique(np.concatenate([[0, N - 1, N // 2], rng.integers(0, N, 24)]))
         sub = dict(h, qweight=h["qweight"][pick], scales=h["scales"][pick])
         assert np_ref.rel_l2(y.cpu().numpy()[:, pick], oracle.decode_linears([sub], M, 0)[0]) < 1e-5
+
+
+# Inputs whose scales are among the smallest normal numbers: results of ordinary inputs times a power of two.
+@pytest.mark.parametrize("M", [9, 30])
+def test_rows_plan_with_inputs_of_any_size(M):
+    say("rows plan, inputs of any size", M)
+    bulk = bulk_layer(M, 100)
+    entries, _ = model_entries([(300, 512, 0), (129, 1536, 1), (2500, 2048, 2)], (0, 0), M=M, seed=8790)
+    for e in entries + [bulk[0]]:
+        e["x"][:, 0] = 64.0                                  # (every scale at least half of 1)
+    ran = []
+    for power in (0, -124):
+        for e in entries + [bulk[0]]:
+            e["x"].mul_(2.0 ** power)
+        dl = nvq.DecodeList(entries + [bulk[0]], M, 0)
+        assert kernels_of(dl) == ["rows"]
+        dl.run_plan()
+        torch.cuda.synchronize()
+        ran.append([e["y"].clone() for e in entries + [bulk[0]]])
+        dl.close()
+    for y, tiny in zip(*ran):
+        want = y.double() * 2.0 ** -124
+        big = want.abs() >= 2.0 ** -126
+        assert torch.equal(tiny.double()[big], want[big])
 
 
 @pytest.mark.parametrize("M,kernel", [(2, "rings"), (16, "rings"), (17, "rings"), (32, "rings"), (17, "rows"),
