@@ -443,6 +443,11 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
                     const int m = mt * 16 + kb * 4 + jj;
                     xs[mt][jj] = codes && m < M ? as_global<float>(P.xscale)[m] : 1.0f;
                 }
+            // (all of them before the first store: a load is waited for together with what was issued before it)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) asm volatile("" : "+v"(xs[mt][jj]));
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 const RowRef o = locate_row(P.segs, ((cur.unit + w) * R + r) * 16 + n, 0);
