@@ -680,6 +680,23 @@ void order_phases(GroupPlan &gp, GroupBatch &b) {
                   "three phases have the room");
 }
 
+// The groups of a part (gemv_rows.hip: up to four units of one phase), and of the part that has the most.
+int part_groups(const GroupPlan &gp, const GroupBatch &b, int part) {
+    const int from = (int)gp.parts[(size_t)(b.part_first + part)], to = (int)gp.parts[(size_t)(b.part_first + part + 1)];
+    int groups = 0;
+    for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
+        const GroupPhase &g = gp.tab[(size_t)p];
+        const int units = std::min(to, g.unit_begin + g.unit_count) - std::max(from, g.unit_begin);
+        if (units > 0) groups += rows_groups(units);
+    }
+    return groups;
+}
+int most_groups(const GroupPlan &gp, const GroupBatch &b) {
+    int most = 0;
+    for (int t = 0; t < b.nparts; ++t) most = std::max(most, part_groups(gp, b, t));
+    return most;
+}
+
 GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
                      bool ordered, const Workspace &ws) {
     GroupPlan gp;
@@ -712,7 +729,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
             cur.nimg = 0;
         }
         if (cur.kind == kGroupRows) {
-            cur.grid = rows_grid(cur.nunits, cur.nparts, M);
+            cur.grid = rows_grid(most_groups(gp, cur), cur.nparts, M);
             order_phases(gp, cur);
         }
         gp.batches.push_back(cur);

@@ -133,11 +133,12 @@ int launch_gemv_mfma_ring(const GroupPhase *tab, const uint32_t *part_tab, int n
                           int M, uint32_t *status, hipStream_t st);
 
 // The same work for long lists of 2 to 32 tokens, from the inputs themselves (codes and scales of
-// launch_quant_act_group for the W4A8 phases); grid = rows_grid(); tickets: eight words that
+// launch_quant_act_group for the W4A8 phases); grid: rows_grid() of its groups; tickets: eight words that
 // are zero.  order: nparts + 1 indices into what follows, then the phases of every part in the order
 // they are taken in (null: as they stand).
 constexpr int kRowsMinTokens = 17;
-int rows_grid(int nunits, int nparts, int M);
+int rows_groups(int units);  // of one phase in one part
+int rows_grid(int groups, int nparts, int M);  // groups: of the part with the most of them
 int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, const uint32_t *order, int grid,
                      int M, uint32_t *tickets, hipStream_t st);
 

@@ -423,6 +423,24 @@ def test_batches_of_17_tokens_and_more_run_as_a_grid_if_there_is_enough_work(M):
     assert all(b["grid"] > 0 for b in nvq.plan_describe_batches(many, 16, ordered=True)[1])
 
 
+# The grid with shared activations has a workgroup for every group (four units of one phase in one part) of the part
+# with the most, as long as they are resident together: four per compute unit up to 16 tokens, three beyond.
+@pytest.mark.parametrize("M,phases,rows,K", [(17, 200, 160, 1024), (32, 150, 250, 1024), (12, 40, 2600, 1024),
+                                             (16, 200, 700, 1024), (25, 12, 4096, 2560), (16, 30, 3000, 1536)])
+def test_grid_of_shared_activations_has_a_workgroup_per_group(M, phases, rows, K):
+    a = Arena()
+    layers = [linear(a, rows + 32 * (i % 3), K, a.take(M * K * 2), prec=i % 2, M=M) for i in range(phases)]
+    ring, batches = nvq.plan_describe_batches(layers, M)
+    assert ring and len(batches) == 1
+    b = batches[0]
+    assert b["jobs"] == phases // 2                # (this grid: codes for the W4A8 phases alone)
+    units = [(l.N + 31) // 32 for l in layers]
+    first = np.concatenate([[0], np.cumsum(units)])
+    groups = [sum(-(-max(0, min(hi, first[p + 1]) - max(lo, first[p])) // 4) for p in range(phases))
+              for lo, hi in zip(b["cuts"][:-1], b["cuts"][1:])]
+    assert b["grid"] == min(8 * max(groups), (4 if M <= 16 else 3) * 256)
+
+
 def test_lists_the_persistent_small_batch_kernel_does_not_take():
     a = Arena()
     x = a.take(32 * 4096 * 2)
