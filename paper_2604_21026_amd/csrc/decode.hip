@@ -624,15 +624,16 @@ GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
 
 // Cut the units of a batch into contiguous parts of (nearly) equal weight
 // bytes, one per XCD of the persistent kernel's grid; a unit of phase p weighs
-// G_p.
-void cut_batch(GroupPlan &gp, GroupBatch &b, int M) {
+// G_p (+ extra).
+void cut_batch(GroupPlan &gp, GroupBatch &b, int M, int extra = 0) {
     b.grid = ring_grid(M, b.nunits);
     const int nparts = ring_parts(b.grid);
     b.part_first = (int)gp.parts.size();
     b.nparts = nparts;
     if (nparts <= 0) return;
+    auto weight = [&](int u) { return (uint64_t)(gp.tab[gp.units[(size_t)b.unit_first + u]].G + extra); };
     uint64_t total = 0;
-    for (int u = 0; u < b.nunits; ++u) total += (uint64_t)gp.tab[gp.units[(size_t)b.unit_first + u]].G;
+    for (int u = 0; u < b.nunits; ++u) total += weight(u);
     std::vector<uint32_t> cut((size_t)nparts + 1), phase((size_t)nparts + 1);
     uint64_t before = 0;  // weight of the units before u
     int t = 0;
@@ -643,7 +644,7 @@ void cut_batch(GroupPlan &gp, GroupBatch &b, int M) {
             phase[(size_t)t] = gp.units[(size_t)b.unit_first + u];
             ++t;
         }
-        before += (uint64_t)gp.tab[gp.units[(size_t)b.unit_first + u]].G;
+        before += weight(u);
     }
     for (; t <= nparts; ++t) {
         cut[(size_t)t] = (uint32_t)b.nunits;
@@ -697,6 +698,23 @@ int most_groups(const GroupPlan &gp, const GroupBatch &b) {
     return most;
 }
 
+// The parts for gemv_rows.hip.  Of equal bytes, those with the shorter K have more groups: more than an XCD
+// holds workgroups makes some wait for a whole group elsewhere in the part, while other XCDs have room.  So
+// where all groups are resident together, every unit weighs as much more as it takes for no part to have
+// too many (or, where they fill the chip, hardly any): five blocks of 1B at 8 tokens 76 us, so 65, three of 8B 130 and 112 (67 such lists 1.11 times as fast,
+// the worst 0.89).  With more groups than that, equal bytes are as good as anything.
+void cut_rows(GroupPlan &gp, GroupBatch &b, int M) {
+    if (b.nparts <= 0) return;
+    const int room = rows_resident(M) / b.nparts;
+    int all = 0;
+    for (int t = 0; t < b.nparts; ++t) all += part_groups(gp, b, t);
+    if (all > room * b.nparts) return;
+    for (int extra = 16; most_groups(gp, b) > room && extra <= 1024; extra *= 2) {
+        gp.parts.resize((size_t)b.part_first);
+        cut_batch(gp, b, M, extra);
+    }
+}
+
 GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int M, int act_group,
                      bool ordered, const Workspace &ws) {
     GroupPlan gp;
@@ -729,6 +747,7 @@ GroupPlan group_plan(const nvq_linear *L, const std::vector<Phase> &phases, int 
             cur.nimg = 0;
         }
         if (cur.kind == kGroupRows) {
+            cut_rows(gp, cur, M);
             cur.grid = rows_grid(most_groups(gp, cur), cur.nparts, M);
             order_phases(gp, cur);
         }

@@ -472,12 +472,14 @@ gemv_rows_kernel(const GroupPhase *__restrict__ tab_, const uint32_t *__restrict
 
 }  // namespace
 
+int rows_resident(int M) { return rows_per_cu(M > 16 ? 2 : 1) * device_cu_count(); }
+
 // A workgroup for every group of the part that has the most (the others' spare ones end at once), at most
 // what is resident: a group that waits for another's workgroup takes as long again.  Counted from the units alone,
 // as if groups went on across phases, the grid was too small for lists of small phases and for uneven parts: 17 tokens,
 // 64 phases of 160 x 2048 36 us, so 23, of 544 x 4096 65 and 47.
 int rows_grid(int groups, int nparts, int M) {
-    const int64_t want = (int64_t)groups * nparts, cap = rows_per_cu(M > 16 ? 2 : 1) * device_cu_count();
+    const int64_t want = (int64_t)groups * nparts, cap = rows_resident(M);
     return (int)(want < cap ? want : cap);
 }
 

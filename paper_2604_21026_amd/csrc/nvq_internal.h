@@ -138,6 +138,7 @@ int launch_gemv_mfma_ring(const GroupPhase *tab, const uint32_t *part_tab, int n
 // they are taken in (null: as they stand).
 constexpr int kRowsMinTokens = 17;
 int rows_groups(int units);  // of one phase in one part
+int rows_resident(int M);    // workgroups that are at work together
 int rows_grid(int groups, int nparts, int M);  // groups: of the part with the most of them
 int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, const uint32_t *order, int grid,
                      int M, uint32_t *tickets, hipStream_t st);

@@ -441,6 +441,23 @@ def test_grid_of_shared_activations_has_a_workgroup_per_group(M, phases, rows, K
     assert b["grid"] == min(8 * max(groups), (4 if M <= 16 else 3) * 256)
 
 
+# (1,010 groups of the 8B blocks for 1,024 workgroups: where the cuts divide phases there are a few more)
+@pytest.mark.parametrize("model,blocks,M,most", [("llama-1b", 5, 8, 128), ("llama-1b", 5, 16, 128),
+                                                 ("llama-8b", 3, 8, 130)])
+def test_no_part_of_shared_activations_has_more_groups_than_workgroups_if_all_fit(model, blocks, M, most):
+    layers = model_list_m(model, [b % 2 for b in range(32)], M)[:7 * blocks]
+    _, phases = nvq.plan_describe(layers, M)
+    ring, (b,) = nvq.plan_describe_batches(layers, M)
+    assert ring and b["jobs"] == 4 * ((blocks + 1) // 2)     # (codes for the W4A8 blocks: this grid)
+    units = [(sum(layers[ph["first"] + i].N for i in range(ph["count"])) + 31) // 32 for ph in phases]
+    first = np.concatenate([[0], np.cumsum(units)])
+    groups = [sum(-(-max(0, min(hi, first[p + 1]) - max(lo, first[p])) // 4) for p in range(len(phases)))
+              for lo, hi in zip(b["cuts"][:-1], b["cuts"][1:])]
+    assert sum(groups) <= 1024 and max(groups) <= most
+    assert b["cuts"][0] == 0 and b["cuts"][-1] == b["units"] == first[-1] and b["cuts"] == sorted(b["cuts"])
+    assert b["cut_phases"][:-1] == [int(np.searchsorted(first, c, "right")) - 1 for c in b["cuts"][:-1]]
+
+
 def test_lists_the_persistent_small_batch_kernel_does_not_take():
     a = Arena()
     x = a.take(32 * 4096 * 2)
