@@ -17,6 +17,7 @@
 #include <cmath>
 #include <mutex>
 #include <new>
+#include <utility>
 #include <vector>
 
 #include "decode_stream.h"
@@ -562,6 +563,42 @@ struct GroupPlan {
     std::vector<GroupBatch> batches;
 };
 
+// The groups of a part (gemv_rows.hip: up to four units of one phase), of all, and of the part that has the most.
+int part_groups(const GroupPlan &gp, const GroupBatch &b, int part) {
+    const int from = (int)gp.parts[(size_t)(b.part_first + part)], to = (int)gp.parts[(size_t)(b.part_first + part + 1)];
+    int groups = 0;
+    for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
+        const GroupPhase &g = gp.tab[(size_t)p];
+        const int units = std::min(to, g.unit_begin + g.unit_count) - std::max(from, g.unit_begin);
+        if (units > 0) groups += rows_groups(units);
+    }
+    return groups;
+}
+int all_groups(const GroupPlan &gp, const GroupBatch &b) {
+    int all = 0;
+    for (int t = 0; t < b.nparts; ++t) all += part_groups(gp, b, t);
+    return all;
+}
+int most_groups(const GroupPlan &gp, const GroupBatch &b) {
+    int most = 0;
+    for (int t = 0; t < b.nparts; ++t) most = std::max(most, part_groups(gp, b, t));
+    return most;
+}
+
+// 256s of inputs of the longest of the last `count` groups, the longest K first.
+int last_steps(const GroupPlan &gp, const GroupBatch &b, int count) {
+    std::vector<std::pair<int, int>> phases;  // steps, groups
+    for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p)
+        phases.emplace_back(gp.tab[(size_t)p].G / 8, rows_groups(gp.tab[(size_t)p].unit_count));
+    std::sort(phases.begin(), phases.end());
+    int steps = 0;
+    for (size_t i = 0; i < phases.size() && count > 0; ++i) {
+        steps = phases[i].first;
+        count -= phases[i].second;
+    }
+    return steps;
+}
+
 // How a batch is worked off.  Up to 16 tokens: the per-tile grid (gemv_mfma.hip), the persistent one
 // whose waves share the activations (gemv_rows.hip) or the one fed through LDS rings, which has the better rate, but sixteen microseconds before it and one for every
 // 256 inputs of the widest phase; both add in the same order.  Linear estimates as below, fitted to
@@ -577,9 +614,12 @@ struct GroupPlan {
 // for lists beyond those and 20 MB, and up to 500 MB: whole models keep to the rings, whose tests name them
 // too, although it is the faster one there (the step of 8B at 2, 8 and 16 tokens 798, 897, 985 through the
 // rings, 719, 790, 886).  It is estimated as below (10 % rms over 109 lists).  Per-tile grid / rings / rows:
-// 8 tokens, five blocks of 3072 x 8192 103 / 84 / 88, eight 151 / 112 / 106; four of 8B 174 / 132 / 117; twelve of 1B
+// 8 tokens, eight blocks of 3072 x 8192 151 / 112 / 106; four of 8B 174 / 132 / 117; twelve of 1B
 // 144 / 113 / 98, of 1024 x 3072 39 / 51 / 42, sixteen 48 / 61 / 44; 2 tokens, four of 8B 152 / 128 / 113; 16
-// tokens 202 / 138 / 119.  From
+// tokens 202 / 138 / 119.  What that estimate does not see is a second, nearly empty round: with up to 15 % more
+// groups than are resident together, and those that come last not much shorter, a list keeps to the rings (five blocks of 3072 x 8192, 1,080 groups for 1,024 workgroups,
+// 8 tokens 103 / 80 / 88, six of 1B 84 / 74 / 79; of 1,007 lists drawn 46 were 2 to 9 % slower on this grid than
+// through the rings, without those 5, and the choice as good on average: 1.069).  From
 // 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
 // activations (gemv_rows.hip), and launches phase by phase (gemv_slice.h), by what they were measured to
 // take (us; MB of weights, phases, the largest K): 123 lists of 4 to 64 phases and 2 to 980 MB, where
@@ -613,7 +653,9 @@ GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
         const bool per_tile = b.nphases >= 4 && mb >= 1.5 && (narrow || many) && tiles * (narrow ? 1.15 : 1.3) < rings;
         const double rows = rows_us(5.9 + 1.79 * widest, 10.5 + 0.113 * b.nphases + mb / (5.77 - 0.065 * M));
         const bool between = mb <= 500.0 && (many || (narrow && b.nphases >= 4 && mb >= 20.0));
-        if (between && rows < (per_tile ? tiles : rings)) return kGroupRows;
+        const int over = all_groups(gp, b) - rows_resident(M);
+        const bool crowded = over > 0 && 20 * over <= 3 * rows_resident(M) && 5 * last_steps(gp, b, over) >= widest;
+        if (between && !crowded && rows < (per_tile ? tiles : rings)) return kGroupRows;
         return per_tile ? kGroupTiles : kGroupRing;
     }
     const double ring = 12.6 + 0.57 * widest + 0.27 * b.nphases + mb / 2.9;
@@ -681,23 +723,6 @@ void order_phases(GroupPlan &gp, GroupBatch &b) {
                   "three phases have the room");
 }
 
-// The groups of a part (gemv_rows.hip: up to four units of one phase), and of the part that has the most.
-int part_groups(const GroupPlan &gp, const GroupBatch &b, int part) {
-    const int from = (int)gp.parts[(size_t)(b.part_first + part)], to = (int)gp.parts[(size_t)(b.part_first + part + 1)];
-    int groups = 0;
-    for (int p = b.phase_first; p < b.phase_first + b.nphases; ++p) {
-        const GroupPhase &g = gp.tab[(size_t)p];
-        const int units = std::min(to, g.unit_begin + g.unit_count) - std::max(from, g.unit_begin);
-        if (units > 0) groups += rows_groups(units);
-    }
-    return groups;
-}
-int most_groups(const GroupPlan &gp, const GroupBatch &b) {
-    int most = 0;
-    for (int t = 0; t < b.nparts; ++t) most = std::max(most, part_groups(gp, b, t));
-    return most;
-}
-
 // The parts for gemv_rows.hip.  Of equal bytes, those with the shorter K have more groups: more than an XCD
 // holds workgroups makes some wait for a whole group elsewhere in the part, while other XCDs have room.  So
 // where all groups are resident together, every unit weighs as much more as it takes for no part to have
@@ -706,9 +731,7 @@ int most_groups(const GroupPlan &gp, const GroupBatch &b) {
 void cut_rows(GroupPlan &gp, GroupBatch &b, int M) {
     if (b.nparts <= 0) return;
     const int room = rows_resident(M) / b.nparts;
-    int all = 0;
-    for (int t = 0; t < b.nparts; ++t) all += part_groups(gp, b, t);
-    if (all > room * b.nparts) return;
+    if (all_groups(gp, b) > room * b.nparts) return;
     for (int extra = 16; most_groups(gp, b) > room && extra <= 1024; extra *= 2) {
         gp.parts.resize((size_t)b.part_first);
         cut_batch(gp, b, M, extra);

@@ -458,6 +458,17 @@ def test_no_part_of_shared_activations_has_more_groups_than_workgroups_if_all_fi
     assert b["cut_phases"][:-1] == [int(np.searchsorted(first, c, "right")) - 1 for c in b["cuts"][:-1]]
 
 
+# Up to 16 tokens, a little more groups of rows than workgroups are resident together (1,104 and 1,080 for 1,024):
+# through the rings, whose jobs are all the phases; with fewer and with many more on the grid of shared activations.
+@pytest.mark.parametrize("model,blocks,rings", [("llama-1b", 5, False), ("llama-1b", 6, True), ("llama-1b", 7, False),
+                                                ("llama-3b", 4, False), ("llama-3b", 5, True), ("llama-3b", 6, False)])
+@pytest.mark.parametrize("M", [8, 16])
+def test_a_second_round_that_is_nearly_empty_keeps_a_list_to_the_rings(model, blocks, rings, M):
+    layers = model_list_m(model, [b % 2 for b in range(32)], M)[:7 * blocks]
+    ring, (b,) = nvq.plan_describe_batches(layers, M)
+    assert ring and b["grid"] > 0 and b["jobs"] == (4 * blocks if rings else 4 * ((blocks + 1) // 2))
+
+
 def test_lists_the_persistent_small_batch_kernel_does_not_take():
     a = Arena()
     x = a.take(32 * 4096 * 2)
