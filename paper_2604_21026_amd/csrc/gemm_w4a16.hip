@@ -515,17 +515,19 @@ gemm_w4a16_tile_kernel(const unsigned char *__restrict__ qw, const unsigned char
     constexpr int kEven = kWOps + kScOps + NA, kOdd = NA;  // loads of an even and an odd pair's list
     __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds];
 
-    // Tiles are numbered along the tokens first, in bands of kBand token tiles; workgroup b runs on
-    // XCD b % 8 and takes one of that XCD's eighth of the numbers, so that its 32 workgroups share
+    // Tiles are numbered along the tokens first, beyond eight token tiles in bands of kBand of them; workgroup b
+    // runs on XCD b % 8 and takes one of that XCD's eighth of the numbers, so that its 32 workgroups share
     // a few token tiles and a few row ranges in their L2.  Without the bands an XCD's workgroups all
     // read other activations where there are 32 token tiles: 128 x 64 then waited for the memory behind
     // L2 (4096 tokens, 2560 rows, K = 8192: 372 us, 203 with bands of 4; 128 x 128 212 -> 185, 128 x
-    // 256 224 -> 222).  Bands of 8: within 2 %; 2 and 16: up to 4 and 7 % slower.
+    // 256 224 -> 222).  Bands of 8: within 2 %; 2 and 16: up to 4 and 7 % slower.  Five to eight token tiles
+    // are one band: cut in two the second is a narrow one that reads its weights for few tokens (259 x 1472 x 4320
+    // 13.5 us, so 12.3, 148 x 1536 x 4992 10.0 and 9.2; 213 drawn products of so many tiles 1 % faster on average).
     const int tiles = row_tiles * token_tiles, per_xcd = (tiles + 7) >> 3;
     const int tile = ((int)blockIdx.x & 7) * per_xcd + ((int)blockIdx.x >> 3);
     if (tile >= tiles) return;
     int band0 = 0, width = token_tiles, in_band = tile;
-    if (token_tiles > kBand) {
+    if (token_tiles > 2 * kBand) {
         band0 = tile / (row_tiles * kBand) * kBand;
         width = token_tiles - band0 < kBand ? token_tiles - band0 : kBand;
         in_band = tile - row_tiles * band0;

@@ -2034,11 +2034,19 @@ def test_gemm_w4a16_tiles_of_eight_waves(tile, M, N, K, off, monkeypatch):
     assert torch.equal(whole[M // 2:], last) and torch.equal(whole, shifted)
 
 
-# Token tiles go in bands of four: one whole band, a second of one tile, three of which the last has
-# three; every result once, several row tiles.  Tolerance as above.
+# Token tiles go in bands of four where there are more than eight: one band of four or five, three of which the last
+# has three; every result once, several row tiles.  Tolerance as above.
 @pytest.mark.parametrize("tile", ["128x256", "128x128", "128x64", "64x64", "64x32", "32x32"])
 @pytest.mark.parametrize("tiles", [4, 5, 11])
 def test_gemm_w4a16_bands_of_token_tiles(tile, tiles, monkeypatch):
+    tokens, rows = (int(v) for v in tile.split("x"))
+    test_gemm_w4a16_small_tiles_match_oracle(tile, (tiles - 1) * tokens + 1, 2 * rows + 8, 160, 0, monkeypatch)
+
+
+# Eight token tiles are one band, nine three.
+@pytest.mark.parametrize("tile", ["128x256", "128x64", "64x32", "32x32"])
+@pytest.mark.parametrize("tiles", [8, 9])
+def test_gemm_w4a16_first_band_of_token_tiles(tile, tiles, monkeypatch):
     tokens, rows = (int(v) for v in tile.split("x"))
     test_gemm_w4a16_small_tiles_match_oracle(tile, (tiles - 1) * tokens + 1, 2 * rows + 8, 160, 0, monkeypatch)
 
