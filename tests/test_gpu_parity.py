@@ -2052,13 +2052,18 @@ def test_gemm_w4a16_first_band_of_token_tiles(tile, tiles, monkeypatch):
 
 
 # Products that end a little past a whole round of all compute units go in two launches, split by
-# rows (the first three at 256 units) or by tokens: rows no multiple of 8, K that ends inside a block,
+# rows or by tokens (what is asked for at 256 units): rows no multiple of 8, K that ends inside a block,
 # scales off their alignment, the two parts of different kinds.  Nothing outside of the result is
 # written.  Tolerance as above.
-@pytest.mark.parametrize("M,N,K,off", [(2049, 4104, 800, 0), (2049, 4133, 800, 1), (2049, 2056, 2048, 0),
-                                       (1300, 3079, 2080, 0), (1281, 3079, 2048, 0), (2049, 2117, 2048, 1)])
-def test_gemm_w4a16_in_two_launches(M, N, K, off):
-    say("gemm in two launches", M, N, K, off)
+@pytest.mark.parametrize("M,N,K,off,by", [(2049, 4104, 800, 0, "rows"), (2049, 4133, 800, 1, "rows"),
+                                          (2049, 2056, 2048, 0, "rows"), (1300, 3079, 2080, 0, "tokens"),
+                                          (1281, 3079, 2048, 0, "tokens"), (2049, 2117, 2048, 1, "tokens")])
+def test_gemm_w4a16_in_two_launches(M, N, K, off, by):
+    say("gemm in two launches", M, N, K, off, by)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        a, b = nvq.gemm_describe(M, N, K, scales_at=2 * off)
+        assert (b["first_row"] > 0, b["first_token"] > 0) == (by == "rows", by == "tokens")
+        assert (a["tile_tokens"], a["tile_rows"]) != (b["tile_tokens"], b["tile_rows"])
     _, q, s = packed(9300 + N, N, K)
     xh = act(9400 + K, M, K)
     want = oracle.gemm_w4a16_dense(q, s, u16(xh))
