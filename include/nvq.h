@@ -384,6 +384,18 @@ int nvq_plan_describe_skips(const nvq_linear *layers, int n, int M, int act_grou
 int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M, int act_group, int flags,
                               int32_t *out, int out_words);
 /*
+ * nvq_plan_describe_kernels -- likewise what runs the products of each of those
+ * batches: out[0] = batches, then one word per batch.
+ */
+enum {
+    NVQ_BATCH_TILES = 0,   /* a grid of short workgroups, one per row tile */
+    NVQ_BATCH_RINGS = 1,   /* a persistent grid fed through LDS rings */
+    NVQ_BATCH_SHARED = 2,  /* a persistent grid whose waves share the activations */
+    NVQ_BATCH_PHASES = 3,  /* launches phase by phase */
+};
+int nvq_plan_describe_kernels(const nvq_linear *layers, int n, int M, int act_group, int flags,
+                              int32_t *out, int out_words);
+/*
  * nvq_plan_describe_steps -- likewise the launches per phase (what a plan runs
  * that is neither the batch-1 persistent kernel nor grouped, and what
  * nvq_decode_linears_static runs if its scratch has room): out[0] = steps, then

@@ -1419,6 +1419,28 @@ extern "C" int nvq_plan_describe_batches(const nvq_linear *layers, int n, int M,
     return NVQ_OK;
 }
 
+extern "C" int nvq_plan_describe_kernels(const nvq_linear *layers, int n, int M, int act_group, int flags,
+                                         int32_t *out, int out_words) {
+    using namespace nvq;
+    if (!out || out_words < 1 || (flags & ~NVQ_PLAN_ORDERED)) return NVQ_ERR_INVALID_ARG;
+    ListSizes ls;
+    const int rc = check_layers(layers, n, M, act_group, &ls);
+    if (rc != NVQ_OK) return rc;
+    const std::vector<Phase> phases = group_phases(layers, n);
+    if (check_phase_hazards(layers, phases, M) != NVQ_OK) return NVQ_ERR_INVALID_ARG;
+    Workspace none = {};  // pointers into it are computed, never followed
+    const GroupPlan gp = group_plan(layers, phases, M, act_group, (flags & NVQ_PLAN_ORDERED) != 0, none);
+    const size_t batches = gp.tab.empty() ? 0 : gp.batches.size();
+    if ((size_t)out_words < 1 + batches) return NVQ_ERR_WORKSPACE;
+    *out++ = (int32_t)batches;
+    for (size_t b = 0; b < batches; ++b)
+        *out++ = gp.batches[b].kind == kGroupTiles  ? NVQ_BATCH_TILES
+                 : gp.batches[b].kind == kGroupRing ? NVQ_BATCH_RINGS
+                 : gp.batches[b].kind == kGroupRows ? NVQ_BATCH_SHARED
+                                                    : NVQ_BATCH_PHASES;
+    return NVQ_OK;
+}
+
 extern "C" int nvq_plan_describe_steps(const nvq_linear *layers, int n, int M, int act_group, int flags,
                                        int32_t *out, int out_words) {
     using namespace nvq;

@@ -29,7 +29,7 @@ EXPORTS = (
     "nvq_decode_status", "nvq_decode_linears_static",
     "nvq_plan_create", "nvq_plan_run", "nvq_plan_info", "nvq_plan_status", "nvq_plan_trace",
     "nvq_plan_destroy", "nvq_plan_describe", "nvq_plan_describe_batches",
-    "nvq_plan_describe_skips", "nvq_plan_describe_steps",
+    "nvq_plan_describe_skips", "nvq_plan_describe_kernels", "nvq_plan_describe_steps",
     "nvq_dequant_bf16", "nvq_gemm_w4a16", "nvq_gemm_describe", "nvq_rms_norm_bf16", "nvq_silu_mul_bf16", "nvq_precision_from_scores", "nvq_token_norms", "nvq_mcap_scores", "nvq_stream_read", "nvq_stream_copy",
 )
 
@@ -107,6 +107,7 @@ def lib() -> C.CDLL:
     L.nvq_plan_describe.argtypes = [vp, ci, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_describe_batches.argtypes = [vp, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_describe_skips.argtypes = [vp, ci, ci, ci, ci, ci, vp, sz, vp]
+    L.nvq_plan_describe_kernels.argtypes = [vp, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_describe_steps.argtypes = [vp, ci, ci, ci, ci, vp, ci]
     L.nvq_plan_destroy.restype = None
     L.nvq_precision_from_scores.argtypes = [vp, ci, C.c_double, C.c_double, vp]
@@ -444,6 +445,17 @@ def plan_describe_batches(linears: Sequence[Linear], M: int, ordered: bool = Fal
                         parts=nparts, cuts=list(o[6:6 + nparts + 1]),
                         cut_phases=list(o[15:15 + nparts + 1])))
     return bool(out[1]), res
+
+
+def plan_describe_kernels(linears: Sequence[Linear], M: int, ordered: bool = False):
+    """What runs the products of each batch of the grouped small-batch launches (no device needed):
+    "tiles", "rings", "rows" (shared activations) or "phases" (see nvq_plan_describe_kernels)."""
+    n = len(linears)
+    arr = (Linear * max(n, 1))(*linears)
+    out = (C.c_int32 * (1 + max(n, 1)))()
+    _check(lib().nvq_plan_describe_kernels(C.byref(arr), n, M, 0, PLAN_ORDERED if ordered else 0, out,
+                                           1 + max(n, 1)), "nvq_plan_describe_kernels")
+    return [("tiles", "rings", "rows", "phases")[k] for k in out[1:1 + out[0]]]
 
 
 def plan_describe_steps(linears: Sequence[Linear], M: int, act_group: int = 0, ordered: bool = False):

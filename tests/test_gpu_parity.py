@@ -937,12 +937,8 @@ def test_w4a8_scales_of_any_size(M, group, N, K):
 
 # ---- grouped small-batch walker (2..32 tokens on the matrix cores) -------------------
 def kernels_of(dl, ordered=False):
-    """Per batch of a plan that is issued in batches: what it runs on (see nvq_plan_describe_batches;
-    lists that take the grid with shared activations are long, more than a group of rows per compute
-    unit)."""
-    cus = torch.cuda.get_device_properties(0).multi_processor_count
-    _, batches = nvq.plan_describe_batches([dl.arr[i] for i in range(dl.n)], dl.M, ordered)
-    return ["phases" if b["grid"] == 0 else "rings" if b["grid"] <= cus else "rows" for b in batches]
+    """Per batch of a plan that is issued in batches: what it runs on."""
+    return nvq.plan_describe_kernels([dl.arr[i] for i in range(dl.n)], dl.M, ordered)
 
 
 def bulk_layer(M, mbytes, K=2048, seed=8990):
@@ -1187,6 +1183,29 @@ def test_rows_plan_up_to_16_tokens(M, bits, mbytes):
     test_grid_sums_are_added_in_the_stated_order(M, "rows")
 
 
+# The shortest lists that take the grid with shared activations: from 17 tokens on fewer groups than compute units,
+# parts of a few groups; phases of three units, of one unit, of one row.
+@pytest.mark.parametrize("M,phases,rows,K", [(17, 30, 340, 1024), (32, 24, 420, 1024), (20, 16, 700, 1024),
+                                             (17, 40, 220, 1024), (16, 40, 1900, 1024)])
+def test_rows_plan_of_short_lists(M, phases, rows, K):
+    say("rows plan, short list", M, phases, rows, K)
+    shapes = [(rows + 37 * (p % 5), K, p) for p in range(phases)] + [(1, 512, phases), (33, 1024, phases + 1)]
+    entries, host = model_entries(shapes, (0,), M=M, seed=8660)
+    for i, (e, h) in enumerate(zip(entries, host)):
+        e["precision"] = h["precision"] = i % 2
+    ys_ref = oracle.decode_linears(host, M, 0)
+    dl = nvq.DecodeList(entries, M, 0)
+    assert kernels_of(dl) == ["rows"]
+    for rep in range(2):
+        for e in entries:
+            e["y"].fill_(9.0)
+        dl.run_plan()
+        torch.cuda.synchronize()
+        for i, (e, y_r) in enumerate(zip(entries, ys_ref)):
+            assert np_ref.rel_l2(e["y"].cpu().numpy(), y_r) < 1e-5, (rep, i)
+    dl.close()
+
+
 @pytest.mark.parametrize("M", [17, 32])
 def test_rows_plan_short_batches_run_phase_by_phase(M):
     """Forced order: every phase is a batch of its own, too small for the persistent grid."""
@@ -1233,7 +1252,7 @@ def test_short_lists_of_the_rings_kind_run_as_the_per_tile_grid(M):
                             y=torch.zeros((M, N), dtype=torch.float32, device=DEV)))
     dl = nvq.DecodeList(entries, M, 0)
     info = dl.plan_info()
-    assert info["grouped"] and not info["persistent_grouped"] and kernels_of(dl) == ["phases"]
+    assert info["grouped"] and not info["persistent_grouped"] and kernels_of(dl) == ["tiles"]
     assert not dl.plan_timed_out()
     g = torch.cuda.CUDAGraph()
     for rep in range(4):

@@ -465,6 +465,7 @@ def test_no_part_of_shared_activations_has_more_groups_than_workgroups_if_all_fi
 @pytest.mark.parametrize("M", [8, 16])
 def test_a_second_round_that_is_nearly_empty_keeps_a_list_to_the_rings(model, blocks, rings, M):
     layers = model_list_m(model, [b % 2 for b in range(32)], M)[:7 * blocks]
+    assert nvq.plan_describe_kernels(layers, M) == ["rings" if rings else "rows"]
     ring, (b,) = nvq.plan_describe_batches(layers, M)
     assert ring and b["grid"] > 0 and b["jobs"] == (4 * blocks if rings else 4 * ((blocks + 1) // 2))
 
