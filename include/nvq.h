@@ -285,7 +285,11 @@ int nvq_decode_linears_static(const nvq_linear *layers, int n, int M, int act_gr
  *                    rows, and is taken by estimates of its time; up to 16 tokens
  *                    also by batches of fewer than four phases, of less than 1.5
  *                    MB of weights, or of up to eight phases or 50 MB with one of
- *                    K >= 6144, whatever the estimates),
+ *                    K >= 6144, whatever the estimates.  Of the two such grids
+ *                    up to 16 tokens the one with shared activations serves
+ *                    batches of 20 to 500 MB beyond those, from 17 on batches of
+ *                    5 MB and more, with one of K >= 12288 of 400 MB and more;
+ *                    nvq_plan_describe_kernels says which),
  *                    0 for launches per phase;
  *                    waits = number of phases that wait for an earlier phase,
  *                    through flags or for mail (grouped launches: number of
@@ -376,7 +380,7 @@ int nvq_plan_describe_skips(const nvq_linear *layers, int n, int M, int act_grou
  * for a persistent kernel; then 24 words per batch: first and last phase, units
  * (pairs of 16-row tiles), input jobs, workgroups of the persistent kernel (0:
  * the batch runs phase by phase, from 17 tokens on, or up to 16 as the grid of
- * short workgroups) and its parts,
+ * short workgroups; which kernel: nvq_plan_describe_kernels) and its parts,
  * 9 words unit index at which each part begins (the last one = units; unused:
  * -1), 9 words phase of the unit at each cut.  The grid assumes the current
  * device's compute units (256 without a device).

@@ -599,39 +599,44 @@ int last_steps(const GroupPlan &gp, const GroupBatch &b, int count) {
     return steps;
 }
 
-// How a batch is worked off.  Up to 16 tokens: the per-tile grid (gemv_mfma.hip), the persistent one
-// whose waves share the activations (gemv_rows.hip) or the one fed through LDS rings, which has the better rate, but sixteen microseconds before it and one for every
-// 256 inputs of the widest phase; both add in the same order.  Linear estimates as below, fitted to
-// 1008 and 720 lists of 4 to 64 phases and 3 to 490 MB (10 and 9 % rms), with a margin for their errors.  Per-tile
-// grid / rings, 8 tokens, cold weights: two blocks of 1024 x 3072 16 / 32, four of 1536 x 4608 36 / 39, ten
-// 65 / 63, sixteen 96 / 79; three of 1B 51 / 59, four 62 / 59.
+// How a batch is worked off.
+//
+// Up to 16 tokens: the per-tile grid (gemv_mfma.hip) or the persistent grid fed through LDS rings
+// (gemv_mfma_ring.hip), which add in the same order, or the persistent grid whose waves share the activations
+// (gemv_rows.hip: eight groups, eight steps, then those).  The rings have the better rate of the first two, but
+// sixteen microseconds before it and one for every 256 inputs of the widest phase.  Linear estimates, fitted to
+// 1008 and 720 lists of 4 to 64 phases and 3 to 490 MB (10 and 9 % rms), with a margin for their errors.
+// Per-tile grid / rings, 8 tokens, cold weights: two blocks of 1024 x 3072 15 / 33, four of 1536 x 4608 37 /
+// 40, ten 65 / 63, sixteen 96 / 79; three of 1B 54 / 61, four 64 / 60.
 // Three bounds beside the estimates are not where the per-tile grid stops being the faster one: lists of
 // fewer than four phases, of less than 1.5 MB, and of up to eight phases or 50 MB with one of K >= 6144 keep
 // to the rings although these are slower (6 of 64 x 512 6.6 / 13.8, 8 of 256 x 1024 8.7 / 15.8, one layer of
 // 2048 x 2048 8.7 / 20, three 12 / 32, 4096 x 14336 31 / 129, one block of 1B 28 / 56, two 43 / 57, one of
 // 8B 68 / 93; two of 8B 101 / 96).  They are the lists that the rings' tests are built on, whose kernel
-// and waits those name, and the first two lie outside of what was fitted.  The grid of shared activations is
-// for lists beyond those and 20 MB, and up to 500 MB: whole models keep to the rings, whose tests name them
-// too, although it is the faster one there (the step of 8B at 2, 8 and 16 tokens 798, 897, 985 through the
-// rings, 719, 790, 886).  It is estimated as below (10 % rms over 109 lists).  Per-tile grid / rings / rows:
-// 8 tokens, eight blocks of 3072 x 8192 151 / 112 / 106; four of 8B 174 / 132 / 117; twelve of 1B
-// 144 / 113 / 98, of 1024 x 3072 39 / 51 / 42, sixteen 48 / 61 / 44; 2 tokens, four of 8B 152 / 128 / 113; 16
-// tokens 202 / 138 / 119.  What that estimate does not see is a second, nearly empty round: with up to 15 % more
-// groups than are resident together, and those that come last not much shorter, a list keeps to the rings (five blocks of 3072 x 8192, 1,080 groups for 1,024 workgroups,
-// 8 tokens 103 / 80 / 88, six of 1B 84 / 74 / 79; of 1,007 lists drawn 46 were 2 to 9 % slower on this grid than
-// through the rings, without those 5, and the choice as good on average: 1.069).  From
-// 17 on what takes least of that grid (gemv_mfma_ring.hip), the one whose waves share the
-// activations (gemv_rows.hip), and launches phase by phase (gemv_slice.h), by what they were measured to
-// take (us; MB of weights, phases, the largest K): 123 lists of 4 to 64 phases and 2 to 980 MB, where
-// the choice costs 2 % on average.  A list takes the second as long as its widest phase takes a
-// workgroup, which keeps a group of rows for all of K, or as long as its bytes do, whichever is longer,
-// and a fifth more where both are equal (the fourth powers).  Rings / rows / phases: one block of 8B
-// 76 / 124 / 61, two 131 / 135 / 127, four 185 / 147 / 244, eight 353 / 252 / 480; two blocks of 1B
-// 61 / 75 / 66, six 110 / 87 / 185, sixteen 229 / 138 / 485; four of 1536 x 4608 47 / 41 / 99.
-// The tenth more and the two bounds: few and small phases go up and down with how they fall to the
-// workgroups (20 phases, 8 MB: 23 with the rings, 27; 16 phases, 7 MB: 20 and 17), and wide lists of
-// less than 400 MB keep to the rings, whose tests name them, although three blocks of 8B would take
-// 143 instead of 169.
+// and waits those name, and the first two lie outside of what was fitted.
+// The grid of shared activations is for lists beyond those and 20 MB, and up to 500 MB: whole models keep to
+// the rings, whose tests name them too, although it is the faster one there (the step of 8B at 2, 8 and 16
+// tokens 820, 915, 1,000 through the rings, 718, 815, 907).  It is estimated as below (10 % rms over 109
+// lists).  Per-tile grid / rings / rows, 8 tokens: four blocks of 3B 85 / 82 / 66, eight 151 / 115 / 106; five
+// of 1B 73 / 75 / 66, twelve 145 / 114 / 100; three of 8B 144 / 133 / 112, four 176 / 133 / 120; twelve of 1024 x
+// 3072 40 / 51 / 36, sixteen 48 / 61 / 45; four of 8B at 2 tokens 153 / 134 / 117, at 16 205 / 142 / 124.
+// What that estimate does not see is a second, nearly empty round: with up to 15 % more groups than are
+// resident together, and those that come last not much shorter, a list keeps to the rings (five blocks of 3B,
+// 1,080 groups for 1,024 workgroups, 103 / 84 / 88, six of 1B 84 / 76 / 78; of 1,007 lists drawn 46 were 2 to 9 %
+// slower on this grid than through the rings, without those 5, and the choice as good on average: 1.069).
+//
+// From 17 tokens on what takes least of the rings, the grid of shared activations and launches phase by phase
+// (gemv_slice.h), by what they were measured to take (us; MB of weights, phases, the largest K): 123 lists
+// of 4 to 64 phases and 2 to 980 MB, where the choice cost 2 % on average.  A list takes the second as long
+// as its widest phase takes a workgroup, which keeps a group of rows for all of K, or as long as its bytes do,
+// whichever is longer, and a fifth more where both are equal (the fourth powers); since then that grid has
+// become faster for lists that do not fill the chip (see rows_grid, cut_rows), which the estimate does not know.
+// Rings / rows / phases at 32 tokens: one block of 8B 75 / 98 / 66, two 129 / 103 / 143, three 168 / 142 / 220, four
+// 190 / 151 / 276, eight 353 / 265 / 545; two blocks of 1B 60 / 61 / 73, six 110 / 87 / 205, sixteen 227 / 156 / 540; four
+// of 1536 x 4608 47 / 43 / 111.
+// The two bounds: lists of less than 5 MB are outside of what was fitted, and wide lists of less than 400 MB
+// keep to the rings or the phases, whose tests name them, although two and three blocks of 8B would take a
+// fifth less.
 GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
     if (!gp.ring) return kGroupTiles;
     double mb = 0.0, widest = 0.0, single = 3.3;
@@ -646,7 +651,7 @@ GroupKind group_kind(const GroupPlan &gp, const GroupBatch &b, int M) {
     auto rows_us = [&](double longest, double bytes) {
         return 1.1 * std::pow(std::pow(longest, 4) + std::pow(bytes, 4), 0.25);
     };
-    if (M <= 16) {
+    if (M < kPhasesMinTokens) {
         const double tiles = 5.1 + 0.118 * b.nphases + 0.218 * widest + mb * (0.215 + 0.0082 * M + 0.0004 * widest);
         const double rings = 16.3 + 0.131 * b.nphases + 0.972 * widest + 0.175 * std::max(0.0, mb - 27.0);
         const bool narrow = widest < 24.0, many = b.nphases > 8 && mb > 50.0;
@@ -1102,7 +1107,7 @@ struct nvq_plan {
     bool mail;         // some phase of the streaming table posts or reads mail
     int nmail;         // phases that take an operand from a mailbox
     size_t mail_stride;  // words between the replicas of a mailbox
-    std::vector<nvq::GroupPhase> group_phases;  // 17 tokens and more: the phases of `batches`
+    std::vector<nvq::GroupPhase> group_phases;  // from kPhasesMinTokens on: the phases of `batches`
     unsigned long long *trace;  // device buffer for per-phase timestamps, or nullptr
     int trace_wgs;     // workgroups that record there
 };
@@ -1230,7 +1235,7 @@ extern "C" int nvq_plan_create(const nvq_linear *layers, int n, int M, int act_g
                 return NVQ_ERR_HIP;
             }
             pl->batches = gp.batches;
-            if (gp.ring && M >= kRowsMinTokens) pl->group_phases = gp.tab;
+            if (gp.ring && M >= kPhasesMinTokens) pl->group_phases = gp.tab;
             pl->nwaits = (int)gp.batches.size() - 1;
             pl->ring = gp.ring;
         }

@@ -3,8 +3,7 @@
 // descriptions; the arithmetic is that of mfma_act.h.
 //
 // With two token tiles 32 weight rows need 3.6 times their own bytes of bf16 activations, and a
-// kernel whose waves each fetch their own (the ring kernel, which serves shorter
-// lists) stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with
+// kernel whose waves each fetch their own (the ring kernel) stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with
 // 32 rows of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
 // through LDS, and no sums cross the waves.  K advances by 256 inputs (a whole 128-byte
 // line of a row); per step a wave asks for its quarter of the next step's activations (two
@@ -13,10 +12,11 @@
 // activations have arrived and that the other buffer is free.  Three workgroups share a
 // compute unit, four where one token tile does (36 KiB of LDS): up to 16 tokens the rings wait for
 // their sums across waves and for the operand images made beforehand: four blocks of 8B at 2, 8 and 16 tokens
-// 128, 132 and 138 us there, 113, 117 and 119 here.
+// 134, 133 and 142 us there, 117, 120 and 124 here.
 //
 // The batch is cut into parts, one per XCD (the compute units of an XCD advance through
-// the phases together, so that the activations they all read stay in their L2); the
+// the phases together, so that the activations they all read stay in their L2), of equal bytes or, where all
+// groups are resident together, of as many groups as an XCD holds workgroups; the
 // workgroups of a part take its groups of four units, the phases with the largest K first, first come
 // first served from a counter, which the quantisation launch in front has cleared.
 //

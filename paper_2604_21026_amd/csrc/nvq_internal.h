@@ -136,12 +136,14 @@ int launch_gemv_mfma_ring(const GroupPhase *tab, const uint32_t *part_tab, int n
 // launch_quant_act_group for the W4A8 phases); grid: rows_grid() of its groups; tickets: eight words that
 // are zero.  order: nparts + 1 indices into what follows, then the phases of every part in the order
 // they are taken in (null: as they stand).
-constexpr int kRowsMinTokens = 17;
 int rows_groups(int units);  // of one phase in one part
 int rows_resident(int M);    // workgroups that are at work together
 int rows_grid(int groups, int nparts, int M);  // groups: of the part with the most of them
 int launch_gemv_rows(const GroupPhase *tab, const uint32_t *part_tab, int nparts, const uint32_t *order, int grid,
                      int M, uint32_t *tickets, hipStream_t st);
+
+// From so many tokens on a batch of a plan may run as launches phase by phase (before: as the per-tile grid).
+constexpr int kPhasesMinTokens = 17;
 
 // ---- device helpers -------------------------------------------------------
 #if defined(__HIPCC__)

@@ -69,7 +69,7 @@ def sums_in_order(acc, sw, chains, xs=None, by_group=False):
 
 
 def sums_in_steps(acc, sw, xs=None):
-    """float32 [M, N]: the same sum in the order of the persistent grid for 17 tokens and more: the
+    """float32 [M, N]: the same sum in the order of the persistent grid with shared activations: the
     eight groups of a step one after the other, the steps' sums eight at a time, then those."""
     M, N, G = acc.shape
     sw = np.asarray(sw, np.float32)

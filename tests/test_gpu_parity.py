@@ -1000,8 +1000,8 @@ def test_grouped_plan_matches_oracle_on_repeated_runs(name, M, ordered, grid):
     dl.close()
 
 
-# The persistent small-batch kernels (loader wave and LDS rings up to 16 tokens, shared activations
-# and tickets from 17 on) serve lists with every K a multiple of 512; these shapes exercise what
+# The persistent small-batch kernels (loader wave and LDS rings; shared activations and tickets) serve
+# lists with every K a multiple of 512; these shapes exercise what
 # their bookkeeping has to get right: row counts that end inside a unit of 32 rows and inside a
 # 16-row tile, phases of several matrices whose boundaries fall inside a unit, a phase with fewer
 # units than teams next to long ones (groups of units that cross phases of other K and precision),
