@@ -731,8 +731,9 @@ void order_phases(GroupPlan &gp, GroupBatch &b) {
 // The parts for gemv_rows.hip.  Of equal bytes, those with the shorter K have more groups: more than an XCD
 // holds workgroups makes some wait for a whole group elsewhere in the part, while other XCDs have room.  So
 // where all groups are resident together, every unit weighs as much more as it takes for no part to have
-// too many (or, where they fill the chip, hardly any): five blocks of 1B at 8 tokens 76 us, so 65, three of 8B 130 and 112 (67 such lists 1.11 times as fast,
-// the worst 0.89).  With more groups than that, equal bytes are as good as anything.
+// too many (or, where they fill the chip, hardly any): five blocks of 1B at 8 tokens 76 us, so 65, three of 8B
+// 130 and 112 (67 such lists 1.11 times as fast, the worst 0.89).  With more groups than that, equal bytes are
+// as good as anything.
 void cut_rows(GroupPlan &gp, GroupBatch &b, int M) {
     if (b.nparts <= 0) return;
     const int room = rows_resident(M) / b.nparts;

@@ -3,8 +3,8 @@
 // descriptions; the arithmetic is that of mfma_act.h.
 //
 // With two token tiles 32 weight rows need 3.6 times their own bytes of bf16 activations, and a
-// kernel whose waves each fetch their own (the ring kernel) stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a time: four waves, each with
-// 32 rows of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
+// kernel whose waves each fetch their own (the ring kernel) stands at 3 TB/s of weights.  So a workgroup takes 128 rows at a
+// time: four waves, each with 32 rows of its own (two 16-row tiles, a unit of the batch) and all of K, share the activations
 // through LDS, and no sums cross the waves.  K advances by 256 inputs (a whole 128-byte
 // line of a row); per step a wave asks for its quarter of the next step's activations (two
 // buffers) and, once the current step's weights and scales are in registers, for its next
